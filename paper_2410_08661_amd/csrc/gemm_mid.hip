@@ -1,0 +1,382 @@
+// Forward of 4-bit layers for 17 to about a hundred rows: several sequences decoded together, short prompts, draft tokens.
+// (Paper Sec. 3.2.1; the rows between the matrix-vector kernels' 16 and the sizes at which 256 x 256 tiles occupy the GPU.)
+//
+// A layer's codes are read once per panel of up to 48 rows, where passes of the 16-row kernel read them once per 16 rows
+// and the tiled GEMM leaves OC / 256 of 256 compute units working on the whole contraction.  What bounds the kernel: every
+// workgroup reads its panel of X in full (48 rows x 2 IC bytes against 8 IC bytes of codes per tile of 16 channels), so the
+// rows' trips from L2 weigh as much as the weights from memory: 4096 x 11008 at 48 rows moves 270 MB through the L2s in
+// 24 us.  Hence as few, as wide workgroups as still occupy every CU (rule at fwd_mid).
+//
+// Mapping: 16x16x32 MFMA, rows of X as the A operand, 16 channels as the B operand (a packed word is a lane's 8 contraction
+// elements), a group of 128 columns at a time.  The workgroup's waves take every KS-th group each and share nothing until
+// the end, so the main loop has no barrier: a wave brings its group's rows to a piece of LDS of its own (whole 256-byte row
+// pieces, nibble order, chunks XOR-placed by the row: free of bank conflicts), reads them back as fragments once and
+// multiplies all its channel tiles.  Dequantization as in the 16-row kernels, on the accumulator and without rounding the
+// weights: s (sum x (1024 + q) - (1024 + z) Sx), two FMAs per accumulator and group.  The next group's rows, codes and
+// parameters are requested while this one is multiplied.  Partial tiles meet in LDS in a fixed order (fp32).
+// Measured (passes or GEMM before -> now, us): 4096 x 4096, M = 40: 18.4 -> 10.2; 12288 x 4096 (q/k/v), M = 40: 26.9 -> 16.7;
+// 22016 x 4096 (gate/up), M = 48: 39 -> 30; 4096 x 11008, M = 40: 38.6 -> 23.7; 13824 x 5120, M = 64: 62 (46 with a K-split
+// workspace) -> 32; 4096 x 4096, M = 96: 37 (24) -> 12.
+// Tried and not kept: 64 rows per panel (registers spill, 2 to 5 times slower), codes two groups ahead for more than two
+// channel tiles (spills), parameters of four groups per request (no faster, and the waves' shares come out uneven).
+#include <type_traits>
+
+#include <climits>
+#include "qeft_internal.h"
+
+namespace qeft {
+namespace {
+
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ h8 as_h8(u4 v) { return __builtin_bit_cast(h8, v); }
+__device__ __forceinline__ uint32_t pack2(float a, float b) { return __builtin_bit_cast(uint32_t, h2{(_Float16)a, (_Float16)b}); }
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// 8 consecutive activations to the order in which the codes of a word come out of the conversion: (0,4)(1,5)(2,6)(3,7)
+__device__ __forceinline__ u4 permute_x(u4 v) {
+    u4 r;
+    r.x = __builtin_amdgcn_perm(v.z, v.x, 0x05040100u);
+    r.y = __builtin_amdgcn_perm(v.z, v.x, 0x07060302u);
+    r.z = __builtin_amdgcn_perm(v.w, v.y, 0x05040100u);
+    r.w = __builtin_amdgcn_perm(v.w, v.y, 0x07060302u);
+    return r;
+}
+
+struct MidArgs {
+    const uint32_t* qweight[MAX_GROUP];
+    const __half* scales[MAX_GROUP];
+    const __half* zeros[MAX_GROUP];
+    const __half* weak[MAX_GROUP];
+    __half* Y[MAX_GROUP];
+    int64_t ldy[MAX_GROUP];
+    int oc[MAX_GROUP];
+    int tile_begin[MAX_GROUP];   // first tile of 16 NT channels of layer i; INT_MAX when absent
+    int n_tiles, tiles_m;        // tiles of channels over all layers, panels of 16 MT rows
+    const __half* X;
+    int64_t ldx;
+    int M, kq, k, ng, stride, gs;
+};
+
+// One workgroup: 16 NT channels x 16 MT rows of Y over the whole contraction, which its KS waves divide; the partial tiles
+// meet in LDS at the end (fp32, fixed order).
+template <int MT, int NT>
+__global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    constexpr int XB = MT * 16 * 256;            // a group of activations: 16 MT rows of 256 bytes
+    constexpr int PB = 64 * 4;                   // (zero-point, scale) of a group, up to 64 channels
+    constexpr bool FULL = NT == 1;               // activations of the next group: all in flight at once, or half by half
+    constexpr int H = FULL ? 4 * MT : 2 * MT;    // 16-byte requests in flight (a request: 4 rows)
+    const int lane = threadIdx.x & 63;
+    const int KS = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, kb = lane >> 4;
+
+    const int per_xcd = (A.n_tiles * A.tiles_m + 7) >> 3;
+    const int v = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (v >= A.n_tiles * A.tiles_m) return;
+    const int t_n = v / A.tiles_m, t_m = v - t_n * A.tiles_m;
+    const int li = (t_n >= A.tile_begin[1]) + (t_n >= A.tile_begin[2]) + (t_n >= A.tile_begin[3]);
+    const int oc = A.oc[li];
+    const int o0 = (t_n - A.tile_begin[li]) * (16 * NT), m0 = t_m * (16 * MT);
+
+    unsigned char* mine = lds + (size_t)wave * XB;
+    unsigned char* par = lds + (size_t)KS * XB + (size_t)wave * PB;
+    const int last_g = A.ng - 1;
+
+    const unsigned char* wbase = reinterpret_cast<const unsigned char*>(A.qweight[li] + (size_t)o0 * A.stride);
+    const __half* sbase = A.scales[li] + (size_t)o0 * A.gs;
+    const __half* zbase = A.zeros[li] + (size_t)o0 * A.gs;
+    uint32_t woff[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) woff[t] = (uint32_t)min(16 * t + n, oc - 1 - o0) * (uint32_t)(A.stride * 4) + 16u * kb;
+    const uint32_t poff = (uint32_t)min(min(lane, 16 * NT - 1), oc - 1 - o0) * (uint32_t)A.gs;
+    const int xr = lane >> 4, xc = lane & 15;    // request u of a group of activations: row 4 u + xr, chunk xc
+    const unsigned char* xbase = reinterpret_cast<const unsigned char*>(A.X + (size_t)m0 * A.ldx);
+    const uint32_t xpitch = (uint32_t)A.ldx * 2u;
+    const int mlast = A.M - 1 - m0;
+    const uint32_t xoff0 = (uint32_t)xr * xpitch, xlast = (uint32_t)min(mlast, 16 * MT) * xpitch;
+
+    constexpr int D = MT == 2 && NT <= 2 ? 2 : 1;   // groups of codes on the way
+    u4 wq[D][NT], raw[H];
+    uint32_t ps, pz;
+    auto load_w = [&](int set, int t, int g) { wq[set][t] = *reinterpret_cast<const u4*>(wbase + (size_t)(64 * min(g, last_g)) + woff[t]); };
+    auto load_x = [&](u4& r, int u, int g) {
+        const uint32_t off = min(xoff0 + (uint32_t)(4 * u) * xpitch, xlast) + (uint32_t)(2 * min(128 * g + 8 * xc, A.kq - 8));
+        r = *reinterpret_cast<const u4*>(xbase + off);
+    };
+    // parameters of a group: a lane fetches those of one channel and hands them out through LDS
+    auto load_par = [&](int g) {
+        ps = reinterpret_cast<const uint16_t*>(sbase + min(g, last_g))[poff];
+        pz = reinterpret_cast<const uint16_t*>(zbase + min(g, last_g))[poff];
+    };
+    auto put_par = [&]() { *reinterpret_cast<uint32_t*>(par + 4 * lane) = pz | (ps << 16); };
+    // requests u0 .. of group g into LDS; columns past Kq become zeros
+    auto put_x = [&](const u4* r, int u0, int cnt, int g) {
+        if (128 * g + 128 > A.kq) {
+            const bool live = 128 * g + 8 * xc < A.kq;
+#pragma unroll
+            for (int u = 0; u < cnt; ++u) {
+                const u4 z = u4{0u, 0u, 0u, 0u};
+                const int row = 4 * (u0 + u) + xr;
+                *reinterpret_cast<u4*>(mine + row * 256 + ((xc ^ (row & 15)) << 4)) = live ? permute_x(r[u]) : z;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < cnt; ++u) {
+                const int row = 4 * (u0 + u) + xr;
+                *reinterpret_cast<u4*>(mine + row * 256 + ((xc ^ (row & 15)) << 4)) = permute_x(r[u]);
+            }
+        }
+    };
+
+    f4 acc[MT][NT];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[a][t] = f4{0.f, 0.f, 0.f, 0.f};
+
+    uint32_t mask = 0x000f000fu, magic = 0x64006400u;
+    u4 ones = u4{0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};
+    asm volatile("" : "+v"(mask), "+v"(magic), "+v"(ones.x), "+v"(ones.y), "+v"(ones.z), "+v"(ones.w));
+
+    // weak block: 32 columns at a time, dealt to the waves; the first of a wave is requested ahead of everything else
+    u4 xw[MT], ww[NT];
+    const int kpos = max(A.k, 8), nweak = (A.k + 31) >> 5;
+    auto load_weak = [&](int b) {
+        const int cc = min(32 * b + 8 * kb, kpos - 8);
+#pragma unroll
+        for (int a = 0; a < MT; ++a)
+            xw[a] = *reinterpret_cast<const u4*>(xbase + (size_t)min(16 * a + n, mlast) * xpitch + 2 * min(A.kq + cc, A.kq + A.k - 8));
+#pragma unroll
+        for (int t = 0; t < NT; ++t) ww[t] = *reinterpret_cast<const u4*>(A.weak[li] + (size_t)min(o0 + 16 * t + n, oc - 1) * A.k + cc);
+    };
+    auto mul_weak = [&](int b) {
+        const bool live = 32 * b + 8 * kb < A.k;   // both operands: nothing past the block may meet the zeros of the other
+        const u4 z = u4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const u4 wl = live ? ww[t] : z;
+#pragma unroll
+            for (int a = 0; a < MT; ++a) acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(live ? xw[a] : z), as_h8(wl), acc[a][t], 0, 0, 0);
+        }
+    };
+
+    load_weak(wave);
+    if (wave >= A.ng) mul_weak(wave);
+    else {
+        auto group = [&](int i) { return i * KS + wave; };   // the wave's i-th group
+        const int ngw = (A.ng - wave + KS - 1) / KS;
+        {
+            u4 r0[4 * MT];
+            load_par(group(0));
+#pragma unroll
+            for (int u = 0; u < 4 * MT; ++u) load_x(r0[u], u, group(0));
+#pragma unroll
+            for (int t = 0; t < NT; ++t) load_w(0, t, group(0));
+            if constexpr (D == 2) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) load_w(1, t, group(1));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            mul_weak(wave);
+            put_par();
+            put_x(r0, 0, 4 * MT, group(0));
+        }
+        // group i: its activations are in LDS, its codes in set i % 2; the next group's activations and the codes of
+        // the one after are on the way
+        auto step = [&](int i, auto set_c) {
+            constexpr int SET = decltype(set_c)::value;
+            const int gn = group(i + 1), gw = group(i + D);
+            u4 xa[MT][4];
+            wave_lds_fence();
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    xa[a][q] = *reinterpret_cast<const u4*>(mine + (16 * a + n) * 256 + (((4 * kb + q) ^ n) << 4));
+            uint32_t zs[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) zs[t] = *reinterpret_cast<const uint32_t*>(par + 4 * (16 * t + n));
+            wave_lds_fence();
+            load_par(gn);
+#pragma unroll
+            for (int u = 0; u < H; ++u) load_x(raw[u], u, gn);
+            f4 sx[MT];
+#pragma unroll
+            for (int a = 0; a < MT; ++a) sx[a] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int a = 0; a < MT; ++a) sx[a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa[a][q]), as_h8(ones), sx[a], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const u4 w = wq[SET][t];
+                f4 tmp[MT];
+#pragma unroll
+                for (int a = 0; a < MT; ++a) tmp[a] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t wi = w[q];
+                    const u4 c = u4{(wi & mask) | magic, ((wi >> 4) & mask) | magic, ((wi >> 8) & mask) | magic, ((wi >> 12) & mask) | magic};
+#pragma unroll
+                    for (int a = 0; a < MT; ++a) tmp[a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa[a][q]), as_h8(c), tmp[a], 0, 0, 0);
+                }
+                load_w(SET, t, gw);
+                const h2 p = __builtin_bit_cast(h2, zs[t]);
+                const float sf = (float)p.y, cz = -(1024.f + (float)p.x);
+#pragma unroll
+                for (int a = 0; a < MT; ++a)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[a][t][e] = fmaf(sf, fmaf(cz, sx[a][e], tmp[a][e]), acc[a][t][e]);
+                if (!FULL && t == NT / 2 - 1) {
+                    put_x(raw, 0, H, gn);
+#pragma unroll
+                    for (int u = 0; u < H; ++u) load_x(raw[u], H + u, gn);
+                }
+            }
+            put_x(raw, FULL ? 0 : H, H, gn);
+            put_par();
+        };
+        int i = 0;
+        if constexpr (D == 2) {
+#pragma clang loop unroll(disable)
+            for (; i + 1 < ngw; i += 2) {
+                step(i, std::integral_constant<int, 0>{});
+                step(i + 1, std::integral_constant<int, 1>{});
+            }
+        } else {
+#pragma clang loop unroll(disable)
+            for (; i + 1 < ngw; ++i) step(i, std::integral_constant<int, 0>{});
+        }
+        if (i < ngw) step(i, std::integral_constant<int, 0>{});
+    }
+
+    for (int b = wave + KS; b < nweak; b += KS) {
+        load_weak(b);
+        mul_weak(b);
+    }
+
+    // the waves' partial tiles meet in LDS (at most 4 channel tiles at a time); wave w sums tiles w, w + KS, ...
+    constexpr int NC = NT < 4 ? NT : 4;
+    __half* Y = A.Y[li] + (size_t)m0 * A.ldy[li] + o0;
+    const int64_t ldy = A.ldy[li];
+#pragma unroll
+    for (int t0 = 0; t0 < NT; t0 += NC) {
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < MT; ++a)
+#pragma unroll
+            for (int t = 0; t < NC; ++t)
+                if (t0 + t < NT) *reinterpret_cast<f4*>(mine + ((a * NC + t) << 10) + 16 * lane) = acc[a][t0 + t < NT ? t0 + t : 0];
+        __syncthreads();
+        for (int q = wave; q < MT * NC; q += KS) {
+            f4 y = f4{0.f, 0.f, 0.f, 0.f};
+            for (int w = 0; w < KS; ++w) {
+                const f4 p = *reinterpret_cast<const f4*>(lds + (size_t)w * XB + (q << 10) + 16 * lane);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] += p[e];
+            }
+            // lane (n, kb) holds rows 4 kb .. 4 kb + 3 of channel n; a 4 x 4 transpose inside each quad of lanes gives it
+            // channels 4 (n / 4) .. + 3 of row 4 kb + n % 4: one 8-byte store
+            const uint32_t p0 = pack2(y[0], y[1]), p1 = pack2(y[2], y[3]);
+            const bool hi = (lane & 2) != 0, odd = (lane & 1) != 0;
+            auto swap2 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false); };   // lane ^ 2
+            auto swap1 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false); };   // lane ^ 1
+            const uint32_t other = swap2(hi ? p0 : p1);
+            const uint32_t lo2 = hi ? other : p0, hi2 = hi ? p1 : other;   // channels (n % 4) & 1 and + 2 of the quad, this lane's two rows
+            const uint32_t lo1 = swap1(lo2), hi1 = swap1(hi2);
+            const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+            // even lane: (own row-0, neighbour's row-0); odd lane: (neighbour's row-1, own row-1)
+            const uint32_t q0 = __builtin_amdgcn_perm(lo1, lo2, sel), q1 = __builtin_amdgcn_perm(hi1, hi2, sel);
+            const int a = q / NC, t = t0 + q % NC;
+            const int m = 16 * a + 4 * kb + (n & 3), o = 16 * t + 4 * (n >> 2);
+            if (t < NT && m <= mlast && o0 + o < oc) *reinterpret_cast<u2*>(Y + (size_t)m * ldy + o) = u2{q0, q1};
+        }
+    }
+}
+
+template <int MT, int NT>
+hipError_t launch_mid(const MidArgs& A, int KS, hipStream_t s) {
+    static bool attr = false;
+    const size_t lds_bytes = (size_t)KS * (MT * 4096 + 256);
+    if (!attr) {
+        hipError_t e = hipFuncSetAttribute((const void*)fwd_mid_kernel<MT, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (MT * 4096 + 256));
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    fwd_mid_kernel<MT, NT><<<8 * ceil_div((int64_t)A.n_tiles * A.tiles_m, 8), 64 * KS, lds_bytes, s>>>(A);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// (Rows are addressed with 32-bit offsets from the panel's first: 48 rows of up to 2^24 elements.)
+bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx) {
+    return M > 16 && L.bits == 4 && L.g == 128 && (L.kq % 8) == 0 && (L.k % 8) == 0 && (L.oc % 8) == 0 && ldx <= QEFT_MAX_DIM;
+}
+
+// Up to 96 rows (two panels) always; beyond that only where the caller gives no workspace for a K split and the GEMM's tiles
+// would occupy at most a quarter of the CUs.  (us, M = 96 / 128 here against the GEMM with its split and without: 4096 x 4096
+// 12 / 15 against 24 / 25 and 77; 12288 x 4096 27 / 41 against 36 / 39 and 82; 22016 x 4096 45 / 62 against 56 / 57 and 82;
+// 13824 x 5120 38 / 51 against 47 / 49 and 100.)
+bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws) {
+    return M <= 96 || (!split_ws && M <= 192 && ceil_div(L.oc, 256) <= 64);
+}
+
+// Tiles of 16 NT channels and KS waves.  A CU holds one workgroup of eight waves or two of four (registers), and a workgroup
+// reads its whole panel of X whatever its width, so: the narrowest tile whose workgroups are all resident at eight waves,
+// else at four, else the widest.  (us, 48 rows: 4096 x 4096 NT = 1 / 2 / 3 / 4 at KS = 8: 10.6 / 12.0 / 13.3 / 15.4;
+// 12288 x 4096: 32 / 27 / 17.8 / 20.3, KS = 4 and NT = 3: 19.2; 22016 x 4096 KS = 4: 43 / 30 / 34, KS = 8: 33 at best.)
+hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t ldx, __half* const* Y, const int64_t* ldy, hipStream_t s) {
+    const Layer& L = Ls[0];
+    const int panels = ceil_div(M, 48), MT = ceil_div(M, (int64_t)panels * 16) < 3 ? 2 : 3;
+    const int tiles_m = ceil_div(M, 16 * MT);
+    auto tiles_at = [&](int nt) {
+        int64_t t = 0;
+        for (int i = 0; i < n; ++i) t += ceil_div(Ls[i].oc, 16 * nt);
+        return t;
+    };
+    int NT = 1, KS = 8;
+    while (NT < 4 && tiles_at(NT) * tiles_m > 256) ++NT;
+    if (tiles_at(NT) * tiles_m > 256) {
+        KS = 4;
+        NT = tiles_at(3) * tiles_m <= 512 ? 3 : 4;
+    }
+    KS = L.ng > 0 && KS > L.ng ? L.ng : KS;
+    MidArgs A = {};
+    int tiles = 0;
+    for (int i = 0; i < MAX_GROUP; ++i) {
+        const Layer& Li = Ls[i < n ? i : 0];
+        A.qweight[i] = Li.qweight;
+        A.scales[i] = Li.scales;
+        A.zeros[i] = Li.zeros;
+        A.weak[i] = Li.k > 0 ? Li.weak : reinterpret_cast<const __half*>(Li.qweight);   // (k = 0: a request whose result is not used)
+        A.Y[i] = Y[i < n ? i : 0];
+        A.ldy[i] = ldy[i < n ? i : 0];
+        A.oc[i] = Li.oc;
+        A.tile_begin[i] = i < n ? tiles : INT_MAX;
+        if (i < n) tiles += ceil_div(Li.oc, 16 * NT);
+    }
+    A.n_tiles = tiles;
+    A.tiles_m = tiles_m;
+    A.X = X;
+    A.ldx = ldx;
+    A.M = (int)M;
+    A.kq = L.kq;
+    A.k = L.k;
+    A.ng = L.ng;
+    A.stride = L.stride;
+    A.gs = L.gs;
+    using Launch = hipError_t (*)(const MidArgs&, int, hipStream_t);
+#define QEFT_MID(MT) {launch_mid<MT, 1>, launch_mid<MT, 2>, launch_mid<MT, 3>, launch_mid<MT, 4>}
+    static const Launch table[2][4] = {QEFT_MID(2), QEFT_MID(3)};
+#undef QEFT_MID
+    return table[MT - 2][NT - 1](A, KS, s);
+}
+
+}  // namespace qeft

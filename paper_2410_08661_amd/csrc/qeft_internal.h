@@ -100,6 +100,11 @@ hipError_t gemv_fwd_group(const Layer* Ls, int n, const __half* X, int64_t M, in
 // perm (or nullptr) gathers the activations from original channel order.  *handled = false: not this kernel's shape.
 hipError_t gemv_dot_fwd(const Layer* Ls, int n, const int* perm, const __half* X, __half* const* Y, hipStream_t s, bool* handled);
 
+// ---- forward between the decode sizes and the large GEMM (gemm_mid.hip); Ls[0 .. n) share the input ----
+bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx);
+bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws);   // split_ws: the caller's workspace holds the partial tiles of the GEMM's K split
+hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t ldx, __half* const* Y, const int64_t* ldy, hipStream_t s);
+
 // ---- prefill / fine-tune path: MFMA GEMMs (gemm.hip) ---------------------------------------
 bool gemm_fwd_supported(const Layer& L, int64_t M);
 // ws: optional device workspace of gemm_fwd_split_workspace() bytes (16-byte aligned); with it, launches of few tiles, or with a

@@ -1,0 +1,66 @@
+"""The forward between the decode sizes and the large GEMM (17 to 192 rows), at the edges of its tiles: rows around the
+panels of 32 and 48, channels that end inside a tile of 16 ... 64, rows of fewer groups than waves, a ragged last group,
+weak blocks of none, one and more than eight 32-column steps, a layer without quantized columns, and the group call.
+Tolerance: parity_util's bar (2e-3 in norm and per element); this kernel does not round the weights, so only the fp16 of the
+result is left (2.1e-4 in norm: half an ulp, 2^-12 at most per value, over a uniform mantissa)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import qeft_oracle as qo
+from paper_2410_08661_amd import binding as B
+from paper_2410_08661_amd import synth
+from parity_util import HostLayer, assert_close, pad_cols
+
+pytestmark = pytest.mark.gpu
+
+LAYERS = [
+    (200, 512, 128),            # three groups for eight waves; 200 channels: the last tile ends after 8 of 16
+    (4104, 256 + 8, 8),         # 257 tiles of 16: wider ones, the last mostly empty
+    (1032, 1352, 264),          # nine 32-column weak steps for eight waves; a ragged last group (1088 = 8 x 128 + 64)
+    (264, 1160, 0),             # nothing weak; 9 x 128 + 8 columns
+    (96, 320, 320),             # nothing quantized
+    (16648, 384, 64),           # four-wave workgroups (more tiles than CUs)
+]
+
+
+@pytest.mark.parametrize("oc,ic,k", LAYERS)
+def test_mid_rows(oc, ic, k):
+    layer = HostLayer(oc, ic, k, 4, 128, seed=oc + k)
+    w = layer.to_device()
+    for m in (17, 32, 33, 48, 49, 96, 97, 145):
+        x = synth.make_activations(m, ic, k, seed=m)
+        xd, _ = pad_cols(x)
+        back = torch.full((m + 2, oc + 8), 7.0, dtype=torch.float16, device="cuda")
+        y = back[1:m + 1, :oc]
+        B.qeft_linear_fwd(layer.desc, w, xd, y, ws=False)
+        first = y.clone()
+        B.qeft_linear_fwd(layer.desc, w, xd, y, ws=False)
+        torch.cuda.synchronize()
+        assert torch.equal(first, y), f"M={m}: repeats differ"
+        assert bool((back[0] == 7).all()) and bool((back[m + 1] == 7).all()) and bool((back[:, oc:] == 7).all()), f"M={m}: wrote outside"
+        assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), f"M={m}")
+
+
+@pytest.mark.parametrize("m", [17, 40, 96])
+def test_mid_rows_group(m):
+    layers = [HostLayer(oc, 640, 128, 4, 128, seed=oc) for oc in (264, 4096, 72)]
+    ws = [l.to_device() for l in layers]
+    x = synth.make_activations(m, 640, 128, seed=3)
+    xd, _ = pad_cols(x)
+    ys = B.qeft_linear_fwd_group([l.desc for l in layers], ws, xd)
+    torch.cuda.synchronize()
+    for l, y in zip(layers, ys):
+        assert_close(y.cpu().numpy(), qo.linear_fwd(l.w64, x), f"{l.oc} channels")
+
+
+def test_mid_rows_fractional_zero_points():
+    """Any fp16 zero-point: halves and values outside the code range."""
+    layer = HostLayer(80, 768, 64, 4, 128, seed=5)
+    rng = np.random.default_rng(9)
+    layer.zeros = (rng.integers(-40, 60, layer.zeros.shape) / 2).astype(np.float16)
+    w = layer.to_device()
+    x = synth.make_activations(37, 768, 64, seed=6)
+    y = B.qeft_linear_fwd(layer.desc, w, pad_cols(x)[0], ws=False)
+    torch.cuda.synchronize()
+    assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), "fractional zero-points")
