@@ -188,10 +188,25 @@ __global__ __launch_bounds__(256) void rtn_fused_w4g128_kernel(Layer L, const __
 // derives (scale, zero-point) with the rules above, quantizes and scores the squared weight error;
 // the first candidate with the smallest error is kept (candidate 0 = plain min-max).  One group per
 // 16 lanes (a lane holds 8 consecutive columns; lanes past the group width hold zeros, which cost
-// nothing), four groups per wavefront.  Every operation is a single correctly rounded fp32
-// operation (the intrinsics keep the compiler from fusing multiply and add) and the error is
-// summed in a fixed order - a lane's 8 columns left to right, then a balanced tree over the 16
-// lanes - so that the decisions can be reproduced exactly elsewhere.
+// nothing), four groups per wavefront.  The error is summed in a fixed order - a lane's 8 columns
+// left to right, then a balanced tree over the 16 lanes - so that the decisions can be reproduced
+// exactly elsewhere.
+//
+// The kernel is bound by vector instructions (4096 x 4096, 80 candidates: 1.3 G scores).  What keeps them few:
+//  * Scale, zero-point and reciprocal of 16 candidates are derived at once, one per lane of the group's 16, and handed
+//    round by row broadcasts.
+//  * A column's score needs no division.  r = rint(v * (1 / s)) differs from rint(v / s) only where v / s is exactly half
+//    way between two integers: v and s are fp16, so any other quotient of magnitude 1/4 ... 256 is at least 2^-13 from a tie
+//    (|2 a 2^k - (2 n + 1) b| / 2 b with a, b < 2^11), while the product is off by 2^-15 at most, and larger ones clamp.
+//    On a tie both neighbours leave the same |v - s r| = s / 2, so the score is the same number either way; the codes
+//    themselves are taken at the end by the rules above, with the division.
+//  * v - s r in one fused operation is exact where the product and the difference are rounded separately, because s r is
+//    exact (11 bits times an integer below 16).
+//  * A candidate whose two extreme columns alone already err by more than the best score so far cannot win and is not
+//    scored (the sum of non-negative terms is at least any of them; 2^-10 covers its rounding).  Narrow ranges clip the
+//    extremes hard, so about two thirds of an 80-candidate grid fall away on normally distributed weights.
+// 4096 x 4096, 80 candidates, whole call: 919 us before (two divisions per weight and candidate, every candidate scored, the
+// words in a second pass), 117 us now.
 __device__ __forceinline__ float dpp16_sum(float v) {
     auto mv = [](float x, auto ctrl) {
         return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, false));
@@ -203,9 +218,11 @@ __device__ __forceinline__ float dpp16_sum(float v) {
     return v;
 }
 
+// WORDS: 4-bit codes in groups of 128, whose words the same lanes then store (otherwise rtn_words_kernel does).
+template <bool WORDS>
 __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __half* __restrict__ W, int64_t ldw,
                                                             __half* __restrict__ scales, __half* __restrict__ zeros,
-                                                            int chunks, int n_grid, float step) {
+                                                            uint32_t* __restrict__ qweight, int chunks, int n_grid, float step) {
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
     const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -227,43 +244,81 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
     lo0 = dpp16_min(lo0);
     hi0 = -dpp16_min(-hi0);
     const float qmax = (float)((1 << L.bits) - 1);
-    float best_e = __builtin_inff();
-    __half best_s = __float2half_rn(1.f), best_z = __float2half_rn(0.f);
-    for (int i = 0; i < n_grid; ++i) {
-        const float p = __fsub_rn(1.f, __fmul_rn((float)i, step));
-        const float lo = __fmul_rn(p, lo0), hi = __fmul_rn(p, hi0);
-        const float s32 = __fdiv_rn(__fsub_rn(hi, lo), qmax);
-        __half s16, z16;
-        if (s32 == 0.f) {
-            s16 = __float2half_rn(1.f);
-            z16 = __float2half_rn(0.f);
-        } else {
-            s16 = __float2half_rn(s32);
-            if (__half2float(s16) == 0.f) s16 = __ushort_as_half((unsigned short)1);
-            float z = rintf(__fdiv_rn(__fsub_rn(0.f, lo), __half2float(s16)));
-            z = fminf(fmaxf(z, 0.f), qmax);
-            z16 = __float2half_rn(z);
+    float best_e = __builtin_inff(), best_s = 1.f, best_z = 0.f;
+    // squared-error term of one value under (s, 1 / s, z): nz = -z, uz = qmax - z
+    auto miss = [](float x, float s, float rs, float nz, float uz) {
+        return __builtin_fmaf(-__builtin_amdgcn_fmed3f(rintf(x * rs), nz, uz), s, x);
+    };
+    for (int i0 = 0; i0 < n_grid; i0 += 16) {
+        float s_l, rs_l, z_l, bound_l;   // candidate i0 + t of this lane's group
+        {
+            const float p = __fsub_rn(1.f, __fmul_rn((float)(i0 + t), step));
+            const float lo = __fmul_rn(p, lo0), hi = __fmul_rn(p, hi0);
+            const float s32 = __fdiv_rn(__fsub_rn(hi, lo), qmax);
+            s_l = 1.f;
+            z_l = 0.f;
+            if (s32 != 0.f) {
+                __half s16 = __float2half_rn(s32);
+                if (__half2float(s16) == 0.f) s16 = __ushort_as_half((unsigned short)1);
+                s_l = __half2float(s16);
+                z_l = rintf(__fdiv_rn(__fsub_rn(0.f, lo), s_l));
+                z_l = fminf(fmaxf(z_l, 0.f), qmax);
+            }
+            rs_l = __fdiv_rn(1.f, s_l);
+            const float a = miss(lo0, s_l, rs_l, -z_l, qmax - z_l), b = miss(hi0, s_l, rs_l, -z_l, qmax - z_l);
+            bound_l = (a * a + b * b) * (1.f - 0x1p-10f);
         }
-        const float s = __half2float(s16), z = __half2float(z16);
-        float acc = 0.f;
+        auto candidate = [&](auto j_c) {
+            constexpr int J = decltype(j_c)::value;
+            auto from_j = [](float x) {   // lane J of the row of 16
+                return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + J, 0xf, 0xf, false));
+            };
+            if (i0 + J >= n_grid) return;
+            if (__ballot(from_j(bound_l) < best_e) == 0) return;
+            const float s = from_j(s_l), rs = from_j(rs_l), z = from_j(z_l), uz = qmax - z;
+            float acc = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float q = __fadd_rn(rintf(__fdiv_rn(v[e], s)), z);
-            q = fminf(fmaxf(q, 0.f), qmax);
-            const float d = __fsub_rn(v[e], __fmul_rn(s, __fsub_rn(q, z)));
-            acc = __fadd_rn(acc, __fmul_rn(d, d));
-        }
-        const float err = dpp16_sum(acc);
-        if (err < best_e) {
-            best_e = err;
-            best_s = s16;
-            best_z = z16;
-        }
+            for (int e = 0; e < 8; ++e) {
+                const float d = miss(v[e], s, rs, -z, uz);
+                acc = e == 0 ? __fmul_rn(d, d) : __fadd_rn(acc, __fmul_rn(d, d));
+            }
+            const float err = dpp16_sum(acc);
+            const bool better = err < best_e;
+            best_e = better ? err : best_e;
+            best_s = better ? s : best_s;
+            best_z = better ? z : best_z;
+        };
+        candidate(std::integral_constant<int, 0>{});
+        candidate(std::integral_constant<int, 1>{});
+        candidate(std::integral_constant<int, 2>{});
+        candidate(std::integral_constant<int, 3>{});
+        candidate(std::integral_constant<int, 4>{});
+        candidate(std::integral_constant<int, 5>{});
+        candidate(std::integral_constant<int, 6>{});
+        candidate(std::integral_constant<int, 7>{});
+        candidate(std::integral_constant<int, 8>{});
+        candidate(std::integral_constant<int, 9>{});
+        candidate(std::integral_constant<int, 10>{});
+        candidate(std::integral_constant<int, 11>{});
+        candidate(std::integral_constant<int, 12>{});
+        candidate(std::integral_constant<int, 13>{});
+        candidate(std::integral_constant<int, 14>{});
+        candidate(std::integral_constant<int, 15>{});
     }
     if (t == 0) {
         const bool real = grp < L.ng;
-        scales[(size_t)o * L.gs + grp] = real ? best_s : __float2half_rn(0.f);
-        zeros[(size_t)o * L.gs + grp] = real ? best_z : __float2half_rn(0.f);
+        scales[(size_t)o * L.gs + grp] = __float2half_rn(real ? best_s : 0.f);
+        zeros[(size_t)o * L.gs + grp] = __float2half_rn(real ? best_z : 0.f);
+    }
+    if constexpr (WORDS) {
+        uint32_t out = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float q = __fadd_rn(rintf(__fdiv_rn(v[e], best_s)), best_z);
+            out |= (uint32_t)fminf(fmaxf(q, 0.f), qmax) << (4 * e);
+        }
+        const int word = 16 * grp + t;   // (gs groups of 16 words reach past the row's padded end)
+        if (word < L.stride) qweight[(size_t)o * L.stride + word] = live ? out : 0u;
     }
 }
 
@@ -374,8 +429,13 @@ hipError_t pack_search(const Layer& L, const __half* W, int64_t ldw, int n_grid,
                        __half* scales, __half* zeros, __half* weak, hipStream_t s) {
     if (L.kq > 0) {
         const int chunks = L.gs / 4;
-        search_params_kernel<<<ceil_div((int64_t)L.oc * chunks, 4), 256, 0, s>>>(L, W, ldw, scales, zeros, chunks, n_grid, step);
-        rtn_words_kernel<<<ceil_div((int64_t)L.oc * L.stride, 256), 256, 0, s>>>(L, W, ldw, scales, zeros, qweight);
+        const int grid = ceil_div((int64_t)L.oc * chunks, 4);
+        if (L.bits == 4 && L.g == 128) {
+            search_params_kernel<true><<<grid, 256, 0, s>>>(L, W, ldw, scales, zeros, qweight, chunks, n_grid, step);
+        } else {
+            search_params_kernel<false><<<grid, 256, 0, s>>>(L, W, ldw, scales, zeros, qweight, chunks, n_grid, step);
+            rtn_words_kernel<<<ceil_div((int64_t)L.oc * L.stride, 256), 256, 0, s>>>(L, W, ldw, scales, zeros, qweight);
+        }
     }
     copy2d(W + L.kq, ldw, weak, L.k, L.oc, L.k, s);
     return hipGetLastError();

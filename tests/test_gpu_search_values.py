@@ -1,0 +1,51 @@
+"""The grid-search quantizer on values where its division-free scores and its skipped candidates could go wrong: quotients
+exactly half way between codes, fp16 subnormals, one huge column among small ones, one-sided ranges.  As in the parity
+tests the criterion is checked: parameters of a candidate of the grid, round-to-nearest codes under them, a float64 error
+within 1e-5 of the minimum over the grid (128 fp32 terms: 128 x 2^-24 = 7.6e-6)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import qeft_oracle as qo
+from paper_2410_08661_amd import binding as B
+from parity_util import pad_cols
+
+pytestmark = pytest.mark.gpu
+
+
+def _values(kind, oc, ic):
+    r = np.random.default_rng(17)
+    if kind == "ties":        # multiples of half a step of many candidates
+        return (r.integers(-15, 16, (oc, ic)) * 2.0 ** -6).astype(np.float16)
+    if kind == "subnormal":
+        return (r.integers(-700, 700, (oc, ic)) * 2.0 ** -24).astype(np.float16)
+    if kind == "outlier":
+        w = (r.standard_normal((oc, ic)) * 1e-3).astype(np.float16)
+        w[:, ::61] = np.float16(2.0)
+        return w
+    return np.abs(r.standard_normal((oc, ic)) * 0.02).astype(np.float16)   # one-sided
+
+
+@pytest.mark.parametrize("kind", ["ties", "subnormal", "outlier", "one-sided"])
+@pytest.mark.parametrize("bits,g,k,n_grid,step", [(4, 128, 24, 80, 0.01), (4, 128, 0, 17, 0.05), (3, 64, 8, 33, 0.03)])
+def test_search_criterion(kind, bits, g, k, n_grid, step):
+    oc, ic = 37, 600 + k
+    w = _values(kind, oc, ic)
+    d = B.make_desc(oc, ic, k, bits, g)
+    out = B.Weight(d)
+    out.qweight.fill_(-1)
+    B.qeft_pack_search(d, pad_cols(w)[1][:, :ic], n_grid, step, out)
+    torch.cuda.synchronize()
+    lay = qo.layout(oc, ic, k, bits, g)
+    ng, kq = lay["n_groups"], lay["kq"]
+    s, z = out.scales[:, :ng].cpu().numpy(), out.zeros[:, :ng].cpu().numpy()
+    words = out.qweight.cpu().numpy().view(np.uint32)
+    codes = qo.unpack_codes(words, kq, bits)
+    assert np.array_equal(qo.pack_codes(codes, bits, lay["row_stride_words"]), words)     # padding zero
+    s_all, z_all, e_all = qo.search_candidates(w, k, bits, g, n_grid, step)
+    assert np.all(np.any((s_all.view(np.uint16) == s.view(np.uint16)[None]) & (z_all == z.astype(np.float32)[None]), axis=0))
+    assert np.array_equal(codes, qo.codes_for_params(w, k, bits, g, s, z))
+    wq = qo.dequantize(codes, s, z, np.zeros((oc, 0), dtype=np.float16), g)
+    sq = (w[:, :kq].astype(np.float64) - wq) ** 2
+    err = np.stack([sq[:, i * g:min((i + 1) * g, kq)].sum(axis=1) for i in range(ng)], axis=1)
+    assert np.all(err <= e_all.min(axis=0) * (1 + 1e-5) + 1e-30)
