@@ -173,7 +173,7 @@ size_t qeft_workspace_bytes(const qeft_desc_t* desc, int op, int64_t M);
  * one pass.  X fp16 [M][ldx] (ldx >= IC), Y fp16 [M][ldy] (ldy >= OC).  M <= 16 runs a
  * bandwidth-bound matrix-vector kernel, large M a tiled MFMA GEMM; the token counts in between (up to 96, without a
  * workspace up to 192 where the GEMM would fill only a fraction of the GPU) run a kernel of their own that streams the
- * layer once per 48 tokens.  ws / ws_bytes: optional, see
+ * layer once per 48 tokens, and smaller tiles serve the token counts whose large tiles would leave the GPU idle.  ws / ws_bytes: optional, see
  * qeft_workspace_bytes (4-bit layers: partial tiles of a split launch; 3-bit layers: the fp16 copy and,
  * beyond it, the partial tiles of its split); NULL / 0 is always valid. */
 int qeft_linear_fwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void* X, int64_t M,
@@ -270,7 +270,7 @@ int qeft_weak_grad(const qeft_desc_t* desc, const void* dY, int64_t M, int64_t l
  *     a 3-bit layer - without which its dX takes the slow general kernel): dX with that workspace, then the weak
  *     gradient, as qeft_linear_bwd_dx with its workspace followed by qeft_weak_grad (the workspace serves one after
  *     the other);
- *   - else, where both steps take the tensor-core path and the weak block is at most 128 wide: ONE launch - the
+ *   - else, where both steps take the large tensor-core tiles and the weak block is at most 128 wide: ONE launch - the
  *     weak gradient's workgroups follow the dX tiles in the grid and are dispatched as compute units fall free, so
  *     they run in what the last round of tiles leaves idle (dX of 4096 x 11008 at M = 4096: 688 tiles on 256 units;
  *     350 us against 363 us for the two calls); results as qeft_linear_bwd_dx without workspace followed by

@@ -198,6 +198,7 @@ int qeft_linear_fwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
             if (ws_bytes < need) return QEFT_ERR_WORKSPACE;
         }
         if (fwd_mid_supported(L, M, ldx) && fwd_mid_preferred(L, M, need > 0)) return hip_status(fwd_mid(&L, 1, x, M, ldx, &y, &ldy, s));
+        if (fwd_tile_preferred(L, M, ldx, need > 0)) return hip_status(fwd_tile(L, x, M, ldx, y, ldy, s));
         return hip_status(gemm_fwd(L, x, M, ldx, y, ldy, need > 0 ? ws : nullptr, s));
     }
     if (ws && dense_copy_applies(L, M)) {
@@ -282,6 +283,7 @@ int qeft_linear_bwd_dx(const qeft_desc_t* desc, const qeft_weight_t* w, const vo
             if (!aligned16(ws)) return QEFT_ERR_ALIGN;
             if (ws_bytes < need) return QEFT_ERR_WORKSPACE;
         }
+        if (dx_tile_preferred(L, M, lddy, need > 0)) return hip_status(dx_tile(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, s));
         return hip_status(gemm_dx(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, need > 0 ? ws : nullptr, s));
     }
     if (ws && dense_copy_applies(L, M)) {
@@ -455,7 +457,7 @@ int qeft_linear_bwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
     size_t need_dx = gemm_dx_supported(L, M) ? gemm_dx_split_workspace(L, M) : 0;
     if (dense_copy_applies(L, M)) need_dx = dense_copy_bytes(L);
     const bool split = need_dx > 0 && ws && aligned16(ws) && ws_bytes >= need_dx;
-    if (!split && gemm_dx_dw_supported(L, M))
+    if (!split && gemm_dx_dw_supported(L, M) && !dx_tile_preferred(L, M, lddy, false))   // (few tiles: the small-tile kernel, then the weak gradient)
         return hip_status(gemm_dx_dw(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, (const __half*)Xw, ldxw, dW,
                                      out_dtype == QEFT_DTYPE_F32, accumulate != 0, ws, (hipStream_t)stream));
     st = qeft_linear_bwd_dx(desc, w, dY, M, lddy, dX, lddx, split ? ws : nullptr, split ? ws_bytes : 0, stream);

@@ -105,6 +105,13 @@ bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx);
 bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws);   // split_ws: the caller's workspace holds the partial tiles of the GEMM's K split
 hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t ldx, __half* const* Y, const int64_t* ldy, hipStream_t s);
 
+// ---- forward and input gradient in tiles of 128 channels x 64 / 128 rows (gemm_tile.hip) for layers the GEMMs below support.
+// split_ws: the caller's workspace holds the partial tiles of the GEMM's split ----
+bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws);
+bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws);
+hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s);
+hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s);
+
 // ---- prefill / fine-tune path: MFMA GEMMs (gemm.hip) ---------------------------------------
 bool gemm_fwd_supported(const Layer& L, int64_t M);
 // ws: optional device workspace of gemm_fwd_split_workspace() bytes (16-byte aligned); with it, launches of few tiles, or with a

@@ -1,0 +1,87 @@
+"""Forward and input gradient in tiles of 128 channels x 64 or 128 rows (calls without a split workspace), at their edges:
+rows and channels that end inside a tile, a contraction shorter than the workgroup's shares, a ragged last group or stage,
+weak blocks of none, less than a stage and more stages than shares.  Tolerance: parity_util's bar (weights rounded to fp16
+once, 2^-11 relative each, over at least 64 terms; fp16 results)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import qeft_oracle as qo
+from paper_2410_08661_amd import binding as B
+from paper_2410_08661_amd import synth
+from parity_util import HostLayer, assert_close, pad_cols
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(call, m, cols, what, ref):
+    back = torch.full((m + 2, (cols + 7) // 8 * 8 + 8), 7.0, dtype=torch.float16, device="cuda")
+    out = back[1:m + 1, :cols]
+    call(out)
+    first = out.clone()
+    call(out)
+    torch.cuda.synchronize()
+    assert torch.equal(first, out), f"{what}: repeats differ"
+    assert bool((back[0] == 7).all()) and bool((back[m + 1] == 7).all()) and bool((back[:, cols:] == 7).all()), f"{what}: wrote outside"
+    assert_close(out.cpu().numpy(), ref, what)
+
+
+# (oc, ic, k, rows)
+FWD = [
+    (200, 512 + 64, 64, (97, 193, 320)),          # 200 channels: the second tile mostly empty; one K group has no chunk in the second turn
+    (264, 1352, 264, (257,)),                     # five weak stages for two shares, the last ragged; Kq = 1088 = 17 stages
+    (392, 4080 + 16, 16, (130,)),                 # the last stage 48 columns wide
+    (136, 896, 0, (209,)),                        # nothing weak
+    (4104, 1024 + 8, 8, (777,)),                  # 128-row tiles
+    (2056, 1600, 128, (1000, 515)),
+]
+DX = [
+    (64, 512 + 8, 8, (17, 64)),                   # one stage of rows for eight shares of half-stages
+    (320, 1024 + 136, 136, (65, 130)),            # two weak tiles, the second 8 wide; five stages
+    (1088, 256, 0, (200,)),                       # nothing weak
+    (1024, 3968 + 128, 128, (777, 129)),          # 128-row tiles
+    (4160, 896 + 64, 64, (97,)),
+]
+
+
+@pytest.mark.parametrize("oc,ic,k,rows", FWD)
+def test_forward(oc, ic, k, rows):
+    layer = HostLayer(oc, ic, k, 4, 128, seed=oc + k)
+    w = layer.to_device()
+    for m in rows:
+        x = synth.make_activations(m, ic, k, seed=m)
+        xd, _ = pad_cols(x)
+        _run(lambda out: B.qeft_linear_fwd(layer.desc, w, xd, out, ws=False), m, oc, f"M={m}", qo.linear_fwd(layer.w64, x))
+
+
+@pytest.mark.parametrize("oc,ic,k,rows", DX)
+def test_input_gradient(oc, ic, k, rows):
+    layer = HostLayer(oc, ic, k, 4, 128, seed=oc + k)
+    w = layer.to_device()
+    for m in rows:
+        dy = synth.make_grad_output(m, oc, seed=m)
+        dyd, _ = pad_cols(dy)
+        _run(lambda out: B.qeft_linear_bwd_dx(layer.desc, w, dyd, out, ws=False), m, ic, f"M={m}", qo.linear_bwd_dx(layer.w64, dy))
+
+
+def test_backward_call_equals_the_two_calls():
+    """qeft_linear_bwd with the weak gradient's workspace alone: bit for bit qeft_linear_bwd_dx without one and qeft_weak_grad."""
+    layer = HostLayer(512, 1024 + 128, 128, 4, 128, seed=4)
+    w, m = layer.to_device(), 333
+    x, dy = synth.make_activations(m, 1152, 128, seed=1), synth.make_grad_output(m, 512, seed=2)
+    xd, dyd = pad_cols(x)[0], pad_cols(dy)[0]
+    dx, dw = B.qeft_linear_bwd(layer.desc, w, dyd, xd[:, 1024:])
+    dx2, dw2 = B.qeft_linear_bwd_dx(layer.desc, w, dyd, ws=False), B.qeft_weak_grad(layer.desc, dyd, xd[:, 1024:])
+    torch.cuda.synchronize()
+    assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
+
+
+def test_fractional_zero_points():
+    layer = HostLayer(256, 512 + 64, 64, 4, 128, seed=5)
+    layer.zeros = (np.random.default_rng(9).integers(-40, 60, layer.zeros.shape) / 2).astype(np.float16)
+    w, m = layer.to_device(), 150
+    x, dy = synth.make_activations(m, 576, 64, seed=6), synth.make_grad_output(m, 256, seed=7)
+    y, dx = B.qeft_linear_fwd(layer.desc, w, pad_cols(x)[0], ws=False), B.qeft_linear_bwd_dx(layer.desc, w, pad_cols(dy)[0], ws=False)
+    torch.cuda.synchronize()
+    assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), "forward")
+    assert_close(dx.cpu().numpy(), qo.linear_bwd_dx(layer.w64, dy), "input gradient")
