@@ -1484,6 +1484,11 @@ size_t gemm_fwd_split_workspace(const Layer& L, int64_t M) {
     return split_workspace(ceil_div(L.oc, BT) * ceil_div(M, BT), gemm_fwd_plan(L, M));
 }
 
+GemmSplit gemm_fwd_split(const Layer& L, int64_t M) {
+    const SplitPlan p = gemm_fwd_plan(L, M);
+    return GemmSplit{p.splits, 8 * p.chunks_per_split, ceil_div(L.oc, BT) * ceil_div(M, BT), p.tail_first > 0};
+}
+
 hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, void* ws, hipStream_t s) {
     const int tiles_oc = ceil_div(L.oc, BT), tiles_m = ceil_div(M, BT);
     hipError_t e;
@@ -1528,6 +1533,11 @@ static SplitPlan gemm_dx_plan(const Layer& L, int64_t M) {
 
 size_t gemm_dx_split_workspace(const Layer& L, int64_t M) {
     return split_workspace(ceil_div(L.ic, BT) * ceil_div(M, BT), gemm_dx_plan(L, M));
+}
+
+GemmSplit gemm_dx_split(const Layer& L, int64_t M) {
+    const SplitPlan p = gemm_dx_plan(L, M);
+    return GemmSplit{p.splits, 8 * p.chunks_per_split, ceil_div(L.ic, BT) * ceil_div(M, BT), p.tail_first > 0};
 }
 
 hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s) {

@@ -381,7 +381,8 @@ __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const
 // lane.  Raw codes pass through LDS as they are stored and are read with gfx950's transposing 4-bit load (16 lanes name 16
 // rows of 16 codes; lane s receives the 16 rows of column s, lowest row in the lowest nibble - checked with a probe): what a
 // lane gets is a packed word as in the forward, and the same conversion follows with the rows' zero-points and scales as
-// vectors.  A tile is either quantized or weak (Kq is a multiple of 128 here); weak ones read fp16 with the 16-bit form.
+// vectors.  A tile is either quantized or weak, whatever Kq (the GEMM of gemm.hip
+// puts a partial group and weak columns into one tile and then takes its LDS-staged form); weak ones read fp16 with the 16-bit form.
 template <int J, int KW, int MINW>
 __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const __half* __restrict__ dY, int M, int64_t lddy,
                                                                 __half* __restrict__ dX, int64_t lddx, int tiles_n, int tiles_m) {
@@ -398,7 +399,9 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
     if (tile < 0) return;
     int t_n, t_m;
     tile_coords(tile, tiles_n, tiles_m, t_n, t_m);
-    const int c0 = t_n * 128, m0 = t_m * (32 * J);
+    // quantized tiles first (the last may be part of a group), then those of the weak block
+    const int nq = (L.kq + 127) >> 7;
+    const int c0 = t_n < nq ? t_n * 128 : L.kq + (t_n - nq) * 128, m0 = t_m * (32 * J);
     const int nst = (L.oc + 63) >> 6, turns = (nst + 2 * KW - 1) / (2 * KW);   // a turn: two stages of each K group
     const u4 zero4 = u4{0u, 0u, 0u, 0u};
 
@@ -416,7 +419,7 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    if (c0 < L.kq) {
+    if (t_n < nq) {
         const uint32_t lc = lds_at(lds) + (uint32_t)(KW * 2 * XT + kw * 2 * CT);
         const uint32_t lv = lds_at(lds) + (uint32_t)(KW * (2 * XT + 2 * CT) + kw * 2 * VT);
         // codes: thread tk fetches half a row of the stage (row tk / 2, 32 bytes); parameters: threads 0 .. 63 the scales,
@@ -615,8 +618,10 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
             stage(e + 3, std::integral_constant<int, 3>{});
         }
     }
-    finish<J, KW>(acc, lds, ow, kw, wave, lane, dX, lddx, c0 + 64 * ow, L.ic, m0, M);
+    finish<J, KW>(acc, lds, ow, kw, wave, lane, dX, lddx, c0 + 64 * ow, t_n < nq ? L.kq : L.ic, m0, M);
 }
+
+inline int dx_tiles(const Layer& L) { return ceil_div(L.kq, 128) + ceil_div(L.k, 128); }
 
 template <int J, int KW>
 constexpr int finish_lds() { return 2 * (KW - 1) * 2 * J * 4096; }
@@ -648,7 +653,7 @@ hipError_t launch_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, 
         if (e != hipSuccess) return e;
         attr = true;
     }
-    const int tn = ceil_div(L.ic, 128), tm = ceil_div(M, 32 * J);
+    const int tn = dx_tiles(L), tm = ceil_div(M, 32 * J);
     dx_tile_kernel<J, KW, MINW><<<xcd_grid(tn * tm), 128 * KW, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, tn, tm);
     return hipGetLastError();
 }
@@ -672,29 +677,37 @@ Est est_fwd(const Layer& L, int64_t M) {
 }
 Est est_dx(const Layer& L, int64_t M) {
     const int nst = L.oc / 64;
-    return best_of(2 * ceil_div(nst, 8) * 1.6 + 7, ceil_div(L.ic, 128), M, 1.65, 2 * ceil_div(nst, 4) * 1.3 + 8);
+    return best_of(2 * ceil_div(nst, 8) * 1.6 + 7, dx_tiles(L), M, 1.65, 2 * ceil_div(nst, 4) * 1.3 + 8);
 }
 // the tiled GEMM without a split: rounds of 256 tiles x stages of 64
 double est_gemm(int channels, int64_t M, int stages, double per_stage) {
     const int64_t tiles = (int64_t)ceil_div(channels, 256) * ceil_div(M, 256);
     return (double)((tiles + 255) / 256) * stages * per_stage + 8;
 }
+// the tiled GEMM with every tile split: a share's stages, the partial tiles' traffic (us per slot), the second launch
+double est_split(const GemmSplit& p, double fixed, double per_stage) { return fixed + p.stages * per_stage + 0.035 * p.tiles * p.splits; }
 }  // namespace
 
-// (32-bit offsets from a panel's first row: 128 rows of up to 2^23 elements.)  With a split workspace the forward takes this
-// kernel while one workgroup per CU does: 26 us against 32 (4096 x 4096, M = 333), 29 against 34 (M = 512), 33 against 38
-// (5120 x 5120, M = 333), 45 against 43 beyond (4096 x 4096, M = 777), 62 against 56 on longer rows (4096 x 11008, M = 333).
-// Rows whose quantized part is not whole stages have only the LDS-staged GEMM as the alternative (1.5 times the time).
+// (32-bit offsets from a panel's first row: 128 rows of up to 2^23 elements.)  The estimate has to be 5 % ahead.  Measured
+// with a split workspace, GEMM against this kernel: forward 4096 x 4096, M = 333: 32 us against 26, M = 512: 34 against 29,
+// 5120 x 5120, M = 333: 38 against 33, 6144 x 6144, M = 320: 48 against 44; M = 777 on 4096 x 4096: 43 against 40 (GEMM
+// kept: too close), 4096 x 11008, M = 333: 56 against 62; input gradient 2560 x 7168, M = 320: 36 against 32.
+// Rows whose quantized part is not whole stages have only the LDS-staged GEMM as the alternative, at 2.4 times the time
+// (4096 x 4096 with 8 weak columns, M = 227: 193 us against 26).
 bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws) {
     if (L.ng <= 0 || M <= 16 || ldx > (QEFT_MAX_DIM >> 1)) return false;
-    if (split_ws) return (L.ng + 3) / 4 <= 10 && (int64_t)ceil_div(L.oc, 128) * ceil_div(M, 64) <= 256;
-    const double g = est_gemm(L.oc, M, ceil_div(L.kq, 64) + ceil_div(L.k, 64), 1.15) * (L.kq % 64 == 0 ? 1.0 : 1.5);
+    const GemmSplit p = split_ws ? gemm_fwd_split(L, M) : GemmSplit{1, 0, 0, false};
+    if (p.splits > 1) return !p.tail && est_fwd(L, M).t < 0.95 * est_split(p, 11, 1.45);
+    const double g = est_gemm(L.oc, M, ceil_div(L.kq, 64) + ceil_div(L.k, 64), 1.15) * (L.kq % 64 == 0 ? 1.0 : 2.4);
     return est_fwd(L, M).t < 0.95 * g;
 }
-// The input gradient: whole stages of rows and whole groups of channels.  With a split workspace the GEMM's split is as fast.
+// The input gradient: whole stages of rows.  A partial last group leaves the GEMM its LDS-staged form, at 3.3 to 4.5 times
+// the time (4096 x 4096 with 8 weak columns, M = 227: 310 us; 4096 x 11008, M = 1938: 641 us).
 bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
-    if (L.ng <= 0 || M <= 16 || split_ws || L.oc % 64 != 0 || L.kq % 128 != 0 || L.k % 8 != 0 || lddy > (QEFT_MAX_DIM >> 1)) return false;
-    return est_dx(L, M).t < 0.95 * est_gemm(L.ic, M, L.oc / 64, 1.3);
+    if (L.ng <= 0 || M <= 16 || L.oc % 64 != 0 || lddy > (QEFT_MAX_DIM >> 1)) return false;
+    const GemmSplit p = split_ws ? gemm_dx_split(L, M) : GemmSplit{1, 0, 0, false};
+    if (p.splits > 1) return !p.tail && est_dx(L, M).t < 0.95 * est_split(p, 12, 1.5);
+    return est_dx(L, M).t < 0.95 * est_gemm(L.ic, M, L.oc / 64, 1.3) * (L.kq % 128 == 0 ? 1.0 : 3.3);
 }
 
 hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s) {

@@ -118,6 +118,13 @@ bool gemm_fwd_supported(const Layer& L, int64_t M);
 // sparsely filled last round of tiles, split K (for dX: the weight rows) of those tiles
 hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, void* ws, hipStream_t s);
 size_t gemm_fwd_split_workspace(const Layer& L, int64_t M);
+// what a GEMM with a workspace would do: ways a tile is split, 64-wide stages per way, tiles, and whether only the last round's are
+struct GemmSplit {
+    int splits, stages, tiles;
+    bool tail;
+};
+GemmSplit gemm_fwd_split(const Layer& L, int64_t M);
+GemmSplit gemm_dx_split(const Layer& L, int64_t M);
 bool gemm_dx_supported(const Layer& L, int64_t M);
 hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s);
 size_t gemm_dx_split_workspace(const Layer& L, int64_t M);

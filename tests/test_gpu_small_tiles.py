@@ -41,6 +41,8 @@ DX = [
     (1088, 256, 0, (200,)),                       # nothing weak
     (1024, 3968 + 128, 128, (777, 129)),          # 128-row tiles
     (4160, 896 + 64, 64, (97,)),
+    (192, 1000 + 24, 24, (97, 260)),              # a partial last group of 104 channels, then the weak ones
+    (128, 8 + 200, 200, (33,)),                   # eight quantized channels, two weak tiles
 ]
 
 
