@@ -61,7 +61,7 @@ typedef enum {
  *                          (decode, M <= 16: a kernel of its own when the padded row holds whole groups, i.e.
  *                          12 * G <= row_stride_words, which every Kq that is a multiple of 128 satisfies;
  *                          larger M and the backward pass: as for all 3-bit layers, the tensor-core kernels on
- *                          an fp16 copy in the caller's workspace, see qeft_workspace_bytes, or the slow
+ *                          a copy in the caller's workspace, see qeft_workspace_bytes, or the slow
  *                          general kernels without one). */
 enum { QEFT_LAYOUT_CANONICAL = 0, QEFT_LAYOUT_DENSE3 = 1 };
 
@@ -161,9 +161,10 @@ int qeft_unpack(const qeft_desc_t* desc, const qeft_weight_t* w, uint8_t* codes,
  * 32 MiB (forward of 5120 x 13824 at M = 4096, 320 tiles on 256 units: 515 us against 651 us).
  * QEFT_OP_FWD / QEFT_OP_BWD_DX report OC * IC * 2 bytes for 3-bit layers
  * at M > 16 (plus the partial tiles of a split of the copy's columns or rows as above, used when the whole
- * amount is given): with that workspace (16-byte aligned) the call dequantizes the layer once into it as fp16 and
- * runs the tensor-core kernels on the copy - the paper's own training path, dequantize then a dense product
- * (Sec. 4.3, App. A.2) - and without it (ws NULL) the slow general kernel; a workspace that is too small is
+ * amount is given): with that workspace (16-byte aligned) the call rewrites the layer once into it and runs the
+ * tensor-core kernels on the copy - the codes in the 4-bit layout for groups of 128 and 2^20 weights or more, else the
+ * whole layer dequantized to fp16 (the paper's own training path, dequantize then a dense product; Sec. 4.3, App. A.2) -
+ * and without it (ws NULL) the slow general kernel; a workspace that is too small is
  * QEFT_ERR_WORKSPACE.  The copy is rewritten by every call (the weak block may have changed).
  * QEFT_OP_BWD (qeft_linear_bwd): the larger of QEFT_OP_WEAK_GRAD's amount, which that call requires, and
  * QEFT_OP_BWD_DX's, which it uses when given (the two steps use the workspace one after the other). */

@@ -72,9 +72,13 @@ int check_matrix(const void* p, int64_t M, int64_t ld, int64_t width) {
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? QEFT_OK : QEFT_ERR_HIP; }
 
-// 3-bit layers at GEMM sizes: the tiled kernels convert 4-bit codes only, so the layer is dequantized once
-// into a caller-provided fp16 [OC][IC] workspace and multiplied as a layer whose columns are all weak
-// (the paper's own training path: dequantize, then a dense product; Sec. 4.3 / App. A.2).
+// 3-bit layers at GEMM sizes: the kernels there convert 4-bit codes only.  In groups of 128 the codes are rewritten once in
+// the 4-bit layout (a quarter of an fp16 copy's bytes: 5120 x 5120 7 to 8 us against 17) and multiplied as the 4-bit layer
+// with the same parameters and weak block; other group sizes are dequantized into an fp16 [OC][IC] copy and multiplied
+// as a layer whose columns are all weak (the paper's own training path: dequantize, then a dense product; Sec. 4.3 /
+// App. A.2).  So are layers of fewer than 2^20 weights: either copy takes about 3 us there, and for them the workspace keeps
+// holding the dequantized layer after the call, as it always has.  Either lies at the head of the caller's workspace, which is sized for the fp16 copy and a split of it; the
+// split's partial tiles follow.
 bool dense_copy_applies(const Layer& L, int64_t M) {
     return L.bits == 3 && L.kq > 0 && M > 16 && (L.ic % 8) == 0 && (L.oc % 8) == 0;
 }
@@ -91,6 +95,33 @@ Layer dense_copy_layer(const Layer& L, const void* ws) {
     D.scales = D.zeros = nullptr;
     D.weak = (const __half*)ws;
     return D;
+}
+
+bool nibble_copy_applies(const Layer& L, int64_t M) {
+    return dense_copy_applies(L, M) && L.g == 128 && L.kq % 8 == 0 && L.k % 8 == 0 && (int64_t)L.oc * L.ic >= ((int64_t)1 << 20);
+}
+Layer nibble_copy_layer(const Layer& L, const void* ws) {
+    Layer D = L;
+    D.bits = 4;
+    D.dense = 0;
+    D.words = (L.kq + 7) / 8;
+    D.stride = (D.words + 15) / 16 * 16;
+    D.qweight = (const uint32_t*)ws;
+    return D;
+}
+size_t nibble_copy_bytes(const Layer& D) { return ((size_t)D.oc * D.stride * 4 + 255) / 256 * 256; }
+
+// The forward of a layer the tiled kernels support, by rows and by what fills the GPU; split_ws: room for
+// gemm_fwd_split_workspace() bytes, or NULL.
+hipError_t fwd_rows(const Layer& L, const __half* x, int64_t M, int64_t ldx, __half* y, int64_t ldy, void* split_ws, hipStream_t s) {
+    const bool split = split_ws != nullptr;
+    if (fwd_mid_supported(L, M, ldx) && fwd_mid_preferred(L, M, split)) return fwd_mid(&L, 1, x, M, ldx, &y, &ldy, s);
+    if (fwd_tile_preferred(L, M, ldx, split)) return fwd_tile(L, x, M, ldx, y, ldy, s);
+    return gemm_fwd(L, x, M, ldx, y, ldy, split_ws, s);
+}
+hipError_t dx_rows(const Layer& L, const __half* dy, int64_t M, int64_t lddy, __half* dx, int64_t lddx, void* split_ws, hipStream_t s) {
+    if (dx_tile_preferred(L, M, lddy, split_ws != nullptr)) return dx_tile(L, dy, M, lddy, dx, lddx, s);
+    return gemm_dx(L, dy, M, lddy, dx, lddx, split_ws, s);
 }
 
 }  // namespace
@@ -197,13 +228,18 @@ int qeft_linear_fwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
             if (!aligned16(ws)) return QEFT_ERR_ALIGN;
             if (ws_bytes < need) return QEFT_ERR_WORKSPACE;
         }
-        if (fwd_mid_supported(L, M, ldx) && fwd_mid_preferred(L, M, need > 0)) return hip_status(fwd_mid(&L, 1, x, M, ldx, &y, &ldy, s));
-        if (fwd_tile_preferred(L, M, ldx, need > 0)) return hip_status(fwd_tile(L, x, M, ldx, y, ldy, s));
-        return hip_status(gemm_fwd(L, x, M, ldx, y, ldy, need > 0 ? ws : nullptr, s));
+        return hip_status(fwd_rows(L, x, M, ldx, y, ldy, need > 0 ? ws : nullptr, s));
     }
     if (ws && dense_copy_applies(L, M)) {
         if (!aligned16(ws)) return QEFT_ERR_ALIGN;
         if (ws_bytes < dense_copy_bytes(L)) return QEFT_ERR_WORKSPACE;
+        const Layer N = nibble_copy_layer(L, ws);
+        if (nibble_copy_applies(L, M) && gemm_fwd_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
+            if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
+            const size_t need = gemm_fwd_split_workspace(N, M);
+            void* split_ws = (need > 0 && ws_bytes >= nibble_copy_bytes(N) + need) ? (char*)ws + nibble_copy_bytes(N) : nullptr;
+            return hip_status(fwd_rows(N, x, M, ldx, y, ldy, split_ws, s));
+        }
         const Layer D = dense_copy_layer(L, ws);
         if (gemm_fwd_supported(D, M)) {
             hipError_t e = dequantize_fp16(L, (__half*)ws, s);
@@ -283,12 +319,18 @@ int qeft_linear_bwd_dx(const qeft_desc_t* desc, const qeft_weight_t* w, const vo
             if (!aligned16(ws)) return QEFT_ERR_ALIGN;
             if (ws_bytes < need) return QEFT_ERR_WORKSPACE;
         }
-        if (dx_tile_preferred(L, M, lddy, need > 0)) return hip_status(dx_tile(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, s));
-        return hip_status(gemm_dx(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, need > 0 ? ws : nullptr, s));
+        return hip_status(dx_rows(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, need > 0 ? ws : nullptr, s));
     }
     if (ws && dense_copy_applies(L, M)) {
         if (!aligned16(ws)) return QEFT_ERR_ALIGN;
         if (ws_bytes < dense_copy_bytes(L)) return QEFT_ERR_WORKSPACE;
+        const Layer N = nibble_copy_layer(L, ws);
+        if (nibble_copy_applies(L, M) && gemm_dx_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
+            if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
+            const size_t need = gemm_dx_split_workspace(N, M);
+            void* split_ws = (need > 0 && ws_bytes >= nibble_copy_bytes(N) + need) ? (char*)ws + nibble_copy_bytes(N) : nullptr;
+            return hip_status(dx_rows(N, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s));
+        }
         const Layer D = dense_copy_layer(L, ws);
         if (gemm_dx_supported(D, M)) {
             hipError_t e = dequantize_fp16(L, (__half*)ws, s);

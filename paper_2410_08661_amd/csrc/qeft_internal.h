@@ -71,6 +71,8 @@ hipError_t pack_codes(const Layer& L, const uint8_t* codes, const __half* scales
 hipError_t unpack(const Layer& L, uint8_t* codes, __half* scales, __half* zeros, __half* weak, hipStream_t s);
 // The whole mixed weight as fp16 [OC][IC] (IC a multiple of 8): s (q - z) rounded once, then the weak block.
 hipError_t dequantize_fp16(const Layer& L, __half* out, hipStream_t s);
+// The codes of a 3-bit layer in the 4-bit layout, [OC][stride4] words of which words4 hold codes (Kq a multiple of 8).
+hipError_t expand3(const Layer& L, uint32_t* out, int words4, int stride4, hipStream_t s);
 
 // ---- decode path: fused dequant matrix-vector product for M <= 16 (gemv.hip) -------------
 bool gemv_supported(const Layer& L, int64_t M, int64_t ldx);

@@ -1,0 +1,32 @@
+"""3-bit layers of 17 rows and more with a workspace: the codes rewritten in the 4-bit layout, then that layout's kernels.
+Both 3-bit layouts; rows that end inside a word of either, weak blocks of 8 and 136, row counts of each kernel behind it,
+workspaces of the stated size and of the fp16 copy alone.  Tolerance: parity_util's bar (fp16 weights, fp16 results)."""
+import pytest
+import torch
+
+from oracle import qeft_oracle as qo
+from paper_2410_08661_amd import binding as B
+from paper_2410_08661_amd import synth
+from parity_util import HostLayer, assert_close, pad_cols
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("oc,ic,k", [(4096, 344, 8), (832, 1208 + 136, 136), (1024, 2048, 128), (16384, 72, 0), (128, 344, 8)])
+def test_three_bit_rows(oc, ic, k, dense):
+    h = HostLayer(oc, ic, k, 3, 128, seed=oc + ic, dense=dense)
+    w = h.to_device()
+    for m in (17, 96, 97, 300):
+        x, dy = synth.make_activations(m, ic, k, seed=m), synth.make_grad_output(m, oc, seed=m + 1)
+        xd, dyd = pad_cols(x)[0], pad_cols(dy)[0]
+        for op, call, ref in ((B.QEFT_OP_FWD, lambda ws: B.qeft_linear_fwd(h.desc, w, xd, ws=ws), qo.linear_fwd(h.w64, x)),
+                              (B.QEFT_OP_BWD_DX, lambda ws: B.qeft_linear_bwd_dx(h.desc, w, dyd, ws=ws), qo.linear_bwd_dx(h.w64, dy))):
+            n = B.qeft_workspace_bytes(h.desc, op, m)
+            assert n >= 2 * oc * ic
+            for size in {n, 2 * oc * ic}:
+                back = torch.full((size + 64,), 0x5A, dtype=torch.uint8, device="cuda")
+                out = call(back[:size])
+                torch.cuda.synchronize()
+                assert bool((back[size:] == 0x5A).all()), f"M={m}: wrote past the workspace"
+                assert_close(out.cpu().numpy(), ref, f"op {op}, M={m}, workspace {size}")
