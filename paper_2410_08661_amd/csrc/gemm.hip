@@ -1575,22 +1575,40 @@ bool weak_grad_mfma_supported(int oc, int k, int64_t M) {
 }
 
 namespace {
-// split of the tokens for the strip kernel: about one workgroup per CU (more splits would add
-// slab traffic comparable to dY itself), every split a whole number of stages
-void weak_grad_strip_split(int oc, int k, int64_t M, int& splits, int& chunk) {
+// The most ways the tokens are split for the strip kernel: about one workgroup per CU, every split a whole number of
+// stages.  The workspace is sized for it.
+int weak_grad_strip_most(int oc, int k, int64_t M) {
     const int tiles = ceil_div(oc, WG_OC) * ceil_div(k, 128);
     const int stages = ceil_div(M, BK);
     int want = ceil_div(256, tiles);
     if (want > stages) want = stages;
     if (want < 1) want = 1;
-    chunk = ceil_div(stages, want) * BK;
+    return ceil_div(M, ceil_div(stages, want) * BK);
+}
+// The split taken: a stage of 64 tokens costs a workgroup about 0.62 us, more in proportion past one workgroup per CU, a split
+// the second launch and the partial slabs' way through memory (2 us and 0.65 us per MB).  Measured, as many splits as above
+// against the rule's, us: 4096 channels, k = 128, M = 256 / 512 / 1000: 12.6 / 13.0 / 14.7 against 7.7 / 9.3 / 13.7 (one,
+// one, two; four at M = 4096 either way); 11008 channels, M = 512 / 2048: 20.5 / 28.1 against 10.3 / 24.8 (one; two at
+// M = 4096: 41 against 43); 1024 channels, k = 256, M = 2048: 15.6 against 13.9 (four of eight).
+void weak_grad_strip_split(int oc, int k, int64_t M, int& splits, int& chunk) {
+    const int tiles = ceil_div(oc, WG_OC) * ceil_div(k, 128);
+    const int stages = ceil_div(M, BK), most = weak_grad_strip_most(oc, k, M);
+    const double slab_mb = (double)oc * k * 4e-6;
+    double best = 1e30;
+    for (int s = 1; s <= most; ++s) {
+        const double w = (double)tiles * s / 256.0;
+        const double t = (w > 1 ? w : 1) * 0.62 * ceil_div(stages, s) + (s > 1 ? 2.0 + 0.65 * s * slab_mb : 0.0);
+        if (t < best) {
+            best = t;
+            chunk = ceil_div(stages, s) * BK;
+        }
+    }
     splits = ceil_div(M, chunk);
 }
 }  // namespace
 
 size_t weak_grad_mfma_workspace(int oc, int k, int64_t M) {
-    int splits, chunk;
-    weak_grad_strip_split(oc, k, M, splits, chunk);
+    const int splits = weak_grad_strip_most(oc, k, M);
     return splits > 1 ? (size_t)splits * oc * k * sizeof(float) : 0;
 }
 

@@ -701,12 +701,13 @@ bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws) {
     const double g = est_gemm(L.oc, M, ceil_div(L.kq, 64) + ceil_div(L.k, 64), 1.15) * (L.kq % 64 == 0 ? 1.0 : 2.4);
     return est_fwd(L, M).t < 0.95 * g;
 }
-// The input gradient: whole stages of rows.  A partial last group leaves the GEMM its LDS-staged form, at 3.3 to 4.5 times
+// The input gradient: whole stages of rows.  Against the split the estimate has to be a quarter ahead (its weak tiles run
+// longer than estimated: 4096 x 4096, M = 512, 35 us either way).  A partial last group leaves the GEMM its LDS-staged form, at 3.3 to 4.5 times
 // the time (4096 x 4096 with 8 weak columns, M = 227: 310 us; 4096 x 11008, M = 1938: 641 us).
 bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
     if (L.ng <= 0 || M <= 16 || L.oc % 64 != 0 || lddy > (QEFT_MAX_DIM >> 1)) return false;
     const GemmSplit p = split_ws ? gemm_dx_split(L, M) : GemmSplit{1, 0, 0, false};
-    if (p.splits > 1) return !p.tail && est_dx(L, M).t < 0.95 * est_split(p, 12, 1.5);
+    if (p.splits > 1) return !p.tail && est_dx(L, M).t < 0.75 * est_split(p, 12, 1.5);
     return est_dx(L, M).t < 0.95 * est_gemm(L.ic, M, L.oc / 64, 1.3) * (L.kq % 128 == 0 ? 1.0 : 3.3);
 }
 
