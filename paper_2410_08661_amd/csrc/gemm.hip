@@ -24,6 +24,7 @@
 // activations of quantized stages are permuted to match.
 #include <cstdlib>
 #include <type_traits>
+#include <utility>
 
 #include "gemm_common.h"
 
@@ -166,13 +167,13 @@ constexpr int REGA_LDS = 4 * TILE_BYTES;   // X0 X1 and one tile for the weak bl
 // per row).  QUADS = false: accumulator tile t_i row 8 g + 4 fk + e is i = 32 t_i + row; QUADS =
 // true (the input-gradient kernel's quantized halves): it is i = 4 (row % 16) + t_i + 2 (row / 16).
 // i0 and ni multiples of 8, out rows 16-byte aligned.  No barrier: one wave, in-order LDS.
-template <bool QUADS>
-__device__ __forceinline__ void store_f16_lds_64x256(const f16v (&acc)[2][8], unsigned char* stage, __half* out, int64_t ld,
+template <bool QUADS, int JT>
+__device__ __forceinline__ void store_f16_lds(const f16v (&acc)[2][JT], unsigned char* stage, __half* out, int64_t ld,
                                                      int i0, int ni, int j0, int nj, int lane) {
     const int fr = lane & 31, fk = lane >> 5;
     auto pack = [](float a, float b) { return h2_bits(h2{(_Float16)a, (_Float16)b}); };
 #pragma unroll
-    for (int tj = 0; tj < 8; ++tj) {
+    for (int tj = 0; tj < JT; ++tj) {
         unsigned char* row = stage + (tj * 32 + fr) * 128;
         const int sw = fr & 7;
         if (!QUADS) {
@@ -195,7 +196,7 @@ __device__ __forceinline__ void store_f16_lds_64x256(const f16v (&acc)[2][8], un
     const int c = lane & 7, r8 = lane >> 3;
     const int i = i0 + 8 * c;
 #pragma unroll 8
-    for (int it = 0; it < 32; ++it) {
+    for (int it = 0; it < 4 * JT; ++it) {
         const int r = 8 * it + r8;
         const u4 v = *reinterpret_cast<const u4*>(stage + r * 128 + ((c ^ (r & 7)) << 4));
         if (j0 + r < nj && i < ni) *reinterpret_cast<u4*>(out + (size_t)(j0 + r) * ld + i) = v;
@@ -207,18 +208,27 @@ __device__ __forceinline__ void store_f16_lds_64x256(const f16v (&acc)[2][8], un
 // BT halves); splitk_reduce_kernel adds the partials.  Either every tile is split (launches with too few tiles to occupy
 // the CUs) or only those of the last, partly filled round (split_tile).  sps is a multiple of 8 stages, so every split
 // starts on a boundary of the four-group parameter fetches.
+// J: panels of 32 J rows.  The last panel of 256 rows may be mostly empty (333 rows: two panels, 65 % of them rows); the
+// launch then keeps its panels and tiles and takes the smallest J that covers the rows in as many equal panels.
+template <int... Ts, class F>
+__device__ __forceinline__ void each_step(std::integer_sequence<int, Ts...>, F&& f) {
+    (f(std::integral_constant<int, Ts>{}), ...);
+}
+
+template <int J>
 __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __half* __restrict__ X, int M, int64_t ldx,
                                                             __half* __restrict__ Y, int64_t ldy, int tiles_oc, int wide_stores,
                                                             int splits, int sps, int tail_first, __half* __restrict__ part) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tiles_all = tiles_oc * ((M + BT - 1) / BT);
+    constexpr int PM = 32 * J;
+    const int tiles_m = (M + PM - 1) / PM, tiles_all = tiles_oc * tiles_m;
     int tile, sp, slot;
     if (!split_tile(tiles_all, tail_first, splits, tile, sp, slot)) return;
     int t_oc, t_m;
-    tile_coords(tile, tiles_oc, (M + BT - 1) / BT, t_oc, t_m);
-    const int oc0 = t_oc * BT, m0 = t_m * BT;
+    tile_coords(tile, tiles_oc, tiles_m, t_oc, t_m);
+    const int oc0 = t_oc * BT, m0 = t_m * PM;
     const bool is_split = slot >= 0;
     const bool last_split = !is_split || sp == splits - 1;
     const int s_first = sp * sps;                                      // first stage of this workgroup
@@ -251,7 +261,7 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     const char* zt = reinterpret_cast<const char*>(L.zeros + (size_t)oc0 * L.gs) + s_first;
     const char* xt = reinterpret_cast<const char*>(X + (size_t)m0 * ldx) + 2 * BK * s_first;
     const char* wk = reinterpret_cast<const char*>(L.weak + (size_t)oc0 * L.k) + (weak_split ? 2 * BK * s_first : 0);
-    uint32_t aoff[2], szoff[2], xoff[8];
+    uint32_t aoff[2], szoff[2], xoff[J];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const uint32_t row = (uint32_t)min(wave * 64 + 32 * i + fr, L.oc - 1 - oc0);
@@ -260,7 +270,7 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     }
     const int xr = tid >> 3, xc = tid & 7;   // X chunk u of this thread: tile row xr + 32 u, chunk column xc
 #pragma unroll
-    for (int u = 0; u < 8; ++u) xoff[u] = ((uint32_t)min(xr + 32 * u, M - 1 - m0) * (uint32_t)ldx + 8u * xc) * 2u;
+    for (int u = 0; u < J; ++u) xoff[u] = ((uint32_t)min(xr + 32 * u, M - 1 - m0) * (uint32_t)ldx + 8u * xc) * 2u;
     auto sbase = [](const char* p) {
         asm volatile("" : "+s"(p));
         return (gptr)p;
@@ -279,11 +289,11 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     }
 
     u4 araw[2][2];      // codes: set = stage parity, row block i; word ks of the stage in component ks
-    u4 xv[8];           // X of the stage after the current one
+    u4 xv[J];           // X of the stage after the current one
     u2 szs[2], szz[2];  // scales / zero-points of four consecutive groups, per row block
     uint32_t lsz[2];    // latched group: zero-point in the low half, scale in the high half
     u4 afr[2][2];       // A fragments as packed halfs, written one pair at a time
-    h8 bfr[2][8];
+    h8 bfr[2][J];
     uint32_t cq[8];     // the conversion pipeline: one register per pair of the k-block being converted
     uint32_t w8[2];     // word >> 8 per row block
     u4 px;              // the X chunk being permuted
@@ -311,11 +321,11 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
         bfr[set][j] = *reinterpret_cast<const lds_h8*>(fb[kn ^ (4 * (j & 1))] + (uint32_t)(j * 4096 + buf * TILE_BYTES));
     };
 
-    f16v acc[2][8];
+    f16v acc[2][J];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+        for (int j = 0; j < J; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
@@ -323,28 +333,28 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     // (branch-free fetches: columns past k read the row's last 8 and are zeroed when stored)
     const int nw = (nwf || !last_split) ? 0 : (L.k + BK - 1) / BK;
     const u4 zero4 = u4{0u, 0u, 0u, 0u};
-    u4 wa[8], wb[8];
+    u4 wa[8], wb[J];
     auto load_weak = [&](int w) {
         const int col = min(BK * w + 8 * xc, L.k - 8);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int r = xr + 32 * u;
             wa[u] = ld16(L.weak + (size_t)min(oc0 + r, L.oc - 1) * L.k + col);
-            wb[u] = ld16(X + (size_t)min(m0 + r, M - 1) * ldx + L.kq + col);
+            if (u < J) wb[u < J ? u : 0] = ld16(X + (size_t)min(m0 + r, M - 1) * ldx + L.kq + col);
         }
     };
 
     if (nq > 0) {
         const int s1 = min(1, nq - 1), s1x = min(1, ns - 1);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) load_x(u, 0);
+        for (int u = 0; u < J; ++u) load_x(u, 0);
 #pragma unroll
         for (int i = 0; i < 2; ++i) load_a(0, i, 0);
         load_sz(0);
 #pragma unroll
         for (int i = 0; i < 2; ++i) load_a(1, i, s1);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < J; ++u) {
             put_x(u, 0);
             load_x(u, s1x);
         }
@@ -360,21 +370,22 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
         px = u4{0u, 0u, 0u, 0u};
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 8; ++j) read_b(0, j, 0, 0);
+        for (int j = 0; j < J; ++j) read_b(0, j, 0, 0);
 
         // stage st: X in buffer CUR, codes in set CUR
         auto stage = [&](int st, auto cur_c) {
-            constexpr int CUR = decltype(cur_c)::value, NXT = CUR ^ 1;
+            constexpr int CUR = decltype(cur_c)::value, NXT = CUR ^ 1, S = 2 * J;   // S: steps per k-block
             const int sl = min(st + 2, nq - 1), slx = min(st + 2, ns - 1);   // the activations run on into the weak stages
             // keep "base + constant" from being hoisted out of the loop into a register per constant:
             // inside the stage it folds into the instruction's offset field
             asm volatile("" : "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]), "+v"(fb[4]), "+v"(fb[5]), "+v"(fb[6]), "+v"(fb[7]));
             asm volatile("" : "+v"(xw[0]), "+v"(xw[1]), "+v"(aoff[0]), "+v"(aoff[1]));
-            asm volatile("" : "+v"(xoff[0]), "+v"(xoff[1]), "+v"(xoff[2]), "+v"(xoff[3]), "+v"(xoff[4]), "+v"(xoff[5]), "+v"(xoff[6]), "+v"(xoff[7]));
+#pragma unroll
+            for (int u = 0; u < J; ++u) asm volatile("" : "+v"(xoff[u]));
             auto step = [&](auto t_c) {
-                constexpr int T = decltype(t_c)::value, ks = T >> 4, t = T & 15, i = t >> 3, j = t & 7, kn = (ks + 1) & 3;
+                constexpr int T = decltype(t_c)::value, ks = T / S, t = T % S, i = t / J, j = t % J, kn = (ks + 1) & 3;
                 constexpr int SRC = ks < 3 ? CUR : NXT;   // where the next k-block comes from
-                if (T == 50 && CUR == 1) {
+                if (T == 3 * S + (J == 8 ? 2 : 0) && CUR == 1) {
                     // the pairs converted from here on belong to the next stage, which opens a new group:
                     // latch it, and when it was the last of the four held in registers fetch the
                     // following four (needed two stages from now)
@@ -387,26 +398,45 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
                 // two dependent instructions: pair a = t / 2 is masked at step 2a, rebased at 2a + 1,
                 // has its zero-point subtracted at 2a + 2 and is scaled at 2a + 3 (the last pair
                 // finishes in the first two steps of the following k-block, before its row block is used).
-                constexpr int a = t >> 1, ap = (a + 7) & 7;   // this step's young pair, and the one two steps older
-                constexpr int aci = a >> 2, apci = ap >> 2;
-                const h2 zs_old = bits_h2(lsz[apci]);
+                const h2 b0 = h2{(_Float16)1024.f, (_Float16)1024.f}, b1 = h2{(_Float16)64.f, (_Float16)64.f};
+                if constexpr (J == 8) {
+                    constexpr int a = t >> 1, ap = (a + 7) & 7;   // this step's young pair, and the one two steps older
+                    constexpr int aci = a >> 2, apci = ap >> 2;
+                    const h2 zs_old = bits_h2(lsz[apci]);
+                    if ((t & 1) == 0) {
+                        const uint32_t w = araw[SRC][aci][kn];
+                        if ((a & 3) == 1) w8[aci] = w >> 8;
+                        const uint32_t src = (a & 3) < 2 ? w : w8[aci];
+                        cq[a] = (a & 1) ? ((src & cst.m1) | cst.g1) : ((src & cst.m0) | cst.g0);
+                        cq[ap] = h2_bits(bits_h2(cq[ap]) - h2{zs_old.x, zs_old.x});
+                    } else {
+                        cq[a] = h2_bits(bits_h2(cq[a]) - ((a & 1) ? b1 : b0));
+                        // pair 7 of the previous conversion belongs to the k-block now being multiplied
+                        afr[a == 0 ? (ks & 1) : (kn & 1)][apci][ap & 3] = h2_bits(bits_h2(cq[ap]) * h2{zs_old.y, zs_old.y});
+                    }
+                } else {   // fewer steps: the four operations of the eight pairs one after the other, evenly over the k-block
+#pragma unroll
+                    for (int o = 32 * t / S; o < 32 * (t + 1) / S; ++o) {
+                        const int pr = o & 7, ci = pr >> 2;
+                        const h2 zs = bits_h2(lsz[ci]);
+                        if (o < 8) {
+                            const uint32_t w = araw[SRC][ci][kn];
+                            if ((pr & 3) == 2) w8[ci] = w >> 8;
+                            const uint32_t src = (pr & 3) < 2 ? w : w8[ci];
+                            cq[pr] = (pr & 1) ? ((src & cst.m1) | cst.g1) : ((src & cst.m0) | cst.g0);
+                        } else if (o < 16) cq[pr] = h2_bits(bits_h2(cq[pr]) - ((pr & 1) ? b1 : b0));
+                        else if (o < 24) cq[pr] = h2_bits(bits_h2(cq[pr]) - h2{zs.x, zs.x});
+                        else afr[kn & 1][ci][pr & 3] = h2_bits(bits_h2(cq[pr]) * h2{zs.y, zs.y});
+                    }
+                }
                 if ((t & 1) == 0) {
-                    const uint32_t w = araw[SRC][aci][kn];
-                    if ((a & 3) == 1) w8[aci] = w >> 8;
-                    const uint32_t src = (a & 3) < 2 ? w : w8[aci];
-                    cq[a] = (a & 1) ? ((src & cst.m1) | cst.g1) : ((src & cst.m0) | cst.g0);
-                    cq[ap] = h2_bits(bits_h2(cq[ap]) - h2{zs_old.x, zs_old.x});
                     read_b(kn & 1, t >> 1, SRC, kn);
-                    if (T >= 4 && T <= 32 && (T & 3) == 0) {   // the chunk permuted in the two odd steps before
+                    if constexpr (T >= 4 && T <= 4 * J && (T & 3) == 0) {   // the chunk permuted in the two odd steps before
                         constexpr int u = (T >> 2) - 1;
                         *reinterpret_cast<lds_u4*>(xw[u & 1] + (uint32_t)((u >> 1) * 8192 + NXT * TILE_BYTES)) = px;
                     }
                 } else {
-                    const h2 b0 = h2{(_Float16)1024.f, (_Float16)1024.f}, b1 = h2{(_Float16)64.f, (_Float16)64.f};
-                    cq[a] = h2_bits(bits_h2(cq[a]) - ((a & 1) ? b1 : b0));
-                    // pair 7 of the previous conversion belongs to the k-block now being multiplied
-                    afr[a == 0 ? (ks & 1) : (kn & 1)][apci][ap & 3] = h2_bits(bits_h2(cq[ap]) * h2{zs_old.y, zs_old.y});
-                    if (T < 32) {   // X chunk u of the next stage: half of the permutation per odd step
+                    if constexpr (T < 4 * J) {   // X chunk u of the next stage: half of the permutation per odd step
                         constexpr int u = T >> 2;
                         if ((T & 2) == 0) {
                             px.x = __builtin_amdgcn_perm(xv[u].z, xv[u].x, 0x05040100u);
@@ -417,30 +447,13 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
                             load_x(u, slx);
                         }
                     }
-                    if (ks == 3 && j == 7) load_a(CUR, i, sl);
+                    if (ks == 3 && j == J - 1 && J % 2 == 0) load_a(CUR, i, sl);
                 }
-                if (T == 47) __syncthreads();
+                if (ks == 3 && j == J - 1 && J % 2 == 1) load_a(CUR, i, sl);   // (an odd J puts these steps on either parity)
+                if (T == 3 * S - 1) __syncthreads();
                 __builtin_amdgcn_sched_barrier(0);
             };
-            auto steps8 = [&](auto b_c) {
-                constexpr int B = decltype(b_c)::value;
-                step(std::integral_constant<int, B + 0>{});
-                step(std::integral_constant<int, B + 1>{});
-                step(std::integral_constant<int, B + 2>{});
-                step(std::integral_constant<int, B + 3>{});
-                step(std::integral_constant<int, B + 4>{});
-                step(std::integral_constant<int, B + 5>{});
-                step(std::integral_constant<int, B + 6>{});
-                step(std::integral_constant<int, B + 7>{});
-            };
-            steps8(std::integral_constant<int, 0>{});
-            steps8(std::integral_constant<int, 8>{});
-            steps8(std::integral_constant<int, 16>{});
-            steps8(std::integral_constant<int, 24>{});
-            steps8(std::integral_constant<int, 32>{});
-            steps8(std::integral_constant<int, 40>{});
-            steps8(std::integral_constant<int, 48>{});
-            steps8(std::integral_constant<int, 56>{});
+            each_step(std::make_integer_sequence<int, 4 * S>{}, step);
         };
         int st = 0;
         for (; st + 1 < nq; st += 2) {
@@ -480,16 +493,16 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
         if (nq == 0) {   // no stage has run yet: start the activation pipeline here
             const int s1x = min(1, ns - 1);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) load_x(u, 0);
+            for (int u = 0; u < J; ++u) load_x(u, 0);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < J; ++u) {
                 put_x(u, 0);
                 load_x(u, s1x);
             }
             px = u4{0u, 0u, 0u, 0u};
             __syncthreads();
 #pragma unroll
-            for (int j = 0; j < 8; ++j) read_b(0, j, 0, 0);
+            for (int j = 0; j < J; ++j) read_b(0, j, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -499,7 +512,7 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
 
         // weak stage w: X in buffer CUR
         auto wstage = [&](int w, auto cur_c) {
-            constexpr int CUR = decltype(cur_c)::value, NXT = CUR ^ 1;
+            constexpr int CUR = decltype(cur_c)::value, NXT = CUR ^ 1, S = 2 * J;   // S: steps per k-block
             const int slx = min(nq + w + 2, ns - 1);
             uint32_t wo1[2], wo2[2];   // this thread's rows in the next stage and in the one after
 #pragma unroll
@@ -509,25 +522,28 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
             }
             asm volatile("" : "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]), "+v"(fb[4]), "+v"(fb[5]), "+v"(fb[6]), "+v"(fb[7]));
             asm volatile("" : "+v"(xw[0]), "+v"(xw[1]), "+v"(wo1[0]), "+v"(wo1[1]), "+v"(wo2[0]), "+v"(wo2[1]));
-            asm volatile("" : "+v"(xoff[0]), "+v"(xoff[1]), "+v"(xoff[2]), "+v"(xoff[3]), "+v"(xoff[4]), "+v"(xoff[5]), "+v"(xoff[6]), "+v"(xoff[7]));
+#pragma unroll
+            for (int u = 0; u < J; ++u) asm volatile("" : "+v"(xoff[u]));
             auto step = [&](auto t_c) {
-                constexpr int T = decltype(t_c)::value, ks = T >> 4, t = T & 15, i = t >> 3, j = t & 7, kn = (ks + 1) & 3;
+                constexpr int T = decltype(t_c)::value, ks = T / S, t = T % S, i = t / J, j = t % J, kn = (ks + 1) & 3;
                 constexpr int SRC = ks < 3 ? CUR : NXT;          // tile of the next k-block
+                constexpr int O0 = J == 8 ? 4 : 2, L0 = J == 8 ? 10 : (J > 4 ? 8 : 6), L1 = J == 8 ? 12 : (J > 5 ? 10 : (J > 4 ? 9 : 7));
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, afr[ks & 1][i]), bfr[ks & 1][j], acc[i][j], 0, 0, 0);
                 if ((t & 1) == 0) {
                     read_b(kn & 1, t >> 1, SRC, kn);
-                    if (T >= 4 && T <= 32 && (T & 3) == 0) {   // the chunk permuted in the two odd steps before
+                    if constexpr (T >= 4 && T <= 4 * J && (T & 3) == 0) {   // the chunk permuted in the two odd steps before
                         constexpr int u = (T >> 2) - 1;
                         *reinterpret_cast<lds_u4*>(xw[u & 1] + (uint32_t)((u >> 1) * 8192 + NXT * TILE_BYTES)) = px;
                     }
                     // the next k-block's fragments (k-block 0 of the next stage behind the last one), one row block
                     // per step; each register is then refilled with the same k-block one stage on
-                    if (t == 4) order_w(0, kn, kn & 1);
-                    if (t == 6) order_w(1, kn, kn & 1);
-                    if (t == 10) load_w(0, kn, ks < 3 ? wo1[0] : wo2[0]);
-                    if (t == 12) load_w(1, kn, ks < 3 ? wo1[1] : wo2[1]);
+                    if (t == O0) order_w(0, kn, kn & 1);
+                    if (t == O0 + 2) order_w(1, kn, kn & 1);
+                    if (t == L0) load_w(0, kn, ks < 3 ? wo1[0] : wo2[0]);
+                    if (t == L1) load_w(1, kn, ks < 3 ? wo1[1] : wo2[1]);
                 } else {
-                    if (T < 32) {   // X chunk u of the next stage: half of the permutation per odd step
+                    if (t == L1) load_w(1, kn, ks < 3 ? wo1[1] : wo2[1]);
+                    if constexpr (T < 4 * J) {   // X chunk u of the next stage: half of the permutation per odd step
                         constexpr int u = T >> 2;
                         if ((T & 2) == 0) {
                             px.x = __builtin_amdgcn_perm(xv[u].z, xv[u].x, 0x05040100u);
@@ -539,28 +555,10 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
                         }
                     }
                 }
-                if (T == 47) __syncthreads();
+                if (T == 3 * S - 1) __syncthreads();
                 __builtin_amdgcn_sched_barrier(0);
             };
-            auto steps8 = [&](auto b_c) {
-                constexpr int B = decltype(b_c)::value;
-                step(std::integral_constant<int, B + 0>{});
-                step(std::integral_constant<int, B + 1>{});
-                step(std::integral_constant<int, B + 2>{});
-                step(std::integral_constant<int, B + 3>{});
-                step(std::integral_constant<int, B + 4>{});
-                step(std::integral_constant<int, B + 5>{});
-                step(std::integral_constant<int, B + 6>{});
-                step(std::integral_constant<int, B + 7>{});
-            };
-            steps8(std::integral_constant<int, 0>{});
-            steps8(std::integral_constant<int, 8>{});
-            steps8(std::integral_constant<int, 16>{});
-            steps8(std::integral_constant<int, 24>{});
-            steps8(std::integral_constant<int, 32>{});
-            steps8(std::integral_constant<int, 40>{});
-            steps8(std::integral_constant<int, 48>{});
-            steps8(std::integral_constant<int, 56>{});
+            each_step(std::make_integer_sequence<int, 4 * S>{}, step);
         };
         int w = 0;
         if (nq & 1) {   // the first weak stage sits in tile 1
@@ -587,7 +585,7 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
 #pragma unroll
         for (int u = 2 * q; u < 2 * q + 2; ++u) {
             *reinterpret_cast<u4*>(sA + tile_off(xr + 32 * u, xc)) = ok ? wa[u] : zero4;
-            *reinterpret_cast<u4*>(sB + tile_off(xr + 32 * u, xc)) = ok ? wb[u] : zero4;
+            if (u < J) *reinterpret_cast<u4*>(sB + tile_off(xr + 32 * u, xc)) = ok ? wb[u < J ? u : 0] : zero4;
         }
     };
     if (nw > 0) {
@@ -599,12 +597,12 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     for (int w = 0; w < nw; ++w) {
         const unsigned char* sB = lds + (w & 1) * TILE_BYTES;
         const unsigned char* sA = lds + (2 + (w & 1)) * TILE_BYTES;
-        FragsT<2, 8> f[2];
-        load_frags_t<2, 8>(f[0], sA, sB, wave * 64, 0, lane, 0);
+        FragsT<2, J> f[2];
+        load_frags_t<2, J>(f[0], sA, sB, wave * 64, 0, lane, 0);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            if (ks < 3) load_frags_t<2, 8>(f[(ks + 1) & 1], sA, sB, wave * 64, 0, lane, ks + 1);
-            mfma_block_t<2, 8>(f[ks & 1], acc);
+            if (ks < 3) load_frags_t<2, J>(f[(ks + 1) & 1], sA, sB, wave * 64, 0, lane, ks + 1);
+            mfma_block_t<2, J>(f[ks & 1], acc);
             if (w + 1 < nw) store_weak(w + 1, ks);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -613,9 +611,9 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     }
     if (wide_stores) __syncthreads();   // the epilogue reuses the tiles
     if (wide_stores)
-        store_f16_lds_64x256<false>(acc, lds + wave * TILE_BYTES, Y, ldy, oc0 + wave * 64, L.oc, m0, M, lane);
+        store_f16_lds<false, J>(acc, lds + wave * TILE_BYTES, Y, ldy, oc0 + wave * 64, L.oc, m0, M, lane);
     else
-        store_f16_t<2, 8>(acc, Y, ldy, oc0 + wave * 64, L.oc, m0, M, lane);
+        store_f16_t<2, J>(acc, Y, ldy, oc0 + wave * 64, L.oc, m0, M, lane);
 }
 
 // ======================================================================================= backward dX
@@ -1046,7 +1044,7 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
             QEFT_STEPS64(step)
         };
         run_stages(stage);
-        store_f16_lds_64x256<true>(acc, lds + wave * TILE_BYTES, dX, lddx, icw, L.kq, m0, M, lane);
+        store_f16_lds<true, 8>(acc, lds + wave * TILE_BYTES, dX, lddx, icw, L.kq, m0, M, lane);
     };
 
     // ---- a wave in a weak half --------------------------------------------------------------------------
@@ -1083,7 +1081,7 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
             QEFT_STEPS64(step)
         };
         run_stages(stage);
-        store_f16_lds_64x256<false>(acc, lds + wave * TILE_BYTES, dX, lddx, icw, L.ic, m0, M, lane);
+        store_f16_lds<false, 8>(acc, lds + wave * TILE_BYTES, dX, lddx, icw, L.ic, m0, M, lane);
     };
 #undef QEFT_STEPS64
 #undef QEFT_STEPS8
@@ -1392,21 +1390,21 @@ bool gemm_fwd_supported(const Layer& L, int64_t M) {
 namespace {
 // Sum of the partial tiles of the split tiles: workgroup (tail index, r) adds the `splits` slots of rows 8 r .. 8 r + 7
 // of one tile, 8 outputs (16 bytes) per thread, fp32 sum in split order, one rounding.  n: columns of the output
-// (tiles_n tiles of them).
+// (tiles_n tiles of them); pm: rows of a panel (a slot has room for 256).
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const __half* __restrict__ part, int splits, int tiles_all, int tiles_n,
-                                                            int tail_first, int M, int n, __half* __restrict__ Y, int64_t ldy) {
+                                                            int tail_first, int M, int pm, int n, __half* __restrict__ Y, int64_t ldy) {
     const int tt = blockIdx.x >> 5, part32 = blockIdx.x & 31;
     const int tile = split_tail_tile(tiles_all, tail_first, tt);
     if (tile < 0) return;
     int t_n, t_m;
-    tile_coords(tile, tiles_n, (M + BT - 1) / BT, t_n, t_m);
-    const int n0 = t_n * BT, m0 = t_m * BT;
+    tile_coords(tile, tiles_n, (M + pm - 1) / pm, t_n, t_m);
+    const int n0 = t_n * BT, m0 = t_m * pm;
     const bool wide = (ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
     const __half* p0 = part + (size_t)tt * splits * (BT * BT);
     {
         const int row = part32 * 8 + (threadIdx.x >> 5), c = threadIdx.x & 31;
         const int m = m0 + row, col = n0 + 8 * c;
-        if (m >= M || col >= n) return;
+        if (row >= pm || m >= M || col >= n) return;
         float acc[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = 0.f;
@@ -1493,24 +1491,32 @@ hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __h
     const int tiles_oc = ceil_div(L.oc, BT), tiles_m = ceil_div(M, BT);
     hipError_t e;
     if (L.kq % BK == 0 && (L.kq > 0 || (L.k > 0 && L.k % BK == 0))) {   // whole stages: weights straight into MFMA operand registers
-        static bool attr = false;
-        if (!attr) {
-            e = hipFuncSetAttribute((const void*)gemm_fwd_rega_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, REGA_LDS);
+        // as many panels as of 256 rows, each of the fewest rows: the tiles, the splits and the workspace stay what they are,
+        // and a tile multiplies less padding (us, panels of 256 rows before -> now: 13824 x 5120 with its split, M = 300 / 333 /
+        // 400 / 1300: 74 / 75 / 77 / 204 -> 58 / 65 / 72 / 185; 4096 x 11008, M = 777: 96 -> 89; multiples of 256 unchanged)
+        using Kern = void (*)(Layer, const __half*, int, int64_t, __half*, int64_t, int, int, int, int, int, __half*);
+        static const Kern table[5] = {gemm_fwd_rega_kernel<4>, gemm_fwd_rega_kernel<5>, gemm_fwd_rega_kernel<6>, gemm_fwd_rega_kernel<7>,
+                                      gemm_fwd_rega_kernel<8>};
+        static bool attr[5] = {};
+        const int rows = ceil_div(M, tiles_m), j = rows <= 128 ? 4 : ceil_div(rows, 32);
+        const Kern kern = table[j - 4];
+        if (!attr[j - 4]) {
+            e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, REGA_LDS);
             if (e != hipSuccess) return e;
-            attr = true;
+            attr[j - 4] = true;
         }
         const int tiles = tiles_oc * tiles_m;
         const int wide = (ldy % 8 == 0) && (reinterpret_cast<uintptr_t>(Y) % 16 == 0);
         const SplitPlan p = ws ? gemm_fwd_plan(L, M) : SplitPlan();
         if (p.splits > 1) {
             __half* part = (__half*)ws;
-            gemm_fwd_rega_kernel<<<split_grid(tiles, p.tail_first, p.splits), 256, REGA_LDS, s>>>(L, X, (int)M, ldx, Y, ldy, tiles_oc, wide, p.splits,
-                                                                                                 p.chunks_per_split * 8, p.tail_first, part);
+            kern<<<split_grid(tiles, p.tail_first, p.splits), 256, REGA_LDS, s>>>(L, X, (int)M, ldx, Y, ldy, tiles_oc, wide, p.splits,
+                                                                                 p.chunks_per_split * 8, p.tail_first, part);
             splitk_reduce_kernel<<<32 * split_tail_tiles(tiles, p.tail_first), 256, 0, s>>>(part, p.splits, tiles, tiles_oc, p.tail_first, (int)M,
-                                                                                           L.oc, Y, ldy);
+                                                                                           32 * j, L.oc, Y, ldy);
             return hipGetLastError();
         }
-        gemm_fwd_rega_kernel<<<xcd_grid(tiles), 256, REGA_LDS, s>>>(L, X, (int)M, ldx, Y, ldy, tiles_oc, wide, 1, 0, 0, nullptr);
+        kern<<<xcd_grid(tiles), 256, REGA_LDS, s>>>(L, X, (int)M, ldx, Y, ldy, tiles_oc, wide, 1, 0, 0, nullptr);
     } else {
         static bool attr = false;
         e = raise_lds_limit((const void*)gemm_fwd_kernel, attr);
@@ -1557,7 +1563,7 @@ hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __
             gemm_dx_rega_kernel<<<split_grid(tiles, p.tail_first, p.splits), 256, DX_LDS, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, p.splits,
                                                                                               p.chunks_per_split * 8 * BK, p.tail_first, part);
             splitk_reduce_kernel<<<32 * split_tail_tiles(tiles, p.tail_first), 256, 0, s>>>(part, p.splits, tiles, tiles_ic, p.tail_first, (int)M,
-                                                                                           L.ic, dX, lddx);
+                                                                                           BT, L.ic, dX, lddx);
             return hipGetLastError();
         }
         gemm_dx_rega_kernel<<<xcd_grid(tiles), 256, DX_LDS, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, 1, 0, 0, nullptr);

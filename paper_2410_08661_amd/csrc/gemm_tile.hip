@@ -679,6 +679,11 @@ Est est_dx(const Layer& L, int64_t M) {
     const int nst = L.oc / 64;
     return best_of(2 * ceil_div(nst, 8) * 1.6 + 7, dx_tiles(L), M, 1.65, 2 * ceil_div(nst, 4) * 1.3 + 8);
 }
+// share of a 256-row tile's time that a GEMM panel of M rows takes (the forward's panels are cut to the rows)
+double panel(int64_t M) {
+    const int rows = ceil_div(M, ceil_div(M, 256)), j = rows <= 128 ? 4 : ceil_div(rows, 32);
+    return 0.15 + 0.85 * j / 8;
+}
 // the tiled GEMM without a split: rounds of 256 tiles x stages of 64
 double est_gemm(int channels, int64_t M, int stages, double per_stage) {
     const int64_t tiles = (int64_t)ceil_div(channels, 256) * ceil_div(M, 256);
@@ -697,8 +702,8 @@ double est_split(const GemmSplit& p, double fixed, double per_stage) { return fi
 bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws) {
     if (L.ng <= 0 || M <= 16 || ldx > (QEFT_MAX_DIM >> 1)) return false;
     const GemmSplit p = split_ws ? gemm_fwd_split(L, M) : GemmSplit{1, 0, 0, false};
-    if (p.splits > 1) return !p.tail && est_fwd(L, M).t < 0.95 * est_split(p, 11, 1.45);
-    const double g = est_gemm(L.oc, M, ceil_div(L.kq, 64) + ceil_div(L.k, 64), 1.15) * (L.kq % 64 == 0 ? 1.0 : 2.4);
+    if (p.splits > 1) return !p.tail && est_fwd(L, M).t < 0.95 * est_split(p, 11, 1.45 * panel(M));
+    const double g = est_gemm(L.oc, M, ceil_div(L.kq, 64) + ceil_div(L.k, 64), 1.15 * (L.kq % 64 == 0 ? panel(M) : 1.0)) * (L.kq % 64 == 0 ? 1.0 : 2.4);
     return est_fwd(L, M).t < 0.95 * g;
 }
 // The input gradient: whole stages of rows.  Against the split the estimate has to be a quarter ahead (its weak tiles run
