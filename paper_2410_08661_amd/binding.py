@@ -107,7 +107,8 @@ def _ptr(t) -> int:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream's handle without the Stream object around it: 0.2 us against 2.8, of an 8 us call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def make_desc(out_features, in_features, n_weak, bits=4, group_size=128, layout=0) -> qeft_desc_t:
