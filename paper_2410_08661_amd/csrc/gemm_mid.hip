@@ -261,6 +261,23 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
         mul_weak(b);
     }
 
+    // One output in plain order.  An infinite activation makes a group's sum x (1024 + q) and its Sx infinite alike, and their
+    // difference no number where x s (q - z) is an infinity: outputs that come out as no number are taken again from the
+    // weights themselves (until the sum is no number there either, which it then stays).
+    auto plain = [&](int m, int o) {
+        const __half* x = A.X + (size_t)m * A.ldx;
+        const uint32_t* words = A.qweight[li] + (size_t)o * A.stride;
+        const __half *sc = A.scales[li] + (size_t)o * A.gs, *zp = A.zeros[li] + (size_t)o * A.gs, *wk = A.weak[li] + (size_t)o * A.k;
+        float r = 0.f;
+#pragma clang loop unroll(disable)
+        for (int j = 0; j < A.kq + A.k && r == r; ++j) {
+            const float w = j < A.kq ? __half2float(sc[j >> 7]) * ((float)((words[j >> 3] >> (4 * (j & 7))) & 15u) - __half2float(zp[j >> 7]))
+                                     : __half2float(wk[j - A.kq]);
+            r = fmaf(__half2float(x[j]), w, r);
+        }
+        return r;
+    };
+
     // the waves' partial tiles meet in LDS (at most 4 channel tiles at a time); wave w sums tiles w, w + KS, ...
     constexpr int NC = NT < 4 ? NT : 4;
     __half* Y = A.Y[li] + (size_t)m0 * A.ldy[li] + o0;
@@ -281,6 +298,10 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) y[e] += p[e];
             }
+            const int row = 16 * (q / NC) + 4 * kb, col = 16 * (t0 + q % NC) + n;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (__builtin_expect(y[e] != y[e], 0) && t0 + q % NC < NT && row + e <= mlast && o0 + col < oc) y[e] = plain(m0 + row + e, o0 + col);
             // lane (n, kb) holds rows 4 kb .. 4 kb + 3 of channel n; a 4 x 4 transpose inside each quad of lanes gives it
             // channels 4 (n / 4) .. + 3 of row 4 kb + n % 4: one 8-byte store
             const uint32_t p0 = pack2(y[0], y[1]), p1 = pack2(y[2], y[3]);

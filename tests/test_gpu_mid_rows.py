@@ -64,3 +64,29 @@ def test_mid_rows_fractional_zero_points():
     y = B.qeft_linear_fwd(layer.desc, w, pad_cols(x)[0], ws=False)
     torch.cuda.synchronize()
     assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), "fractional zero-points")
+
+
+@pytest.mark.parametrize("oc,ic,k", [(200, 512, 128), (1032, 1352, 264), (264, 1160, 0)])
+def test_mid_rows_infinite_activations(oc, ic, k):
+    """Infinities as the sum itself treats them: x w where that is infinite, no number from inf x 0 and inf - inf."""
+    layer = HostLayer(oc, ic, k, 4, 128, seed=oc)
+    layer.codes[3, :] = 5                       # a whole row of zeros: inf x 0
+    layer.zeros[3, :] = 5
+    layer.qweight = qo.pack_codes(layer.codes, 4, layer.lay["row_stride_words"])
+    w = layer.to_device()
+    for m in (17, 40, 96):
+        x = synth.make_activations(m, ic, k, seed=m)
+        inf = np.float16(np.inf)
+        x[0, 5], x[3, ic - 1], x[m - 1, layer.kq - 1] = inf, -inf, inf
+        x[7, [2, 300]] = inf, -inf
+        x[11, 130] = np.nan
+        with np.errstate(invalid="ignore"):
+            want = np.stack([(row * layer.w64).sum(axis=1) for row in x.astype(np.float64)])
+        y = B.qeft_linear_fwd(layer.desc, w, pad_cols(x)[0], ws=False)
+        torch.cuda.synchronize()
+        got = y.cpu().numpy().astype(np.float64)
+        fine = np.isfinite(want)
+        assert np.array_equal(np.isfinite(got), fine) and np.array_equal(np.isnan(got), np.isnan(want)), f"M={m}"
+        assert np.array_equal(np.sign(got[np.isinf(want)]), np.sign(want[np.isinf(want)])), f"M={m}"
+        rows = fine.all(axis=1)
+        assert_close(y.cpu().numpy()[rows], want[rows], f"M={m}, finite rows")
