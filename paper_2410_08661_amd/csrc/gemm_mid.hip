@@ -341,12 +341,17 @@ bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx) {
     return M > 16 && L.bits == 4 && L.g == 128 && (L.kq % 8) == 0 && (L.k % 8) == 0 && (L.oc % 8) == 0 && ldx <= QEFT_MAX_DIM;
 }
 
-// Up to 96 rows (two panels) always; beyond that only where the caller gives no workspace for a K split and the GEMM's tiles
-// would occupy at most a quarter of the CUs.  (us, M = 96 / 128 here against the GEMM with its split and without: 4096 x 4096
-// 12 / 15 against 24 / 25 and 77; 12288 x 4096 27 / 41 against 36 / 39 and 82; 22016 x 4096 45 / 62 against 56 / 57 and 82;
-// 13824 x 5120 38 / 51 against 47 / 49 and 100.)
+// Up to 96 rows (two panels) always; up to 192 (four) where the alternative leaves most of the GPU idle: without a workspace
+// for a K split, where the GEMM's tiles would occupy at most a quarter of the CUs; with one, for layers of few channels whose
+// codes over all panels are few - the split's fixed cost (partial tiles, second launch) is then more than half of its time.
+// us, here against the GEMM with its split (and without): 4096 x 4096 at M = 97 / 128 / 192: 16.7 / 15.8 / 16.9 against 19.4 /
+// 19.7 / 23.3 (77); 5120 x 5120 at 97 / 144 / 145: 19.5 / 20.3 / 26.0 against 22.2 / 24.5 / 24.6; 1024 x 8192 at 128: 15.2
+// against 21.1; 2048 x 2048: 9.3 against 15.6; but 8192 x 2048 at 128: 16.5 against 15.9; 4096 x 11008: 39 against 28; 12288 x
+// 4096: 41 against 39 (82); 22016 x 4096: 62 against 57 (82); 13824 x 5120: 51 against 49 (100).
 bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws) {
-    return M <= 96 || (!split_ws && M <= 192 && ceil_div(L.oc, 256) <= 64);
+    if (M <= 96 || M > 192) return M <= 96;
+    if (!split_ws) return ceil_div(L.oc, 256) <= 64;
+    return L.oc <= 5120 && (int64_t)ceil_div(M, 48) * L.oc * L.ic <= (int64_t)3 * 5120 * 5120;
 }
 
 // Tiles of 16 NT channels and KS waves.  A CU holds one workgroup of eight waves or two of four (registers), and a workgroup

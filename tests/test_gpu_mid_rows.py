@@ -90,3 +90,19 @@ def test_mid_rows_infinite_activations(oc, ic, k):
         assert np.array_equal(np.sign(got[np.isinf(want)]), np.sign(want[np.isinf(want)])), f"M={m}"
         rows = fine.all(axis=1)
         assert_close(y.cpu().numpy()[rows], want[rows], f"M={m}, finite rows")
+
+
+@pytest.mark.parametrize("m", [97, 144, 192])
+def test_mid_rows_with_a_split_workspace(m):
+    """Few channels: this kernel rather than the K split, so the same bits with the workspace as without."""
+    layer = HostLayer(1032, 2056, 136, 4, 128, seed=m)
+    w = layer.to_device()
+    x = synth.make_activations(m, 2056, 136, seed=m)
+    xd = pad_cols(x)[0]
+    room = B.qeft_workspace_bytes(layer.desc, B.QEFT_OP_FWD, m)
+    assert room > 0
+    y = B.qeft_linear_fwd(layer.desc, w, xd, ws=torch.empty(room, dtype=torch.uint8, device="cuda"))
+    plain = B.qeft_linear_fwd(layer.desc, w, xd, ws=False)
+    torch.cuda.synchronize()
+    assert torch.equal(y, plain)
+    assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), f"M={m}")
