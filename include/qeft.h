@@ -172,11 +172,11 @@ size_t qeft_workspace_bytes(const qeft_desc_t* desc, int op, int64_t M);
 
 /* Forward of the fused layer (Sec. 3.2.1): Y = X[:, :Kq] . dq(Q)^T + X[:, Kq:] . weak^T in
  * one pass.  X fp16 [M][ldx] (ldx >= IC), Y fp16 [M][ldy] (ldy >= OC).  M <= 16 runs a
- * bandwidth-bound matrix-vector kernel, large M a tiled MFMA GEMM; the token counts in between (up to 96, without a
- * workspace up to 192 where the GEMM would fill only a fraction of the GPU) run a kernel of their own that streams the
- * layer once per 48 tokens, and smaller tiles serve the token counts whose large tiles would leave the GPU idle.  ws / ws_bytes: optional, see
- * qeft_workspace_bytes (4-bit layers: partial tiles of a split launch; 3-bit layers: the fp16 copy and,
- * beyond it, the partial tiles of its split); NULL / 0 is always valid. */
+ * bandwidth-bound matrix-vector kernel, large M a tiled MFMA GEMM; the token counts in between (up to 96; up to
+ * 192 for layers of few channels) run a kernel of their own that streams the layer once per 48 tokens, and smaller
+ * tiles serve the token counts whose large tiles would leave the GPU idle; neither touches a workspace that is given
+ * for the split.  ws / ws_bytes: optional, see qeft_workspace_bytes (4-bit layers: partial tiles of a split launch;
+ * 3-bit layers: the copy and, beyond it, the partial tiles of a split); NULL / 0 is always valid. */
 int qeft_linear_fwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void* X, int64_t M,
                     int64_t ldx, void* Y, int64_t ldy, void* ws, size_t ws_bytes, void* stream);
 

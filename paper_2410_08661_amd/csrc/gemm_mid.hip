@@ -1,4 +1,4 @@
-// Forward of 4-bit layers for 17 to about a hundred rows: several sequences decoded together, short prompts, draft tokens.
+// Forward of 4-bit layers for 17 to 192 rows: several sequences decoded together, short prompts, draft tokens.
 // (Paper Sec. 3.2.1; the rows between the matrix-vector kernels' 16 and the sizes at which 256 x 256 tiles occupy the GPU.)
 //
 // A layer's codes are read once per panel of up to 48 rows, where passes of the 16-row kernel read them once per 16 rows
