@@ -111,6 +111,15 @@ Layer nibble_copy_layer(const Layer& L, const void* ws) {
 }
 size_t nibble_copy_bytes(const Layer& D) { return ((size_t)D.oc * D.stride * 4 + 255) / 256 * 256; }
 
+// Room for the fp16 partial tiles of a split behind the 4-bit copy N, or NULL.  need, need_dense: what the split takes on this
+// copy and on the fp16 one.  Only with the whole amount that qeft_workspace_bytes reports: the bytes of the fp16 copy alone
+// would often hold the smaller copy and a split too, but a caller who gave no more keeps every sum in fp32.
+void* nibble_split_room(const Layer& N, size_t need, size_t need_dense, void* ws, size_t ws_bytes) {
+    const size_t at = nibble_copy_bytes(N);
+    const bool whole = need_dense > 0 && ws_bytes >= dense_copy_bytes(N) + need_dense;
+    return whole && need > 0 && ws_bytes >= at + need ? (char*)ws + at : nullptr;
+}
+
 // The forward of a layer the tiled kernels support, by rows and by what fills the GPU; split_ws: room for
 // gemm_fwd_split_workspace() bytes, or NULL.
 hipError_t fwd_rows(const Layer& L, const __half* x, int64_t M, int64_t ldx, __half* y, int64_t ldy, void* split_ws, hipStream_t s) {
@@ -236,8 +245,7 @@ int qeft_linear_fwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
         const Layer N = nibble_copy_layer(L, ws);
         if (nibble_copy_applies(L, M) && gemm_fwd_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
             if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
-            const size_t need = gemm_fwd_split_workspace(N, M);
-            void* split_ws = (need > 0 && ws_bytes >= nibble_copy_bytes(N) + need) ? (char*)ws + nibble_copy_bytes(N) : nullptr;
+            void* split_ws = nibble_split_room(N, gemm_fwd_split_workspace(N, M), gemm_fwd_split_workspace(dense_copy_layer(L, ws), M), ws, ws_bytes);
             return hip_status(fwd_rows(N, x, M, ldx, y, ldy, split_ws, s));
         }
         const Layer D = dense_copy_layer(L, ws);
@@ -327,8 +335,7 @@ int qeft_linear_bwd_dx(const qeft_desc_t* desc, const qeft_weight_t* w, const vo
         const Layer N = nibble_copy_layer(L, ws);
         if (nibble_copy_applies(L, M) && gemm_dx_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
             if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
-            const size_t need = gemm_dx_split_workspace(N, M);
-            void* split_ws = (need > 0 && ws_bytes >= nibble_copy_bytes(N) + need) ? (char*)ws + nibble_copy_bytes(N) : nullptr;
+            void* split_ws = nibble_split_room(N, gemm_dx_split_workspace(N, M), gemm_dx_split_workspace(dense_copy_layer(L, ws), M), ws, ws_bytes);
             return hip_status(dx_rows(N, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s));
         }
         const Layer D = dense_copy_layer(L, ws);

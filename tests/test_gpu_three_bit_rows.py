@@ -30,3 +30,28 @@ def test_three_bit_rows(oc, ic, k, dense):
                 torch.cuda.synchronize()
                 assert bool((back[size:] == 0x5A).all()), f"M={m}: wrote past the workspace"
                 assert_close(out.cpu().numpy(), ref, f"op {op}, M={m}, workspace {size}")
+
+
+# One rounding to fp16 is 2.1e-4 in norm over a uniform mantissa.  A call that keeps its sums in fp32 has two, independent of each
+# other: the weights' and the result's, 2.9e-4; fp16 partial sums are a third, 3.6e-4.  The bound lies half way.
+TWO_ROUNDINGS = 3.25e-4
+
+
+def _error(out, ref):
+    return float((out.double() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("dense", [False, True])
+def test_sums_stay_in_fp32_without_room_for_a_split(dense):
+    """The bytes of the fp16 copy alone: no fp16 partial tiles, also where they would fit behind the smaller copy."""
+    oc = ic = 5120
+    h = HostLayer(oc, ic, 128, 3, 128, seed=5, dense=dense)
+    w, w64 = h.to_device(), torch.from_numpy(h.w64).cuda()
+    for m in (40, 300, 1003):
+        xd = torch.from_numpy(synth.make_activations(m, ic, 0, seed=m)).cuda()
+        dyd = torch.from_numpy(synth.make_grad_output(m, oc, seed=m)).cuda()
+        ws = torch.empty(2 * oc * ic, dtype=torch.uint8, device="cuda")
+        for what, out, ref in (("forward", B.qeft_linear_fwd(h.desc, w, xd, ws=ws), xd.double() @ w64.t()),
+                               ("dX", B.qeft_linear_bwd_dx(h.desc, w, dyd, ws=ws), dyd.double() @ w64)):
+            err = _error(out, ref)
+            assert err <= TWO_ROUNDINGS, f"{what}, M={m}: {err:.3e}"
