@@ -54,6 +54,7 @@ int make_layer(const qeft_desc_t* d, const qeft_weight_t* w, Layer* L) {
     L->gs = (int)lay.group_stride;
     L->words = (int)lay.words_per_row;
     L->stride = (int)lay.row_stride_words;
+    L->once = 0;
     L->qweight = (const uint32_t*)w->qweight;
     L->scales = (const __half*)w->scales;
     L->zeros = (const __half*)w->zeros;
@@ -106,6 +107,7 @@ Layer nibble_copy_layer(const Layer& L, const void* ws) {
     D.dense = 0;
     D.words = (L.kq + 7) / 8;
     D.stride = (D.words + 15) / 16 * 16;
+    D.once = 1;   // as the fp16 copy does: s (q - z) in fp32, rounded once
     D.qweight = (const uint32_t*)ws;
     return D;
 }

@@ -215,7 +215,7 @@ __device__ __forceinline__ void each_step(std::integer_sequence<int, Ts...>, F&&
     (f(std::integral_constant<int, Ts>{}), ...);
 }
 
-template <int J>
+template <int J, bool ONCE>
 __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __half* __restrict__ X, int M, int64_t ldx,
                                                             __half* __restrict__ Y, int64_t ldy, int tiles_oc, int wide_stores,
                                                             int splits, int sps, int tail_first, __half* __restrict__ part) {
@@ -292,6 +292,8 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     u4 xv[J];           // X of the stage after the current one
     u2 szs[2], szz[2];  // scales / zero-points of four consecutive groups, per row block
     uint32_t lsz[2];    // latched group: zero-point in the low half, scale in the high half
+    float nzs[2];       // ... and - zero-point * scale (ONCE)
+    _Float16 lo[8];     // first halves of the pairs (ONCE)
     u4 afr[2][2];       // A fragments as packed halfs, written one pair at a time
     h8 bfr[2][J];
     uint32_t cq[8];     // the conversion pipeline: one register per pair of the k-block being converted
@@ -312,6 +314,7 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
         for (int i = 0; i < 2; ++i) {
             const uint64_t s64 = ((uint64_t)szs[i].y << 32) | szs[i].x, z64 = ((uint64_t)szz[i].y << 32) | szz[i].x;
             lsz[i] = ((uint32_t)(z64 >> sh) & 0xffffu) | ((uint32_t)(s64 >> sh) << 16);
+            if constexpr (ONCE) nzs[i] = neg_zs(bits_h2(lsz[i]).x, bits_h2(lsz[i]).y);
         }
     };
     auto put_x = [&](int u, int buf) {
@@ -360,7 +363,15 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
         }
         latch(0);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) afr[0][i] = __builtin_bit_cast(u4, dequant_word(araw[0][i].x, lsz[i], cst));
+        for (int i = 0; i < 2; ++i) {
+            const h8 raw = __builtin_bit_cast(h8, dequant_word(araw[0][i].x, ONCE ? 0x3c000000u : lsz[i], cst));   // (z = 0, s = 1: the codes)
+            h8 w = raw;
+            if constexpr (ONCE) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = dequant_once(raw[e], bits_h2(lsz[i]).y, nzs[i]);
+            }
+            afr[0][i] = __builtin_bit_cast(u4, w);
+        }
         // the pipeline finishes "the previous k-block's last pair" in its first two steps: hand it
         // that pair of the first k-block in the state it expects (masked and rebased)
         cq[7] = h2_bits(bits_h2(((araw[0][1].x >> 8) & cst.m1) | cst.g1) - h2{(_Float16)64.f, (_Float16)64.f});
@@ -396,8 +407,8 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, afr[ks & 1][i]), bfr[ks & 1][j], acc[i][j], 0, 0, 0);
                 // Conversion of the next k-block's two words, software-pipelined so that no step holds
                 // two dependent instructions: pair a = t / 2 is masked at step 2a, rebased at 2a + 1,
-                // has its zero-point subtracted at 2a + 2 and is scaled at 2a + 3 (the last pair
-                // finishes in the first two steps of the following k-block, before its row block is used).
+                // has its zero-point subtracted at 2a + 2 and is scaled at 2a + 3 (ONCE: its first half, its second half;
+                // the last pair finishes in the first two steps of the following k-block, before its row block is used).
                 const h2 b0 = h2{(_Float16)1024.f, (_Float16)1024.f}, b1 = h2{(_Float16)64.f, (_Float16)64.f};
                 if constexpr (J == 8) {
                     constexpr int a = t >> 1, ap = (a + 7) & 7;   // this step's young pair, and the one two steps older
@@ -408,11 +419,13 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
                         if ((a & 3) == 1) w8[aci] = w >> 8;
                         const uint32_t src = (a & 3) < 2 ? w : w8[aci];
                         cq[a] = (a & 1) ? ((src & cst.m1) | cst.g1) : ((src & cst.m0) | cst.g0);
-                        cq[ap] = h2_bits(bits_h2(cq[ap]) - h2{zs_old.x, zs_old.x});
+                        if constexpr (ONCE) lo[ap] = dequant_once_first(bits_h2(cq[ap]).x, zs_old.y, nzs[apci]);
+                        else cq[ap] = h2_bits(bits_h2(cq[ap]) - h2{zs_old.x, zs_old.x});
                     } else {
                         cq[a] = h2_bits(bits_h2(cq[a]) - ((a & 1) ? b1 : b0));
                         // pair 7 of the previous conversion belongs to the k-block now being multiplied
-                        afr[a == 0 ? (ks & 1) : (kn & 1)][apci][ap & 3] = h2_bits(bits_h2(cq[ap]) * h2{zs_old.y, zs_old.y});
+                        afr[a == 0 ? (ks & 1) : (kn & 1)][apci][ap & 3] =
+                            h2_bits(ONCE ? h2{lo[ap], dequant_once(bits_h2(cq[ap]).y, zs_old.y, nzs[apci])} : bits_h2(cq[ap]) * h2{zs_old.y, zs_old.y});
                     }
                 } else {   // fewer steps: the four operations of the eight pairs one after the other, evenly over the k-block
 #pragma unroll
@@ -425,8 +438,12 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
                             const uint32_t src = (pr & 3) < 2 ? w : w8[ci];
                             cq[pr] = (pr & 1) ? ((src & cst.m1) | cst.g1) : ((src & cst.m0) | cst.g0);
                         } else if (o < 16) cq[pr] = h2_bits(bits_h2(cq[pr]) - ((pr & 1) ? b1 : b0));
-                        else if (o < 24) cq[pr] = h2_bits(bits_h2(cq[pr]) - h2{zs.x, zs.x});
-                        else afr[kn & 1][ci][pr & 3] = h2_bits(bits_h2(cq[pr]) * h2{zs.y, zs.y});
+                        else if (o < 24) {
+                            if constexpr (ONCE) lo[pr] = dequant_once_first(bits_h2(cq[pr]).x, zs.y, nzs[ci]);
+                            else cq[pr] = h2_bits(bits_h2(cq[pr]) - h2{zs.x, zs.x});
+                        } else
+                            afr[kn & 1][ci][pr & 3] =
+                                h2_bits(ONCE ? h2{lo[pr], dequant_once(bits_h2(cq[pr]).y, zs.y, nzs[ci])} : bits_h2(cq[pr]) * h2{zs.y, zs.y});
                     }
                 }
                 if ((t & 1) == 0) {
@@ -722,11 +739,14 @@ constexpr int DX_LINE = 144;                      // 64 rows x 2 bytes + 16: con
 constexpr int DX_HALF = 128 * DX_LINE;            // lines of one half (a quantized half uses the first 32)
 constexpr int DX_LINES = 2 * DX_HALF;
 constexpr int DX_SZ = 2 * 2 * 64 * 2;             // [half][zero, scale][row] fp16
+constexpr int DX_SZ_ONCE = 2 * (64 * 4 + 64 * 2); // [half][- zero * scale fp32, scale fp16][row]
 constexpr int DX_LINE_BASE = 2 * TILE_BYTES;      // dY0 dY1 | lines0 lines1 | sz0 sz1
 constexpr int DX_SZ_BASE = DX_LINE_BASE + 2 * DX_LINES;
-constexpr int DX_LDS = DX_SZ_BASE + 2 * DX_SZ;
+constexpr int DX_LDS = DX_SZ_BASE + 2 * DX_SZ_ONCE;
 
-template <int H0, int H1>   // kinds of the tile's two halves: 0 quantized, 1 weak
+// H0, H1: kinds of the tile's two halves: 0 quantized, 1 weak.  ONCE: see dequant_once; the rows' - zero * scale in fp32 then take the
+// zero-points' place (four registers, and a third LDS read per k-block).
+template <int H0, int H1, bool ONCE>
 __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict__ dY, int M, int64_t lddy,
                                         __half* __restrict__ dX, int64_t lddx, int ic0, int m0, unsigned char* lds) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -737,6 +757,8 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
     using lds_u4 = __attribute__((address_space(3))) u4;
     using lds_u32 = __attribute__((address_space(3))) uint32_t;
     using lds_u16 = __attribute__((address_space(3))) unsigned short;
+    using lds_f32 = __attribute__((address_space(3))) float;
+    using lds_f4 = __attribute__((address_space(3))) f4;
     using lds_h8 = __attribute__((address_space(3))) h8;
     using gptr = const __attribute__((address_space(1))) char*;
     using g_u4 = const __attribute__((address_space(1))) u4;
@@ -798,7 +820,9 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
         const int half = (H0 == 1) ? n / 2 : 1;
         wwr[n] = lds0 + DX_LINE_BASE + (uint32_t)half * DX_HALF + (uint32_t)(8 * (xc + 8 * (n & 1))) * DX_LINE + lw;
     }
-    uint32_t szw = lds0 + DX_SZ_BASE + (uint32_t)((tid >> 6) & 1) * 256u + (uint32_t)(tid & 63) * 2u;
+    constexpr uint32_t SZ = ONCE ? DX_SZ_ONCE : DX_SZ, SC = ONCE ? 256 : 128;   // bytes of a buffer; where a half's scales start
+    uint32_t szw = lds0 + DX_SZ_BASE + (uint32_t)((tid >> 6) & 1) * (SZ / 2) + (uint32_t)(tid & 63) * 2u;
+    const uint32_t szw4 = szw + (uint32_t)((tid & 63) * 2);
 
     u4 dyv[8];            // dY of the stage after the current one
     u4 cw0, cw1;          // its code words (two rows)
@@ -834,8 +858,12 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
     };
     auto put_sz = [&](int buf) {
         if (sz_wave) {
-            *reinterpret_cast<lds_u16*>(szw + (uint32_t)(buf * DX_SZ)) = zv;
-            *reinterpret_cast<lds_u16*>(szw + (uint32_t)(128 + buf * DX_SZ)) = sv;
+            if constexpr (ONCE)
+                *reinterpret_cast<lds_f32*>(szw4 + (uint32_t)(buf * SZ)) =
+                    neg_zs(__builtin_bit_cast(_Float16, zv), __builtin_bit_cast(_Float16, sv));
+            else
+                *reinterpret_cast<lds_u16*>(szw + (uint32_t)(buf * SZ)) = zv;
+            *reinterpret_cast<lds_u16*>(szw + (uint32_t)(SC + buf * SZ)) = sv;
         }
     };
     auto put_weak = [&](int n, int buf) {    // channel e of the block: rows 2 rp | 2 rp + 1
@@ -969,16 +997,22 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
             for (int kn = 0; kn < 4; ++kn)
                 crd[kn] = lds0 + DX_LINE_BASE + (uint32_t)half * DX_HALF + (uint32_t)ln * DX_LINE + ((uint32_t)((fk ^ cl) ^ (2 * kn)) << 4);
         }
-        uint32_t szr = lds0 + DX_SZ_BASE + (uint32_t)half * 256u + 16u * fk;
+        uint32_t szr = lds0 + DX_SZ_BASE + (uint32_t)half * (SZ / 2) + 16u * fk;
         uint32_t nsh = 8u * (uint32_t)(fr >> 4);
         u4 cf;            // code words of the k-block being converted: register p = rows 2p | 2p+1
         u4 cfs;           // ... shifted to this lane's nibbles
         h8 zf, sf;        // zero-points and scales of its 8 rows
+        f4 nzs[2];        // - zero-point * scale (ONCE)
+        _Float16 lo[8];   // first halves of the pairs (ONCE)
         uint32_t cq[8];   // the conversion pipeline, one register per pair
         auto read_codes = [&](int buf, int kn) {
             cf = *reinterpret_cast<const lds_u4*>(crd[kn] + (uint32_t)(buf * DX_LINES));
-            zf = *reinterpret_cast<const lds_h8*>(szr + (uint32_t)(32 * kn + buf * DX_SZ));
-            sf = *reinterpret_cast<const lds_h8*>(szr + (uint32_t)(128 + 32 * kn + buf * DX_SZ));
+            if constexpr (ONCE) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) nzs[h] = *reinterpret_cast<const lds_f4*>(szr + 16u * fk + (uint32_t)(64 * kn + 16 * h + buf * SZ));
+            } else
+                zf = *reinterpret_cast<const lds_h8*>(szr + (uint32_t)(32 * kn + buf * SZ));
+            sf = *reinterpret_cast<const lds_h8*>(szr + (uint32_t)(SC + 32 * kn + buf * SZ));
         };
         const h2 b0 = h2{(_Float16)1024.f, (_Float16)1024.f}, b1 = h2{(_Float16)64.f, (_Float16)64.f};
         // pair a = 4 t + p (fragment t, register p) goes through: mask, rebase, zero-point, scale
@@ -992,11 +1026,13 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
         };
         auto cv_zero = [&](auto a_c) {
             constexpr int a = decltype(a_c)::value, p = a & 3;
-            cq[a] = h2_bits(bits_h2(cq[a]) - h2{zf[2 * p], zf[2 * p + 1]});
+            if constexpr (ONCE) lo[a] = dequant_once_first(bits_h2(cq[a]).x, sf[2 * p], nzs[p >> 1][2 * (p & 1)]);
+            else cq[a] = h2_bits(bits_h2(cq[a]) - h2{zf[2 * p], zf[2 * p + 1]});
         };
         auto cv_scale = [&](auto a_c, int set) {
             constexpr int a = decltype(a_c)::value, p = a & 3;
-            afr[set][a >> 2][p] = h2_bits(bits_h2(cq[a]) * h2{sf[2 * p], sf[2 * p + 1]});
+            afr[set][a >> 2][p] = h2_bits(ONCE ? h2{lo[a], dequant_once(bits_h2(cq[a]).y, sf[2 * p + 1], nzs[p >> 1][2 * (p & 1) + 1])}
+                                               : bits_h2(cq[a]) * h2{sf[2 * p], sf[2 * p + 1]});
         };
         // pair a enters the pipeline at step 4 + a of the k-block (the lines are read at step 0, shifted
         // at step 3) and leaves it at step 7 + a <= 14
@@ -1097,6 +1133,7 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
 // a multiple of 64: whole stages) and stores its partial tile as fp16 into its slot of `part`; splitk_reduce_kernel
 // adds them.  Which tiles are split: split_tile.  The rows of a stored layer are independent, so a split is simply the
 // layer made of those rows.
+template <bool ONCE>
 __device__ __forceinline__ void dx_rega_body(unsigned char* lds, Layer L, const __half* __restrict__ dY, int M, int64_t lddy,
                                              __half* __restrict__ dX, int64_t lddx, int tiles_ic, int splits,
                                              int rps, int tail_first, __half* __restrict__ part) {
@@ -1121,15 +1158,16 @@ __device__ __forceinline__ void dx_rega_body(unsigned char* lds, Layer L, const 
     // a half is weak when it starts at or past Kq (Kq % 128 == 0); without a weak block the surplus
     // half of the last tile runs as a quantized one on clamped addresses and stores nothing
     const bool w0 = L.k > 0 && ic0 >= L.kq, w1 = L.k > 0 && ic0 + 128 >= L.kq;
-    if (w0) dx_tile<1, 1>(L, dY, M, lddy, dX, lddx, ic0, m0, lds);
-    else if (w1) dx_tile<0, 1>(L, dY, M, lddy, dX, lddx, ic0, m0, lds);
-    else dx_tile<0, 0>(L, dY, M, lddy, dX, lddx, ic0, m0, lds);
+    if (w0) dx_tile<1, 1, ONCE>(L, dY, M, lddy, dX, lddx, ic0, m0, lds);
+    else if (w1) dx_tile<0, 1, ONCE>(L, dY, M, lddy, dX, lddx, ic0, m0, lds);
+    else dx_tile<0, 0, ONCE>(L, dY, M, lddy, dX, lddx, ic0, m0, lds);
 }
+template <bool ONCE>
 __global__ __launch_bounds__(256) void gemm_dx_rega_kernel(Layer L, const __half* __restrict__ dY, int M, int64_t lddy,
                                                            __half* __restrict__ dX, int64_t lddx, int tiles_ic, int splits,
                                                            int rps, int tail_first, __half* __restrict__ part) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-    dx_rega_body(lds, L, dY, M, lddy, dX, lddx, tiles_ic, splits, rps, tail_first, part);
+    dx_rega_body<ONCE>(lds, L, dY, M, lddy, dX, lddx, tiles_ic, splits, rps, tail_first, part);
 }
 
 // ======================================================================================= weak gradient
@@ -1350,7 +1388,7 @@ __global__ __launch_bounds__(256) void gemm_dx_dw_kernel(Layer L, const __half* 
         weak_grad_strip_body(lds, (int)blockIdx.x - n_dx, L.oc, L.k, dY, M, lddy, Xw, ldxw, part, splits, chunk, dW, out_f32, accumulate);
         return;
     }
-    dx_rega_body(lds, L, dY, M, lddy, dX, lddx, tiles_ic, 1, 0, 0, nullptr);
+    dx_rega_body<false>(lds, L, dY, M, lddy, dX, lddx, tiles_ic, 1, 0, 0, nullptr);
 }
 
 __global__ __launch_bounds__(256) void weak_grad_reduce_kernel(const float* __restrict__ part, int splits, int64_t n,
@@ -1495,15 +1533,17 @@ hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __h
         // and a tile multiplies less padding (us, panels of 256 rows before -> now: 13824 x 5120 with its split, M = 300 / 333 /
         // 400 / 1300: 74 / 75 / 77 / 204 -> 58 / 65 / 72 / 185; 4096 x 11008, M = 777: 96 -> 89; multiples of 256 unchanged)
         using Kern = void (*)(Layer, const __half*, int, int64_t, __half*, int64_t, int, int, int, int, int, __half*);
-        static const Kern table[5] = {gemm_fwd_rega_kernel<4>, gemm_fwd_rega_kernel<5>, gemm_fwd_rega_kernel<6>, gemm_fwd_rega_kernel<7>,
-                                      gemm_fwd_rega_kernel<8>};
-        static bool attr[5] = {};
+#define QEFT_REGA(ONCE) {gemm_fwd_rega_kernel<4, ONCE>, gemm_fwd_rega_kernel<5, ONCE>, gemm_fwd_rega_kernel<6, ONCE>, \
+                         gemm_fwd_rega_kernel<7, ONCE>, gemm_fwd_rega_kernel<8, ONCE>}
+        static const Kern table[2][5] = {QEFT_REGA(false), QEFT_REGA(true)};
+#undef QEFT_REGA
+        static bool attr[2][5] = {};
         const int rows = ceil_div(M, tiles_m), j = rows <= 128 ? 4 : ceil_div(rows, 32);
-        const Kern kern = table[j - 4];
-        if (!attr[j - 4]) {
+        const Kern kern = table[L.once][j - 4];
+        if (!attr[L.once][j - 4]) {
             e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, REGA_LDS);
             if (e != hipSuccess) return e;
-            attr[j - 4] = true;
+            attr[L.once][j - 4] = true;
         }
         const int tiles = tiles_oc * tiles_m;
         const int wide = (ldy % 8 == 0) && (reinterpret_cast<uintptr_t>(Y) % 16 == 0);
@@ -1550,23 +1590,24 @@ hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __
     const int tiles_m = ceil_div(M, BT), tiles_ic = ceil_div(L.ic, BT);
     hipError_t e;
     if (L.oc % BK == 0 && L.kq % 128 == 0 && L.k % 8 == 0) {
-        static bool attr = false;
-        if (!attr) {
-            e = hipFuncSetAttribute((const void*)gemm_dx_rega_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, DX_LDS);
+        static bool attr[2] = {};
+        const auto kern = L.once ? gemm_dx_rega_kernel<true> : gemm_dx_rega_kernel<false>;
+        if (!attr[L.once]) {
+            e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DX_LDS);
             if (e != hipSuccess) return e;
-            attr = true;
+            attr[L.once] = true;
         }
         const int tiles = tiles_ic * tiles_m;
         const SplitPlan p = ws ? gemm_dx_plan(L, M) : SplitPlan();
         if (p.splits > 1) {
             __half* part = (__half*)ws;
-            gemm_dx_rega_kernel<<<split_grid(tiles, p.tail_first, p.splits), 256, DX_LDS, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, p.splits,
+            kern<<<split_grid(tiles, p.tail_first, p.splits), 256, DX_LDS, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, p.splits,
                                                                                               p.chunks_per_split * 8 * BK, p.tail_first, part);
             splitk_reduce_kernel<<<32 * split_tail_tiles(tiles, p.tail_first), 256, 0, s>>>(part, p.splits, tiles, tiles_ic, p.tail_first, (int)M,
                                                                                            BT, L.ic, dX, lddx);
             return hipGetLastError();
         }
-        gemm_dx_rega_kernel<<<xcd_grid(tiles), 256, DX_LDS, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, 1, 0, 0, nullptr);
+        kern<<<xcd_grid(tiles), 256, DX_LDS, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, 1, 0, 0, nullptr);
     } else {
         static bool attr = false;
         e = raise_lds_limit((const void*)gemm_dx_kernel, attr);

@@ -57,6 +57,19 @@ __device__ __forceinline__ uint32_t dequant_pair(uint32_t hbits, h2 z2, h2 s2) {
     return h2_bits(((bits_h2(hbits) - k1024) - z2) * s2);
 }
 
+// One weight with one rounding for any zero-point: q s - z s in fp32, rounded to fp16 (nzs = -z s is exact: 11 x 11 bits; for whole
+// z of 11 bits or less so is the difference, and the result is dequant_pair's).  One v_fma_mix instruction that writes half a
+// register: a pair takes two, as the packed subtraction and product do.  Only the 4-bit copies of 3-bit layers are converted so
+// (the fp16 copy they replace has the single rounding); it costs 0 to 5 % of a call (us, packed -> this: 4096 x 11008 in 3 bits, dense
+// codes, forward at 1003 / 2048 rows 107 / 177 -> 110 / 182, input gradient 102 / 181 -> 104 / 188; 4096 x 4096, 512 rows: 36 -> 38).
+__device__ __forceinline__ _Float16 dequant_once(_Float16 q, _Float16 s, float nzs) { return (_Float16)__builtin_fmaf((float)q, (float)s, nzs); }
+__device__ __forceinline__ _Float16 dequant_once_first(_Float16 q, _Float16 s, float nzs) {
+    _Float16 r = dequant_once(q, s, nzs);
+    asm("" : "+v"(r));   // (else the compiler joins the halves: two fp32 results and a conversion, three instructions)
+    return r;
+}
+__device__ __forceinline__ float neg_zs(_Float16 z, _Float16 s) { return -((float)z * (float)s); }
+
 // 8 halfs x0..x7 -> (x0,x4)(x1,x5)(x2,x6)(x3,x7): the order nibbles leave the mask-and-or conversion
 __device__ __forceinline__ u4 permute_x(u4 v) {
     u4 r;

@@ -30,6 +30,8 @@ namespace {
 typedef __attribute__((address_space(3))) u4 lds_u4;
 typedef __attribute__((address_space(3))) h8 lds_h8;
 typedef __attribute__((address_space(3))) uint16_t lds_u16;
+typedef __attribute__((address_space(3))) float lds_f32;
+typedef __attribute__((address_space(3))) f4 lds_f4;
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef short s8 __attribute__((ext_vector_type(8)));
@@ -135,6 +137,10 @@ struct Conv {
     }
     __device__ __forceinline__ void zero(int p, h2 z) { cq[p] = h2_bits(bits_h2(cq[p]) - z); }
     __device__ __forceinline__ uint32_t scale(int p, h2 s) const { return h2_bits(bits_h2(cq[p]) * s); }
+    // the same pair with one rounding (see dequant_once), half by half
+    _Float16 lo[8];
+    __device__ __forceinline__ void first(int p, h2 s, float nzs) { lo[p] = dequant_once_first(bits_h2(cq[p]).x, s.x, nzs); }
+    __device__ __forceinline__ uint32_t second(int p, h2 s, float nzs) const { return h2_bits(h2{lo[p], dequant_once(bits_h2(cq[p]).y, s.y, nzs)}); }
 };
 
 // The rows of the activation operand ([m][contraction], fp16): the 128 threads of a K group fetch its tile of 32 J rows x
@@ -174,7 +180,7 @@ struct RowTile {
 };
 
 // ---- forward -----------------------------------------------------------------------------------------------------
-template <int J, int KW, int MINW>
+template <int J, int KW, int MINW, bool ONCE>
 __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const __half* __restrict__ X, int M, int64_t ldx, __half* __restrict__ Y,
                                                                  int64_t ldy, int tiles_n, int tiles_m) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -293,12 +299,14 @@ __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const
     h8 bfr[4][J];   // fragments are read two k-blocks ahead
     u4 afr[2][2];
     h2 z2[2], s2[2];
+    float mzs[2];   // - zero-point * scale (ONCE)
     auto latch = [&](int q) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const h2 sv = bits_h2(q < 2 ? szs[i].x : szs[i].y), zv = bits_h2(q < 2 ? szz[i].x : szz[i].y);
             z2[i] = (q & 1) ? h2{zv.y, zv.y} : h2{zv.x, zv.x};
             s2[i] = (q & 1) ? h2{sv.y, sv.y} : h2{sv.x, sv.x};
+            if constexpr (ONCE) mzs[i] = neg_zs(z2[i].x, s2[i].x);
         }
     };
 #pragma unroll
@@ -308,8 +316,9 @@ __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const
     for (int p = 0; p < 8; ++p) {
         cv.mask(p, araw[0][p >> 2].x);
         cv.base(p);
-        cv.zero(p, z2[p >> 2]);
-        afr[0][p >> 2][p & 3] = cv.scale(p, s2[p >> 2]);
+        if constexpr (ONCE) cv.first(p, s2[p >> 2], mzs[p >> 2]);
+        else cv.zero(p, z2[p >> 2]);
+        afr[0][p >> 2][p & 3] = ONCE ? cv.second(p, s2[p >> 2], mzs[p >> 2]) : cv.scale(p, s2[p >> 2]);
     }
 #pragma unroll
     for (int j = 0; j < J; ++j) bfr[0][j] = x.frag(j, 0, 0), bfr[1][j] = x.frag(j, 0, 1);
@@ -344,8 +353,11 @@ __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const
                     const int ph = o >> 3, p = o & 7;
                     if (ph == 0) cv.mask(p, araw[EN % DA][p >> 2][kn]);
                     else if (ph == 1) cv.base(p);
-                    else if (ph == 2) cv.zero(p, z2[p >> 2]);
-                    else afr[kn & 1][p >> 2][p & 3] = cv.scale(p, s2[p >> 2]);
+                    else if (ph == 2) {
+                        if constexpr (ONCE) cv.first(p, s2[p >> 2], mzs[p >> 2]);
+                        else cv.zero(p, z2[p >> 2]);
+                    } else
+                        afr[kn & 1][p >> 2][p & 3] = ONCE ? cv.second(p, s2[p >> 2], mzs[p >> 2]) : cv.scale(p, s2[p >> 2]);
                 }
                 if (m % 2 == 0) bfr[(ks + 2) & 3][m / 2] = x.frag(m / 2, ks < 2 ? CUR : NXT, (ks + 2) & 3);
                 // next stage's activations: chunk u permuted in slot 2 u, stored and refilled in slot 2 u + 1
@@ -383,14 +395,15 @@ __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const
 // lane gets is a packed word as in the forward, and the same conversion follows with the rows' zero-points and scales as
 // vectors.  A tile is either quantized or weak, whatever Kq (the GEMM of gemm.hip
 // puts a partial group and weak columns into one tile and then takes its LDS-staged form); weak ones read fp16 with the 16-bit form.
-template <int J, int KW, int MINW>
+template <int J, int KW, int MINW, bool ONCE>
 __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const __half* __restrict__ dY, int M, int64_t lddy,
                                                                 __half* __restrict__ dX, int64_t lddx, int tiles_n, int tiles_m) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     constexpr int DX = 2;
     using Rows = RowTile<J, DX>;
     constexpr int NX = Rows::NX, XT = Rows::XT, S = 2 * J;
-    constexpr int CT = 64 * 64, VT = 8 * 32;    // a stage of codes (64 rows of 128 channels) and of parameters (per 8 rows: zero-points, scales)
+    // a stage of codes (64 rows of 128 channels) and of parameters (per 8 rows: zero-points, scales; ONCE: fp32 - zero-point * scale, scales)
+    constexpr int CT = 64 * 64, VS = ONCE ? 32 : 16, VT = 8 * (VS + 16);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ow = wave & 1, kw = wave >> 1;
@@ -429,23 +442,27 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
         const uint32_t wpitch = (uint32_t)L.stride * 4u;
         const unsigned char* pt = reinterpret_cast<const unsigned char*>((ow == 0 ? L.scales : L.zeros) + c0 / 128);   // (threads 0 .. 63: wave 0 of the K group)
         const uint32_t coff = (uint32_t)crow * wpitch + 32u * cpart, poff = (uint32_t)prow * (uint32_t)(L.gs * 2);
+        const unsigned char* st_ = reinterpret_cast<const unsigned char*>(L.scales + c0 / 128);
         u4 cw[DX][2];
-        uint32_t pv[DX];
+        uint32_t pv[DX], ps[DX];   // ps: the scale beside the zero-point (ONCE)
         auto load_c = [&](int set, int st) {   // (stages past the last repeat it; their rows of dY are zeroed)
             const int sc = min(st, nst - 1);
             gptr p = sbase(wt + (size_t)(64 * sc) * wpitch) + coff;
             cw[set][0] = *reinterpret_cast<g_u4*>(p);
             cw[set][1] = *reinterpret_cast<g_u4*>(p + 16);
             pv[set] = *reinterpret_cast<g_u16*>(sbase(pt + (size_t)(64 * sc) * (uint32_t)(L.gs * 2)) + poff);
+            if constexpr (ONCE) ps[set] = *reinterpret_cast<g_u16*>(sbase(st_ + (size_t)(64 * sc) * (uint32_t)(L.gs * 2)) + poff);
         };
         // chunk c (32 channels) of row r sits in slot c ^ (r / 4 % 4): the 16 rows of a transposing read then spread over the banks
         const uint32_t cst = lc + (uint32_t)(crow * 64);
         const uint32_t csw = (uint32_t)((crow >> 2) & 3);
-        const uint32_t pst = lv + (uint32_t)((prow >> 3) * 32 + (ow == 0 ? 16 : 0) + 2 * ((prow & 3) * 2 + ((prow >> 2) & 1)));
+        const int pat = (prow & 3) * 2 + ((prow >> 2) & 1);   // rows r and r + 4 of 8 side by side, as a word's pairs
+        const uint32_t pst = lv + (uint32_t)((prow >> 3) * (VS + 16) + (ow == 0 ? VS + 2 * pat : (VS / 8) * pat));
         auto put_c = [&](int set, int buf) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) *reinterpret_cast<lds_u4*>(cst + (((2 * cpart + h) ^ csw) << 4) + (uint32_t)(buf * CT)) = cw[set][h];
-            *reinterpret_cast<lds_u16*>(pst + (uint32_t)(buf * VT)) = (uint16_t)pv[set];
+            if (ONCE && ow == 1) *reinterpret_cast<lds_f32*>(pst + (uint32_t)(buf * VT)) = neg_zs(bits_h2(pv[set]).x, bits_h2(ps[set]).x);
+            else *reinterpret_cast<lds_u16*>(pst + (uint32_t)(buf * VT)) = (uint16_t)pv[set];
         };
         // a transposing read hands lane s of each 16 the 16 rows of column s of a 16 x 16 block of codes; block row 32 p + 16 fk,
         // column block 32 i + 16 (lane / 16 % 2) of the wave's 64 channels
@@ -458,10 +475,24 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
             raw[p][i] = __builtin_amdgcn_ds_read_tr4_b64_v2i32((lds_v2i*)(size_t)(trb[i] + (uint32_t)(p * 2048 + buf * CT)));
         };
         u4 zv[2], sv[2];
-        const uint32_t vb = lv + 64u * fk;
+        f4 nzs[2][2];
+        const uint32_t vb = lv + (uint32_t)(2 * (VS + 16)) * fk;
         auto read_par = [&](int set, int ks, int buf) {
-            zv[set] = *reinterpret_cast<const lds_u4*>(vb + (uint32_t)(chunk_of(ks) * 32 + buf * VT));
-            sv[set] = *reinterpret_cast<const lds_u4*>(vb + (uint32_t)(chunk_of(ks) * 32 + 16 + buf * VT));
+            const uint32_t at = vb + (uint32_t)(chunk_of(ks) * (VS + 16) + buf * VT);
+            if constexpr (ONCE) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) nzs[set][h] = *reinterpret_cast<const lds_f4*>(at + (uint32_t)(16 * h));
+            } else
+                zv[set] = *reinterpret_cast<const lds_u4*>(at);
+            sv[set] = *reinterpret_cast<const lds_u4*>(at + VS);
+        };
+        auto convert_zero = [&](Conv& c, int set, int p) {
+            if constexpr (ONCE) c.first(p, bits_h2(sv[set][p & 3]), nzs[set][(p & 3) >> 1][2 * (p & 1)]);
+            else c.zero(p, bits_h2(zv[set][p & 3]));
+        };
+        auto convert_scale = [&](const Conv& c, int set, int p) {
+            if constexpr (ONCE) return c.second(p, bits_h2(sv[set][p & 3]), nzs[set][(p & 3) >> 1][2 * (p & 1) + 1]);
+            else return c.scale(p, bits_h2(sv[set][p & 3]));
         };
 
 #pragma unroll
@@ -494,8 +525,8 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
         for (int p = 0; p < 8; ++p) {
             cv.mask(p, (uint32_t)raw[0][p >> 2].x);
             cv.base(p);
-            cv.zero(p, bits_h2(zv[0][p & 3]));
-            afr[0][p >> 2][p & 3] = cv.scale(p, bits_h2(sv[0][p & 3]));
+            convert_zero(cv, 0, p);
+            afr[0][p >> 2][p & 3] = convert_scale(cv, 0, p);
         }
         read_par(0, 2, 0);
         for (int t = 0; t < turns; ++t) {
@@ -518,8 +549,8 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
                         const int ph = o >> 3, p = o & 7;
                         if (ph == 0) cv.mask(p, (uint32_t)raw[kn >> 1][p >> 2][kn & 1]);
                         else if (ph == 1) cv.base(p);
-                        else if (ph == 2) cv.zero(p, bits_h2(zv[kn & 1][p & 3]));
-                        else afr[kn & 1][p >> 2][p & 3] = cv.scale(p, bits_h2(sv[kn & 1][p & 3]));
+                        else if (ph == 2) convert_zero(cv, kn & 1, p);
+                        else afr[kn & 1][p >> 2][p & 3] = convert_scale(cv, kn & 1, p);
                     }
                     if (m % 2 == 0) bfr[(ks + 2) & 3][m / 2] = x.frag(m / 2, ks < 2 ? CUR : NXT, chunk_of((ks + 2) & 3));
                     // the second half's codes early in k-block 0, the next stage's first half behind the barrier
@@ -626,35 +657,35 @@ inline int dx_tiles(const Layer& L) { return ceil_div(L.kq, 128) + ceil_div(L.k,
 template <int J, int KW>
 constexpr int finish_lds() { return 2 * (KW - 1) * 2 * J * 4096; }
 
-template <int J, int KW, int MINW>
+template <int J, int KW, int MINW, bool ONCE>
 hipError_t launch_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s) {
     static bool attr = false;
     constexpr int XL = KW * 2 * 32 * J * 128, LDS_BYTES = XL > finish_lds<J, KW>() ? XL : finish_lds<J, KW>();
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void*)fwd_tile_kernel<J, KW, MINW>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute((const void*)fwd_tile_kernel<J, KW, MINW, ONCE>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
         attr = true;
     }
     const int tn = ceil_div(L.oc, 128), tm = ceil_div(M, 32 * J);
     Layer A = L;
     if (A.k == 0) A.weak = reinterpret_cast<const __half*>(A.qweight);   // requests whose result is not used
-    fwd_tile_kernel<J, KW, MINW><<<xcd_grid(tn * tm), 128 * KW, LDS_BYTES, s>>>(A, X, (int)M, ldx, Y, ldy, tn, tm);
+    fwd_tile_kernel<J, KW, MINW, ONCE><<<xcd_grid(tn * tm), 128 * KW, LDS_BYTES, s>>>(A, X, (int)M, ldx, Y, ldy, tn, tm);
     return hipGetLastError();
 }
 
-template <int J, int KW, int MINW>
+template <int J, int KW, int MINW, bool ONCE>
 hipError_t launch_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s) {
     static bool attr = false;
-    constexpr int XT = 32 * J * 128, QL = KW * (2 * XT + 2 * 4096 + 2 * 256), WL = KW * 2 * (XT / 2 + 32 * 272);
+    constexpr int XT = 32 * J * 128, QL = KW * (2 * XT + 2 * 4096 + 2 * (ONCE ? 384 : 256)), WL = KW * 2 * (XT / 2 + 32 * 272);
     constexpr int A = QL > WL ? QL : WL, LDS_BYTES = A > finish_lds<J, KW>() ? A : finish_lds<J, KW>();
     static_assert(LDS_BYTES <= 160 * 1024, "");
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void*)dx_tile_kernel<J, KW, MINW>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute((const void*)dx_tile_kernel<J, KW, MINW, ONCE>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
         attr = true;
     }
     const int tn = dx_tiles(L), tm = ceil_div(M, 32 * J);
-    dx_tile_kernel<J, KW, MINW><<<xcd_grid(tn * tm), 128 * KW, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, tn, tm);
+    dx_tile_kernel<J, KW, MINW, ONCE><<<xcd_grid(tn * tm), 128 * KW, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, tn, tm);
     return hipGetLastError();
 }
 
@@ -717,10 +748,14 @@ bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
 }
 
 hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s) {
-    return est_fwd(L, M).j == 2 ? launch_fwd<2, 2, 2>(L, X, M, ldx, Y, ldy, s) : launch_fwd<4, 2, 1>(L, X, M, ldx, Y, ldy, s);
+    const bool two = est_fwd(L, M).j == 2;
+    if (L.once) return two ? launch_fwd<2, 2, 2, true>(L, X, M, ldx, Y, ldy, s) : launch_fwd<4, 2, 1, true>(L, X, M, ldx, Y, ldy, s);
+    return two ? launch_fwd<2, 2, 2, false>(L, X, M, ldx, Y, ldy, s) : launch_fwd<4, 2, 1, false>(L, X, M, ldx, Y, ldy, s);
 }
 hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s) {
-    return est_dx(L, M).j == 2 ? launch_dx<2, 4, 2>(L, dY, M, lddy, dX, lddx, s) : launch_dx<4, 2, 1>(L, dY, M, lddy, dX, lddx, s);
+    const bool two = est_dx(L, M).j == 2;
+    if (L.once) return two ? launch_dx<2, 4, 2, true>(L, dY, M, lddy, dX, lddx, s) : launch_dx<4, 2, 1, true>(L, dY, M, lddy, dX, lddx, s);
+    return two ? launch_dx<2, 4, 2, false>(L, dY, M, lddy, dX, lddx, s) : launch_dx<4, 2, 1, false>(L, dY, M, lddy, dX, lddx, s);
 }
 
 }  // namespace qeft

@@ -18,6 +18,7 @@ struct Layer {
     int gs;        // row pitch of scales / zeros in elements (ng rounded up to a multiple of 8)
     int words;     // used words per row
     int stride;    // words per row incl. padding (multiple of 4)
+    int once;      // 1 (the 4-bit copy of a 3-bit layer): the tiled kernels round s (q - z) once also where z is fractional
     const uint32_t* qweight;
     const __half* scales;
     const __half* zeros;

@@ -1,6 +1,7 @@
 """3-bit layers of 17 rows and more with a workspace: the codes rewritten in the 4-bit layout, then that layout's kernels.
 Both 3-bit layouts; rows that end inside a word of either, weak blocks of 8 and 136, row counts of each kernel behind it,
 workspaces of the stated size and of the fp16 copy alone.  Tolerance: parity_util's bar (fp16 weights, fp16 results)."""
+import numpy as np
 import pytest
 import torch
 
@@ -33,8 +34,9 @@ def test_three_bit_rows(oc, ic, k, dense):
 
 
 # One rounding to fp16 is 2.1e-4 in norm over a uniform mantissa.  A call that keeps its sums in fp32 has two, independent of each
-# other: the weights' and the result's, 2.9e-4; fp16 partial sums are a third, 3.6e-4.  The bound lies half way.
-TWO_ROUNDINGS = 3.25e-4
+# other: the weights' and the result's, 2.9e-4; fp16 partial sums are a third, 3.6e-4; a fourth would make 4.2e-4.  The bounds
+# lie half way.
+TWO_ROUNDINGS, THREE_ROUNDINGS = 3.25e-4, 3.9e-4
 
 
 def _error(out, ref):
@@ -55,3 +57,21 @@ def test_sums_stay_in_fp32_without_room_for_a_split(dense):
                                ("dX", B.qeft_linear_bwd_dx(h.desc, w, dyd, ws=ws), dyd.double() @ w64)):
             err = _error(out, ref)
             assert err <= TWO_ROUNDINGS, f"{what}, M={m}: {err:.3e}"
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("oc,ic,k", [(5120, 5120, 128), (2048, 4096, 64)])
+def test_fractional_zero_points_are_rounded_once(oc, ic, k, dense):
+    """Zero-points between 0 and 1: q - z is no fp16 number, and s (q - z) is still rounded once, in every kernel a row count
+    leads to (panels of 128 to 256 rows, small tiles, both forms of the input gradient)."""
+    h = HostLayer(oc, ic, k, 3, 128, seed=oc + k, dense=dense)
+    h.zeros = np.random.default_rng(7).uniform(0.05, 0.95, h.zeros.shape).astype(np.float16)
+    w, w64 = h.to_device(), torch.from_numpy(h.w64).cuda()
+    for m in (40, 128, 200, 300, 333, 420, 1003, 1024):
+        xd = torch.from_numpy(synth.make_activations(m, ic, 0, seed=m)).cuda()
+        dyd = torch.from_numpy(synth.make_grad_output(m, oc, seed=m)).cuda()
+        for what, op, call, ref in (("forward", B.QEFT_OP_FWD, lambda ws: B.qeft_linear_fwd(h.desc, w, xd, ws=ws), xd.double() @ w64.t()),
+                                    ("dX", B.QEFT_OP_BWD_DX, lambda ws: B.qeft_linear_bwd_dx(h.desc, w, dyd, ws=ws), dyd.double() @ w64)):
+            for size, bound in ((2 * oc * ic, TWO_ROUNDINGS), (B.qeft_workspace_bytes(h.desc, op, m), THREE_ROUNDINGS)):
+                err = _error(call(torch.empty(size, dtype=torch.uint8, device="cuda")), ref)
+                assert err <= bound, f"{what}, M={m}, workspace {size}: {err:.3e}"
