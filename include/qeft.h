@@ -162,8 +162,9 @@ int qeft_unpack(const qeft_desc_t* desc, const qeft_weight_t* w, uint8_t* codes,
  * QEFT_OP_FWD / QEFT_OP_BWD_DX report OC * IC * 2 bytes for 3-bit layers
  * at M > 16 (plus the partial tiles of a split of the copy's columns or rows as above, used when the whole
  * amount is given): with that workspace (16-byte aligned) the call rewrites the layer once into it and runs the
- * tensor-core kernels on the copy - the codes in the 4-bit layout for groups of 128 and 2^20 weights or more, else the
- * whole layer dequantized to fp16 (the paper's own training path, dequantize then a dense product; Sec. 4.3, App. A.2) -
+ * tensor-core kernels on the copy - the codes in the 4-bit layout for groups of 128 and 2^20 weights or more where the kernel
+ * for them is the faster one, else the whole layer dequantized to fp16 (the paper's own training path, dequantize then a dense
+ * product; Sec. 4.3, App. A.2); either way s (q - z) is rounded to fp16 at most once -
  * and without it (ws NULL) the slow general kernel; a workspace that is too small is
  * QEFT_ERR_WORKSPACE.  The copy is rewritten by every call (the weak block may have changed).
  * QEFT_OP_BWD (qeft_linear_bwd): the larger of QEFT_OP_WEAK_GRAD's amount, which that call requires, and

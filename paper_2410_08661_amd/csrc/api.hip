@@ -73,13 +73,15 @@ int check_matrix(const void* p, int64_t M, int64_t ld, int64_t width) {
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? QEFT_OK : QEFT_ERR_HIP; }
 
-// 3-bit layers at GEMM sizes: the kernels there convert 4-bit codes only.  In groups of 128 the codes are rewritten once in
-// the 4-bit layout (a quarter of an fp16 copy's bytes: 5120 x 5120 7 to 8 us against 17) and multiplied as the 4-bit layer
-// with the same parameters and weak block; other group sizes are dequantized into an fp16 [OC][IC] copy and multiplied
-// as a layer whose columns are all weak (the paper's own training path: dequantize, then a dense product; Sec. 4.3 /
-// App. A.2).  So are layers of fewer than 2^20 weights: either copy takes about 3 us there, and for them the workspace keeps
-// holding the dequantized layer after the call, as it always has.  Either lies at the head of the caller's workspace, which is sized for the fp16 copy and a split of it; the
-// split's partial tiles follow.
+// 3-bit layers at GEMM sizes: the kernels there convert 4-bit codes only.  Either the codes are rewritten once in the 4-bit
+// layout (a quarter of an fp16 copy's bytes: 5120 x 5120 7 to 8 us against 17) and multiplied as the 4-bit layer with the same
+// parameters and weak block, or the layer is dequantized into an fp16 [OC][IC] copy and multiplied as one whose columns are all
+// weak (the paper's own training path: dequantize, then a dense product; Sec. 4.3 / App. A.2).  Groups of 128 take the first
+// where its kernel is the faster one (fwd_copy4_preferred, dx_copy4_preferred), other group sizes the second.  So do layers of
+// fewer than 2^20 weights: for them the workspace holds the dequantized layer after the call, which the parity tests compare
+// word for word (the 4-bit copy would be faster there too: 960 x 1024 at 40 rows, forward 9 us against 20, dX 14 against 27).
+// The copy lies at the head of the caller's workspace, which is sized for the fp16 one and a split of it; the split's partial
+// tiles follow.
 bool dense_copy_applies(const Layer& L, int64_t M) {
     return L.bits == 3 && L.kq > 0 && M > 16 && (L.ic % 8) == 0 && (L.oc % 8) == 0;
 }
@@ -113,13 +115,12 @@ Layer nibble_copy_layer(const Layer& L, const void* ws) {
 }
 size_t nibble_copy_bytes(const Layer& D) { return ((size_t)D.oc * D.stride * 4 + 255) / 256 * 256; }
 
-// Room for the fp16 partial tiles of a split behind the 4-bit copy N, or NULL.  need, need_dense: what the split takes on this
-// copy and on the fp16 one.  Only with the whole amount that qeft_workspace_bytes reports: the bytes of the fp16 copy alone
-// would often hold the smaller copy and a split too, but a caller who gave no more keeps every sum in fp32.
-void* nibble_split_room(const Layer& N, size_t need, size_t need_dense, void* ws, size_t ws_bytes) {
+// Room for `need` bytes of a split's partial tiles behind the 4-bit copy, or NULL.  Asked for only where the caller gave the whole
+// amount that qeft_workspace_bytes reports: the bytes of the fp16 copy alone would often hold the smaller copy and a split too,
+// but a caller who gave no more keeps every sum in fp32.
+void* behind_nibble_copy(const Layer& N, size_t need, void* ws, size_t ws_bytes) {
     const size_t at = nibble_copy_bytes(N);
-    const bool whole = need_dense > 0 && ws_bytes >= dense_copy_bytes(N) + need_dense;
-    return whole && need > 0 && ws_bytes >= at + need ? (char*)ws + at : nullptr;
+    return need > 0 && ws_bytes >= at + need ? (char*)ws + at : nullptr;
 }
 
 // The forward of a layer the tiled kernels support, by rows and by what fills the GPU; split_ws: room for
@@ -244,19 +245,20 @@ int qeft_linear_fwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
     if (ws && dense_copy_applies(L, M)) {
         if (!aligned16(ws)) return QEFT_ERR_ALIGN;
         if (ws_bytes < dense_copy_bytes(L)) return QEFT_ERR_WORKSPACE;
-        const Layer N = nibble_copy_layer(L, ws);
+        const Layer N = nibble_copy_layer(L, ws), D = dense_copy_layer(L, ws);
+        const size_t need = gemm_fwd_supported(D, M) ? gemm_fwd_split_workspace(D, M) : 0;
+        const bool whole = need > 0 && ws_bytes >= dense_copy_bytes(L) + need;   // what the caller gave holds a split of the fp16 copy too
         if (nibble_copy_applies(L, M) && gemm_fwd_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
-            if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
-            void* split_ws = nibble_split_room(N, gemm_fwd_split_workspace(N, M), gemm_fwd_split_workspace(dense_copy_layer(L, ws), M), ws, ws_bytes);
-            return hip_status(fwd_rows(N, x, M, ldx, y, ldy, split_ws, s));
+            void* split_ws = whole ? behind_nibble_copy(N, gemm_fwd_split_workspace(N, M), ws, ws_bytes) : nullptr;
+            if (fwd_copy4_preferred(N, D, M, ldx, split_ws != nullptr, whole)) {
+                if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
+                return hip_status(fwd_rows(N, x, M, ldx, y, ldy, split_ws, s));
+            }
         }
-        const Layer D = dense_copy_layer(L, ws);
         if (gemm_fwd_supported(D, M)) {
             hipError_t e = dequantize_fp16(L, (__half*)ws, s);
             if (e != hipSuccess) return QEFT_ERR_HIP;
-            // what the caller gave beyond the copy serves a split of its columns (all of it or nothing)
-            const size_t need = gemm_fwd_split_workspace(D, M);
-            void* split_ws = (need > 0 && ws_bytes >= dense_copy_bytes(L) + need) ? (char*)ws + dense_copy_bytes(L) : nullptr;
+            void* split_ws = whole ? (char*)ws + dense_copy_bytes(L) : nullptr;
             return hip_status(gemm_fwd(D, x, M, ldx, y, ldy, split_ws, s));
         }
     }
@@ -334,19 +336,20 @@ int qeft_linear_bwd_dx(const qeft_desc_t* desc, const qeft_weight_t* w, const vo
     if (ws && dense_copy_applies(L, M)) {
         if (!aligned16(ws)) return QEFT_ERR_ALIGN;
         if (ws_bytes < dense_copy_bytes(L)) return QEFT_ERR_WORKSPACE;
-        const Layer N = nibble_copy_layer(L, ws);
+        const Layer N = nibble_copy_layer(L, ws), D = dense_copy_layer(L, ws);
+        const size_t need = gemm_dx_supported(D, M) ? gemm_dx_split_workspace(D, M) : 0;
+        const bool whole = need > 0 && ws_bytes >= dense_copy_bytes(L) + need;   // what the caller gave holds a split of the fp16 copy too
         if (nibble_copy_applies(L, M) && gemm_dx_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
-            if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
-            void* split_ws = nibble_split_room(N, gemm_dx_split_workspace(N, M), gemm_dx_split_workspace(dense_copy_layer(L, ws), M), ws, ws_bytes);
-            return hip_status(dx_rows(N, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s));
+            void* split_ws = whole ? behind_nibble_copy(N, gemm_dx_split_workspace(N, M), ws, ws_bytes) : nullptr;
+            if (dx_copy4_preferred(N, D, M, lddy, split_ws != nullptr, whole)) {
+                if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
+                return hip_status(dx_rows(N, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s));
+            }
         }
-        const Layer D = dense_copy_layer(L, ws);
         if (gemm_dx_supported(D, M)) {
             hipError_t e = dequantize_fp16(L, (__half*)ws, s);
             if (e != hipSuccess) return QEFT_ERR_HIP;
-            // what the caller gave beyond the copy serves a row split of it (all of it or nothing)
-            const size_t need = gemm_dx_split_workspace(D, M);
-            void* split_ws = (need > 0 && ws_bytes >= dense_copy_bytes(L) + need) ? (char*)ws + dense_copy_bytes(L) : nullptr;
+            void* split_ws = whole ? (char*)ws + dense_copy_bytes(L) : nullptr;
             return hip_status(gemm_dx(D, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s));
         }
     }

@@ -112,6 +112,10 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
 // split_ws: the caller's workspace holds the partial tiles of the GEMM's split ----
 bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws);
 bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws);
+// Of the two copies of a 3-bit layer, N (4-bit codes) and D (fp16), whether N is the one to multiply (never where its kernel would
+// round s (q - z) twice); split_n, split_d: room for the split behind either
+bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx, bool split_n, bool split_d);
+bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy, bool split_n, bool split_d);
 hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s);
 hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s);
 

@@ -31,13 +31,13 @@ def _judge(measure, what):
         pytest.xfail(f"{what}: {t_lib:.1f} us against {t_alt:.1f} us (more than 10 % slower than the alternative)")
 
 
-def _layer(oc, ic, k, seed):
+def _layer(oc, ic, k, seed, bits=4):
     gen = torch.Generator(device="cuda").manual_seed(seed)
-    d = B.make_desc(oc, ic, k, 4, 128)
+    d = B.make_desc(oc, ic, k, bits, 128)
     w = B.Weight(d)
     w.qweight.random_(-2**31, 2**31 - 1, generator=gen)
     w.scales.copy_((torch.rand(w.scales.shape, generator=gen, device="cuda") * 0.008 + 0.004).half())
-    w.zeros.copy_(torch.randint(0, 16, w.zeros.shape, generator=gen, device="cuda").half())
+    w.zeros.copy_(torch.randint(0, 2 ** bits, w.zeros.shape, generator=gen, device="cuda").half())
     w.weak.copy_((torch.randn(w.weak.shape, generator=gen, device="cuda") * 0.02).half())
     return d, w, gen
 
@@ -87,3 +87,25 @@ def test_workspace_never_costs_more_than_ten_percent(oc, ic, m):
             continue                     # no split planned for this launch: both calls are the same
         ws = torch.empty(n, dtype=torch.uint8, device="cuda")
         _judge(lambda: (_us(lambda: call(ws)), _us(lambda: call(False))), f"{name} {oc}x{ic} M={m} with the workspace against without")
+
+
+@pytest.mark.parametrize("oc,ic,k,m", [(8192, 8192, 64, 2048), (4096, 4096, 64, 1003), (11008, 4096, 8, 512), (13824, 5120, 16, 1003)])
+def test_three_bit_rows_no_slower_than_an_fp16_copy(oc, ic, k, m):
+    """3-bit layers whose last group is partial: the call with its workspace against the dense product that the boundary offers
+    (a layer whose columns are all weak, with its workspace) after one pass that writes those fp16 weights."""
+    d, w, gen = _layer(oc, ic, k, oc + m, bits=3)
+    dense, wd, _ = _layer(oc, ic, ic, 1)
+    src = wd.weak.clone()
+    x = torch.randn((m, ic), generator=gen, device="cuda").half()
+    dy = (torch.randn((m, oc), generator=gen, device="cuda") * 0.01).half()
+    y = torch.empty((m, oc), dtype=torch.float16, device="cuda")
+    dx = torch.empty((m, ic), dtype=torch.float16, device="cuda")
+    for name, op, call in (("forward", B.QEFT_OP_FWD, lambda d, w, ws: B.qeft_linear_fwd(d, w, x, y, ws=ws)),
+                           ("dX", B.QEFT_OP_BWD_DX, lambda d, w, ws: B.qeft_linear_bwd_dx(d, w, dy, dx, ws=ws))):
+        ws = torch.empty(B.qeft_workspace_bytes(d, op, m), dtype=torch.uint8, device="cuda")
+        n = B.qeft_workspace_bytes(dense, op, m)
+        wsd = torch.empty(n, dtype=torch.uint8, device="cuda") if n else False
+        def through_copy():
+            wd.weak.copy_(src)
+            call(dense, wd, wsd)
+        _judge(lambda: (_us(lambda: call(d, w, ws)), _us(through_copy)), f"3-bit {name} {oc}x{ic} k={k} M={m} against the product of an fp16 copy")
