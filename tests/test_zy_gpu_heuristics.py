@@ -109,3 +109,24 @@ def test_three_bit_rows_no_slower_than_an_fp16_copy(oc, ic, k, m):
             wd.weak.copy_(src)
             call(dense, wd, wsd)
         _judge(lambda: (_us(lambda: call(d, w, ws)), _us(through_copy)), f"3-bit {name} {oc}x{ic} k={k} M={m} against the product of an fp16 copy")
+
+
+@pytest.mark.parametrize("oc,k,m", [(13824, 64, 3000), (13824, 16, 2048), (4096, 96, 777)])
+def test_weak_gradient_of_a_narrow_block(oc, k, m):
+    """How the tokens are split: a weak block narrower than 128 reads the same gradients as one of 128 and forms fewer products
+    (its partly filled strips cost a stage more than full ones, which leaves it up to 1.2 times as long)."""
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    dy = (torch.randn((m, oc), generator=gen, device="cuda") * 0.01).half()
+    x = torch.randn((m, 1024), generator=gen, device="cuda").half()
+    def run(k):
+        d = B.make_desc(oc, 1024, k)
+        dw = torch.empty((oc, k), dtype=torch.float32, device="cuda")
+        n = B.qeft_workspace_bytes(d, B.QEFT_OP_WEAK_GRAD, m)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda") if n else None
+        return lambda: B.qeft_weak_grad(d, dy, x[:, 1024 - k:], dw, ws=ws)
+    narrow, full = run(k), run(128)
+    for attempt in range(2):
+        t, t_full = _us(narrow), _us(full)
+        if t <= 1.3 * t_full:
+            return
+    pytest.fail(f"weak gradient {oc} channels, M={m}: k={k} {t:.1f} us, k=128 {t_full:.1f} us")
