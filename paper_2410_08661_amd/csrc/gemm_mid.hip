@@ -261,21 +261,63 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
         mul_weak(b);
     }
 
-    // One output in plain order.  An infinite activation makes a group's sum x (1024 + q) and its Sx infinite alike, and their
-    // difference no number where x s (q - z) is an infinity: outputs that come out as no number are taken again from the
-    // weights themselves (until the sum is no number there either, which it then stays).
-    auto plain = [&](int m, int o) {
-        const __half* x = A.X + (size_t)m * A.ldx;
-        const uint32_t* words = A.qweight[li] + (size_t)o * A.stride;
+    // An infinite activation makes a group's sum x (1024 + q) and its Sx infinite alike, and their difference no number where
+    // x s (q - z) is an infinity.  Outputs that come out as no number are therefore taken again from the products x w that are not
+    // finite, which alone decide.  A wave does it, a row of its tile at a time: it looks through the row's quantized columns, 1024
+    // per turn, and forms the products of the groups in which something is not finite, lane (n, kb) for channel n and the group's
+    // columns 32 kb .. + 31.  (4096 x 11008, one infinity late in one of 40 rows: 22 us -> 32; the whole sum in plain order by a lane
+    // per output: 2180.)  want: the channels asked for.
+    auto repair_row = [&](int m, int col, uint32_t want) {
+        const unsigned char* x = reinterpret_cast<const unsigned char*>(A.X + (size_t)m * A.ldx);
+        const int o = min(o0 + col, oc - 1);
+        const unsigned char* words = reinterpret_cast<const unsigned char*>(A.qweight[li] + (size_t)o * A.stride);
         const __half *sc = A.scales[li] + (size_t)o * A.gs, *zp = A.zeros[li] + (size_t)o * A.gs, *wk = A.weak[li] + (size_t)o * A.k;
         float r = 0.f;
-#pragma clang loop unroll(disable)
-        for (int j = 0; j < A.kq + A.k && r == r; ++j) {
-            const float w = j < A.kq ? __half2float(sc[j >> 7]) * ((float)((words[j >> 3] >> (4 * (j & 7))) & 15u) - __half2float(zp[j >> 7]))
-                                     : __half2float(wk[j - A.kq]);
-            r = fmaf(__half2float(x[j]), w, r);
+        auto add = [&](float p) { r += p - p == 0.f ? 0.f : p; };
+        auto settled = [&]() {   // every channel asked for is no number already
+            uint64_t b = __ballot(r != r);
+            b |= b >> 32;
+            b |= b >> 16;
+            return ((uint32_t)b & want) == want;
+        };
+        for (int j = 8 * kb; j < A.k; j += 32) {
+            const h8 xv = as_h8(*reinterpret_cast<const u4*>(x + 2 * (size_t)(A.kq + j))), wv = as_h8(*reinterpret_cast<const u4*>(wk + j));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) add((float)xv[e] * (float)wv[e]);
         }
-        return r;
+        auto not_finite = [](u4 v) {
+            bool f = false;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) f = f || (v[e] & 0x7c00u) == 0x7c00u || (v[e] & 0x7c000000u) == 0x7c000000u;
+            return f;
+        };
+#pragma clang loop unroll(disable)
+        for (int c0 = 0; c0 < A.kq && !settled(); c0 += 1024) {
+            u4 v[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) v[t] = *reinterpret_cast<const u4*>(x + 2 * (size_t)min(c0 + 512 * t + 8 * lane, A.kq - 8));
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const uint64_t found = __ballot(not_finite(v[t]));   // (columns past Kq repeat the row's last 8)
+#pragma clang loop unroll(disable)
+                for (int s = 0; s < 4; ++s) {
+                    const int g = (c0 >> 7) + 4 * t + s;
+                    if (g >= A.ng || ((found >> (16 * s)) & 0xffffu) == 0) continue;
+                    const float a = __half2float(sc[g]), b = __half2float(zp[g]);
+                    const u4 w = *reinterpret_cast<const u4*>(words + 64 * (size_t)g + 16 * kb);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int c = 128 * g + 32 * kb + 8 * q;
+                        const h8 xv = as_h8(*reinterpret_cast<const u4*>(x + 2 * (size_t)min(c, A.kq - 8)));
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (c < A.kq) add((float)xv[e] * (a * ((float)((w[q] >> (4 * e)) & 15u) - b)));
+                    }
+                }
+            }
+        }
+        r += __shfl_xor(r, 16);
+        return r + __shfl_xor(r, 32);
     };
 
     // the waves' partial tiles meet in LDS (at most 4 channel tiles at a time); wave w sums tiles w, w + KS, ...
@@ -299,9 +341,21 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
                 for (int e = 0; e < 4; ++e) y[e] += p[e];
             }
             const int row = 16 * (q / NC) + 4 * kb, col = 16 * (t0 + q % NC) + n;
+            if (A.ng > 0) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (__builtin_expect(y[e] != y[e], 0) && t0 + q % NC < NT && row + e <= mlast && o0 + col < oc) y[e] = plain(m0 + row + e, o0 + col);
+                for (int e = 0; e < 4; ++e) {
+                    const uint64_t bad = __ballot(y[e] != y[e] && t0 + q % NC < NT && row + e <= mlast && o0 + col < oc);
+                    if (__builtin_expect(bad != 0, 0)) {
+#pragma clang loop unroll(disable)
+                        for (int b = 0; b < 4; ++b) {
+                            const uint32_t want = (uint32_t)(bad >> (16 * b)) & 0xffffu;
+                            if (want == 0) continue;
+                            const float r = repair_row(m0 + row - 4 * kb + 4 * b + e, col, want);
+                            if (kb == b && y[e] != y[e] && r - r != 0.f) y[e] = r;
+                        }
+                    }
+                }
+            }
             // lane (n, kb) holds rows 4 kb .. 4 kb + 3 of channel n; a 4 x 4 transpose inside each quad of lanes gives it
             // channels 4 (n / 4) .. + 3 of row 4 kb + n % 4: one 8-byte store
             const uint32_t p0 = pack2(y[0], y[1]), p1 = pack2(y[2], y[3]);

@@ -92,6 +92,34 @@ def test_mid_rows_infinite_activations(oc, ic, k):
         assert_close(y.cpu().numpy()[rows], want[rows], f"M={m}, finite rows")
 
 
+def test_mid_rows_infinite_activations_of_long_rows():
+    """The columns are looked through 1024 at a time: infinities in each part of a row, in its last group (64 columns) and beside
+    the weak block's, alone and against each other; whole rows of them."""
+    layer = HostLayer(520, 4256, 32, 4, 128, seed=11)
+    layer.codes[3, :] = 5
+    layer.zeros[3, :] = 5
+    layer.qweight = qo.pack_codes(layer.codes, 4, layer.lay["row_stride_words"])
+    w = layer.to_device()
+    inf = np.float16(np.inf)
+    for m in (17, 48, 96):
+        x = synth.make_activations(m, layer.ic, 32, seed=m)
+        for r, cols in enumerate(([0], [1023], [1024], [2047, 2048], [3071, 4222], [4160], [4223], [4224], [4255, 7], [4096, 4223])):
+            x[r, cols] = inf
+        x[9, 4223] = -inf
+        x[10, [1, 4000]] = inf, np.nan
+        x[11, :] = inf
+        x[m - 1, 4100] = -inf
+        with np.errstate(invalid="ignore"):
+            want = np.stack([(row * layer.w64).sum(axis=1) for row in x.astype(np.float64)])
+        y = B.qeft_linear_fwd(layer.desc, w, pad_cols(x)[0], ws=False)
+        torch.cuda.synchronize()
+        got = y.cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isfinite(got), np.isfinite(want)) and np.array_equal(np.isnan(got), np.isnan(want)), f"M={m}"
+        assert np.array_equal(np.sign(got[np.isinf(want)]), np.sign(want[np.isinf(want)])), f"M={m}"
+        rows = np.isfinite(want).all(axis=1)
+        assert_close(y.cpu().numpy()[rows], want[rows], f"M={m}, finite rows")
+
+
 @pytest.mark.parametrize("m", [97, 144, 192])
 def test_mid_rows_with_a_split_workspace(m):
     """Few channels: this kernel rather than the K split, so the same bits with the workspace as without."""

@@ -130,3 +130,16 @@ def test_weak_gradient_of_a_narrow_block(oc, k, m):
         if t <= 1.3 * t_full:
             return
     pytest.fail(f"weak gradient {oc} channels, M={m}: k={k} {t:.1f} us, k=128 {t_full:.1f} us")
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_a_row_that_is_not_finite_costs_no_more_than_a_few_calls(value):
+    """One such activation, late in one row of 40: outputs that are no number are taken again, which must stay small beside the call."""
+    d, w, gen = _layer(4096, 11008, 128, 3)
+    x = torch.randn((40, 11008), generator=gen, device="cuda").half()
+    y = torch.empty((40, 4096), dtype=torch.float16, device="cuda")
+    t = _us(lambda: B.qeft_linear_fwd(d, w, x, y, ws=False))
+    x[7, 10800] = value
+    t_bad = _us(lambda: B.qeft_linear_fwd(d, w, x, y, ws=False))
+    print(f"\nfinite {t:.1f} us, one value {value}: {t_bad:.1f} us")
+    assert t_bad <= 3 * t
