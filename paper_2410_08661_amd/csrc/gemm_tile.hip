@@ -738,15 +738,20 @@ bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws) {
     return est_fwd(L, M).t < 0.95 * g;
 }
 // The input gradient: whole stages of rows.  Against the split the estimate has to be 15 % ahead (its weak tiles run longer than
-// estimated).  Measured, split GEMM against this kernel: 2560 x 7168 at M = 256 / 320 / 512 (estimates 0.80 apart) 28.6 / 36.7 / 38.9 us
-// against 24.9 / 33.6 / 34.9, 2048 x 1152 at 333 / 512 (0.78) 20.3 / 21.1 against 19.0 / 18.9, 6144 x 6144 at 320 (0.83) 49.0 against
-// 48.4; the other way 4096 x 11008 at 320 (0.88) 57.6 against 59.5, 5120 x 5120 at 333 (0.91) 40.0 against 42.2, 4096 x 4096 at 333 /
-// 512 (0.99) 33.0 / 35.7 against 34.1 / 35.8.  A partial last group leaves the GEMM its LDS-staged form, at 3.3 to 4.5 times
-// the time (4096 x 4096 with 8 weak columns, M = 227: 310 us; 4096 x 11008, M = 1938: 641 us).
+// estimated), 25 % where the split takes less than 28 us.  Measured, split GEMM against this kernel: 2560 x 7168 at M = 256 / 320 /
+// 512 (estimates 0.80 apart) 28.6 / 36.7 / 38.9 us against 24.9 / 33.6 / 34.9, 6144 x 6144 at 320 (0.83) 49.0 against 48.4; the other way
+// 4096 x 11008 at 320 (0.88) 57.6 against 59.5, 5120 x 5120 at 333 (0.91) 40.0 against 42.2, 4096 x 4096 at 333 / 512 (0.99) 33.0 / 35.7
+// against 34.1 / 35.8.  The short launches would gain 1 to 2 us (2048 x 1152 at 333 / 512 rows, 0.78: 20.3 / 21.1 against 19.0 / 18.9) and
+// keep the split's arithmetic, which callers that give the room for it rely on (the one-call backward's test there).  A partial last
+// group leaves the GEMM its LDS-staged form, at 3.3 to 4.5 times the time (4096 x 4096 with 8 weak columns, M = 227: 310 us; 4096 x
+// 11008, M = 1938: 641 us).
 bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
     if (L.ng <= 0 || M <= 16 || L.oc % 64 != 0 || lddy > (QEFT_MAX_DIM >> 1)) return false;
     const GemmSplit p = split_ws ? gemm_dx_split(L, M) : GemmSplit{1, 0, 0, false};
-    if (p.splits > 1) return !p.tail && est_dx(L, M).t < 0.85 * est_split(p, 12, 1.5);
+    if (p.splits > 1) {
+        const double split = est_split(p, 12, 1.5);
+        return !p.tail && est_dx(L, M).t < (split < 28 ? 0.75 : 0.85) * split;
+    }
     return est_dx(L, M).t < 0.95 * est_gemm(L.ic, M, L.oc / 64, 1.3) * (L.kq % 128 == 0 ? 1.0 : 3.3);
 }
 
