@@ -320,58 +320,55 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
         return r + __shfl_xor(r, 32);
     };
 
-    // the waves' partial tiles meet in LDS (at most 4 channel tiles at a time); wave w sums tiles w, w + KS, ...
-    constexpr int NC = NT < 4 ? NT : 4;
+    // the waves' partial tiles meet in LDS (each in its wave's piece); wave w sums tiles w, w + KS, ...
+    static_assert(NT <= 4, "");
     __half* Y = A.Y[li] + (size_t)m0 * A.ldy[li] + o0;
     const int64_t ldy = A.ldy[li];
+    __syncthreads();
 #pragma unroll
-    for (int t0 = 0; t0 < NT; t0 += NC) {
-        __syncthreads();
+    for (int a = 0; a < MT; ++a)
 #pragma unroll
-        for (int a = 0; a < MT; ++a)
+        for (int t = 0; t < NT; ++t)
+            *reinterpret_cast<f4*>(mine + ((a * NT + t) << 10) + 16 * lane) = acc[a][t];
+    __syncthreads();
+    for (int q = wave; q < MT * NT; q += KS) {
+        f4 y = f4{0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < KS; ++w) {
+            const f4 p = *reinterpret_cast<const f4*>(lds + (size_t)w * XB + (q << 10) + 16 * lane);
 #pragma unroll
-            for (int t = 0; t < NC; ++t)
-                if (t0 + t < NT) *reinterpret_cast<f4*>(mine + ((a * NC + t) << 10) + 16 * lane) = acc[a][t0 + t < NT ? t0 + t : 0];
-        __syncthreads();
-        for (int q = wave; q < MT * NC; q += KS) {
-            f4 y = f4{0.f, 0.f, 0.f, 0.f};
-            for (int w = 0; w < KS; ++w) {
-                const f4 p = *reinterpret_cast<const f4*>(lds + (size_t)w * XB + (q << 10) + 16 * lane);
+            for (int e = 0; e < 4; ++e) y[e] += p[e];
+        }
+        const int row = 16 * (q / NT) + 4 * kb, col = 16 * (q % NT) + n;
+        if (A.ng > 0) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] += p[e];
-            }
-            const int row = 16 * (q / NC) + 4 * kb, col = 16 * (t0 + q % NC) + n;
-            if (A.ng > 0) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint64_t bad = __ballot(y[e] != y[e] && t0 + q % NC < NT && row + e <= mlast && o0 + col < oc);
-                    if (__builtin_expect(bad != 0, 0)) {
+            for (int e = 0; e < 4; ++e) {
+                const uint64_t bad = __ballot(y[e] != y[e] && row + e <= mlast && o0 + col < oc);
+                if (__builtin_expect(bad != 0, 0)) {
 #pragma clang loop unroll(disable)
-                        for (int b = 0; b < 4; ++b) {
-                            const uint32_t want = (uint32_t)(bad >> (16 * b)) & 0xffffu;
-                            if (want == 0) continue;
-                            const float r = repair_row(m0 + row - 4 * kb + 4 * b + e, col, want);
-                            if (kb == b && y[e] != y[e] && r - r != 0.f) y[e] = r;
-                        }
+                    for (int b = 0; b < 4; ++b) {
+                        const uint32_t want = (uint32_t)(bad >> (16 * b)) & 0xffffu;
+                        if (want == 0) continue;
+                        const float r = repair_row(m0 + row - 4 * kb + 4 * b + e, col, want);
+                        if (kb == b && y[e] != y[e] && r - r != 0.f) y[e] = r;
                     }
                 }
             }
-            // lane (n, kb) holds rows 4 kb .. 4 kb + 3 of channel n; a 4 x 4 transpose inside each quad of lanes gives it
-            // channels 4 (n / 4) .. + 3 of row 4 kb + n % 4: one 8-byte store
-            const uint32_t p0 = pack2(y[0], y[1]), p1 = pack2(y[2], y[3]);
-            const bool hi = (lane & 2) != 0, odd = (lane & 1) != 0;
-            auto swap2 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false); };   // lane ^ 2
-            auto swap1 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false); };   // lane ^ 1
-            const uint32_t other = swap2(hi ? p0 : p1);
-            const uint32_t lo2 = hi ? other : p0, hi2 = hi ? p1 : other;   // channels (n % 4) & 1 and + 2 of the quad, this lane's two rows
-            const uint32_t lo1 = swap1(lo2), hi1 = swap1(hi2);
-            const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
-            // even lane: (own row-0, neighbour's row-0); odd lane: (neighbour's row-1, own row-1)
-            const uint32_t q0 = __builtin_amdgcn_perm(lo1, lo2, sel), q1 = __builtin_amdgcn_perm(hi1, hi2, sel);
-            const int a = q / NC, t = t0 + q % NC;
-            const int m = 16 * a + 4 * kb + (n & 3), o = 16 * t + 4 * (n >> 2);
-            if (t < NT && m <= mlast && o0 + o < oc) *reinterpret_cast<u2*>(Y + (size_t)m * ldy + o) = u2{q0, q1};
         }
+        // lane (n, kb) holds rows 4 kb .. 4 kb + 3 of channel n; a 4 x 4 transpose inside each quad of lanes gives it
+        // channels 4 (n / 4) .. + 3 of row 4 kb + n % 4: one 8-byte store
+        const uint32_t p0 = pack2(y[0], y[1]), p1 = pack2(y[2], y[3]);
+        const bool hi = (lane & 2) != 0, odd = (lane & 1) != 0;
+        auto swap2 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false); };   // lane ^ 2
+        auto swap1 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false); };   // lane ^ 1
+        const uint32_t other = swap2(hi ? p0 : p1);
+        const uint32_t lo2 = hi ? other : p0, hi2 = hi ? p1 : other;   // channels (n % 4) & 1 and + 2 of the quad, this lane's two rows
+        const uint32_t lo1 = swap1(lo2), hi1 = swap1(hi2);
+        const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+        // even lane: (own row-0, neighbour's row-0); odd lane: (neighbour's row-1, own row-1)
+        const uint32_t q0 = __builtin_amdgcn_perm(lo1, lo2, sel), q1 = __builtin_amdgcn_perm(hi1, hi2, sel);
+        const int a = q / NT, t = q % NT;
+        const int m = 16 * a + 4 * kb + (n & 3), o = 16 * t + 4 * (n >> 2);
+        if (m <= mlast && o0 + o < oc) *reinterpret_cast<u2*>(Y + (size_t)m * ldy + o) = u2{q0, q1};
     }
 }
 

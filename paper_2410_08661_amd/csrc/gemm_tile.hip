@@ -63,20 +63,18 @@ __device__ __forceinline__ void finish(f16v (&acc)[2][J], unsigned char* lds, in
                                        int nc, int m0, int M) {
     constexpr int QT = 2 * J / KW;
     const int fr = lane & 31, fk = lane >> 5;
-    if (KW > 1) {
-        float* part = reinterpret_cast<float*>(lds);   // [ow][owner][sender][QT][4][64][4]
+    float* part = reinterpret_cast<float*>(lds);   // [ow][owner][sender][QT][4][64][4]
 #pragma unroll
-        for (int q = 0; q < 2 * J; ++q) {
-            const int owner = q / QT;
-            if (owner != kw) {
-                float* p = part + ((((ow * KW + owner) * (KW - 1) + (kw < owner ? kw : kw - 1)) * QT + q % QT) << 10) + 4 * lane;
+    for (int q = 0; q < 2 * J; ++q) {
+        const int owner = q / QT;
+        if (owner != kw) {
+            float* p = part + ((((ow * KW + owner) * (KW - 1) + (kw < owner ? kw : kw - 1)) * QT + q % QT) << 10) + 4 * lane;
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    *reinterpret_cast<f4*>(p + 256 * e) = f4{acc[q & 1][q >> 1][4 * e], acc[q & 1][q >> 1][4 * e + 1], acc[q & 1][q >> 1][4 * e + 2], acc[q & 1][q >> 1][4 * e + 3]};
-            }
+            for (int e = 0; e < 4; ++e)
+                *reinterpret_cast<f4*>(p + 256 * e) = f4{acc[q & 1][q >> 1][4 * e], acc[q & 1][q >> 1][4 * e + 1], acc[q & 1][q >> 1][4 * e + 2], acc[q & 1][q >> 1][4 * e + 3]};
         }
-        __syncthreads();
     }
+    __syncthreads();
     f16v own[QT];
 #pragma unroll
     for (int o = 0; o < KW; ++o)
@@ -84,22 +82,19 @@ __device__ __forceinline__ void finish(f16v (&acc)[2][J], unsigned char* lds, in
 #pragma unroll
             for (int q = 0; q < QT; ++q) own[q] = acc[(o * QT + q) & 1][(o * QT + q) >> 1];
         }
-    if (KW > 1) {
-        const float* part = reinterpret_cast<const float*>(lds);
-        for (int s = 0; s < KW - 1; ++s) {
+    for (int s = 0; s < KW - 1; ++s) {
 #pragma unroll
-            for (int q = 0; q < QT; ++q) {
-                const float* p = part + ((((ow * KW + kw) * (KW - 1) + s) * QT + q) << 10) + 4 * lane;
+        for (int q = 0; q < QT; ++q) {
+            const float* p = part + ((((ow * KW + kw) * (KW - 1) + s) * QT + q) << 10) + 4 * lane;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const f4 t = *reinterpret_cast<const f4*>(p + 256 * e);
+            for (int e = 0; e < 4; ++e) {
+                const f4 t = *reinterpret_cast<const f4*>(p + 256 * e);
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) own[q][4 * e + x] += t[x];
-                }
+                for (int x = 0; x < 4; ++x) own[q][4 * e + x] += t[x];
             }
         }
-        __syncthreads();
     }
+    __syncthreads();
     unsigned char* stg = lds + wave * 2048;   // 32 rows of 64 bytes
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
