@@ -20,7 +20,7 @@ LAYERS = [
     (1032, 1352, 264),          # nine 32-column weak steps for eight waves; a ragged last group (1088 = 8 x 128 + 64)
     (264, 1160, 0),             # nothing weak; 9 x 128 + 8 columns
     (96, 320, 320),             # nothing quantized
-    (16648, 384, 64),           # four-wave workgroups (more tiles than CUs)
+    (16648, 384, 64),           # more tiles than CUs; three waves of one group each
 ]
 
 
@@ -40,6 +40,42 @@ def test_mid_rows(oc, ic, k):
         assert torch.equal(first, y), f"M={m}: repeats differ"
         assert bool((back[0] == 7).all()) and bool((back[m + 1] == 7).all()) and bool((back[:, oc:] == 7).all()), f"M={m}: wrote outside"
         assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), f"M={m}")
+
+
+@pytest.mark.parametrize("oc,kq", [
+    (2056, 25 * 128 + 64),      # tiles of 32 channels, eight waves: four groups each or three, the last ragged
+    (4104, 25 * 128 + 64),      # ... of 48
+    (6152, 25 * 128 + 64),      # ... of 64
+    (8200, 10 * 128 + 64),      # four waves: three groups each or two; tiles of 48
+    (12296, 10 * 128 + 64),     # ... of 64
+])
+def test_mid_rows_many_groups_per_wave(oc, kq):
+    """What one turn of a wave's loop fetches for the next: two and three 16-row tiles, every tile width."""
+    layer = HostLayer(oc, kq + 128, 128, 4, 128, seed=oc)
+    w, w64 = layer.to_device(), torch.from_numpy(layer.w64).cuda()
+    for m in (64, 96):
+        x = synth.make_activations(m, layer.ic, 128, seed=m)
+        xd = pad_cols(x)[0]
+        y = B.qeft_linear_fwd(layer.desc, w, xd, ws=False)
+        again = B.qeft_linear_fwd(layer.desc, w, xd, ws=False)
+        ref = xd.double() @ w64.t()
+        torch.cuda.synchronize()
+        assert torch.equal(y, again), f"M={m}: repeats differ"
+        assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"M={m}")
+
+
+@pytest.mark.parametrize("m", [20, 40, 96])
+def test_mid_rows_group_of_many_tiles(m):
+    """More tiles than CUs over three layers: four waves, three groups each or two."""
+    layers = [HostLayer(oc, 10 * 128 + 64 + 72, 72, 4, 128, seed=oc) for oc in (8200, 8264, 136)]
+    ws = [l.to_device() for l in layers]
+    x = synth.make_activations(m, layers[0].ic, 72, seed=4)
+    xd, _ = pad_cols(x)
+    ys = B.qeft_linear_fwd_group([l.desc for l in layers], ws, xd)
+    for l, y in zip(layers, ys):
+        ref = xd.double() @ torch.from_numpy(l.w64).cuda().t()
+        torch.cuda.synchronize()
+        assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"{l.oc} channels")
 
 
 @pytest.mark.parametrize("m", [17, 40, 96])

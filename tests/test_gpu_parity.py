@@ -253,7 +253,7 @@ GROUP_CASES = [  # ic, k, bits, [oc per layer], Ms
     (1024 + 128, 128, 4, [256, 64, 64], [1, 3]),        # query / key / value of different widths
     (512 + 64, 64, 4, [176, 176], [1, 4]),              # gate / up; a workgroup straddles the two layers
     (2048 + 128, 128, 4, [40, 24, 520, 8], [2]),        # four layers, ragged tiles
-    (1024 + 128, 128, 4, [256, 64], [9, 40]),           # more rows than the one-launch kernel takes: per-layer calls
+    (1024 + 128, 128, 4, [256, 64], [9, 40]),           # 9 rows: more than the one-launch decode kernel takes; 40: one launch of the mid-row kernel
     (640 + 40, 40, 3, [96, 32], [1]),                   # 3-bit: per-layer calls
 ]
 
@@ -601,9 +601,12 @@ def test_backward_in_one_call_three_bit(dense):
 
 @pytest.mark.parametrize("oc,ic,k,m", [
     (256, 4096 + 128, 128, 300),     # 2 tiles, 64 quantized stages: 8 splits of 8 stages, the weak block in the last
-    (528, 2560 + 64, 64, 64),        # 3 tiles (one ragged), 40 stages: 5 splits
-    (200, 1088 + 72, 72, 130),       # 17 stages: splits of 16 and 1 stage, ragged weak block (LDS-staged weak stages in the last split)
-    (1000, 3072, 0, 100),            # no weak block
+    (528, 2560 + 64, 64, 64),        # up to 96 rows, few channels up to 192: a kernel of its own, with the workspace as without
+    (200, 1088 + 72, 72, 130),
+    (1000, 3072, 0, 100),
+    (16648, 1088 + 72, 72, 100),     # 66 tiles, 17 stages: splits of 8, 8 and 1 stage, ragged weak block (LDS-staged weak stages in the last split)
+    (24584, 1088 + 72, 72, 250),     # 97 tiles: splits of 16 and 1 stage
+    (5384, 4096, 0, 110),            # no weak block: 8 splits
     (8448, 2048 + 128, 128, 2048),   # 264 tiles: 32 per XCD unsplit, the 33rd of each XCD in 4 splits
     (9448, 2048 + 128, 128, 1700),   # 259 tiles (ragged both ways): the last XCD has fewer tiles and no split one
 ])
@@ -633,7 +636,8 @@ def test_forward_k_split_with_workspace(oc, ic, k, m):
 
 @pytest.mark.parametrize("oc,ic,k,m", [
     (4096, 256 + 128, 128, 300),     # 2 x 2 tiles (the second half weak, then empty), 64 stages of rows: 8 splits
-    (1088, 640, 0, 64),              # 17 stages: splits of 16 and 1, no weak block
+    (1088, 640, 0, 64),              # small tiles, with the workspace as without
+    (2112, 640, 0, 64),              # 33 stages: four splits of 8 and one of 1, no weak block
     (2560, 1024 + 64, 64, 130),      # mixed last tile, 40 stages: 5 splits
     (2048, 8320 + 128, 128, 2048),   # 264 tiles: the 33rd of each XCD (the half-quantized, half-weak last one) in 4 splits
     (2112, 9344 + 128, 128, 1700),   # 259 tiles (split ones all quantized), 33 stages: 3 splits, the last of one stage

@@ -15,6 +15,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("oc,ic,k,rows", [
     (520, 4096 + 64, 64, (100, 150, 180, 220, 256, 300, 333, 430)),    # split; direct weak stages
     (328, 4096 + 72, 72, (131, 192, 385, 512)),                        # split; ragged weak block
+    (328, 4096 + 72, 72, (300, 333)),                                  # ... at 160 and 192 rows per panel
+    (5384, 4096 + 72, 72, (100, 128, 150, 180)),                       # one panel (layers of few channels run the mid-row kernel there)
+    (5384, 4096 + 64, 64, (97, 110)),
     (16648, 256, 0, (140, 333)),                                       # more tiles than a split is planned for
     (16648, 192 + 64, 64, (165, 222)),
 ])

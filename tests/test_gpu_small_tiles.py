@@ -30,13 +30,14 @@ def _run(call, m, cols, what, ref):
 FWD = [
     (200, 512 + 64, 64, (97, 193, 320)),          # 200 channels: the second tile mostly empty; one K group has no chunk in the second turn
     (264, 1352, 264, (257,)),                     # five weak stages for two shares, the last ragged; Kq = 1088 = 17 stages
-    (392, 4080 + 16, 16, (130,)),                 # the last stage 48 columns wide
+    (392, 4080 + 16, 16, (130, 200, 400)),        # the last stage 48 columns wide (130 rows: the mid-row kernel)
     (136, 896, 0, (209,)),                        # nothing weak
     (4104, 1024 + 8, 8, (777,)),                  # 128-row tiles
     (2056, 1600, 128, (1000, 515)),
 ]
 DX = [
-    (64, 512 + 8, 8, (17, 64)),                   # one stage of rows for eight shares of half-stages
+    (64, 512 + 8, 8, (17, 64)),                   # (whole groups, one stage: the large tiles)
+    (64, 504 + 16, 16, (17, 64)),                 # one stage of rows for eight shares of half-stages
     (320, 1024 + 136, 136, (65, 130)),            # two weak tiles, the second 8 wide; five stages
     (1088, 256, 0, (200,)),                       # nothing weak
     (1024, 3968 + 128, 128, (777, 129)),          # 128-row tiles

@@ -1,10 +1,10 @@
 """Perf-informational: the host-side choices between kernels, on shapes OFF the Llama-2 grid.
 
-Two choices are made from time models fitted to the Llama-2 shapes: several 16-token passes of the matrix-vector
-kernel instead of a GEMM that would fill a fraction of the compute units (forward without workspace, 16 < M <= 256),
-and splitting the contraction of some or all tiles over the optional workspace.  These tests time the library's
-choice and the alternative that the boundary lets a caller force (the passes as calls on 16-row slices; the call
-without the workspace) with HIP events and require the choice to be at most 10 % slower than that alternative.
+The choices are made from row counts and time models fitted to the Llama-2 shapes: which forward kernel serves the rows between the
+decode sizes and the large GEMM, whether the contraction of some or all tiles is split over the optional workspace, which copy of
+a 3-bit layer is multiplied, how many ways the weak gradient splits its tokens.  These tests time the library's
+choice and an alternative that the boundary lets a caller force (calls on 16-row slices; the call without the workspace; the
+product of an fp16 copy; a wider weak block) with HIP events and require the choice to be at most 10 % slower than that alternative.
 No numerics here (the parity tests cover every path); a failure means a heuristic needs refitting, not a wrong
 result.  Timings on a shared machine wobble, so a miss is measured a second time, and only a miss of more than 25 %
 fails the test; one between 10 % and 25 % is reported as an expected-failure note with the figures.  The file is named
