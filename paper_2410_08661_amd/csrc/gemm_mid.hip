@@ -339,19 +339,18 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
             for (int e = 0; e < 4; ++e) y[e] += p[e];
         }
         const int row = 16 * (q / NT) + 4 * kb, col = 16 * (q % NT) + n;
-        if (A.ng > 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint64_t bad = __ballot(y[e] != y[e] && row + e <= mlast && o0 + col < oc);
-                if (__builtin_expect(bad != 0, 0)) {
+        const float any = (y[0] + y[1]) + (y[2] + y[3]);   // (no number as well where two infinities cancel: looked at one by one below)
+        if (__builtin_expect(A.ng > 0 && __ballot(any != any) != 0, 0)) {
 #pragma clang loop unroll(disable)
-                    for (int b = 0; b < 4; ++b) {
-                        const uint32_t want = (uint32_t)(bad >> (16 * b)) & 0xffffu;
-                        if (want == 0) continue;
-                        const float r = repair_row(m0 + row - 4 * kb + 4 * b + e, col, want);
-                        if (kb == b && y[e] != y[e] && r - r != 0.f) y[e] = r;
-                    }
-                }
+            for (int i = 0; i < 16; ++i) {   // row 4 b + e of the tile
+                const int b = i >> 2, e = i & 3;
+                const float mine_y = e == 0 ? y[0] : (e == 1 ? y[1] : (e == 2 ? y[2] : y[3]));
+                const uint32_t want = (uint32_t)(__ballot(mine_y != mine_y && row + e <= mlast && o0 + col < oc) >> (16 * b)) & 0xffffu;
+                if (want == 0) continue;
+                const float r = repair_row(m0 + row - 4 * kb + i, col, want);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (t == e && kb == b && y[t] != y[t] && r - r != 0.f) y[t] = r;
             }
         }
         // lane (n, kb) holds rows 4 kb .. 4 kb + 3 of channel n; a 4 x 4 transpose inside each quad of lanes gives it
