@@ -60,7 +60,7 @@ def test_sums_stay_in_fp32_without_room_for_a_split(dense):
 
 
 @pytest.mark.parametrize("dense", [False, True])
-@pytest.mark.parametrize("oc,ic,k", [(5120, 5120, 128), (2048, 4096, 64)])
+@pytest.mark.parametrize("oc,ic,k", [(5120, 5120, 128), (2048, 4096, 64), (5376, 4160, 64)])
 def test_fractional_zero_points_are_rounded_once(oc, ic, k, dense):
     """Zero-points between 0 and 1: q - z is no fp16 number, and s (q - z) is still rounded once, in every kernel a row count
     leads to (panels of 128 to 256 rows, small tiles, both forms of the input gradient)."""
