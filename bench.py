@@ -295,7 +295,7 @@ def main():
     pack_search_us = e0.elapsed_time(e1) * 1e3 / 5
 
     # 3-bit storage of the same up-projection (Tab. 5's 3-bit models), both layouts: decode over rotating packed
-    # copies, and the forward at M = 4096 through the dequantized fp16 copy
+    # copies, and the forward at M = 4096 through the copy in the 4-bit layout
     three_bit = {"layer": "11008x4096, w3 g128 k=128"}
     w3 = synth_weight(11008, 4096)
     f1 = ft[1]

@@ -268,7 +268,7 @@ int qeft_weak_grad(const qeft_desc_t* desc, const void* dY, int64_t M, int64_t l
  * dW (+)= dY^T . Xw for the weak block, arguments as in qeft_linear_bwd_dx and qeft_weak_grad.  The same kernels
  * run as in those two calls, and the results equal theirs bit for bit; what the call chooses is how they go out:
  *   - with room in ws for what qeft_linear_bwd_dx can use (qeft_workspace_bytes(desc, QEFT_OP_BWD, M), the larger
- *     of the two steps' amounts: the partial tiles of a row split of dX where that split applies, the fp16 copy of
+ *     of the two steps' amounts: the partial tiles of a row split of dX where that split applies, the copy of
  *     a 3-bit layer - without which its dX takes the slow general kernel): dX with that workspace, then the weak
  *     gradient, as qeft_linear_bwd_dx with its workspace followed by qeft_weak_grad (the workspace serves one after
  *     the other);

@@ -506,7 +506,7 @@ int qeft_linear_bwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
     if (need_dw > 0 && (!ws || ws_bytes < need_dw || !aligned16(ws))) return QEFT_ERR_WORKSPACE;
     // room for the partial tiles of a row split of dX: that split fills a sparse last round of tiles better than the
     // weak gradient's strips do, so it goes first (the strips' partial sums reuse the same bytes afterwards)
-    // (a 3-bit layer: room for its fp16 copy - without it dX would take the slow general kernel - and, beyond that, for
+    // (a 3-bit layer: room for its copy - without it dX would take the slow general kernel - and, beyond that, for
     // the copy's own split; qeft_linear_bwd_dx uses what it is given)
     size_t need_dx = gemm_dx_supported(L, M) ? gemm_dx_split_workspace(L, M) : 0;
     if (dense_copy_applies(L, M)) need_dx = dense_copy_bytes(L);

@@ -10,7 +10,7 @@
 // Mapping: 16x16x32 MFMA, rows of X as the A operand, 16 channels as the B operand (a packed word is a lane's 8 contraction
 // elements), a group of 128 columns at a time.  The workgroup's waves take every KS-th group each and share nothing until
 // the end, so the main loop has no barrier: a wave brings its group's rows to a piece of LDS of its own (whole 256-byte row
-// pieces, nibble order, chunks XOR-placed by the row: free of bank conflicts), reads them back as fragments once and
+// pieces, nibble order, chunks XOR-placed by the row; a fifth of the LDS cycles are conflicts), reads them back as fragments once and
 // multiplies all its channel tiles.  Dequantization as in the 16-row kernels, on the accumulator and without rounding the
 // weights: s (sum x (1024 + q) - (1024 + z) Sx), two FMAs per accumulator and group.  The next group's rows, codes and
 // parameters are requested while this one is multiplied.  Partial tiles meet in LDS in a fixed order (fp32).

@@ -10,7 +10,7 @@
 //
 // What bounds it: vector issue.  An MFMA 32x32x16 holds a SIMD's issue for 12 of its 32 cycles and every vector instruction
 // for 4, also with two waves per SIMD (measured: 33 cycles per MFMA with up to 5 of them, 44 with 8, 60 with 12).  A wave of
-// 64 rows converts 17 instructions per word for 2 products each and runs 11 per MFMA; of 128 rows 6.  A launch costs 8 to
+// 64 rows converts 17 instructions per word for 2 products each and runs 11.8 per MFMA (counted); of 128 rows 7.2 to 7.5.  A launch costs 8 to
 // 10 us beyond its stages (first fetches from HBM, the exchange of partial tiles, stores).
 // Measured, without a workspace, before -> now (us): forward 4096 x 4096 at M = 333 / 512 / 777: 77 -> 26 / 29 / 40,
 // 4096 x 11008 at 512: 206 -> 72; input gradient 4096 x 4096 at 333 / 512 / 777: 90 -> 31 / 35 / 50, 11008 x 4096 at 512:
