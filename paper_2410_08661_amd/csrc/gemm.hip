@@ -1632,9 +1632,9 @@ int weak_grad_strip_most(int oc, int k, int64_t M) {
     if (want < 1) want = 1;
     return ceil_div(M, ceil_div(stages, want) * BK);
 }
-// The split taken: a stage of 64 tokens costs a workgroup about 0.62 us where the strip's 128 weak columns all exist, 1.05 where
+// The split taken: a stage of 64 tokens costs a workgroup about 0.62 us where the strip's 128 weak columns all exist, 1.06 where
 // some do not; workgroups past one per CU count in full there, by 0.3 here (a stage that waits leaves room for another's); a
-// split costs the second launch and the partial slabs' way through memory (2 us and 0.65 us per MB).  Measured, as many splits as
+// split costs the second launch and its partial slab's way through memory (2 us once, 0.13 us and 0.65 us per MB each).  Measured, as many splits as
 // above against the rule's, us: 4096 channels, k = 128, M = 200 / 512 / 1003: 12.3 / 12.4 / 14.1 against 7.6 / 9.0 / 13.1 (one, one,
 // two; four at M = 4096 either way); 11008 channels, M = 512 / 2048: 19.0 / 26.0 against 9.5 / 22.6 (one; two at M = 3000);
 // 1024 channels, k = 128, M = 2048: 14.5 against 12.2 (four of eight).  Narrower blocks, one split against two: 13824 channels,
@@ -1643,11 +1643,11 @@ void weak_grad_strip_split(int oc, int k, int64_t M, int& splits, int& chunk) {
     const int tiles = ceil_div(oc, WG_OC) * ceil_div(k, 128);
     const int stages = ceil_div(M, BK), most = weak_grad_strip_most(oc, k, M);
     const bool full = k % 128 == 0;
-    const double slab_mb = (double)oc * k * 4e-6, stage_us = full ? 0.62 : 1.05;
+    const double slab_mb = (double)oc * k * 4e-6, stage_us = full ? 0.62 : 1.06;
     double best = 1e30;
     for (int s = 1; s <= most; ++s) {
         const double w = (double)tiles * s / 256.0;
-        const double t = (w <= 1 ? 1 : (full ? w : 0.7 + 0.3 * w)) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + 0.65 * s * slab_mb : 0.0);
+        const double t = (w <= 1 ? 1 : (full ? w : 0.7 + 0.3 * w)) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + (0.13 + 0.65 * slab_mb) * s : 0.0);
         if (t < best) {
             best = t;
             chunk = ceil_div(stages, s) * BK;
