@@ -431,33 +431,41 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
         const uint32_t lc = lds_at(lds) + (uint32_t)(KW * 2 * XT + kw * 2 * CT);
         const uint32_t lv = lds_at(lds) + (uint32_t)(KW * (2 * XT + 2 * CT) + kw * 2 * VT);
         // codes: thread tk fetches half a row of the stage (row tk / 2, 32 bytes); parameters: threads 0 .. 63 the scales,
-        // 64 .. 127 the zero-points, one row each
+        // 64 .. 127 the zero-points, one row each (ONCE: a row's two lie 32 lanes apart in one wave, which swaps its halves and stores both
+        // values from both lanes; a branch here would make the compiler wait for every request on the way, and these requests, 64
+        // cache lines each, are as dear as the codes')
         const unsigned char* wt = reinterpret_cast<const unsigned char*>(L.qweight) + c0 / 2;
-        const int crow = tk >> 1, cpart = tk & 1, prow = tk & 63;
+        const int crow = tk >> 1, cpart = tk & 1, prow = ONCE ? 32 * ow + (lane & 31) : tk & 63;
         const uint32_t wpitch = (uint32_t)L.stride * 4u;
         const unsigned char* pt = reinterpret_cast<const unsigned char*>((ow == 0 ? L.scales : L.zeros) + c0 / 128);   // (threads 0 .. 63: wave 0 of the K group)
         const uint32_t coff = (uint32_t)crow * wpitch + 32u * cpart, poff = (uint32_t)prow * (uint32_t)(L.gs * 2);
-        const unsigned char* st_ = reinterpret_cast<const unsigned char*>(L.scales + c0 / 128);
+        const unsigned char* pl = reinterpret_cast<const unsigned char*>((lane < 32 ? L.scales : L.zeros) + c0 / 128) + poff;   // (ONCE)
         u4 cw[DX][2];
-        uint32_t pv[DX], ps[DX];   // ps: the scale beside the zero-point (ONCE)
+        uint32_t pv[DX];
         auto load_c = [&](int set, int st) {   // (stages past the last repeat it; their rows of dY are zeroed)
             const int sc = min(st, nst - 1);
             gptr p = sbase(wt + (size_t)(64 * sc) * wpitch) + coff;
             cw[set][0] = *reinterpret_cast<g_u4*>(p);
             cw[set][1] = *reinterpret_cast<g_u4*>(p + 16);
-            pv[set] = *reinterpret_cast<g_u16*>(sbase(pt + (size_t)(64 * sc) * (uint32_t)(L.gs * 2)) + poff);
-            if constexpr (ONCE) ps[set] = *reinterpret_cast<g_u16*>(sbase(st_ + (size_t)(64 * sc) * (uint32_t)(L.gs * 2)) + poff);
+            const size_t at = (size_t)(64 * sc) * (uint32_t)(L.gs * 2);
+            if constexpr (ONCE) pv[set] = *(g_u16*)(pl + at);
+            else pv[set] = *reinterpret_cast<g_u16*>(sbase(pt + at) + poff);
         };
         // chunk c (32 channels) of row r sits in slot c ^ (r / 4 % 4): the 16 rows of a transposing read then spread over the banks
         const uint32_t cst = lc + (uint32_t)(crow * 64);
         const uint32_t csw = (uint32_t)((crow >> 2) & 3);
         const int pat = (prow & 3) * 2 + ((prow >> 2) & 1);   // rows r and r + 4 of 8 side by side, as a word's pairs
-        const uint32_t pst = lv + (uint32_t)((prow >> 3) * (VS + 16) + (ow == 0 ? VS + 2 * pat : (VS / 8) * pat));
+        const uint32_t pst = lv + (uint32_t)((prow >> 3) * (VS + 16) + (ow == 0 && !ONCE ? VS + 2 * pat : (VS / 8) * pat));
+        const uint32_t pss = lv + (uint32_t)((prow >> 3) * (VS + 16) + VS + 2 * pat);   // (ONCE)
         auto put_c = [&](int set, int buf) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) *reinterpret_cast<lds_u4*>(cst + (((2 * cpart + h) ^ csw) << 4) + (uint32_t)(buf * CT)) = cw[set][h];
-            if (ONCE && ow == 1) *reinterpret_cast<lds_f32*>(pst + (uint32_t)(buf * VT)) = neg_zs(bits_h2(pv[set]).x, bits_h2(ps[set]).x);
-            else *reinterpret_cast<lds_u16*>(pst + (uint32_t)(buf * VT)) = (uint16_t)pv[set];
+            if constexpr (ONCE) {
+                const auto sz = __builtin_amdgcn_permlane32_swap(pv[set], pv[set], false, false);   // the scale, the zero-point
+                *reinterpret_cast<lds_f32*>(pst + (uint32_t)(buf * VT)) = neg_zs(bits_h2(sz[1]).x, bits_h2(sz[0]).x);
+                *reinterpret_cast<lds_u16*>(pss + (uint32_t)(buf * VT)) = (uint16_t)sz[0];
+            } else
+                *reinterpret_cast<lds_u16*>(pst + (uint32_t)(buf * VT)) = (uint16_t)pv[set];
         };
         // a transposing read hands lane s of each 16 the 16 rows of column s of a 16 x 16 block of codes; block row 32 p + 16 fk,
         // column block 32 i + 16 (lane / 16 % 2) of the wave's 64 channels
