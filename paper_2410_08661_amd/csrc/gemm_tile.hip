@@ -761,23 +761,20 @@ bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
 // A 3-bit layer whose quantized columns are not whole stages (forward: 64 columns) or whole groups (input gradient): its 4-bit copy
 // N has the kernels above but not the register GEMM, which its fp16 copy D always has, with a split where there is room.  Either
 // way's time is the kernel's estimate and the copy's pass (and, for D, four times the weights to read), fitted to both ways of 190
-// random calls of 65 layers at 17 to 4000 rows (7 to 11 % spread).  The estimate has to be 13 % (forward) or 10 % ahead: the choice
-// is then slower than the fp16 copy by more than 3 % in 3 of 461 calls and within 1 % of the faster way on average.  us, 4-bit copy against fp16 copy: input gradient of 8192 x 8192 with 64 weak
+// random calls of 65 layers at 17 to 4000 rows (7 to 11 % spread).  The estimate has to be 6 % (forward) or 10 % ahead: the choice is
+// then slower than the fp16 copy by more than 3 % in 2 of 828 other calls (5 % at most) and within 1 % of the faster way on average.  us, 4-bit copy against fp16 copy: input gradient of 8192 x 8192 with 64 weak
 // columns at M = 48 / 200 / 333 / 2048: 75 / 112 / 113 / 434 against 91 / 99 / 119 / 277; forward of 13824 x 5120 with 16 at M = 210 / 571 /
 // 1066: 64 / 150 / 234 against 116 / 180 / 243, of 5120 x 13824 with 72 at M = 803: 256 against 189.
-namespace {
-double est_split_or_not(const GemmSplit& p, int channels, int64_t M, int stages, double per_stage, double split_fixed, double split_stage) {
-    if (p.splits <= 1) return est_gemm(channels, M, stages, per_stage);
-    if (!p.tail) return est_split(p, split_fixed, split_stage);
-    return est_gemm(channels, M, stages, per_stage) - stages * per_stage + p.stages * split_stage + split_fixed;   // the last round's tiles only
-}
-}  // namespace
 bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx, bool split_n, bool split_d) {
     if (N.kq % 64 == 0 || (fwd_mid_supported(N, M, ldx) && fwd_mid_preferred(N, M, split_n))) return true;
     if (!fwd_tile_preferred(N, M, ldx, split_n)) return false;
     const GemmSplit p = split_d ? gemm_fwd_split(D, M) : GemmSplit{1, 0, 0, false};
-    const double whole = D.ic % 64 == 0 ? panel(M) : 2.4, n = (double)N.oc * N.ic / (1 << 20);
-    return est_fwd(N, M).t + 0.2 * n + 3.5 < 0.87 * (1.1 * est_split_or_not(p, D.oc, M, ceil_div(D.ic, 64), 1.15 * whole, 11, 1.45 * whole) + 1.2 * n);
+    const double n = (double)N.oc * N.ic / (1 << 20);
+    double t16;
+    if (D.ic % 64 != 0) t16 = 1.1 * est_gemm(D.oc, M, ceil_div(D.ic, 64), 1.15 * 2.4) + 1.2 * n;
+    else if (p.splits > 1 && !p.tail) t16 = 8 + 1.31 * p.stages + 0.09 * p.tiles * p.splits + n;
+    else t16 = est_gemm(D.oc, M, D.ic / 64, 1.45 * panel(M)) + 2 + 1.1 * n - (p.tail ? 1.45 * (D.ic / 64 * panel(M) - p.stages) - 10 : 0);
+    return est_fwd(N, M).t + 0.2 * n + 3.5 < 0.94 * t16;
 }
 bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy, bool split_n, bool split_d) {
     if (N.oc % 64 != 0) return false;
@@ -785,7 +782,9 @@ bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy,
     if (!dx_tile_preferred(N, M, lddy, split_n)) return false;
     const GemmSplit p = split_d ? gemm_dx_split(D, M) : GemmSplit{1, 0, 0, false};
     const double rounds = (int64_t)dx_tiles(N) * ceil_div(M, 64) > 512 ? 1.25 : 1.0, n = (double)N.oc * N.ic / (1 << 20);   // (a third round of tiles is underestimated)
-    return rounds * est_dx(N, M).t + 0.28 * n + 1.5 < 0.9 * (1.05 * est_split_or_not(p, D.ic, M, D.oc / 64, 1.3, 12, 1.5) + 0.85 * n);
+    double gemm = est_gemm(D.ic, M, D.oc / 64, 1.3);
+    if (p.splits > 1) gemm = p.tail ? gemm - D.oc / 64 * 1.3 + p.stages * 1.5 + 12 : est_split(p, 12, 1.5);   // (tail: the last round's tiles only)
+    return rounds * est_dx(N, M).t + 0.28 * n + 1.5 < 0.9 * (1.05 * gemm + 0.85 * n);
 }
 
 hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s) {
