@@ -1634,7 +1634,8 @@ int weak_grad_strip_most(int oc, int k, int64_t M) {
 }
 // The split taken: a stage of 64 tokens costs a workgroup about 0.62 us where the strip's 128 weak columns all exist, 1.06 where
 // some do not; workgroups past one per CU count in full there, by 0.3 here (a stage that waits leaves room for another's); a
-// split costs the second launch and its partial slab's way through memory (2 us once, 0.13 us and 0.65 us per MB each).  Measured, as many splits as
+// split costs the second launch and its partial slab's way through memory (2 us once, 0.65 us per MB
+// and, in narrower blocks, 0.13 us each).  Measured, as many splits as
 // above against the rule's, us: 4096 channels, k = 128, M = 200 / 512 / 1003: 12.3 / 12.4 / 14.1 against 7.6 / 9.0 / 13.1 (one, one,
 // two; four at M = 4096 either way); 11008 channels, M = 512 / 2048: 19.0 / 26.0 against 9.5 / 22.6 (one; two at M = 3000);
 // 1024 channels, k = 128, M = 2048: 14.5 against 12.2 (four of eight).  Narrower blocks, one split against two: 13824 channels,
@@ -1647,7 +1648,7 @@ void weak_grad_strip_split(int oc, int k, int64_t M, int& splits, int& chunk) {
     double best = 1e30;
     for (int s = 1; s <= most; ++s) {
         const double w = (double)tiles * s / 256.0;
-        const double t = (w <= 1 ? 1 : (full ? w : 0.7 + 0.3 * w)) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + (0.13 + 0.65 * slab_mb) * s : 0.0);
+        const double t = (w <= 1 ? 1 : (full ? w : 0.7 + 0.3 * w)) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + ((full ? 0.0 : 0.13) + 0.65 * slab_mb) * s : 0.0);
         if (t < best) {
             best = t;
             chunk = ceil_div(stages, s) * BK;
