@@ -761,10 +761,11 @@ bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
 // A 3-bit layer whose quantized columns are not whole stages (forward: 64 columns) or whole groups (input gradient): its 4-bit copy
 // N has the kernels above but not the register GEMM, which its fp16 copy D always has, with a split where there is room.  Either
 // way's time is the kernel's estimate and the copy's pass (and, for D, four times the weights to read), fitted to both ways of 190
-// random calls of 65 layers at 17 to 4000 rows (7 to 11 % spread).  The estimate has to be 6 % (forward) or 10 % ahead: the choice is
-// then slower than the fp16 copy by more than 3 % in 2 of 828 other calls (5 % at most) and within 1 % of the faster way on average.  us, 4-bit copy against fp16 copy: input gradient of 8192 x 8192 with 64 weak
-// columns at M = 48 / 200 / 333 / 2048: 75 / 112 / 113 / 434 against 91 / 99 / 119 / 277; forward of 13824 x 5120 with 16 at M = 210 / 571 /
-// 1066: 64 / 150 / 234 against 116 / 180 / 243, of 5120 x 13824 with 72 at M = 803: 256 against 189.
+// random calls of 65 layers at 17 to 4000 rows (7 to 11 % spread).  The estimate has to be 6 % (forward) or 10 % ahead: the choice
+// is then slower than the fp16 copy by more than 3 % in 2 of 828 other calls (5 % at most) and within 1 % of the faster way on
+// average.  us, 4-bit copy against fp16 copy: input gradient of 8192 x 8192 with 64 weak columns at M = 48 / 200 / 333 / 2048: 73 / 109 /
+// 109 / 434 against 91 / 99 / 119 / 277; forward of 13824 x 5120 with 16 at M = 210 / 571 / 1066: 64 / 150 / 234 against 116 / 180 / 243, of
+// 5120 x 13824 with 72 at M = 803: 256 against 189.
 bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx, bool split_n, bool split_d) {
     if (N.kq % 64 == 0 || (fwd_mid_supported(N, M, ldx) && fwd_mid_preferred(N, M, split_n))) return true;
     if (!fwd_tile_preferred(N, M, ldx, split_n)) return false;
