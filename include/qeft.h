@@ -58,7 +58,8 @@ typedef enum {
  *                          (bit b of the row = bit b % 32 of word b / 32), 32 codes in 3 words, codes may
  *                          straddle words: 3.0 bits per quantized weight, the storage that the 3-bit model
  *                          sizes of the paper's Tab. 5 correspond to.  Every entry point takes either layout
- *                          (decode, M <= 16: a kernel of its own when the padded row holds whole groups, i.e.
+ *                          (the stored codes are multiplied as they are at up to 96 rows, further for small layers,
+ *                          and at any M without a workspace, when the padded row holds whole groups, i.e.
  *                          12 * G <= row_stride_words, which every Kq that is a multiple of 128 satisfies;
  *                          larger M and the backward pass: as for all 3-bit layers, the tensor-core kernels on
  *                          a copy in the caller's workspace, see qeft_workspace_bytes, or the slow
@@ -162,10 +163,11 @@ int qeft_unpack(const qeft_desc_t* desc, const qeft_weight_t* w, uint8_t* codes,
  * QEFT_OP_FWD / QEFT_OP_BWD_DX report OC * IC * 2 bytes for 3-bit layers
  * at M > 16 (plus the partial tiles of a split of the copy's columns or rows as above, used when the whole
  * amount is given): with that workspace (16-byte aligned) the call rewrites the layer once into it and runs the
- * tensor-core kernels on the copy - the codes in the 4-bit layout for groups of 128 and 2^20 weights or more where the kernel
+ * tensor-core kernels on the copy (forwards of up to 96 rows, further for small layers, multiply the stored codes
+ * and leave the workspace alone) - the codes in the 4-bit layout for groups of 128 and 2^20 weights or more where the kernel
  * for them is the faster one, else the whole layer dequantized to fp16 (the paper's own training path, dequantize then a dense
  * product; Sec. 4.3, App. A.2); either way s (q - z) is rounded to fp16 at most once -
- * and without it (ws NULL) the slow general kernel; a workspace that is too small is
+ * and without it (ws NULL) the forward multiplies the stored codes and the input gradient takes the slow general kernel; a workspace that is too small is
  * QEFT_ERR_WORKSPACE.  The copy is rewritten by every call (the weak block may have changed).
  * QEFT_OP_BWD (qeft_linear_bwd): the larger of QEFT_OP_WEAK_GRAD's amount, which that call requires, and
  * QEFT_OP_BWD_DX's, which it uses when given (the two steps use the workspace one after the other). */

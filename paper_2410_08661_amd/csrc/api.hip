@@ -248,6 +248,7 @@ int qeft_linear_fwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
         const Layer N = nibble_copy_layer(L, ws), D = dense_copy_layer(L, ws);
         const size_t need = gemm_fwd_supported(D, M) ? gemm_fwd_split_workspace(D, M) : 0;
         const bool whole = need > 0 && ws_bytes >= dense_copy_bytes(L) + need;   // what the caller gave holds a split of the fp16 copy too
+        if (fwd_mid3_preferred(L, M, ldx)) return hip_status(fwd_mid(&L, 1, x, M, ldx, &y, &ldy, s));
         if (nibble_copy_applies(L, M) && gemm_fwd_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
             void* split_ws = whole ? behind_nibble_copy(N, gemm_fwd_split_workspace(N, M), ws, ws_bytes) : nullptr;
             if (fwd_copy4_preferred(N, D, M, ldx, split_ws != nullptr, whole)) {
@@ -262,6 +263,7 @@ int qeft_linear_fwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
             return hip_status(gemm_fwd(D, x, M, ldx, y, ldy, split_ws, s));
         }
     }
+    if (M > 16 && L.bits == 3 && fwd_mid_supported(L, M, ldx)) return hip_status(fwd_mid(&L, 1, x, M, ldx, &y, &ldy, s));
     if (gemv_supported(L, M, ldx)) {
         // the matrix-vector kernel takes up to 16 rows per pass
         for (int64_t m0 = 0; m0 < M; m0 += 16) {
@@ -290,9 +292,12 @@ int qeft_linear_fwd_group(int n, const qeft_desc_t* descs, const qeft_weight_t* 
     if (st != QEFT_OK) return st;
     if (M == 0) return QEFT_OK;
     hipStream_t s = (hipStream_t)stream;
-    if (n > 1 && gemm_fwd_supported(Ls[0], M) && fwd_mid_supported(Ls[0], M, ldx) && fwd_mid_preferred(Ls[0], M, false)) {
+    const auto mid = [&](const Layer& L) {
+        return M > 16 && fwd_mid_supported(L, M, ldx) && (L.bits == 3 || (gemm_fwd_supported(L, M) && fwd_mid_preferred(L, M, false)));
+    };
+    if (n > 1 && mid(Ls[0])) {
         bool all = true;   // (the other layers differ in OC only)
-        for (int i = 1; i < n; ++i) all = all && fwd_mid_supported(Ls[i], M, ldx) && fwd_mid_preferred(Ls[i], M, false);
+        for (int i = 1; i < n; ++i) all = all && mid(Ls[i]);
         if (all) {
             __half* ys[QEFT_MAX_GROUP];
             for (int i = 0; i < n; ++i) ys[i] = (__half*)Y[i];

@@ -1,5 +1,5 @@
-// Forward of 4-bit layers for 17 to 192 rows: several sequences decoded together, short prompts, draft tokens.
-// (Paper Sec. 3.2.1; the rows between the matrix-vector kernels' 16 and the sizes at which 256 x 256 tiles occupy the GPU.)
+// Forward of 4-bit layers for 17 to 192 rows and of 3-bit layers from 2 rows on: several sequences decoded together, short prompts,
+// draft tokens.  (Paper Sec. 3.2.1; the rows between the matrix-vector kernels' 16 and the sizes at which 256 x 256 tiles occupy the GPU.)
 //
 // A layer's codes are read once per panel of up to 48 rows, where passes of the 16-row kernel read them once per 16 rows
 // and the tiled GEMM leaves OC / 256 of 256 compute units working on the whole contraction.  What bounds the kernel: every
@@ -17,6 +17,10 @@
 // Measured (passes or GEMM before -> now, us): 4096 x 4096, M = 40: 18.4 -> 10.2; 12288 x 4096 (q/k/v), M = 40: 26.9 -> 16.7;
 // 22016 x 4096 (gate/up), M = 48: 39 -> 30; 4096 x 11008, M = 40: 38.6 -> 23.7; 13824 x 5120, M = 64: 62 (46 with a K-split
 // workspace) -> 32; 4096 x 4096, M = 96: 37 (24) -> 12.
+// 3-bit codes are multiplied as they are stored (Codes3).  Against the kernel that converted them to fp16 weights at up to 16 rows, and
+// that kernel's passes or a copy in the 4-bit layout above (us, ten codes a word): 5120 x 5120, M = 2 / 16 / 40: 11.4 / 14.5 / 24.6 -> 8.5 /
+// 9.8 / 14.5; 15360 x 5120 (q/k/v) M = 8 / 40: 39.6 / 125 -> 15.8 / 26.6; 27648 x 5120 (gate/up) M = 8: 41 -> 26.5; 512 x 512, M = 8: 8.6 -> 3.8.
+// The small row counts are bound by the work per tile beside the codes (fragments, sums), the others as above.
 // Tried and not kept: 64 rows per panel (registers spill, 2 to 5 times slower), codes two groups ahead for more than two
 // channel tiles (spills), parameters of four groups per request (no faster, and the waves' shares come out uneven).
 #include <type_traits>
@@ -32,6 +36,8 @@ typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u3w __attribute__((ext_vector_type(3), aligned(4)));   // three / four words at any word of a row
+typedef uint32_t u4w __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ h8 as_h8(u4 v) { return __builtin_bit_cast(h8, v); }
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return __builtin_bit_cast(uint32_t, h2{(_Float16)a, (_Float16)b}); }
@@ -45,6 +51,48 @@ __device__ __forceinline__ u4 permute_x(u4 v) {
     r.z = __builtin_amdgcn_perm(v.w, v.y, 0x05040100u);
     r.w = __builtin_amdgcn_perm(v.w, v.y, 0x07060302u);
     return r;
+}
+
+// How a layer's codes are stored.
+enum Fmt { W4 = 0, W3_DENSE = 1, W3_TEN = 2 };
+
+// Three-bit codes.  A lane's 32 columns of a group are 96 consecutive bits of a dense row: three words.  Ten codes to a word
+// (W3_TEN): columns 32 c .. + 31 start at code p = 32 c % 10 of word 32 c / 10, and p <= 8, so they lie in four words whose 30-bit
+// payloads are first joined to the same three (nine instructions, the shift 3 p the lane's own).  Each ten of the 32 codes then become
+// five pairs (i, i + 5): the upper five move up one bit, to the upper half, and every pair is a shift and a mask away; codes 30 and 31
+// are a pair of their own.  38 instructions per 32 codes where a field extract and a multiplication per pair took 50.
+struct Codes3 {
+    uint32_t y[3], r;
+    template <Fmt F>
+    __device__ __forceinline__ void take(u4 w, uint32_t shift) {
+        uint32_t a = w.x, b = w.y, c = w.z;
+        if (F == W3_TEN) {
+            const uint32_t c0 = w.x | (w.y << 30), c1 = (w.y >> 2) | (w.z << 28), c2 = (w.z >> 4) | (w.w << 26), c3 = w.w >> 6;
+            a = __builtin_amdgcn_alignbit(c1, c0, shift);
+            b = __builtin_amdgcn_alignbit(c2, c1, shift);
+            c = __builtin_amdgcn_alignbit(c3, c2, shift);
+        }
+        const uint32_t t1 = __builtin_amdgcn_alignbit(b, a, 30), t2 = __builtin_amdgcn_alignbit(c, b, 28), t3 = c >> 26;
+        y[0] = (a & 0xffffu) | ((a << 1) & 0xffff0000u);
+        y[1] = (t1 & 0xffffu) | ((t1 << 1) & 0xffff0000u);
+        y[2] = (t2 & 0xffffu) | ((t2 << 1) & 0xffff0000u);
+        r = t3 | (t3 << 13);
+    }
+    __device__ __forceinline__ uint32_t bits(int P) const { return P == 15 ? r : (y[P / 5 < 3 ? P / 5 : 0] >> (3 * (P % 5))); }   // pair P at bits 0 .. 2 of each half
+};
+
+// 32 consecutive activations in the order of those pairs
+__device__ __forceinline__ void pair_x3(u4 (&v)[4]) {
+    uint32_t o[16];
+#pragma unroll
+    for (int P = 0; P < 15; ++P) {
+        const int lo = 10 * (P / 5) + P % 5, hi = lo + 5;
+        const uint32_t a = v[lo >> 3][(lo >> 1) & 3], b = v[hi >> 3][(hi >> 1) & 3];
+        o[P] = __builtin_amdgcn_perm(b, a, ((lo & 1) ? 0x0302u : 0x0100u) | ((hi & 1) ? 0x07060000u : 0x05040000u));
+    }
+    o[15] = v[3][3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = u4{o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]};
 }
 
 struct MidArgs {
@@ -64,13 +112,15 @@ struct MidArgs {
 
 // One workgroup: 16 NT channels x 16 MT rows of Y over the whole contraction, which its KS waves divide; the partial tiles
 // meet in LDS at the end (fp32, fixed order).
-template <int MT, int NT>
+// XR: requests of activations per group, 4 rows each (MT = 1: as many as there are rows; else all of the tile's).
+template <int MT, int NT, Fmt F, int XR>
 __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int XB = MT * 16 * 256;            // a group of activations: 16 MT rows of 256 bytes
     constexpr int PB = 64 * 4;                   // (zero-point, scale) of a group, up to 64 channels
-    constexpr bool FULL = NT == 1;               // activations of the next group: all in flight at once, or half by half
-    constexpr int H = FULL ? 4 * MT : 2 * MT;    // 16-byte requests in flight (a request: 4 rows)
+    static_assert(MT == 1 || XR == 4 * MT, "");
+    constexpr bool FULL = NT == 1 || MT == 1;    // activations of the next group: all in flight at once, or half by half
+    constexpr int H = FULL ? XR : XR / 2;        // 16-byte requests in flight (a request: 4 rows)
     const int lane = threadIdx.x & 63;
     const int KS = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -93,7 +143,7 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     const __half* zbase = A.zeros[li] + (size_t)o0 * A.gs;
     uint32_t woff[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) woff[t] = (uint32_t)min(16 * t + n, oc - 1 - o0) * (uint32_t)(A.stride * 4) + 16u * kb;
+    for (int t = 0; t < NT; ++t) woff[t] = (uint32_t)min(16 * t + n, oc - 1 - o0) * (uint32_t)(A.stride * 4) + (F == W4 ? 16u * kb : (F == W3_DENSE ? 12u * kb : 0u));
     const uint32_t poff = (uint32_t)min(min(lane, 16 * NT - 1), oc - 1 - o0) * (uint32_t)A.gs;
     const int xr = lane >> 4, xc = lane & 15;    // request u of a group of activations: row 4 u + xr, chunk xc
     const unsigned char* xbase = reinterpret_cast<const unsigned char*>(A.X + (size_t)m0 * A.ldx);
@@ -101,10 +151,23 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     const int mlast = A.M - 1 - m0;
     const uint32_t xoff0 = (uint32_t)xr * xpitch, xlast = (uint32_t)min(mlast, 16 * MT) * xpitch;
 
-    constexpr int D = MT == 2 && NT <= 2 ? 2 : 1;   // groups of codes on the way
+    constexpr int D = (MT == 2 && NT <= 2) || MT == 1 ? 2 : 1;   // groups of codes on the way
     u4 wq[D][NT], raw[H];
     uint32_t ps, pz;
-    auto load_w = [&](int set, int t, int g) { wq[set][t] = *reinterpret_cast<const u4*>(wbase + (size_t)(64 * min(g, last_g)) + woff[t]); };
+    // ten codes per word: the lane's first word of a group and its shift (four words are there: 32 c / 10 + 4 is at most the row's
+    // padded length for every c with a column before Kq; the min is for lanes past it)
+    const uint32_t last_w = 4u * (uint32_t)(A.stride - 4);
+    auto first_word = [&](int g) { return min(4u * ((uint32_t)(128 * g + 32 * kb) / 10u), last_w); };
+    auto shift_of = [&](int g) { return 3u * ((uint32_t)(128 * g + 32 * kb) % 10u); };
+    auto load_w = [&](int set, int t, int g) {
+        const int gc = min(g, last_g);
+        if constexpr (F == W4) wq[set][t] = *reinterpret_cast<const u4*>(wbase + (size_t)(64 * gc) + woff[t]);
+        else if constexpr (F == W3_DENSE) {
+            const u3w v = *reinterpret_cast<const u3w*>(wbase + (size_t)(48 * gc) + woff[t]);
+            wq[set][t] = u4{v.x, v.y, v.z, 0u};
+        } else
+            wq[set][t] = *reinterpret_cast<const u4w*>(wbase + first_word(gc) + woff[t]);
+    };
     auto load_x = [&](u4& r, int u, int g) {
         const uint32_t off = min(xoff0 + (uint32_t)(4 * u) * xpitch, xlast) + (uint32_t)(2 * min(128 * g + 8 * xc, A.kq - 8));
         r = *reinterpret_cast<const u4*>(xbase + off);
@@ -123,13 +186,13 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
             for (int u = 0; u < cnt; ++u) {
                 const u4 z = u4{0u, 0u, 0u, 0u};
                 const int row = 4 * (u0 + u) + xr;
-                *reinterpret_cast<u4*>(mine + row * 256 + ((xc ^ (row & 15)) << 4)) = live ? permute_x(r[u]) : z;
+                *reinterpret_cast<u4*>(mine + row * 256 + ((xc ^ (row & 15)) << 4)) = live ? (F == W4 ? permute_x(r[u]) : r[u]) : z;
             }
         } else {
 #pragma unroll
             for (int u = 0; u < cnt; ++u) {
                 const int row = 4 * (u0 + u) + xr;
-                *reinterpret_cast<u4*>(mine + row * 256 + ((xc ^ (row & 15)) << 4)) = permute_x(r[u]);
+                *reinterpret_cast<u4*>(mine + row * 256 + ((xc ^ (row & 15)) << 4)) = F == W4 ? permute_x(r[u]) : r[u];
             }
         }
     };
@@ -140,7 +203,7 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[a][t] = f4{0.f, 0.f, 0.f, 0.f};
 
-    uint32_t mask = 0x000f000fu, magic = 0x64006400u;
+    uint32_t mask = F == W4 ? 0x000f000fu : 0x00070007u, magic = 0x64006400u;
     u4 ones = u4{0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};
     asm volatile("" : "+v"(mask), "+v"(magic), "+v"(ones.x), "+v"(ones.y), "+v"(ones.z), "+v"(ones.w));
 
@@ -172,10 +235,10 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
         auto group = [&](int i) { return i * KS + wave; };   // the wave's i-th group
         const int ngw = (A.ng - wave + KS - 1) / KS;
         {
-            u4 r0[4 * MT];
+            u4 r0[XR];
             load_par(group(0));
 #pragma unroll
-            for (int u = 0; u < 4 * MT; ++u) load_x(r0[u], u, group(0));
+            for (int u = 0; u < XR; ++u) load_x(r0[u], u, group(0));
 #pragma unroll
             for (int t = 0; t < NT; ++t) load_w(0, t, group(0));
             if constexpr (D == 2) {
@@ -185,7 +248,7 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
             __builtin_amdgcn_sched_barrier(0);
             mul_weak(wave);
             put_par();
-            put_x(r0, 0, 4 * MT, group(0));
+            put_x(r0, 0, XR, group(0));
         }
         // group i: its activations are in LDS, its codes in set i % 2; the next group's activations and the codes of
         // the one after are on the way
@@ -197,8 +260,10 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
 #pragma unroll
             for (int a = 0; a < MT; ++a)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    xa[a][q] = *reinterpret_cast<const u4*>(mine + (16 * a + n) * 256 + (((4 * kb + q) ^ n) << 4));
+                for (int q = 0; q < 4; ++q) {
+                    const int xn = min(n, 4 * XR - 1);   // (rows that were not fetched stand for rows past M)
+                    xa[a][q] = *reinterpret_cast<const u4*>(mine + (16 * a + xn) * 256 + (((4 * kb + q) ^ xn) << 4));
+                }
             uint32_t zs[NT];
 #pragma unroll
             for (int t = 0; t < NT; ++t) zs[t] = *reinterpret_cast<const uint32_t*>(par + 4 * (16 * t + n));
@@ -206,6 +271,11 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
             load_par(gn);
 #pragma unroll
             for (int u = 0; u < H; ++u) load_x(raw[u], u, gn);
+            const uint32_t wshift = F == W3_TEN ? shift_of(group(i)) : 0u;
+            if constexpr (F != W4) {
+#pragma unroll
+                for (int a = 0; a < MT; ++a) pair_x3(xa[a]);
+            }
             f4 sx[MT];
 #pragma unroll
             for (int a = 0; a < MT; ++a) sx[a] = f4{0.f, 0.f, 0.f, 0.f};
@@ -219,10 +289,14 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
                 f4 tmp[MT];
 #pragma unroll
                 for (int a = 0; a < MT; ++a) tmp[a] = f4{0.f, 0.f, 0.f, 0.f};
+                Codes3 c3;
+                if constexpr (F != W4) c3.take<F>(w, wshift);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const uint32_t wi = w[q];
-                    const u4 c = u4{(wi & mask) | magic, ((wi >> 4) & mask) | magic, ((wi >> 8) & mask) | magic, ((wi >> 12) & mask) | magic};
+                    u4 c;
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) c[p] = ((F == W4 ? wi >> (4 * p) : c3.bits(4 * q + p)) & mask) | magic;
 #pragma unroll
                     for (int a = 0; a < MT; ++a) tmp[a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa[a][q]), as_h8(c), tmp[a], 0, 0, 0);
                 }
@@ -285,6 +359,12 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) add((float)xv[e] * (float)wv[e]);
         }
+        auto code3 = [](const unsigned char* row, int j) -> uint32_t {   // the code of column j, one at a time
+            const uint32_t* p = reinterpret_cast<const uint32_t*>(row);
+            if (F == W3_TEN) return (p[j / 10] >> (3 * (j % 10))) & 7u;
+            const int w0 = (3 * j) >> 5, sh = (3 * j) & 31;
+            return ((sh > 29 ? (p[w0] >> sh) | (p[w0 + 1] << (32 - sh)) : p[w0] >> sh)) & 7u;
+        };
         auto not_finite = [](u4 v) {
             bool f = false;
 #pragma unroll
@@ -304,14 +384,15 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
                     const int g = (c0 >> 7) + 4 * t + s;
                     if (g >= A.ng || ((found >> (16 * s)) & 0xffffu) == 0) continue;
                     const float a = __half2float(sc[g]), b = __half2float(zp[g]);
-                    const u4 w = *reinterpret_cast<const u4*>(words + 64 * (size_t)g + 16 * kb);
+                    u4 w = u4{0u, 0u, 0u, 0u};
+                    if constexpr (F == W4) w = *reinterpret_cast<const u4*>(words + 64 * (size_t)g + 16 * kb);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int c = 128 * g + 32 * kb + 8 * q;
                         const h8 xv = as_h8(*reinterpret_cast<const u4*>(x + 2 * (size_t)min(c, A.kq - 8)));
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
-                            if (c < A.kq) add((float)xv[e] * (a * ((float)((w[q] >> (4 * e)) & 15u) - b)));
+                            if (c < A.kq) add((float)xv[e] * (a * ((float)(F == W4 ? (w[q] >> (4 * e)) & 15u : code3(words, c + e)) - b)));
                     }
                 }
             }
@@ -367,20 +448,25 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
         const uint32_t q0 = __builtin_amdgcn_perm(lo1, lo2, sel), q1 = __builtin_amdgcn_perm(hi1, hi2, sel);
         const int a = q / NT, t = q % NT;
         const int m = 16 * a + 4 * kb + (n & 3), o = 16 * t + 4 * (n >> 2);
-        if (m <= mlast && o0 + o < oc) *reinterpret_cast<u2*>(Y + (size_t)m * ldy + o) = u2{q0, q1};
+        if (m <= mlast && o0 + o + 4 <= oc) *reinterpret_cast<u2*>(Y + (size_t)m * ldy + o) = u2{q0, q1};
+        else if (F != W4 && m <= mlast) {   // (4-bit layers come with whole eights of channels)
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (o0 + o + e < oc) reinterpret_cast<uint16_t*>(Y + (size_t)m * ldy + o)[e] = (uint16_t)((e < 2 ? q0 : q1) >> (16 * (e & 1)));
+        }
     }
 }
 
-template <int MT, int NT>
+template <int MT, int NT, Fmt F, int XR>
 hipError_t launch_mid(const MidArgs& A, int KS, hipStream_t s) {
     static bool attr = false;
     const size_t lds_bytes = (size_t)KS * (MT * 4096 + 256);
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void*)fwd_mid_kernel<MT, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (MT * 4096 + 256));
+        hipError_t e = hipFuncSetAttribute((const void*)fwd_mid_kernel<MT, NT, F, XR>, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (MT * 4096 + 256));
         if (e != hipSuccess) return e;
         attr = true;
     }
-    fwd_mid_kernel<MT, NT><<<8 * ceil_div((int64_t)A.n_tiles * A.tiles_m, 8), 64 * KS, lds_bytes, s>>>(A);
+    fwd_mid_kernel<MT, NT, F, XR><<<8 * ceil_div((int64_t)A.n_tiles * A.tiles_m, 8), 64 * KS, lds_bytes, s>>>(A);
     return hipGetLastError();
 }
 
@@ -388,7 +474,9 @@ hipError_t launch_mid(const MidArgs& A, int KS, hipStream_t s) {
 
 // (Rows are addressed with 32-bit offsets from the panel's first: 48 rows of up to 2^24 elements.)
 bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx) {
-    return M > 16 && L.bits == 4 && L.g == 128 && (L.kq % 8) == 0 && (L.k % 8) == 0 && (L.oc % 8) == 0 && ldx <= QEFT_MAX_DIM;
+    if (L.g != 128 || (L.kq % 8) != 0 || (L.k % 8) != 0 || ldx > QEFT_MAX_DIM) return false;
+    if (L.bits == 3) return M > 0 && L.kq >= 8 && (!L.dense || 12 * L.ng <= L.stride);   // (dense: a lane reads 12 bytes of a group, so whole groups fit the padded row)
+    return M > 16 && (L.oc % 8) == 0;
 }
 
 // Up to 96 rows (two panels) always; up to 192 (four) where the alternative leaves most of the GPU idle: without a workspace
@@ -404,13 +492,27 @@ bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws) {
     return L.oc <= 5120 && (int64_t)ceil_div(M, 48) * L.oc * L.ic <= (int64_t)3 * 5120 * 5120;
 }
 
+// 3-bit layers with room for a copy: up to 96 rows, and while the codes over all panels are few - the copy's pass alone is 4 to 10 us
+// and the kernels behind it take as long as for a 4-bit layer.  us, through a copy against here (ten codes a word): 14848 x 4456 at
+// M = 48 / 96: 42 / 52 against 25 / 37; 5120 x 5120 at M = 40 / 96 / 192 / 240 / 333: 24 / 27 / 34 / 37 / 45 against 14 / 17 / 28 /
+// 34 / 53; 4096 x 4096 at 333 / 500: 32 / 39 against 30 / 44; 2048 x 2048 at 500 / 700 / 1000: 21 / 22 / 22 against 16 / 19 / 29; wide layers
+// sooner: 11008 x 4096 at 97: 40 against 43, 12288 x 640 at 240 / 500: 23 / 29 against 18 / 36.  Layers under 2^20 weights have the fp16
+// copy alone: 512 x 512 at 48 / 1000: 17 / 21 against 5 / 7, 1000 x 1000: 49 / 53 against 6 / 12.
+bool fwd_mid3_preferred(const Layer& L, int64_t M, int64_t ldx) {
+    if (!fwd_mid_supported(L, M, ldx)) return false;
+    if (M <= 96) return true;
+    const int64_t panels = ceil_div(M, 48), weights = (int64_t)L.oc * L.ic;
+    if (weights < ((int64_t)1 << 20)) return panels <= 30;
+    return panels <= 15 && panels * weights <= (L.oc <= 5120 ? 5 : 1) * (int64_t)(5120 * 5120);
+}
+
 // Tiles of 16 NT channels and KS waves.  A CU holds one workgroup of eight waves or two of four (registers), and a workgroup
 // reads its whole panel of X whatever its width, so: the narrowest tile whose workgroups are all resident at eight waves,
 // else at four, else the widest.  (us, 48 rows: 4096 x 4096 NT = 1 / 2 / 3 / 4 at KS = 8: 10.6 / 12.0 / 13.3 / 15.4;
 // 12288 x 4096: 32 / 27 / 17.8 / 20.3, KS = 4 and NT = 3: 19.2; 22016 x 4096 KS = 4: 43 / 30 / 34, KS = 8: 33 at best.)
 hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t ldx, __half* const* Y, const int64_t* ldy, hipStream_t s) {
     const Layer& L = Ls[0];
-    const int panels = ceil_div(M, 48), MT = ceil_div(M, (int64_t)panels * 16) < 3 ? 2 : 3;
+    const int panels = ceil_div(M, 48), mt = ceil_div(M, (int64_t)panels * 16), MT = L.bits == 4 && mt < 2 ? 2 : mt;
     const int tiles_m = ceil_div(M, 16 * MT);
     auto tiles_at = [&](int nt) {
         int64_t t = 0;
@@ -423,6 +525,9 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
         KS = 4;
         NT = tiles_at(3) * tiles_m <= 512 ? 3 : 4;
     }
+    // (up to 4 rows, 3-bit codes, many tiles: the panel is little and narrow tiles start sooner; 12288 x 4096 at M = 2: 9.8 us against 11.4,
+    // 15360 x 5120: 14.1 against 15.0, 27648 x 5120: 24.6 against 26.8)
+    if (M <= 4 && NT >= 3) NT = 1, KS = 4;
     KS = L.ng > 0 && KS > L.ng ? L.ng : KS;
     MidArgs A = {};
     int tiles = 0;
@@ -449,10 +554,14 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
     A.stride = L.stride;
     A.gs = L.gs;
     using Launch = hipError_t (*)(const MidArgs&, int, hipStream_t);
-#define QEFT_MID(MT) {launch_mid<MT, 1>, launch_mid<MT, 2>, launch_mid<MT, 3>, launch_mid<MT, 4>}
-    static const Launch table[2][4] = {QEFT_MID(2), QEFT_MID(3)};
+#define QEFT_MID(MT, F, XR) {launch_mid<MT, 1, F, XR>, launch_mid<MT, 2, F, XR>, launch_mid<MT, 3, F, XR>, launch_mid<MT, 4, F, XR>}
+#define QEFT_MID3(F) {QEFT_MID(1, F, 1), QEFT_MID(1, F, 2), QEFT_MID(1, F, 4), QEFT_MID(2, F, 8), QEFT_MID(3, F, 12)}
+    static const Launch w4[2][4] = {QEFT_MID(2, W4, 8), QEFT_MID(3, W4, 12)};
+    static const Launch w3[2][5][4] = {QEFT_MID3(W3_TEN), QEFT_MID3(W3_DENSE)};
+#undef QEFT_MID3
 #undef QEFT_MID
-    return table[MT - 2][NT - 1](A, KS, s);
+    if (L.bits == 4) return w4[MT - 2][NT - 1](A, KS, s);
+    return w3[L.dense ? 1 : 0][MT > 1 ? MT + 1 : (M <= 4 ? 0 : (M <= 8 ? 1 : 2))][NT - 1](A, KS, s);
 }
 
 }  // namespace qeft

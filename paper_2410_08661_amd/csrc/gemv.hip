@@ -34,7 +34,7 @@
 //     products, activations in registers;
 //   * row-batch kernel (any M <= 16): nothing staged, A fragments straight from X, Sx from the
 //     matrix core (fallback for shapes the register kernel does not take);
-//   * 3-bit kernel (any M <= 16): weight-side dequantization, ten codes per word;
+//   * 3-bit layers at 2 <= M <= 16: the kernel of gemm_mid.hip, except dense ones of many tiles at M <= 4 (small-M kernel);
 //   * chunked kernel: each wave stages its own slice, CH steps at a time (fallback only).
 //
 // Every branch around an MFMA is wave-uniform by construction (the wave index goes through
@@ -704,255 +704,6 @@ hipError_t launch_rows(const Layer& L, const __half* X, int M, int64_t ldx, __ha
 }
 
 // =============================================================================================
-// 3-bit kernel: any M <= 16.  Ten codes fill a 32-bit word, so a lane's 128-bit load holds 40
-// consecutive codes of its row and a step of the four k-slot lanes covers 160 columns - groups
-// of 128 columns do not line up with anything the matrix core sums over.  Dequantization is
-// therefore done on the weight side: the 40 codes become five B fragments of 8 fp16 weights
-// (q - z) s each, and five 16x16x32 MFMAs per step accumulate straight into the result.
-//   * a word holds exactly five pairs of codes, so a pair never straddles words: its two codes are
-//     spread to bits 0..2 and 16..18 by one 6-bit field extract and one multiplication by
-//     2^13 + 1, then masked and or-ed with the exponent bits (3 instructions per 2 codes);
-//   * fragment s of lane (n, kb) covers columns 160 j + 40 kb + 8 s .. + 7: one group, since
-//     every such octet starts on a multiple of 8; its (zero-point, scale) pair comes from a table
-//     of the tile's rows in LDS, filled once per workgroup with the same 16-byte-per-lane loads
-//     of 8 groups as in the 4-bit kernel;
-//   * activations are read from X as they are (natural column order), D steps ahead like the
-//     weights, and shared by the R tiles of a wave; octets past Kq are zeroed.
-// LDS: (z, s) fp16 pairs [groups][16 R rows] | reduction slots
-// =============================================================================================
-// DENSE: the dense 3-bit layout (a row is one bit string, 32 codes in 3 words).  A lane then takes
-// 12 bytes = 32 codes = four fragments per step, a step of the four k-slot lanes covers exactly one group
-// of 128 columns, and pair P of a lane sits at bits 6 P of its 96: two of the sixteen pairs straddle words
-// and take one funnel shift more.  Group = step is what lets the dequantization move to the accumulator
-// side (see step_dense): about half the vector instructions of the whole-codes-per-word layout.
-template <int R, int D, int NSZ, bool DENSE>
-__global__ __launch_bounds__(512) void gemv_w3_kernel(Layer L, const __half* __restrict__ X, int M, int64_t ldx,
-                                                      __half* __restrict__ Y, int64_t ldy, int ks_magic, int nsteps) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    const int lane = threadIdx.x & 63;
-    const int KS = blockDim.x >> 6;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 15, kb = lane >> 4;
-    const int row0 = blockIdx.x * (16 * R);
-    const int q_beg = (nsteps * wave * ks_magic) >> 16;                 // a / KS = a * ceil(65536 / KS) >> 16
-    const int q_end = (nsteps * (wave + 1) * ks_magic) >> 16;
-    const int nj = max(q_end - q_beg, 0);
-    const int j_last = max(nj - 1, 0);
-    const int nq = L.ng;
-
-    // ---- requests: group parameters of the workgroup's rows first, then D steps of X and weights ----
-    // chunk c = (tile c / (2 nch), array c % 2, groups 32 (c / 2 % nch) ..): 8 groups per lane
-    const int nch = (nq + 31) >> 5, nchunks = 2 * nch * R;
-    u4 pv[NSZ];
-#pragma unroll
-    for (int i = 0; i < NSZ; ++i) {
-        const int c = min(wave + i * KS, nchunks - 1);
-        const int r = c / (2 * nch), cc = c - r * 2 * nch;
-        const int o = min(row0 + 16 * r + n, L.oc - 1);
-        const int g0 = min(32 * (cc >> 1) + 8 * kb, (int)L.gs - 8);
-        pv[i] = load16(((cc & 1) ? L.zeros : L.scales) + (size_t)o * L.gs + g0);
-    }
-    constexpr int NF = DENSE ? 4 : 5;                 // fragments (octets of columns) per lane and step
-    constexpr int STEP_COLS = 32 * NF, LANE_COLS = 8 * NF;
-    constexpr int STEP_BYTES = DENSE ? 48 : 64, LANE_BYTES = DENSE ? 12 : 16;
-    const unsigned char* wrow[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int o = min(row0 + 16 * r + n, L.oc - 1);
-        wrow[r] = reinterpret_cast<const unsigned char*>(L.qweight + (size_t)o * L.stride);
-    }
-    const int woff0 = STEP_BYTES * q_beg + LANE_BYTES * kb;
-    const int woff_max = 4 * L.stride - LANE_BYTES;   // never reached: the host admits only rows that hold whole steps
-    const __half* xrow = X + (size_t)min(n, M - 1) * ldx;
-    const int col0 = STEP_COLS * q_beg + LANE_COLS * kb;
-    u4 xq[D][NF], wq[D][R];
-    auto load_step = [&](int d, int j) {   // straight-line: the step index is clamped, never tested
-        const int jc = min(j, j_last);
-#pragma unroll
-        for (int s = 0; s < NF; ++s) xq[d][s] = load16(xrow + min(col0 + STEP_COLS * jc + 8 * s, L.kq - 8));
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (DENSE) {
-                const uint32_t* p = reinterpret_cast<const uint32_t*>(wrow[r] + min(woff0 + STEP_BYTES * jc, woff_max));
-                wq[d][r] = u4{p[0], p[1], p[2], 0u};
-            } else {
-                wq[d][r] = load16(wrow[r] + woff0 + STEP_BYTES * (size_t)jc);
-            }
-        }
-    };
-#pragma unroll
-    for (int d = 0; d < D; ++d) load_step(d, d);
-    __builtin_amdgcn_sched_barrier(0);   // nothing below may move above the requests
-
-    // ---- the (zero-point, scale) table ---------------------------------------------------------------
-    unsigned short* szt = reinterpret_cast<unsigned short*>(lds);   // [group][16 R rows][z, s]
-#pragma unroll
-    for (int i = 0; i < NSZ; ++i) {
-        const int c = wave + i * KS;
-        const int r = c / (2 * nch), cc = c - r * 2 * nch;
-        const int g0 = 32 * (cc >> 1) + 8 * kb;
-        if (c < nchunks) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (g0 + e < nq) szt[((g0 + e) * (16 * R) + 16 * r + n) * 2 + ((cc & 1) ? 0 : 1)] = (unsigned short)(pv[i][e >> 1] >> (16 * (e & 1)));
-        }
-    }
-    __syncthreads();
-
-    f4 y[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) y[r] = f4{0.f, 0.f, 0.f, 0.f};
-    const u4 zero4 = u4{0u, 0u, 0u, 0u};
-    uint32_t cmask = 0x00070007u, cmagic = 0x64006400u;
-    asm volatile("" : "+v"(cmask), "+v"(cmagic));
-    const h2 k1024 = h2{(_Float16)1024.f, (_Float16)1024.f};
-    const uint32_t* sz32 = reinterpret_cast<const uint32_t*>(lds);
-
-    // a lane's 40 columns of a step touch at most two groups: both (zero-point, scale) pairs are read
-    // one step ahead, and each fragment picks its own by comparing its first column with the boundary
-    uint32_t zs_lo[R], zs_hi[R];
-    const uint32_t* szl = sz32 + n;
-    auto read_zs = [&](int j) {
-        const int g = min((col0 + STEP_COLS * j) >> 7, nq - 1), gh = min(g + 1, nq - 1);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            zs_lo[r] = szl[g * (16 * R) + 16 * r];
-            zs_hi[r] = szl[gh * (16 * R) + 16 * r];
-        }
-    };
-    read_zs(0);
-    u4 ones = u4{0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};
-    asm volatile("" : "+v"(ones.x), "+v"(ones.y), "+v"(ones.z), "+v"(ones.w));
-    // Dense layout: a step is one group, so the dequantization moves behind the matrix cores as in the
-    // 4-bit kernels: the codes enter as the exact fp16 numbers 1024 + q (three instructions per pair), the
-    // step's sum over its 128 columns is taken in a fresh accumulator, and the group contributes
-    // s (sum x (1024 + q) - (1024 + z) sum x); sum x comes from four more MFMAs against an all-ones
-    // operand, shared by the R tiles, and lands in the accumulator's own layout.
-    auto step_dense = [&](int d, int j) {
-        const int col = col0 + STEP_COLS * j;
-        float sc[R], tc[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const h2 zs = __builtin_bit_cast(h2, zs_lo[r]);
-            sc[r] = (float)zs.y;
-            tc[r] = sc[r] * (1024.f + (float)zs.x);
-        }
-        read_zs(j + 1);
-        f4 sx = f4{0.f, 0.f, 0.f, 0.f}, ya[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) ya[r] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < NF; ++s) {
-            const u4 xa = (col + 8 * s < L.kq && j < nj) ? xq[d][s] : zero4;
-            sx = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa), as_h8(ones), sx, 0, 0, 0);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                u4 b;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    const int P = 4 * s + p;   // pair P of the lane's 16 at bits 6 P .. 6 P + 5 of its three words
-                    const int wi = (6 * P) >> 5, sh = (6 * P) & 31;
-                    const uint32_t six = sh <= 26 ? __builtin_amdgcn_ubfe(wq[d][r][wi], sh, 6)
-                                                  : __builtin_amdgcn_ubfe(__builtin_amdgcn_alignbit(wq[d][r][(wi + 1) & 3], wq[d][r][wi], sh), 0, 6);
-                    b[p] = ((six * 0x2001u) & cmask) | cmagic;   // fp16 pair (1024 + q0, 1024 + q1)
-                }
-                ya[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa), as_h8(b), ya[r], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y[r][e] += sc[r] * ya[r][e] - tc[r] * sx[e];
-    };
-    auto step = [&](int d, int j) {
-        if (DENSE) {
-            step_dense(d, j);
-            return;
-        }
-        const int col = col0 + STEP_COLS * j;
-        const int split = ((col >> 7) + 1) << 7;   // first column of the next group
-        h2 zsl[R], zsh[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            zsl[r] = __builtin_bit_cast(h2, zs_lo[r]);
-            zsh[r] = __builtin_bit_cast(h2, zs_hi[r]);
-        }
-        read_zs(j + 1);
-        f4 ya[R], yb[R];   // two accumulation chains per tile: consecutive MFMAs do not wait for each other
-#pragma unroll
-        for (int r = 0; r < R; ++r) ya[r] = yb[r] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < NF; ++s) {
-            const u4 xa = (col + 8 * s < L.kq && j < nj) ? xq[d][s] : zero4;
-            const bool hi = col + 8 * s >= split;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const h2 zs = hi ? zsh[r] : zsl[r];
-                const h2 z2 = h2{zs.x, zs.x}, s2 = h2{zs.y, zs.y};
-                u4 b;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    const int P = 4 * s + p;   // pair P of the lane's 20: word P / 5, codes 2 (P % 5) and the next
-                    const uint32_t six = __builtin_amdgcn_ubfe(wq[d][r][P / 5], 6 * (P % 5), 6);
-                    const uint32_t codes = ((six * 0x2001u) & cmask) | cmagic;   // fp16 pair (1024 + q0, 1024 + q1)
-                    b[p] = __builtin_bit_cast(uint32_t, ((__builtin_bit_cast(h2, codes) - k1024) - z2) * s2);
-                }
-                if (s & 1) yb[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa), as_h8(b), yb[r], 0, 0, 0);
-                else ya[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa), as_h8(b), ya[r], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y[r][e] += ya[r][e] + yb[r][e];
-    };
-
-    // no branches inside: steps past the wave's range run on clamped loads and zeroed activations
-    for (int j0 = 0; j0 < nj; j0 += D) {
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            step(d, j0 + d);
-            load_step(d, j0 + d + D);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-
-    weak_steps<R>(L, X, M, ldx, row0, wave, KS, n, kb, y);
-    __syncthreads();   // the table is dead: its memory becomes the reduction slots
-    reduce_store<R>(L, y, wave, KS, lane, row0, M, Y, ldy,
-                    [&](int w) { return reinterpret_cast<float*>(lds) + (size_t)(w - 1) * R * 4 * 64; });
-}
-
-// K-split waves of the 3-bit kernel: four (one per SIMD; measured best for 4096 ... 11008 rows), more only
-// when the (zero-point, scale) table would otherwise take more than 4 requests per wave
-int w3_steps(const Layer& L) { return L.dense ? L.ng : ceil_div(L.words, 16); }   // dense: one step per group
-
-int w3_split(const Layer& L, int R) {
-    const int nsteps = w3_steps(L), nchunks = 2 * ceil_div(L.ng, 32) * R;
-    int ks = nsteps < 4 ? (nsteps < 1 ? 1 : nsteps) : 4;
-    while (ks < 8 && ks < nsteps && ceil_div(nchunks, ks) > 4) ++ks;
-    return ks;
-}
-
-template <int R>
-hipError_t launch_w3(const Layer& L, const __half* X, int M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s) {
-    const int tiles = ceil_div(L.oc, 16 * R);
-    const int nsteps = w3_steps(L);
-    const int ks = w3_split(L, R);
-    const int nchunks = 2 * ceil_div(L.ng, 32) * R;
-    const int nsz = ceil_div(nchunks, ks);
-    const size_t table = (size_t)L.ng * 16 * R * 4, red = (size_t)(ks > 1 ? ks - 1 : 1) * R * 4 * 64 * sizeof(float);
-    const size_t lds_bytes = table > red ? table : red;
-    using Kern = void (*)(Layer, const __half*, int, int64_t, __half*, int64_t, int, int);
-    static const Kern table_k[2][4] = {
-        {gemv_w3_kernel<R, 4, 1, false>, gemv_w3_kernel<R, 4, 2, false>, gemv_w3_kernel<R, 4, 3, false>, gemv_w3_kernel<R, 4, 4, false>},
-        {gemv_w3_kernel<R, 4, 1, true>, gemv_w3_kernel<R, 4, 2, true>, gemv_w3_kernel<R, 4, 3, true>, gemv_w3_kernel<R, 4, 4, true>}};
-    if (nsz > 4 || lds_bytes > 64 * 1024) return hipErrorInvalidValue;   // not reached for the shapes gemv_supported admits
-    table_k[L.dense ? 1 : 0][nsz - 1]<<<tiles, 64 * ks, lds_bytes, s>>>(L, X, M, ldx, Y, ldy, ceil_div(65536, ks), nsteps);
-    return hipGetLastError();
-}
-
-// =============================================================================================
 // Register kernel: 3 <= M <= 16, rows of any length in passes of (waves x S) steps.  A workgroup has one wave per K
 // range of S steps, and lane (n, kb) of a wave keeps, for a whole pass, the A fragments of activation row n for its
 // range (4 S registers of 8 halfs: the wave fetches its rows' 512 columns as whole kilobytes, deals them out through
@@ -1132,22 +883,10 @@ constexpr int SMALL_LDS_LIMIT = 144 * 1024;   // of the 160 KB a CU has
 
 }  // namespace
 
-// the 3-bit kernel: its (zero-point, scale) table must fit in LDS and be loadable in 4 requests per wave
-static bool w3_fits(const Layer& L) {
-    // dense layout: a lane reads 12 bytes per group of its row, so whole groups must fit the padded row
-    // (always true when Kq is a multiple of 128: 12 words per group)
-    if (L.dense && 12 * L.ng > L.stride) return false;
-    for (int R = 1; R <= 2; ++R) {
-        const int ks = w3_split(L, R);
-        if (ceil_div(2 * ceil_div(L.ng, 32) * R, ks) > 4 || (size_t)L.ng * 16 * R * 4 > 64 * 1024) return false;
-    }
-    return true;
-}
-
 bool gemv_supported(const Layer& L, int64_t M, int64_t ldx) {
     (void)ldx;
     if (M < 1 || L.g != 128 || (L.kq % 8) != 0 || (L.k % 8) != 0) return false;
-    if (L.bits == 3) return L.kq >= 8 && w3_fits(L);
+    if (L.bits == 3) return fwd_mid_supported(L, 1, 8);   // (any pitch: see gemv_fwd)
     return L.bits == 4;
 }
 
@@ -1281,6 +1020,16 @@ bool launch_regs(const Layer* Ls, int n, const __half* X, int M, int64_t ldx, __
     return true;
 }
 
+// Dense 3-bit layers at 2 to 4 rows: this kernel stages X once per workgroup and wins where a launch has many tiles, the one of
+// gemm_mid.hip elsewhere (us, this against that: 22016 x 4096 at M = 2 / 4: 14.5 / 15.2 against 17.6 / 17.5, 57344 x 8192: 57 / 69
+// against 87 / 92, 8192 x 8192 at M = 2: 10.9 against 12.8; 5120 x 13824 at M = 2 / 4: 16.3 / 23.6 against 15.7 / 17.0, 10240 x 8192 at M = 4:
+// 24.6 against 17.5).
+bool small_w3_preferred(const Layer* Ls, int n, int M) {
+    int tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += ceil_div(Ls[i].oc, 16);
+    return Ls[0].dense && M >= 2 && M <= 4 && tiles >= (M == 2 ? 512 : 1024);
+}
+
 GroupTail no_tail() {
     GroupTail t = {};
     for (int i = 0; i < MAX_GROUP - 1; ++i) t.tile_begin[i] = INT_MAX;
@@ -1297,12 +1046,17 @@ hipError_t gemv_fwd_group(const Layer* Ls, int n, const __half* X, int64_t M64, 
         hipError_t e = gemv_dot_fwd(Ls, n, nullptr, X, Y, s, handled);
         if (e != hipSuccess || *handled) return e;
     }
+    if (L.bits == 3 && !(L.dense && small_w3_preferred(Ls, n, (int)M64))) {
+        bool all = true;
+        for (int i = 0; i < n; ++i) all = all && fwd_mid_supported(Ls[i], M64, ldx);
+        *handled = all;
+        return all ? fwd_mid(Ls, n, X, M64, ldx, Y, ldy, s) : hipSuccess;
+    }
     if (M64 > 2) {    // 5 .. 16 rows: the register kernel (the small-M kernel below stages at most 4 rows); 3 and 4: where it is faster
         hipError_t e = hipSuccess;
         *handled = launch_regs(Ls, n, X, (int)M64, ldx, Y, ldy, s, &e);
         if (*handled || M64 > 4) return e;
     }
-    if (!(L.bits == 4 || L.dense)) return hipSuccess;   // ten 3-bit codes per word: per-layer calls
     GroupTail tail = no_tail();
     int tiles = ceil_div(L.oc, 16);
     for (int i = 1; i < n; ++i) {
@@ -1345,11 +1099,19 @@ hipError_t gemv_fwd(const Layer& L, const __half* X, int64_t M64, int64_t ldx, _
         hipError_t e = gemv_dot_fwd(&L, 1, nullptr, X, &Y, s, &handled);
         if (e != hipSuccess || handled) return e;
     }
-    if (M <= 4 && L.kq >= 8 && L.k >= 8 && (L.bits == 4 || L.dense)) {   // (dense 3-bit: gemv_supported has checked that rows hold whole steps)
+    if (M <= 4 && L.kq >= 8 && L.k >= 8 && (L.bits == 4 || small_w3_preferred(&L, 1, M))) {   // (dense 3-bit: gemv_supported has checked that rows hold whole steps)
         hipError_t err = hipSuccess;
         if (launch_small(L, ceil_div(L.oc, 16), no_tail(), nullptr, X, M, ldx, Y, ldy, s, &err)) return err;
     }
-    if (L.bits == 3) return M > 4 ? launch_w3<2>(L, X, M, ldx, Y, ldy, s) : launch_w3<1>(L, X, M, ldx, Y, ldy, s);
+    if (L.bits == 3) {
+        if (fwd_mid_supported(L, M, ldx)) return fwd_mid(&L, 1, X, M, ldx, &Y, &ldy, s);
+        for (int m = 0; m < M; ++m) {   // (rows too far apart for its 32-bit offsets: one at a time)
+            __half* y = Y + (size_t)m * ldy;
+            hipError_t e = fwd_mid(&L, 1, X + (size_t)m * ldx, 1, 8, &y, &ldy, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     const int steps = L.ng + (L.k + 31) / 32;
     if (L.kq >= 8) {
         // unstaged kernel: R tiles per wave share the activation fragments; four K-split waves per workgroup
