@@ -164,6 +164,12 @@ struct RowTile {
     __device__ __forceinline__ void load(int set, int u, int col, int ncols) {
         v[set][u] = *reinterpret_cast<g_u4*>(sbase(xb) + (xrow[u] + 2u * (uint32_t)min(col + 8 * xc, ncols - 8)));
     }
+    // 64 columns from col on, all of them within the row; after chunk_in_row()
+    __device__ __forceinline__ void load_whole(int set, int u, int col) { v[set][u] = *reinterpret_cast<g_u4*>(sbase(xb + 2 * col) + xrow[u]); }
+    __device__ __forceinline__ void chunk_in_row() {
+#pragma unroll
+        for (int u = 0; u < NX; ++u) xrow[u] += 16u * (uint32_t)xc;
+    }
     __device__ __forceinline__ void put(int u, int buf, u4 x) { *reinterpret_cast<lds_u4*>(xw[u & 3] + (uint32_t)((u >> 2) * 8192 + buf * XT)) = x; }
     __device__ __forceinline__ h8 frag(int j, int buf, int chunk) const {   // chunk: XOR part of the chunk index
         return *reinterpret_cast<const lds_h8*>(fb[chunk ^ (4 * (j & 1))] + (uint32_t)(j * 4096 + buf * XT));
@@ -390,7 +396,8 @@ __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const
 // lane gets is a packed word as in the forward, and the same conversion follows with the rows' zero-points and scales as
 // vectors.  A tile is either quantized or weak, whatever Kq (the GEMM of gemm.hip
 // puts a partial group and weak columns into one tile and then takes its LDS-staged form); weak ones read fp16 with the 16-bit form.
-template <int J, int KW, int MINW, bool ONCE>
+// RAGGED: OC is no multiple of 64.
+template <int J, int KW, int MINW, bool ONCE, bool RAGGED>
 __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const __half* __restrict__ dY, int M, int64_t lddy,
                                                                 __half* __restrict__ dX, int64_t lddx, int tiles_n, int tiles_m) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -418,6 +425,15 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
     Rows x(dY, lddy, m0, M, tk, lx, fr, 2 * fk);
     auto chunk_of = [](int ks) { return 4 * (ks >> 1) + (ks & 1); };
     auto stage_of = [&](int t, int e) { return 2 * ((t + (e >> 1)) * KW + kw) + (e & 1); };
+    // Rows of a stage: 64 from 64 st on; the last stage of an OC that is no multiple of 64 begins at OC - 64, and what it shares with
+    // the one before counts as zeros in dY, as do stages past the last.  (No clamp per row, and no read past the stored matrices.
+    // RAGGED has to be known here: with the selects below in every call, 4096 x 4096 at M = 777 took 52.8 us against 51.3.)
+    auto first_row = [&](int st) { return RAGGED ? min(64 * st, L.oc - 64) : 64 * st; };
+    auto stage_live = [&](int st) { return RAGGED ? st < nst && first_row(st) + 8 * x.xc >= 64 * st : st < nst; };
+    auto load_y = [&](int set, int u, int st) {
+        if constexpr (RAGGED) x.load_whole(set, u, first_row(st));
+        else x.load(set, u, 64 * st, L.oc);
+    };
 
     f16v acc[2][J];
 #pragma unroll
@@ -442,12 +458,13 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
         const unsigned char* pl = reinterpret_cast<const unsigned char*>((lane < 32 ? L.scales : L.zeros) + c0 / 128) + poff;   // (ONCE)
         u4 cw[DX][2];
         uint32_t pv[DX];
+        if constexpr (RAGGED) x.chunk_in_row();
         auto load_c = [&](int set, int st) {   // (stages past the last repeat it; their rows of dY are zeroed)
             const int sc = min(st, nst - 1);
-            gptr p = sbase(wt + (size_t)(64 * sc) * wpitch) + coff;
+            gptr p = sbase(wt + (size_t)first_row(sc) * wpitch) + coff;
             cw[set][0] = *reinterpret_cast<g_u4*>(p);
             cw[set][1] = *reinterpret_cast<g_u4*>(p + 16);
-            const size_t at = (size_t)(64 * sc) * (uint32_t)(L.gs * 2);
+            const size_t at = (size_t)first_row(sc) * (uint32_t)(L.gs * 2);
             if constexpr (ONCE) pv[set] = *(g_u16*)(pl + at);
             else pv[set] = *reinterpret_cast<g_u16*>(sbase(pt + at) + poff);
         };
@@ -502,17 +519,17 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
         for (int d = 0; d < DX; ++d) {
             load_c(d, stage_of(0, d));
 #pragma unroll
-            for (int u = 0; u < NX; ++u) x.load(d, u, 64 * stage_of(0, d), L.oc);
+            for (int u = 0; u < NX; ++u) load_y(d, u, stage_of(0, d));
         }
         __builtin_amdgcn_sched_barrier(0);
         {
-            const bool live = 64 * stage_of(0, 0) + 8 * x.xc < L.oc;
+            const bool live = stage_live(stage_of(0, 0));
             put_c(0, 0);
 #pragma unroll
             for (int u = 0; u < NX; ++u) x.put(u, 0, live ? permute_x(x.v[0][u]) : zero4);
             load_c(0, stage_of(0, DX));
 #pragma unroll
-            for (int u = 0; u < NX; ++u) x.load(0, u, 64 * stage_of(0, DX), L.oc);
+            for (int u = 0; u < NX; ++u) load_y(0, u, stage_of(0, DX));
         }
         __syncthreads();
         Conv cv;
@@ -536,8 +553,8 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
             auto stage = [&](auto e_c) {
                 constexpr int E = decltype(e_c)::value, CUR = E & 1, NXT = CUR ^ 1, SETX = (E + 1) % DX;
                 const int s_put = stage_of(t, E + 1), s_ld = stage_of(t, E + 1 + DX);
-                if (64 * s_put + 64 > L.oc) {   // rows past OC
-                    const bool live = 64 * s_put + 8 * x.xc < L.oc;
+                if (64 * s_put + 64 > L.oc) {   // rows past OC, or before the stage's own
+                    const bool live = stage_live(s_put);
 #pragma unroll
                     for (int u = 0; u < NX; ++u) x.v[SETX][u] = live ? x.v[SETX][u] : zero4;
                 }
@@ -564,7 +581,7 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
                         if (T % 2 == 0) px[u & 1] = permute_x(x.v[SETX][u]);
                         else {
                             x.put(u, NXT, px[u & 1]);
-                            x.load(SETX, u, 64 * s_ld, L.oc);
+                            load_y(SETX, u, s_ld);
                         }
                     }
                     if (T == 2) {
@@ -587,7 +604,7 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
         // weak tile of a panel would end 9 us after the quantized ones), four stages on the way.
         constexpr int WP = 272;                  // bytes per row of 128 weak columns (256 + 16: rows spread over the banks)
         constexpr int WT = 32 * WP, YT = 32 * J * 64, NY = J;
-        const int nst32 = L.oc >> 5, turns32 = (nst32 + KW - 1) / KW;
+        const int nst32 = (L.oc + 31) >> 5, turns32 = (nst32 + KW - 1) / KW;
         const uint32_t ly = lds_at(lds) + (uint32_t)(kw * 2 * YT), lw = lds_at(lds) + (uint32_t)(KW * 2 * YT + kw * 2 * WT);
         const int yr = tk >> 2, yc = tk & 3;     // dY: rows yr + 32 u, chunk yc of the stage's four
         const int wr = tk >> 4, wc = tk & 15;    // weak block: rows wr + 8 u, chunk wc
@@ -598,19 +615,21 @@ __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const 
         const uint32_t woff = (uint32_t)wr * (uint32_t)(L.k * 2) + 2u * (uint32_t)min(c0 - L.kq + 8 * wc, L.k - 8);
         const uint32_t yput = ly + (uint32_t)(yr * 64 + ((yc ^ ((yr >> 2) & 3)) << 4)), wput = lw + (uint32_t)(wr * WP + 16 * wc);
         u4 yv[4][NY], wv[4][4];
+        auto first32 = [&](int st) { return RAGGED ? min(32 * st, L.oc - 32) : 32 * st; };   // (as first_row)
         auto fetch = [&](int set, int e) {   // (stages past the last repeat it; both operands are zeroed)
-            const int st = min(e * KW + kw, nst32 - 1);
+            const int r0 = first32(min(e * KW + kw, nst32 - 1));
 #pragma unroll
-            for (int u = 0; u < NY; ++u) yv[set][u] = *reinterpret_cast<g_u4*>(sbase(x.xb + 64 * st) + yoff[u]);
+            for (int u = 0; u < NY; ++u) yv[set][u] = *reinterpret_cast<g_u4*>(sbase(x.xb + 2 * r0) + yoff[u]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) wv[set][u] = *reinterpret_cast<g_u4*>(sbase(L.weak + (size_t)(32 * st + 8 * u) * L.k) + woff);
+            for (int u = 0; u < 4; ++u) wv[set][u] = *reinterpret_cast<g_u4*>(sbase(L.weak + (size_t)(r0 + 8 * u) * L.k) + woff);
         };
         auto put = [&](int set, int e, int buf) {
-            const bool live = e * KW + kw < nst32;
+            const int st = e * KW + kw, skip = st < nst32 ? 32 * st - first32(st) : 32;   // rows of the stage before its own
+            const bool live = RAGGED ? 8 * yc >= skip : st < nst32;
 #pragma unroll
             for (int u = 0; u < NY; ++u) *reinterpret_cast<lds_u4*>(yput + (uint32_t)(u * 2048 + buf * YT)) = live ? yv[set][u] : zero4;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) *reinterpret_cast<lds_u4*>(wput + (uint32_t)(u * 8 * WP + buf * WT)) = live ? wv[set][u] : zero4;
+            for (int u = 0; u < 4; ++u) *reinterpret_cast<lds_u4*>(wput + (uint32_t)(u * 8 * WP + buf * WT)) = (RAGGED ? wr + 8 * u >= skip : live) ? wv[set][u] : zero4;
         };
 #pragma unroll
         for (int e = 0; e < 4; ++e) fetch(e, e);
@@ -676,19 +695,19 @@ hipError_t launch_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, _
     return hipGetLastError();
 }
 
-template <int J, int KW, int MINW, bool ONCE>
+template <int J, int KW, int MINW, bool ONCE, bool RAGGED>
 hipError_t launch_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s) {
     static bool attr = false;
     constexpr int XT = 32 * J * 128, QL = KW * (2 * XT + 2 * 4096 + 2 * (ONCE ? 384 : 256)), WL = KW * 2 * (XT / 2 + 32 * 272);
     constexpr int A = QL > WL ? QL : WL, LDS_BYTES = A > finish_lds<J, KW>() ? A : finish_lds<J, KW>();
     static_assert(LDS_BYTES <= 160 * 1024, "");
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void*)dx_tile_kernel<J, KW, MINW, ONCE>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute((const void*)dx_tile_kernel<J, KW, MINW, ONCE, RAGGED>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
         attr = true;
     }
     const int tn = dx_tiles(L), tm = ceil_div(M, 32 * J);
-    dx_tile_kernel<J, KW, MINW, ONCE><<<xcd_grid(tn * tm), 128 * KW, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, tn, tm);
+    dx_tile_kernel<J, KW, MINW, ONCE, RAGGED><<<xcd_grid(tn * tm), 128 * KW, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, tn, tm);
     return hipGetLastError();
 }
 
@@ -710,7 +729,7 @@ Est est_fwd(const Layer& L, int64_t M) {
     return best_of(n * 0.68 + 6, ceil_div(L.oc, 128), M, 1.5, n * 1.05 + 8);
 }
 Est est_dx(const Layer& L, int64_t M) {
-    const int nst = L.oc / 64;
+    const int nst = ceil_div(L.oc, 64);
     return best_of(2 * ceil_div(nst, 8) * 1.6 + 7, dx_tiles(L), M, 1.65, 2 * ceil_div(nst, 4) * 1.3 + 8);
 }
 // share of a 256-row tile's time that a GEMM panel of M rows takes (the forward's panels are cut to the rows)
@@ -740,22 +759,23 @@ bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws) {
     const double g = est_gemm(L.oc, M, ceil_div(L.kq, 64) + ceil_div(L.k, 64), 1.15 * (L.kq % 64 == 0 ? panel(M) : 1.0)) * (L.kq % 64 == 0 ? 1.0 : 2.4);
     return est_fwd(L, M).t < 0.95 * g;
 }
-// The input gradient: whole stages of rows.  Against the split the estimate has to be 15 % ahead (its weak tiles run longer than
+// The input gradient.  Against the split the estimate has to be 15 % ahead (its weak tiles run longer than
 // estimated), 25 % where the split takes less than 28 us.  Measured, split GEMM against this kernel: 2560 x 7168 at M = 256 / 320 /
 // 512 (estimates 0.80 apart) 28.6 / 36.7 / 38.9 us against 24.9 / 33.6 / 34.9, 6144 x 6144 at 320 (0.83) 49.0 against 48.4; the other way
 // 4096 x 11008 at 320 (0.88) 57.6 against 59.5, 5120 x 5120 at 333 (0.91) 40.0 against 42.2, 4096 x 4096 at 333 / 512 (0.99) 33.0 / 35.7
 // against 34.1 / 35.8.  The short launches would gain 1 to 2 us (2048 x 1152 at 333 / 512 rows, 0.78: 20.3 / 21.1 against 19.0 / 18.9) and
 // keep the split's arithmetic, which callers that give the room for it rely on (the one-call backward's test there).  A partial last
 // group leaves the GEMM its LDS-staged form, at 3.3 to 4.5 times the time (4096 x 4096 with 8 weak columns, M = 227: 310 us; 4096 x
-// 11008, M = 1938: 641 us).
+// 11008, M = 1938: 641 us), and so does an OC that is no multiple of 64 (us, that form against this kernel: 4104 x 4096 at M = 64 / 777 /
+// 2048: 292 / 292 / 292 against 35 / 60 / 111; 7184 x 5712 at 64 / 512 / 2048: 572 / 569 / 559 against 53 / 93 / 260).
 bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
-    if (L.ng <= 0 || M <= 16 || L.oc % 64 != 0 || lddy > (QEFT_MAX_DIM >> 1)) return false;
+    if (L.ng <= 0 || M <= 16 || lddy > (QEFT_MAX_DIM >> 1)) return false;
     const GemmSplit p = split_ws ? gemm_dx_split(L, M) : GemmSplit{1, 0, 0, false};
     if (p.splits > 1) {
         const double split = est_split(p, 12, 1.5);
         return !p.tail && est_dx(L, M).t < (split < 28 ? 0.75 : 0.85) * split;
     }
-    return est_dx(L, M).t < 0.95 * est_gemm(L.ic, M, L.oc / 64, 1.3) * (L.kq % 128 == 0 ? 1.0 : 3.3);
+    return est_dx(L, M).t < 0.95 * est_gemm(L.ic, M, ceil_div(L.oc, 64), 1.3) * (L.kq % 128 == 0 && L.oc % 64 == 0 ? 1.0 : 3.3);
 }
 
 // A 3-bit layer whose quantized columns are not whole stages (forward: 64 columns) or whole groups (input gradient): its 4-bit copy
@@ -778,12 +798,13 @@ bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx,
     return est_fwd(N, M).t + 0.2 * n + 3.5 < 0.94 * t16;
 }
 bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy, bool split_n, bool split_d) {
-    if (N.oc % 64 != 0) return false;
-    if (N.kq % 128 == 0) return true;
+    if (N.kq % 128 == 0 && N.oc % 64 == 0) return true;
     if (!dx_tile_preferred(N, M, lddy, split_n)) return false;
     const GemmSplit p = split_d ? gemm_dx_split(D, M) : GemmSplit{1, 0, 0, false};
     const double rounds = (int64_t)dx_tiles(N) * ceil_div(M, 64) > 512 ? 1.25 : 1.0, n = (double)N.oc * N.ic / (1 << 20);   // (a third round of tiles is underestimated)
-    double gemm = est_gemm(D.ic, M, D.oc / 64, 1.3);
+    // (rows that are not whole stages leave the fp16 copy the LDS-staged form; us, 4-bit copy against it: 4104 x 4096 with 64 weak columns,
+    // M = 64 / 777 / 2048: 41 / 67 / 174 against 160 / 166 / 168; 4456 x 14848 at 64 / 184 / 777: 51 / 75 / 229 against 206 / 208 / 218)
+    double gemm = D.oc % 64 == 0 ? est_gemm(D.ic, M, D.oc / 64, 1.3) : est_gemm(D.ic, M, ceil_div(D.oc, 64), 2.0);
     if (p.splits > 1) gemm = p.tail ? gemm - D.oc / 64 * 1.3 + p.stages * 1.5 + 12 : est_split(p, 12, 1.5);   // (tail: the last round's tiles only)
     return rounds * est_dx(N, M).t + 0.28 * n + 1.5 < 0.9 * (1.05 * gemm + 0.85 * n);
 }
@@ -794,9 +815,11 @@ hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __h
     return two ? launch_fwd<2, 2, 2, false>(L, X, M, ldx, Y, ldy, s) : launch_fwd<4, 2, 1, false>(L, X, M, ldx, Y, ldy, s);
 }
 hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s) {
-    const bool two = est_dx(L, M).j == 2;
-    if (L.once) return two ? launch_dx<2, 4, 2, true>(L, dY, M, lddy, dX, lddx, s) : launch_dx<4, 2, 1, true>(L, dY, M, lddy, dX, lddx, s);
-    return two ? launch_dx<2, 4, 2, false>(L, dY, M, lddy, dX, lddx, s) : launch_dx<4, 2, 1, false>(L, dY, M, lddy, dX, lddx, s);
+    using Launch = hipError_t (*)(const Layer&, const __half*, int64_t, int64_t, __half*, int64_t, hipStream_t);
+#define QEFT_DX(O, R) {launch_dx<2, 4, 2, O, R>, launch_dx<4, 2, 1, O, R>}
+    static const Launch table[2][2][2] = {{QEFT_DX(false, false), QEFT_DX(false, true)}, {QEFT_DX(true, false), QEFT_DX(true, true)}};
+#undef QEFT_DX
+    return table[L.once ? 1 : 0][L.oc % 64 != 0 ? 1 : 0][est_dx(L, M).j == 2 ? 0 : 1](L, dY, M, lddy, dX, lddx, s);
 }
 
 }  // namespace qeft

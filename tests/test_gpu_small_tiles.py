@@ -67,6 +67,26 @@ def test_input_gradient(oc, ic, k, rows):
         _run(lambda out: B.qeft_linear_bwd_dx(layer.desc, w, dyd, out, ws=False), m, ic, f"M={m}", qo.linear_bwd_dx(layer.w64, dy))
 
 
+@pytest.mark.parametrize("bits,dense", [(4, False), (3, True)])
+@pytest.mark.parametrize("oc,ic,k,rows", [
+    (72, 384 + 128, 128, (17, 64)),               # the second stage has 8 rows of its own, the third weak stage of 32 too
+    (200, 1000 + 136, 136, (65, 129)),            # four stages, the last of 8 rows, for eight shares; partial group, two weak tiles
+    (120, 512, 0, (100,)),
+    (1016, 2048 + 64, 64, (97, 300)),             # 15 whole stages and 56 rows
+    (4104, 896 + 8, 8, (777,)),                   # 128-row tiles
+])
+def test_input_gradient_of_any_number_of_channels(oc, ic, k, rows, bits, dense):
+    """OC no multiple of the stages of 64 (quantized) and 32 (weak) rows: the last begins before its own rows."""
+    layer = HostLayer(oc, ic, k, bits, 128, seed=oc + k, dense=dense)
+    w = layer.to_device()
+    for m in rows:
+        dy = synth.make_grad_output(m, oc, seed=m)
+        dyd, _ = pad_cols(dy)
+        n = B.qeft_workspace_bytes(layer.desc, B.QEFT_OP_BWD_DX, m)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda") if bits == 3 else False
+        _run(lambda out: B.qeft_linear_bwd_dx(layer.desc, w, dyd, out, ws=ws), m, ic, f"M={m}", qo.linear_bwd_dx(layer.w64, dy))
+
+
 def test_backward_call_equals_the_two_calls():
     """qeft_linear_bwd with the weak gradient's workspace alone: bit for bit qeft_linear_bwd_dx without one and qeft_weak_grad."""
     layer = HostLayer(512, 1024 + 128, 128, 4, 128, seed=4)
