@@ -15,7 +15,10 @@
 // Measured, without a workspace, before -> now (us): forward 4096 x 4096 at M = 333 / 512 / 777: 77 -> 26 / 29 / 40,
 // 4096 x 11008 at 512: 206 -> 72; input gradient 4096 x 4096 at 333 / 512 / 777: 90 -> 31 / 35 / 50, 11008 x 4096 at 512:
 // 228 -> 86.  Forward with a K-split workspace, 4096 x 4096 at 333 / 512: 32 / 34 -> 26 / 29; 5120 x 5120 at 333: 38 -> 33.
-// Tried and not kept: four stages of activations on the way instead of two (no change: not latency), weak columns after
+// Tried and not kept: four stages of activations on the way instead of two (no change: not latency), the activations requested half
+// a stage later (10 % slower), codes requested four stages (a cache line) at a time (4 to 15 % slower), four shares of the contraction
+// in the forward (no change at two waves per SIMD, uneven shares), conversions of one operation less (no change: timing variants
+// without conversions or without any memory access still take 80 to 95 % of the time), weak columns after
 // the quantized ones (exposes their fetch), conversions as the compiler orders them (chains of dependent packed operations).
 #include <type_traits>
 #include <utility>
@@ -361,16 +364,23 @@ __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const
                         afr[kn & 1][p >> 2][p & 3] = ONCE ? cv.second(p, s2[p >> 2], mzs[p >> 2]) : cv.scale(p, s2[p >> 2]);
                 }
                 if (m % 2 == 0) bfr[(ks + 2) & 3][m / 2] = x.frag(m / 2, ks < 2 ? CUR : NXT, (ks + 2) & 3);
-                // next stage's activations: chunk u permuted in slot 2 u, stored and refilled in slot 2 u + 1
-                if constexpr (T < 2 * NX) {
-                    constexpr int u = T / 2;
-                    if (T % 2 == 0) px[u & 1] = permute_x(x.v[SETX][u]);
-                    else {
-                        x.put(u, NXT, px[u & 1]);
-                        x.load(SETX, u, 64 * s_ld, L.kq);
-                    }
+                // next stage's activations, chunk by chunk: permuted in one slot, stored and refilled in the next.  128 rows: without
+                // gaps, so that the last stores are long done when the barrier waits for them (4096 x 11008, M = 777: 97.5 us with gaps, 94.3
+                // without); 64 rows: a slot has twice the conversions and no room for both (M = 512: 66.2, without gaps 69.1)
+                constexpr int GAP = J == 2 ? 2 : 1;
+                if constexpr (T % GAP == 0 && T / GAP < NX) px[(T / GAP) & 1] = permute_x(x.v[SETX][T / GAP]);
+                if constexpr (T > 0 && (T - 1) % GAP == 0 && (T - 1) / GAP < NX) {
+                    constexpr int u = (T - 1) / GAP;
+                    x.put(u, NXT, px[u & 1]);
+                    x.load(SETX, u, 64 * s_ld, L.kq);
                 }
-                if (ks == 3 && m == S - 1) load_a(E % DA, stage_of(chunk, E + DA));
+                if (ks == 3 && m == S - 1) {
+                    load_a(E % DA, stage_of(chunk, E + DA));
+                    // the next stage's first conversions stay here, behind this k-block's products: the compiler moves them below the
+                    // branch at the head of that stage otherwise, 34 vector instructions beside no product (4096 x 11008, M = 256: 59 us,
+                    // 55 so)
+                    asm volatile("" : "+v"(afr[0][0]), "+v"(afr[0][1]));
+                }
                 if (ks == 1 && m == S - 1) __syncthreads();
                 __builtin_amdgcn_sched_barrier(0);
             };
