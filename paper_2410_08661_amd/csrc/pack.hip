@@ -188,9 +188,8 @@ __global__ __launch_bounds__(256) void rtn_fused_w4g128_kernel(Layer L, const __
 // derives (scale, zero-point) with the rules above, quantizes and scores the squared weight error;
 // the first candidate with the smallest error is kept (candidate 0 = plain min-max).  One group per
 // 16 lanes (a lane holds 8 consecutive columns; lanes past the group width hold zeros, which cost
-// nothing), four groups per wavefront.  The error is summed in a fixed order - a lane's 8 columns
-// left to right, then a balanced tree over the 16 lanes - so that the decisions can be reproduced
-// exactly elsewhere.
+// nothing), four groups per wavefront.  The error is summed in a fixed order: a lane's 8 columns
+// left to right, one rounding each, then a tree over the 16 lanes.
 //
 // The kernel is bound by vector instructions (4096 x 4096, 80 candidates: 1.3 G scores).  What keeps them few:
 //  * Scale, zero-point and reciprocal of 16 candidates are derived at once, one per lane of the group's 16, and handed
@@ -202,123 +201,191 @@ __global__ __launch_bounds__(256) void rtn_fused_w4g128_kernel(Layer L, const __
 //    themselves are taken at the end by the rules above, with the division.
 //  * v - s r in one fused operation is exact where the product and the difference are rounded separately, because s r is
 //    exact (11 bits times an integer below 16).
-//  * A candidate whose two extreme columns alone already err by more than the best score so far cannot win and is not
-//    scored (the sum of non-negative terms is at least any of them; 2^-10 covers its rounding).  Narrow ranges clip the
-//    extremes hard, so about two thirds of an 80-candidate grid fall away on normally distributed weights.
-// 4096 x 4096, 80 candidates, whole call: 919 us before (two divisions per weight and candidate, every candidate scored, the
-// words in a second pass), 117 us now.
-__device__ __forceinline__ float dpp16_sum(float v) {
+//  * A candidate whose two least and two greatest columns alone already err by more than the best score so far cannot win and is
+//    not scored (the sum of non-negative terms is at least any of them; 2^-10 covers its rounding).  Narrow ranges clip the extremes
+//    hard: of an 80-candidate grid 27 are scored on normally distributed weights at 4 bits, 49 at 3 (31 and 60 by the two extremes
+//    alone), and the rounds of 16 whose widest candidate is beyond hope are not entered.
+//  * Candidates are scored in twos, whose sums over the 16 lanes share their moves; even lanes keep the best of the first ones,
+//    odd lanes of the second ones.
+//  * The weak block is copied by waves of the same launch.
+// 4096 x 4096, 80 candidates, whole call (us): 919 with two divisions per weight and candidate and every candidate scored, 123 with the
+// bound by two columns, single candidates and the copy in a launch of its own, 115 now; 3 bits, ten codes a word 217 -> 191, dense (the
+// words in this pass too) 221 -> 176.  (Vector instructions fell by 15 %, the kernel's own time by 4: what is left runs one per 3.9 cycles.)
+// sum over the 16 lanes of a row whose neighbours (lane ^ 1) are added already, separately for even and odd lanes
+__device__ __forceinline__ float dpp16_sum_rest(float v) {
     auto mv = [](float x, auto ctrl) {
         return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, false));
     };
-    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0xB1>{}));
-    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x4E>{}));
-    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x141>{}));
-    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x140>{}));
+    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x4E>{}));    // lane ^ 2
+    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x124>{}));   // four lanes on (rotation)
+    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x128>{}));   // eight lanes on
     return v;
 }
 
-// WORDS: 4-bit codes in groups of 128, whose words the same lanes then store (otherwise rtn_words_kernel does).
-template <bool WORDS>
+// WORDS: 4: 4-bit codes in groups of 128, 3: dense 3-bit codes in groups of 128, whose words the same lanes then store (0:
+// rtn_words_kernel does).
+template <int WORDS>
 __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __half* __restrict__ W, int64_t ldw,
                                                             __half* __restrict__ scales, __half* __restrict__ zeros,
-                                                            uint32_t* __restrict__ qweight, int chunks, int n_grid, float step) {
+                                                            uint32_t* __restrict__ qweight, __half* __restrict__ weak, int chunks,
+                                                            int copy_waves, int n_grid, float step) {
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-    const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6) - copy_waves;
     const int lane = threadIdx.x & 63;
+    if (wv < 0) {   // the launch's first waves copy the weak block, 8 columns per lane (a launch of its own took 5 us)
+        const int64_t idx = 64 * (wv + copy_waves) + lane;
+        const int per = L.k >> 3;
+        if (idx < (int64_t)L.oc * per) {
+            const int64_t r = idx / per;
+            const int c = 8 * (int)(idx - r * per);
+            *reinterpret_cast<u4*>(weak + r * L.k + c) = *reinterpret_cast<const u4*>(W + r * ldw + L.kq + c);
+        }
+        return;
+    }
     if (wv >= (int64_t)L.oc * chunks) return;
-    const int o = (int)(wv / chunks), ch = (int)(wv % chunks);
+    const int o = (int)((uint32_t)wv / (uint32_t)chunks), ch = (int)((uint32_t)wv - (uint32_t)o * (uint32_t)chunks);   // (2^31 waves would take 2 TB of W)
     const int grp = 4 * ch + (lane >> 4), t = lane & 15;   // grp < gs: chunks = gs / 4
     const int col = grp * L.g + 8 * t;
     const bool live = grp < L.ng && 8 * t < L.g && col < L.kq;   // Kq % 8 == 0: whole octets
     const u4 raw = live ? *reinterpret_cast<const u4*>(W + (size_t)o * ldw + col) : u4{0u, 0u, 0u, 0u};
     const h8 h = __builtin_bit_cast(h8, raw);
-    float v[8], lo0 = 0.f, hi0 = 0.f;
+    float v[8], lo0 = 0.f, hi0 = 0.f, lo1 = 0.f, hi1 = 0.f;   // the group's two least and two greatest values, 0 among them
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         v[e] = (float)h[e];
+        lo1 = __builtin_amdgcn_fmed3f(lo0, lo1, v[e]);
         lo0 = fminf(lo0, v[e]);
+        hi1 = __builtin_amdgcn_fmed3f(hi0, hi1, v[e]);
         hi0 = fmaxf(hi0, v[e]);
     }
-    lo0 = dpp16_min(lo0);
-    hi0 = -dpp16_min(-hi0);
+    auto two_least = [](float& a, float& b) {   // of the 16 lanes of a row, in every lane
+        auto merge = [&](auto ctrl) {
+            auto mv = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, false)); };
+            const float c = mv(a), d = mv(b);
+            b = fminf(fmaxf(a, c), fminf(b, d));
+            a = fminf(a, c);
+        };
+        merge(std::integral_constant<int, 0xB1>{});
+        merge(std::integral_constant<int, 0x4E>{});
+        merge(std::integral_constant<int, 0x141>{});
+        merge(std::integral_constant<int, 0x140>{});
+    };
+    two_least(lo0, lo1);
+    hi0 = -hi0, hi1 = -hi1;
+    two_least(hi0, hi1);
+    hi0 = -hi0, hi1 = -hi1;
     const float qmax = (float)((1 << L.bits) - 1);
-    float best_e = __builtin_inff(), best_s = 1.f, best_z = 0.f;
-    // squared-error term of one value under (s, 1 / s, z): nz = -z, uz = qmax - z
+    // scale and zero-point of candidate i of this lane's group
+    struct Params {
+        float s, z;
+    };
+    auto params = [&](int i) {
+        const float p = __fsub_rn(1.f, __fmul_rn((float)i, step));
+        const float lo = __fmul_rn(p, lo0), hi = __fmul_rn(p, hi0);
+        const float s32 = __fdiv_rn(__fsub_rn(hi, lo), qmax);
+        Params r{1.f, 0.f};
+        if (s32 != 0.f) {
+            __half s16 = __float2half_rn(s32);
+            if (__half2float(s16) == 0.f) s16 = __ushort_as_half((unsigned short)1);
+            r.s = __half2float(s16);
+            r.z = rintf(__fdiv_rn(__fsub_rn(0.f, lo), r.s));
+            r.z = fminf(fmaxf(r.z, 0.f), qmax);
+        }
+        return r;
+    };
+    // error of one value under (s, 1 / s, z): nz = -z, uz = qmax - z
     auto miss = [](float x, float s, float rs, float nz, float uz) {
         return __builtin_fmaf(-__builtin_amdgcn_fmed3f(rintf(x * rs), nz, uz), s, x);
     };
+    auto xor1 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false)); };
+    const bool odd = (t & 1) != 0;
+    // the best of the even candidates in the even lanes, of the odd ones in the odd lanes
+    float best_e = __builtin_inff();
+    int best_i = -1;
     for (int i0 = 0; i0 < n_grid; i0 += 16) {
-        float s_l, rs_l, z_l, bound_l;   // candidate i0 + t of this lane's group
-        {
-            const float p = __fsub_rn(1.f, __fmul_rn((float)(i0 + t), step));
-            const float lo = __fmul_rn(p, lo0), hi = __fmul_rn(p, hi0);
-            const float s32 = __fdiv_rn(__fsub_rn(hi, lo), qmax);
-            s_l = 1.f;
-            z_l = 0.f;
-            if (s32 != 0.f) {
-                __half s16 = __float2half_rn(s32);
-                if (__half2float(s16) == 0.f) s16 = __ushort_as_half((unsigned short)1);
-                s_l = __half2float(s16);
-                z_l = rintf(__fdiv_rn(__fsub_rn(0.f, lo), s_l));
-                z_l = fminf(fmaxf(z_l, 0.f), qmax);
-            }
-            rs_l = __fdiv_rn(1.f, s_l);
-            const float a = miss(lo0, s_l, rs_l, -z_l, qmax - z_l), b = miss(hi0, s_l, rs_l, -z_l, qmax - z_l);
-            bound_l = (a * a + b * b) * (1.f - 0x1p-10f);
-        }
-        auto candidate = [&](auto j_c) {
-            constexpr int J = decltype(j_c)::value;
-            auto from_j = [](float x) {   // lane J of the row of 16
-                return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + J, 0xf, 0xf, false));
+        if (i0 > 0) {
+            // A candidate's codes end within s / 2 of p hi0 and p lo0 (0.52 s covers the roundings of s, z and p), so a value x beyond misses
+            // by x - p hi0 - s / 2 at least, and by more under every narrower candidate: done once that is too much for all groups
+            const float p = 1.f - (float)i0 * step, half = 0.52f * (p * (hi0 - lo0) / qmax);
+            auto beyond = [&](float x) {
+                const float e = fmaxf(fmaxf(x - p * hi0, p * lo0 - x) - half, 0.f);
+                return e * e;
             };
-            if (i0 + J >= n_grid) return;
-            if (__ballot(from_j(bound_l) < best_e) == 0) return;
-            const float s = from_j(s_l), rs = from_j(rs_l), z = from_j(z_l), uz = qmax - z;
-            float acc = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float d = miss(v[e], s, rs, -z, uz);
-                acc = e == 0 ? __fmul_rn(d, d) : __fadd_rn(acc, __fmul_rn(d, d));
-            }
-            const float err = dpp16_sum(acc);
-            const bool better = err < best_e;
-            best_e = better ? err : best_e;
-            best_s = better ? s : best_s;
-            best_z = better ? z : best_z;
+            const float least = (beyond(lo0) + beyond(hi0)) + (beyond(lo1) + beyond(hi1));
+            if (__ballot(!(least * (1.f - 0x1p-7f) > fminf(best_e, xor1(best_e)))) == 0) break;
+        }
+        const Params mine = params(i0 + t);   // candidate i0 + t
+        const float s_l = mine.s, z_l = mine.z, rs_l = __fdiv_rn(1.f, s_l);
+        auto missed = [&](float x) {
+            const float e = miss(x, s_l, rs_l, -z_l, qmax - z_l);
+            return e * e;
         };
-        candidate(std::integral_constant<int, 0>{});
-        candidate(std::integral_constant<int, 1>{});
-        candidate(std::integral_constant<int, 2>{});
-        candidate(std::integral_constant<int, 3>{});
-        candidate(std::integral_constant<int, 4>{});
-        candidate(std::integral_constant<int, 5>{});
-        candidate(std::integral_constant<int, 6>{});
-        candidate(std::integral_constant<int, 7>{});
-        candidate(std::integral_constant<int, 8>{});
-        candidate(std::integral_constant<int, 9>{});
-        candidate(std::integral_constant<int, 10>{});
-        candidate(std::integral_constant<int, 11>{});
-        candidate(std::integral_constant<int, 12>{});
-        candidate(std::integral_constant<int, 13>{});
-        candidate(std::integral_constant<int, 14>{});
-        candidate(std::integral_constant<int, 15>{});
+        const float bound_l = i0 + t < n_grid ? ((missed(lo0) + missed(hi0)) + (missed(lo1) + missed(hi1))) * (1.f - 0x1p-10f) : __builtin_inff();
+        auto pair = [&](auto j_c) {
+            constexpr int J = decltype(j_c)::value;
+            // any of the four groups' candidates J, J + 1 that could still win
+            const float best = fminf(best_e, xor1(best_e));
+            if ((__ballot(bound_l < best) & (0x0003000300030003ull << J)) == 0) return;
+            float acc[2];
+            auto score = [&](auto k_c) {
+                constexpr int K = decltype(k_c)::value;
+                auto from = [](float x) {   // lane J + K of the row of 16
+                    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + J + K, 0xf, 0xf, false));
+                };
+                const float s = from(s_l), rs = from(rs_l), z = from(z_l), uz = qmax - z;
+                float a = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float d = miss(v[e], s, rs, -z, uz);
+                    a = e == 0 ? __fmul_rn(d, d) : __builtin_fmaf(d, d, a);
+                }
+                acc[K] = a;
+            };
+            score(std::integral_constant<int, 0>{});
+            score(std::integral_constant<int, 1>{});
+            // both sums over the 16 lanes at once: the first ends in the even lanes, the second in the odd ones
+            const float err = dpp16_sum_rest(__fadd_rn(odd ? acc[1] : acc[0], xor1(odd ? acc[0] : acc[1])));
+            const bool better = err < best_e && i0 + J + (t & 1) < n_grid;
+            best_e = better ? err : best_e;
+            best_i = better ? i0 + J + (t & 1) : best_i;
+        };
+        pair(std::integral_constant<int, 0>{});
+        pair(std::integral_constant<int, 2>{});
+        pair(std::integral_constant<int, 4>{});
+        pair(std::integral_constant<int, 6>{});
+        pair(std::integral_constant<int, 8>{});
+        pair(std::integral_constant<int, 10>{});
+        pair(std::integral_constant<int, 12>{});
+        pair(std::integral_constant<int, 14>{});
     }
+    // the better of the two classes, the first candidate where they are equal; none (a score that is no number): scale 1
+    const float other_e = xor1(best_e);
+    const int other_i = __builtin_amdgcn_update_dpp(0, best_i, 0xB1, 0xf, 0xf, false);
+    if (other_e < best_e || (other_e == best_e && (uint32_t)other_i < (uint32_t)best_i)) best_i = other_i;
+    Params best = params(best_i);
+    if (best_i < 0) best = Params{1.f, 0.f};
     if (t == 0) {
         const bool real = grp < L.ng;
-        scales[(size_t)o * L.gs + grp] = __float2half_rn(real ? best_s : 0.f);
-        zeros[(size_t)o * L.gs + grp] = __float2half_rn(real ? best_z : 0.f);
+        scales[(size_t)o * L.gs + grp] = __float2half_rn(real ? best.s : 0.f);
+        zeros[(size_t)o * L.gs + grp] = __float2half_rn(real ? best.z : 0.f);
     }
-    if constexpr (WORDS) {
+    if constexpr (WORDS != 0) {
         uint32_t out = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float q = __fadd_rn(rintf(__fdiv_rn(v[e], best_s)), best_z);
-            out |= (uint32_t)fminf(fmaxf(q, 0.f), qmax) << (4 * e);
+            const float q = __fadd_rn(rintf(__fdiv_rn(v[e], best.s)), best.z);
+            out |= (uint32_t)fminf(fmaxf(q, 0.f), qmax) << (WORDS * e);
         }
-        const int word = 16 * grp + t;   // (gs groups of 16 words reach past the row's padded end)
-        if (word < L.stride) qweight[(size_t)o * L.stride + word] = live ? out : 0u;
+        if (!live) out = 0u;
+        if constexpr (WORDS == 4) {
+            const int word = 16 * grp + t;   // (gs groups of 16 words reach past the row's padded end)
+            if (word < L.stride) qweight[(size_t)o * L.stride + word] = out;
+        } else {   // four lanes' 24 bits are three words, of which lane q < 3 has the head in its own bits and the rest in the next lane's
+            const int q = t & 3, word = 12 * grp + 3 * (t >> 2) + q;
+            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)out, 0xF9, 0xf, 0xf, false);   // quad_perm [1,2,3,3]
+            if (q < 3 && word < L.stride) qweight[(size_t)o * L.stride + word] = (out >> (8 * q)) | (next << (24 - 8 * q));
+        }
     }
 }
 
@@ -468,13 +535,18 @@ hipError_t pack_search(const Layer& L, const __half* W, int64_t ldw, int n_grid,
                        __half* scales, __half* zeros, __half* weak, hipStream_t s) {
     if (L.kq > 0) {
         const int chunks = L.gs / 4;
-        const int grid = ceil_div((int64_t)L.oc * chunks, 4);
+        const bool copies = L.k > 0 && (L.k & 7) == 0;   // (the columns then lie 16-byte aligned on both sides)
+        const int copy_waves = copies ? ceil_div((int64_t)L.oc * (L.k >> 3), 64) : 0;
+        const int grid = ceil_div((int64_t)L.oc * chunks + copy_waves, 4);
         if (L.bits == 4 && L.g == 128) {
-            search_params_kernel<true><<<grid, 256, 0, s>>>(L, W, ldw, scales, zeros, qweight, chunks, n_grid, step);
+            search_params_kernel<4><<<grid, 256, 0, s>>>(L, W, ldw, scales, zeros, qweight, weak, chunks, copy_waves, n_grid, step);
+        } else if (L.dense && L.g == 128) {
+            search_params_kernel<3><<<grid, 256, 0, s>>>(L, W, ldw, scales, zeros, qweight, weak, chunks, copy_waves, n_grid, step);
         } else {
-            search_params_kernel<false><<<grid, 256, 0, s>>>(L, W, ldw, scales, zeros, qweight, chunks, n_grid, step);
+            search_params_kernel<0><<<grid, 256, 0, s>>>(L, W, ldw, scales, zeros, qweight, weak, chunks, copy_waves, n_grid, step);
             rtn_words_kernel<<<ceil_div((int64_t)L.oc * L.stride, 256), 256, 0, s>>>(L, W, ldw, scales, zeros, qweight);
         }
+        if (copies) return hipGetLastError();
     }
     copy2d(W + L.kq, ldw, weak, L.k, L.oc, L.k, s);
     return hipGetLastError();

@@ -49,3 +49,32 @@ def test_search_criterion(kind, bits, g, k, n_grid, step):
     sq = (w[:, :kq].astype(np.float64) - wq) ** 2
     err = np.stack([sq[:, i * g:min((i + 1) * g, kq)].sum(axis=1) for i in range(ng)], axis=1)
     assert np.all(err <= e_all.min(axis=0) * (1 + 1e-5) + 1e-30)
+
+
+@pytest.mark.parametrize("oc,kq,k,n_grid,step", [(37, 600, 24, 80, 0.01), (5, 1032, 13, 7, 0.1), (9, 2048, 0, 33, 0.03), (130, 8, 128, 16, 0.05)])
+def test_dense_three_bit_words(oc, kq, k, n_grid, step):
+    """The dense layout in groups of 128 is packed by the searching lanes, 3 words from 4 of them: rows that end inside those, padding,
+    grids that are no whole rounds of 16, weak blocks copied by the same launch and (13 columns) by another."""
+    ic = kq + k
+    w = (np.random.default_rng(oc).standard_normal((oc, ic)) * 0.02).astype(np.float16)
+    d = B.make_desc(oc, ic, k, 3, 128, B.QEFT_LAYOUT_DENSE3)
+    out = B.Weight(d)
+    for a in (out.qweight, out.scales, out.zeros):
+        a.fill_(-1)
+    B.qeft_pack_search(d, pad_cols(w)[1][:, :ic], n_grid, step, out)
+    torch.cuda.synchronize()
+    lay = qo.layout(oc, ic, k, 3, 128, dense=True)
+    ng = lay["n_groups"]
+    s, z = out.scales.cpu().numpy(), out.zeros.cpu().numpy()
+    assert not s[:, ng:].any() and not z[:, ng:].any()
+    s, z = s[:, :ng], z[:, :ng]
+    codes = qo.codes_for_params(w, k, 3, 128, s, z)
+    assert np.array_equal(qo.pack_codes_dense3(codes, lay["row_stride_words"]), out.qweight.cpu().numpy().view(np.uint32))
+    s_all, z_all, e_all = qo.search_candidates(w, k, 3, 128, n_grid, step)
+    assert np.all(np.any((s_all.view(np.uint16) == s.view(np.uint16)[None]) & (z_all == z.astype(np.float32)[None]), axis=0))
+    wq = qo.dequantize(codes, s, z, np.zeros((oc, 0), dtype=np.float16), 128)
+    sq = (w[:, :kq].astype(np.float64) - wq) ** 2
+    err = np.stack([sq[:, i * 128:min((i + 1) * 128, kq)].sum(axis=1) for i in range(ng)], axis=1)
+    assert np.all(err <= e_all.min(axis=0) * (1 + 1e-5) + 1e-30)
+    if k:
+        assert np.array_equal(out.weak.cpu().numpy(), w[:, kq:])
