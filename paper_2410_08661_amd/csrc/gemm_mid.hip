@@ -1,28 +1,31 @@
-// Forward of 4-bit layers for 17 to 192 rows and of 3-bit layers from 2 rows on: several sequences decoded together, short prompts,
-// draft tokens.  (Paper Sec. 3.2.1; the rows between the matrix-vector kernels' 16 and the sizes at which 256 x 256 tiles occupy the GPU.)
+// Forward of 4-bit layers for 2 to 192 rows (up to 16: long rows and small layers) and of 3-bit layers from 2 rows on: several sequences
+// decoded together, short prompts, draft tokens.  (Paper Sec. 3.2.1; the rows between the matrix-vector kernels' 16 and the sizes at which 256 x 256 tiles occupy the GPU.)
 //
 // A layer's codes are read once per panel of up to 48 rows, where passes of the 16-row kernel read them once per 16 rows
 // and the tiled GEMM leaves OC / 256 of 256 compute units working on the whole contraction.  What bounds the kernel: every
-// workgroup reads its panel of X in full (48 rows x 2 IC bytes against 8 IC bytes of codes per tile of 16 channels), so the
-// rows' trips from L2 weigh as much as the weights from memory: 4096 x 11008 at 48 rows moves 270 MB through the L2s in
-// 24 us.  Hence as few, as wide workgroups as still occupy every CU (rule at fwd_mid).
+// workgroup reads its panel of X in full (48 rows x 2 IC bytes against 8 IC bytes of codes per tile of 16 channels), and each
+// kilobyte of it costs a CU about 13 ns on its way through the L1, whatever the order of groups or the pitch of the rows
+// (4096 x 11008 at 8 / 24 / 40 rows: 11.6 / 16.7 / 20.8 us).  Hence as few, as wide workgroups as still occupy every CU (rule at fwd_mid).
 //
 // Mapping: 16x16x32 MFMA, rows of X as the A operand, 16 channels as the B operand (a packed word is a lane's 8 contraction
-// elements), a group of 128 columns at a time.  The workgroup's waves take every KS-th group each and share nothing until
-// the end, so the main loop has no barrier: a wave brings its group's rows to a piece of LDS of its own (whole 256-byte row
-// pieces, nibble order, chunks XOR-placed by the row; a fifth of the LDS cycles are conflicts), reads them back as fragments once and
-// multiplies all its channel tiles.  Dequantization as in the 16-row kernels, on the accumulator and without rounding the
-// weights: s (sum x (1024 + q) - (1024 + z) Sx), two FMAs per accumulator and group.  The next group's rows, codes and
-// parameters are requested while this one is multiplied.  Partial tiles meet in LDS in a fixed order (fp32).
-// Measured (passes or GEMM before -> now, us): 4096 x 4096, M = 40: 18.4 -> 10.2; 12288 x 4096 (q/k/v), M = 40: 26.9 -> 16.7;
-// 22016 x 4096 (gate/up), M = 48: 39 -> 30; 4096 x 11008, M = 40: 38.6 -> 23.7; 13824 x 5120, M = 64: 62 (46 with a K-split
-// workspace) -> 32; 4096 x 4096, M = 96: 37 (24) -> 12.
-// 3-bit codes are multiplied as they are stored (Codes3).  Against the kernel that converted them to fp16 weights at up to 16 rows, and
-// that kernel's passes or a copy in the 4-bit layout above (us, ten codes a word): 5120 x 5120, M = 2 / 16 / 40: 11.4 / 14.5 / 24.6 -> 8.5 /
-// 9.8 / 14.5; 15360 x 5120 (q/k/v) M = 8 / 40: 39.6 / 125 -> 15.8 / 26.6; 27648 x 5120 (gate/up) M = 8: 41 -> 26.5; 512 x 512, M = 8: 8.6 -> 3.8.
-// The small row counts are bound by the work per tile beside the codes (fragments, sums), the others as above.
-// Tried and not kept: 64 rows per panel (registers spill, 2 to 5 times slower), codes two groups ahead for more than two
-// channel tiles (spills), parameters of four groups per request (no faster, and the waves' shares come out uneven).
+// elements), a group of 128 columns at a time.  The workgroup's waves take every KS-th pair of neighbouring groups each and share
+// nothing until the end, so the main loop has no barrier.  A group's rows and a pair's codes go from memory to a piece of the wave's LDS
+// by themselves (buffer loads that write LDS: no registers, so the next group's rows and the next pair's codes are on the way while a
+// group is multiplied), chunks XOR-placed by the row on the way; the wave reads them back as fragments once, the rows into nibble
+// order, and multiplies all its channel tiles.  The codes' way through LDS is for the L1: a lane that fetches its own fragment shares no
+// line with its neighbours, and each of the 64 takes one of the L1's tag cycles, which were 70 % of the CUs' time (counters at
+// M = 40, 22016 x 4096: 34.6k of 50k cycles; matrix pipe 11k, vector issue 19k); 8 rows x 128 bytes per request are 16 cycles.  In pairs,
+// because a half line fetched alone holds a whole one.  Dequantization as in the 16-row kernels, on the accumulator and without
+// rounding the weights: s (sum x (1024 + q) - (1024 + z) Sx), two FMAs per accumulator and group.  Partial tiles meet in LDS in a fixed
+// order (fp32).
+// Measured (rows through registers, lanes fetching their own fragments, single groups -> now, us): 22016 x 4096 (gate/up) at M = 24 / 40 / 64:
+// 24.4 / 29.0 / 41.4 -> 21.2 / 25.3 / 32.1; 4096 x 11008: 18.0 / 23.3 / 24.1 -> 16.7 / 20.8 / 20.1; 5120 x 13824: 30.4 / 37.7 / 37.7 -> 26.3 / 31.3 / 30.2;
+// 8192 x 8192: 20.2 / 24.6 / 29.0 -> 17.7 / 21.0 / 23.6; 4096 x 4096 at M = 40 / 96: 10.6 / 11.9 -> 9.8 / 11.3.
+// 3-bit codes are multiplied as they are stored (Codes3), fetched by the lanes that use them (us, ten codes a word): 5120 x 5120,
+// M = 2 / 16 / 40: 8.0 / 9.2 / 13.4; 15360 x 5120 (q/k/v) M = 8 / 40: 14.9 / 22.9; 27648 x 5120 (gate/up) M = 8: 25.2; 1024 x 2048, M = 8: 4.3.
+// Tried and no faster: X requests that bypass the caches (nt: 10 to 30 % slower), other orders of the groups per workgroup, 80 and 96
+// channels per workgroup (48 rows spill).
+// Tried and not kept: 64 rows per panel (registers spill, 2 to 5 times slower).
 #include <type_traits>
 
 #include <climits>
@@ -41,6 +44,9 @@ typedef uint32_t u4w __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ h8 as_h8(u4 v) { return __builtin_bit_cast(h8, v); }
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return __builtin_bit_cast(uint32_t, h2{(_Float16)a, (_Float16)b}); }
+// waits until at most N of the wave's requests to memory are under way
+template <int N>
+__device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
 __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // 8 consecutive activations to the order in which the codes of a word come out of the conversion: (0,4)(1,5)(2,6)(3,7)
@@ -95,6 +101,12 @@ __device__ __forceinline__ void pair_x3(u4 (&v)[4]) {
     for (int q = 0; q < 4; ++q) v[q] = u4{o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]};
 }
 
+// bytes of LDS of a wave, without the parameters
+constexpr int mid_piece(int MT, int NT, bool codes) {
+    const int main = MT * 4096 + (codes ? NT * 2048 : 0), sum = MT * NT * 1024;
+    return main > sum ? main : sum;
+}
+
 struct MidArgs {
     const uint32_t* qweight[MAX_GROUP];
     const __half* scales[MAX_GROUP];
@@ -116,11 +128,10 @@ struct MidArgs {
 template <int MT, int NT, Fmt F, int XR>
 __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    constexpr int XB = MT * 16 * 256;            // a group of activations: 16 MT rows of 256 bytes
-    constexpr int PB = 64 * 4;                   // (zero-point, scale) of a group, up to 64 channels
+    constexpr int XB = MT * 4096;                        // a wave's piece of LDS: a group of activations, (4-bit) the codes of two groups,
+    constexpr int WB = mid_piece(MT, NT, F == W4);       // (at the end a partial tile),
+    constexpr int PB = NT * 128;                         // and (zero-point, scale) of two groups of up to 64 channels
     static_assert(MT == 1 || XR == 4 * MT, "");
-    constexpr bool FULL = NT == 1 || MT == 1;    // activations of the next group: all in flight at once, or half by half
-    constexpr int H = FULL ? XR : XR / 2;        // 16-byte requests in flight (a request: 4 rows)
     const int lane = threadIdx.x & 63;
     const int KS = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -134,8 +145,8 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     const int oc = A.oc[li];
     const int o0 = (t_n - A.tile_begin[li]) * (16 * NT), m0 = t_m * (16 * MT);
 
-    unsigned char* mine = lds + (size_t)wave * XB;
-    unsigned char* par = lds + (size_t)KS * XB + (size_t)wave * PB;
+    unsigned char* mine = lds + (size_t)wave * WB;
+    unsigned char* par = lds + (size_t)KS * WB + (size_t)wave * PB;
     const int last_g = A.ng - 1;
 
     const unsigned char* wbase = reinterpret_cast<const unsigned char*>(A.qweight[li] + (size_t)o0 * A.stride);
@@ -143,16 +154,18 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     const __half* zbase = A.zeros[li] + (size_t)o0 * A.gs;
     uint32_t woff[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) woff[t] = (uint32_t)min(16 * t + n, oc - 1 - o0) * (uint32_t)(A.stride * 4) + (F == W4 ? 16u * kb : (F == W3_DENSE ? 12u * kb : 0u));
+    for (int t = 0; t < NT; ++t) woff[t] = (uint32_t)min(16 * t + n, oc - 1 - o0) * (uint32_t)(A.stride * 4) + (F == W3_DENSE ? 12u * kb : 0u);
+    static_assert(NT <= 4, "");
     const uint32_t poff = (uint32_t)min(min(lane, 16 * NT - 1), oc - 1 - o0) * (uint32_t)A.gs;
-    const int xr = lane >> 4, xc = lane & 15;    // request u of a group of activations: row 4 u + xr, chunk xc
+    const int xr = lane >> 4, xc = lane & 15;    // request u of a group of activations: row 4 u + xr, to slot xc: chunk xc ^ (row % 16)
     const unsigned char* xbase = reinterpret_cast<const unsigned char*>(A.X + (size_t)m0 * A.ldx);
     const uint32_t xpitch = (uint32_t)A.ldx * 2u;
+    const auto xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(xbase), 0, (int)0xffffffff, 0x00020000);
     const int mlast = A.M - 1 - m0;
     const uint32_t xoff0 = (uint32_t)xr * xpitch, xlast = (uint32_t)min(mlast, 16 * MT) * xpitch;
 
-    constexpr int D = (MT == 2 && NT <= 2) || MT == 1 ? 2 : 1;   // groups of codes on the way
-    u4 wq[D][NT], raw[H];
+    u4 wq[2][NT];         // codes and (zero-point, scale) of two groups
+    uint32_t zs[2][NT];
     uint32_t ps, pz;
     // ten codes per word: the lane's first word of a group and its shift (four words are there: 32 c / 10 + 4 is at most the row's
     // padded length for every c with a column before Kq; the min is for lanes past it)
@@ -161,40 +174,46 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     auto shift_of = [&](int g) { return 3u * ((uint32_t)(128 * g + 32 * kb) % 10u); };
     auto load_w = [&](int set, int t, int g) {
         const int gc = min(g, last_g);
-        if constexpr (F == W4) wq[set][t] = *reinterpret_cast<const u4*>(wbase + (size_t)(64 * gc) + woff[t]);
-        else if constexpr (F == W3_DENSE) {
+        if constexpr (F == W3_DENSE) {
             const u3w v = *reinterpret_cast<const u3w*>(wbase + (size_t)(48 * gc) + woff[t]);
             wq[set][t] = u4{v.x, v.y, v.z, 0u};
         } else
             wq[set][t] = *reinterpret_cast<const u4w*>(wbase + first_word(gc) + woff[t]);
     };
-    auto load_x = [&](u4& r, int u, int g) {
-        const uint32_t off = min(xoff0 + (uint32_t)(4 * u) * xpitch, xlast) + (uint32_t)(2 * min(128 * g + 8 * xc, A.kq - 8));
-        r = *reinterpret_cast<const u4*>(xbase + off);
-    };
-    // parameters of a group: a lane fetches those of one channel and hands them out through LDS
-    auto load_par = [&](int g) {
-        ps = reinterpret_cast<const uint16_t*>(sbase + min(g, last_g))[poff];
-        pz = reinterpret_cast<const uint16_t*>(zbase + min(g, last_g))[poff];
-    };
-    auto put_par = [&]() { *reinterpret_cast<uint32_t*>(par + 4 * lane) = pz | (ps << 16); };
-    // requests u0 .. of group g into LDS; columns past Kq become zeros
-    auto put_x = [&](const u4* r, int u0, int cnt, int g) {
-        if (128 * g + 128 > A.kq) {
-            const bool live = 128 * g + 8 * xc < A.kq;
+    // the rows' 256-byte pieces of group g go to LDS by themselves; columns past Kq repeat the last 8
+    auto load_x = [&](int g) {
+        uint32_t col[4];
 #pragma unroll
-            for (int u = 0; u < cnt; ++u) {
-                const u4 z = u4{0u, 0u, 0u, 0u};
-                const int row = 4 * (u0 + u) + xr;
-                *reinterpret_cast<u4*>(mine + row * 256 + ((xc ^ (row & 15)) << 4)) = live ? (F == W4 ? permute_x(r[u]) : r[u]) : z;
-            }
-        } else {
+        for (int c = 0; c < 4; ++c) col[c] = (uint32_t)(2 * min(128 * g + 8 * (xc ^ (4 * c + xr)), A.kq - 8));
 #pragma unroll
-            for (int u = 0; u < cnt; ++u) {
-                const int row = 4 * (u0 + u) + xr;
-                *reinterpret_cast<u4*>(mine + row * 256 + ((xc ^ (row & 15)) << 4)) = F == W4 ? permute_x(r[u]) : r[u];
-            }
+        for (int u = 0; u < XR; ++u) {
+            const uint32_t off = min(xoff0 + (uint32_t)(4 * u) * xpitch, xlast) + col[u & 3];
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (__attribute__((address_space(3))) void*)(mine + 1024 * u), 16, (int)off, 0, 0, 0);
         }
+    };
+    // codes of groups 2 p and 2 p + 1: 8 rows x 128 bytes per request, so that neighbouring lanes read neighbouring bytes (a lane
+    // fetching its own fragment shares no bytes with its neighbours, and each of its 16 bytes is an access to the L1's tags)
+    const auto wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(wbase), 0, (int)0xffffffff, 0x00020000);
+    unsigned char* codes = mine + XB;
+    auto load_codes = [&](int p) {
+        uint32_t col[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) col[c] = (uint32_t)min(128 * p + 16 * ((lane & 7) ^ (4 * c + (lane >> 4))), 4 * A.stride - 16);
+#pragma unroll
+        for (int u = 0; u < 2 * NT; ++u) {
+            const uint32_t off = (uint32_t)min(8 * u + (lane >> 3), oc - 1 - o0) * (uint32_t)(A.stride * 4) + col[u & 1];
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wbuf, (__attribute__((address_space(3))) void*)(codes + 1024 * u), 16, (int)off, 0, 0, 0);
+        }
+    };
+    // parameters of groups 2 p and 2 p + 1: a lane fetches those of one channel and hands them out through LDS (rows of scales and
+    // zero-points are padded to eights)
+    auto load_par = [&](int p) {
+        ps = *reinterpret_cast<const uint32_t*>(sbase + poff + 2 * min(p, last_g >> 1));
+        pz = *reinterpret_cast<const uint32_t*>(zbase + poff + 2 * min(p, last_g >> 1));
+    };
+    auto put_par = [&]() {
+        if (lane < 16 * NT)
+            *reinterpret_cast<u2*>(par + 8 * lane) = u2{__builtin_amdgcn_perm(ps, pz, 0x05040100u), __builtin_amdgcn_perm(ps, pz, 0x07060302u)};
     };
 
     f4 acc[MT][NT];
@@ -230,32 +249,40 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     };
 
     load_weak(wave);
-    if (wave >= A.ng) mul_weak(wave);
+    if (2 * wave >= A.ng) mul_weak(wave);
     else {
-        auto group = [&](int i) { return i * KS + wave; };   // the wave's i-th group
-        const int ngw = (A.ng - wave + KS - 1) / KS;
+        const int npair = (A.ng + 1) >> 1, npw = (npair - wave + KS - 1) / KS;
+        const int ngw = 2 * npw - ((A.ng & 1) && wave + (npw - 1) * KS == npair - 1 ? 1 : 0);
+        auto group = [&](int i) { return 2 * ((i >> 1) * KS + wave) + (i & 1); };
         {
-            u4 r0[XR];
-            load_par(group(0));
+            load_par(wave);
+            if constexpr (F == W4) load_codes(wave);
+            load_x(group(0));
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (F != W4) {
 #pragma unroll
-            for (int u = 0; u < XR; ++u) load_x(r0[u], u, group(0));
-#pragma unroll
-            for (int t = 0; t < NT; ++t) load_w(0, t, group(0));
-            if constexpr (D == 2) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) load_w(1, t, group(1));
+                for (int t = 0; t < NT; ++t) {
+                    load_w(0, t, group(0));
+                    load_w(1, t, group(1));
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
             mul_weak(wave);
-            put_par();
-            put_x(r0, 0, XR, group(0));
         }
-        // group i: its activations are in LDS, its codes in set i % 2; the next group's activations and the codes of
-        // the one after are on the way
+        // group i: its codes are in set i % 2, its activations reach LDS while group i - 1 is multiplied, its codes a step earlier
         auto step = [&](int i, auto set_c) {
             constexpr int SET = decltype(set_c)::value;
-            const int gn = group(i + 1), gw = group(i + D);
+            const int g = group(i);
             u4 xa[MT][4];
+            __builtin_amdgcn_sched_barrier(0);
+            // even groups wait for all that was requested (3-bit: but the codes), odd ones leave what was requested behind their
+            // activations: the next pair's codes
+            wait_vm<F == W4 ? (SET == 0 ? 0 : 2 * NT) : (SET == 0 ? 2 * NT : 0)>();
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (SET == 0) {
+                asm volatile("" : "+v"(ps), "+v"(pz));   // (used behind the wait, not ahead of it)
+                put_par();
+            }
             wave_lds_fence();
 #pragma unroll
             for (int a = 0; a < MT; ++a)
@@ -264,17 +291,42 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
                     const int xn = min(n, 4 * XR - 1);   // (rows that were not fetched stand for rows past M)
                     xa[a][q] = *reinterpret_cast<const u4*>(mine + (16 * a + xn) * 256 + (((4 * kb + q) ^ xn) << 4));
                 }
-            uint32_t zs[NT];
+            if constexpr (SET == 0) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) zs[t] = *reinterpret_cast<const uint32_t*>(par + 4 * (16 * t + n));
+                for (int t = 0; t < NT; ++t) {
+                    const u2 v = *reinterpret_cast<const u2*>(par + 8 * (16 * t + n));
+                    zs[0][t] = v.x;
+                    zs[1][t] = v.y;
+                    if constexpr (F == W4) {
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) wq[e][t] = *reinterpret_cast<const u4*>(codes + (16 * t + n) * 128 + (((4 * e + kb) ^ (n >> 1)) << 4));
+                    }
+                }
+            }
             wave_lds_fence();
-            load_par(gn);
+            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): all is in registers before its place is filled again
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (SET == 0) load_par((i >> 1) * KS + KS + wave);
+            load_x(group(i + 1));
+            __builtin_amdgcn_sched_barrier(0);   // (the odd group's wait counts the requests behind these)
+            if constexpr (SET == 0 && F == W4) load_codes((i >> 1) * KS + KS + wave);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t wshift = F == W3_TEN ? shift_of(g) : 0u;
+            if (128 * g + 128 > A.kq) {
 #pragma unroll
-            for (int u = 0; u < H; ++u) load_x(raw[u], u, gn);
-            const uint32_t wshift = F == W3_TEN ? shift_of(group(i)) : 0u;
-            if constexpr (F != W4) {
+                for (int q = 0; q < 4; ++q) {
+                    const bool live = 128 * g + 32 * kb + 8 * q < A.kq;
 #pragma unroll
-                for (int a = 0; a < MT; ++a) pair_x3(xa[a]);
+                    for (int a = 0; a < MT; ++a) xa[a][q] = live ? xa[a][q] : u4{0u, 0u, 0u, 0u};
+                }
+            }
+#pragma unroll
+            for (int a = 0; a < MT; ++a) {
+                if constexpr (F != W4) pair_x3(xa[a]);
+                else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) xa[a][q] = permute_x(xa[a][q]);
+                }
             }
             f4 sx[MT];
 #pragma unroll
@@ -300,32 +352,23 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
 #pragma unroll
                     for (int a = 0; a < MT; ++a) tmp[a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa[a][q]), as_h8(c), tmp[a], 0, 0, 0);
                 }
-                load_w(SET, t, gw);
-                const h2 p = __builtin_bit_cast(h2, zs[t]);
+                if constexpr (SET == 1 && F != W4) {
+                    load_w(0, t, group(i + 1));
+                    load_w(1, t, group(i + 2));
+                }
+                const h2 p = __builtin_bit_cast(h2, zs[SET][t]);
                 const float sf = (float)p.y, cz = -(1024.f + (float)p.x);
 #pragma unroll
                 for (int a = 0; a < MT; ++a)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[a][t][e] = fmaf(sf, fmaf(cz, sx[a][e], tmp[a][e]), acc[a][t][e]);
-                if (!FULL && t == NT / 2 - 1) {
-                    put_x(raw, 0, H, gn);
-#pragma unroll
-                    for (int u = 0; u < H; ++u) load_x(raw[u], H + u, gn);
-                }
             }
-            put_x(raw, FULL ? 0 : H, H, gn);
-            put_par();
         };
         int i = 0;
-        if constexpr (D == 2) {
 #pragma clang loop unroll(disable)
-            for (; i + 1 < ngw; i += 2) {
-                step(i, std::integral_constant<int, 0>{});
-                step(i + 1, std::integral_constant<int, 1>{});
-            }
-        } else {
-#pragma clang loop unroll(disable)
-            for (; i + 1 < ngw; ++i) step(i, std::integral_constant<int, 0>{});
+        for (; i + 1 < ngw; i += 2) {
+            step(i, std::integral_constant<int, 0>{});
+            step(i + 1, std::integral_constant<int, 1>{});
         }
         if (i < ngw) step(i, std::integral_constant<int, 0>{});
     }
@@ -402,7 +445,7 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     };
 
     // the waves' partial tiles meet in LDS (each in its wave's piece); wave w sums tiles w, w + KS, ...
-    static_assert(NT <= 4, "");
+    wait_vm<0>();   // (the last step's requests, of a group past the wave's last, go there too)
     __half* Y = A.Y[li] + (size_t)m0 * A.ldy[li] + o0;
     const int64_t ldy = A.ldy[li];
     __syncthreads();
@@ -415,7 +458,7 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     for (int q = wave; q < MT * NT; q += KS) {
         f4 y = f4{0.f, 0.f, 0.f, 0.f};
         for (int w = 0; w < KS; ++w) {
-            const f4 p = *reinterpret_cast<const f4*>(lds + (size_t)w * XB + (q << 10) + 16 * lane);
+            const f4 p = *reinterpret_cast<const f4*>(lds + (size_t)w * WB + (q << 10) + 16 * lane);
 #pragma unroll
             for (int e = 0; e < 4; ++e) y[e] += p[e];
         }
@@ -460,9 +503,10 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
 template <int MT, int NT, Fmt F, int XR>
 hipError_t launch_mid(const MidArgs& A, int KS, hipStream_t s) {
     static bool attr = false;
-    const size_t lds_bytes = (size_t)KS * (MT * 4096 + 256);
+    const size_t lds_bytes = (size_t)KS * (mid_piece(MT, NT, F == W4) + NT * 128);
+    if (lds_bytes > 160 * 1024) return hipErrorInvalidValue;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void*)fwd_mid_kernel<MT, NT, F, XR>, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (MT * 4096 + 256));
+        hipError_t e = hipFuncSetAttribute((const void*)fwd_mid_kernel<MT, NT, F, XR>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr = true;
     }
@@ -476,7 +520,7 @@ hipError_t launch_mid(const MidArgs& A, int KS, hipStream_t s) {
 bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx) {
     if (L.g != 128 || (L.kq % 8) != 0 || (L.k % 8) != 0 || ldx > QEFT_MAX_DIM) return false;
     if (L.bits == 3) return M > 0 && L.kq >= 8 && (!L.dense || 12 * L.ng <= L.stride);   // (dense: a lane reads 12 bytes of a group, so whole groups fit the padded row)
-    return M > 16 && (L.oc % 8) == 0;
+    return M > 1 && (L.oc % 8) == 0 && (M > 16 || L.kq >= 8);
 }
 
 // Up to 96 rows (two panels) always; up to 192 (four) where the alternative leaves most of the GPU idle: without a workspace
@@ -506,13 +550,26 @@ bool fwd_mid3_preferred(const Layer& L, int64_t M, int64_t ldx) {
     return panels <= 15 && panels * weights <= (L.oc <= 5120 ? 5 : 1) * (int64_t)(5120 * 5120);
 }
 
-// Tiles of 16 NT channels and KS waves.  A CU holds one workgroup of eight waves or two of four (registers), and a workgroup
+// 4-bit layers at 2 to 16 rows, `tiles` tiles of 16 channels in the launch: here where a row's contraction does not fit the registers of
+// one workgroup of the 16-row kernel in one pass (more than 32 groups of 128), except very wide launches, and one tile per CU of shorter
+// rows.  us, the 16-row kernel (M = 2: the small-M kernel) against here: 5120 x 5120 at M = 2 / 4 / 8 / 16: 9.3 / 10.3 / 10.9 / 11.5 against 7.5 /
+// 7.4 / 7.7 / 8.5; 5120 x 13824: 17.7 / 23.9 / 20.8 / 23.7 against 17.2 / 17.0 / 18.7 / 21.8; 4096 x 11008 at 4 / 8 / 16: 11.6 / 12.9 / 15.4 against
+// 10.6 / 11.6 / 13.2; 27648 x 5120 (gate/up) at 2 / 4 / 8: 22.7 / 26.6 / 28.7 against 24.6 / 25.6 / 25.4; 1024 x 8192 at 8: 9.4 against 7.3; 57344 x 8192
+// at 4 / 8 / 16: 67 / 77 / 75 against 79 / 76 / 80; at 2, 8192 x 8192: 12.0 against 12.7, 8192 x 28672: 42 against 34; 4096 x 4096 at 2 / 4 / 16: 5.6 / 6.3 / 7.0 against 5.8 / 5.9 / 6.8; but 12288 x 4096 at 8: 10.1
+// against 12.6, 22016 x 4096: 14.5 against 16.6.
+bool fwd_mid_few_preferred(const Layer& L, int64_t M, int64_t ldx, int tiles) {
+    if (L.bits != 4 || M < 2 || M > 16 || !fwd_mid_supported(L, M, ldx)) return false;
+    if (L.ng > 32) return M > 2 ? tiles <= 2048 : tiles <= 320 || (tiles <= 512 && L.ng > 128);
+    return M > 2 && tiles <= 256;
+}
+
+// Tiles of 16 NT channels and KS waves.  A CU holds one workgroup of eight waves or two of four (registers and LDS), and a workgroup
 // reads its whole panel of X whatever its width, so: the narrowest tile whose workgroups are all resident at eight waves,
-// else at four, else the widest.  (us, 48 rows: 4096 x 4096 NT = 1 / 2 / 3 / 4 at KS = 8: 10.6 / 12.0 / 13.3 / 15.4;
-// 12288 x 4096: 32 / 27 / 17.8 / 20.3, KS = 4 and NT = 3: 19.2; 22016 x 4096 KS = 4: 43 / 30 / 34, KS = 8: 33 at best.)
+// else at four, else the widest.  (us at M = 40, KS = 8: 4096 x 4096 NT = 1 / 2: 9.9 / 11.3; 8192 x 8192 NT = 2 / 3 / 4: 21.7 / 24.4 / 30.7;
+// 22016 x 4096: KS = 4 and NT = 2 / 3 / 4: 29.4 / 25.4 / 33.2, KS = 8 and NT = 3: 30.2; 27648 x 5120: KS = 4 48 / 43 / 41.)
 hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t ldx, __half* const* Y, const int64_t* ldy, hipStream_t s) {
     const Layer& L = Ls[0];
-    const int panels = ceil_div(M, 48), mt = ceil_div(M, (int64_t)panels * 16), MT = L.bits == 4 && mt < 2 ? 2 : mt;
+    const int panels = ceil_div(M, 48), MT = ceil_div(M, (int64_t)panels * 16);
     const int tiles_m = ceil_div(M, 16 * MT);
     auto tiles_at = [&](int nt) {
         int64_t t = 0;
@@ -525,10 +582,17 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
         KS = 4;
         NT = tiles_at(3) * tiles_m <= 512 ? 3 : 4;
     }
-    // (up to 4 rows, 3-bit codes, many tiles: the panel is little and narrow tiles start sooner; 12288 x 4096 at M = 2: 9.8 us against 11.4,
+    const bool w4 = L.bits == 4;
+    const int pairs = (L.ng + 1) / 2;   // (a wave's least share is two groups)
+    // (48 rows and four tiles of 4-bit codes leave LDS for seven waves, which take 16 pairs of groups in three turns: 12288 x 4096 at M = 40
+    // 20.8 us so, 19.9 in twos; longer rows stay, 8192 x 28672 at M = 96: 87 against 113)
+    if (w4 && MT == 3 && NT == 4 && KS == 8 && pairs <= 16 && tiles_at(2) * tiles_m <= 512) NT = 2, KS = 4;
+    // (up to 4 rows, many tiles: the panel is little and narrow tiles start sooner; 3-bit codes, 12288 x 4096 at M = 2: 9.8 us against 11.4,
     // 15360 x 5120: 14.1 against 15.0, 27648 x 5120: 24.6 against 26.8)
-    if (M <= 4 && NT >= 3) NT = 1, KS = 4;
-    KS = L.ng > 0 && KS > L.ng ? L.ng : KS;
+    if (!w4 && M <= 4 && NT >= 3) NT = 1, KS = 4;
+    const int fit = 160 * 1024 / (KS == 4 ? 2 : 1) / (mid_piece(MT, NT, w4) + NT * 128);
+    KS = KS > fit ? fit : KS;
+    KS = pairs > 0 && KS > pairs ? pairs : KS;
     MidArgs A = {};
     int tiles = 0;
     for (int i = 0; i < MAX_GROUP; ++i) {
@@ -556,12 +620,12 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
     using Launch = hipError_t (*)(const MidArgs&, int, hipStream_t);
 #define QEFT_MID(MT, F, XR) {launch_mid<MT, 1, F, XR>, launch_mid<MT, 2, F, XR>, launch_mid<MT, 3, F, XR>, launch_mid<MT, 4, F, XR>}
 #define QEFT_MID3(F) {QEFT_MID(1, F, 1), QEFT_MID(1, F, 2), QEFT_MID(1, F, 4), QEFT_MID(2, F, 8), QEFT_MID(3, F, 12)}
-    static const Launch w4[2][4] = {QEFT_MID(2, W4, 8), QEFT_MID(3, W4, 12)};
-    static const Launch w3[2][5][4] = {QEFT_MID3(W3_TEN), QEFT_MID3(W3_DENSE)};
+    static const Launch f4b[5][4] = QEFT_MID3(W4);
+    static const Launch f3b[2][5][4] = {QEFT_MID3(W3_TEN), QEFT_MID3(W3_DENSE)};
 #undef QEFT_MID3
 #undef QEFT_MID
-    if (L.bits == 4) return w4[MT - 2][NT - 1](A, KS, s);
-    return w3[L.dense ? 1 : 0][MT > 1 ? MT + 1 : (M <= 4 ? 0 : (M <= 8 ? 1 : 2))][NT - 1](A, KS, s);
+    const int xi = MT > 1 ? MT + 1 : (M <= 4 ? 0 : (M <= 8 ? 1 : 2));
+    return (w4 ? f4b[xi] : f3b[L.dense ? 1 : 0][xi])[NT - 1](A, KS, s);
 }
 
 }  // namespace qeft

@@ -22,8 +22,8 @@
 // the K steps into contiguous ranges and are reduced through LDS in a fixed order (no
 // atomics: run-to-run deterministic).  Weight loads run several steps ahead in loops without
 // branches (rows are padded to whole steps and rows past OC are clamped, never stored).
-//   * small-M kernel (M <= 4 and X fits in LDS; today M = 2, M = 3 and 4 on rows of several passes, and the dense
-//     3-bit layout at 2 <= M <= 4): the workgroup stages X once (permuted, with
+//   * small-M kernel (M <= 4 and X fits in LDS; today M = 2, M = 3 and 4 on rows of several passes, where the kernel of gemm_mid.hip
+//     does not take them, and the dense 3-bit layout at 2 <= M <= 4): the workgroup stages X once (permuted, with
 //     Sx), one barrier; a launch-latency-shaped prologue (see the kernel).  It also takes a
 //     group of layers that share X (query / key / value, gate / up) as one launch: its tiles
 //     are those of layer 0, then layer 1, ..., each wave picking its layer's pointers;
@@ -34,7 +34,8 @@
 //     products, activations in registers;
 //   * row-batch kernel (any M <= 16): nothing staged, A fragments straight from X, Sx from the
 //     matrix core (fallback for shapes the register kernel does not take);
-//   * 3-bit layers at 2 <= M <= 16: the kernel of gemm_mid.hip, except dense ones of many tiles at M <= 4 (small-M kernel);
+//   * 3-bit layers at 2 <= M <= 16: the kernel of gemm_mid.hip, except dense ones of many tiles at M <= 4 (small-M kernel); 4-bit
+//     layers too where fwd_mid_few_preferred says so (long rows, small layers);
 //   * chunked kernel: each wave stages its own slice, CH steps at a time (fallback only).
 //
 // Every branch around an MFMA is wave-uniform by construction (the wave index goes through
@@ -1046,11 +1047,13 @@ hipError_t gemv_fwd_group(const Layer* Ls, int n, const __half* X, int64_t M64, 
         hipError_t e = gemv_dot_fwd(Ls, n, nullptr, X, Y, s, handled);
         if (e != hipSuccess || *handled) return e;
     }
-    if (L.bits == 3 && !(L.dense && small_w3_preferred(Ls, n, (int)M64))) {
+    int all_tiles = 0;
+    for (int i = 0; i < n; ++i) all_tiles += ceil_div(Ls[i].oc, 16);
+    if (L.bits == 3 ? !(L.dense && small_w3_preferred(Ls, n, (int)M64)) : fwd_mid_few_preferred(L, M64, ldx, all_tiles)) {
         bool all = true;
         for (int i = 0; i < n; ++i) all = all && fwd_mid_supported(Ls[i], M64, ldx);
         *handled = all;
-        return all ? fwd_mid(Ls, n, X, M64, ldx, Y, ldy, s) : hipSuccess;
+        if (all || L.bits == 3) return all ? fwd_mid(Ls, n, X, M64, ldx, Y, ldy, s) : hipSuccess;
     }
     if (M64 > 2) {    // 5 .. 16 rows: the register kernel (the small-M kernel below stages at most 4 rows); 3 and 4: where it is faster
         hipError_t e = hipSuccess;
@@ -1090,6 +1093,7 @@ hipError_t gemv_fwd_perm(const Layer& L, const int* perm, const __half* X, int64
 
 hipError_t gemv_fwd(const Layer& L, const __half* X, int64_t M64, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s) {
     const int M = (int)M64;
+    if (fwd_mid_few_preferred(L, M, ldx, ceil_div(L.oc, 16))) return fwd_mid(&L, 1, X, M, ldx, &Y, &ldy, s);
     if (M > 2) {      // 5 .. 16 rows: activations in registers, any row length; 3 and 4 rows: short rows only
         hipError_t e = hipSuccess;
         if (launch_regs(&L, 1, X, M, ldx, &Y, &ldy, s, &e)) return e;

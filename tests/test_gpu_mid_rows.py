@@ -170,3 +170,42 @@ def test_mid_rows_with_a_split_workspace(m):
     torch.cuda.synchronize()
     assert torch.equal(y, plain)
     assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), f"M={m}")
+
+
+@pytest.mark.parametrize("oc,groups,tail", [
+    (200, 3, 0),        # one tile per workgroup, fewer pairs of groups than waves
+    (1032, 34, 64),     # long rows, an odd number of groups, the last ragged
+    (5128, 33, 0),      # tiles of 32 channels; the last pair is half one
+    (8200, 34, 0),      # ... of 48
+    (12296, 33, 8),     # ... of 64; at 33 rows and more seven waves
+])
+def test_few_rows_of_four_bits(oc, groups, tail):
+    """2 to 16 rows where they take this kernel: one, two and four requests of rows, every tile width, guard rows around Y."""
+    k = 72
+    layer = HostLayer(oc, groups * 128 + tail + k, k, 4, 128, seed=oc)
+    w, w64 = layer.to_device(), torch.from_numpy(layer.w64).cuda()
+    for m in (2, 3, 4, 5, 8, 9, 16, 40):
+        xd = pad_cols(synth.make_activations(m, layer.ic, k, seed=m))[0]
+        back = torch.full((m + 2, oc + 8), 7.0, dtype=torch.float16, device="cuda")
+        y = back[1:m + 1, :oc]
+        B.qeft_linear_fwd(layer.desc, w, xd, y, ws=False)
+        first = y.clone()
+        B.qeft_linear_fwd(layer.desc, w, xd, y, ws=False)
+        ref = xd.double() @ w64.t()
+        torch.cuda.synchronize()
+        assert torch.equal(first, y), f"M={m}: repeats differ"
+        assert bool((back[0] == 7).all()) and bool((back[m + 1] == 7).all()) and bool((back[:, oc:] == 7).all()), f"M={m}: wrote outside"
+        assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"M={m}")
+
+
+@pytest.mark.parametrize("m", [2, 7, 16])
+def test_few_rows_group(m):
+    """Long rows of three layers in one launch, with and without a layer whose channels end inside an eight (other kernels)."""
+    for ocs in ((264, 520, 72), (264, 515, 72)):
+        layers = [HostLayer(oc, 33 * 128 + 40, 40, 4, 128, seed=oc) for oc in ocs]
+        x = synth.make_activations(m, layers[0].ic, 40, seed=m)
+        xd = pad_cols(x)[0]
+        ys = B.qeft_linear_fwd_group([l.desc for l in layers], [l.to_device() for l in layers], xd)
+        torch.cuda.synchronize()
+        for l, y in zip(layers, ys):
+            assert_close(y.cpu().numpy(), qo.linear_fwd(l.w64, x), f"{l.oc} channels")
