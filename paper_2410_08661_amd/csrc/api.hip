@@ -293,7 +293,7 @@ int qeft_linear_fwd_group(int n, const qeft_desc_t* descs, const qeft_weight_t* 
     if (M == 0) return QEFT_OK;
     hipStream_t s = (hipStream_t)stream;
     const auto mid = [&](const Layer& L) {
-        return M > 16 && fwd_mid_supported(L, M, ldx) && (L.bits == 3 || (gemm_fwd_supported(L, M) && fwd_mid_preferred(L, M, false)));
+        return M > 16 && fwd_mid_supported(L, M, ldx) && (L.bits == 3 || (gemm_fwd_supported(L, M) && fwd_mid_group_preferred(L, M)));
     };
     if (n > 1 && mid(Ls[0])) {
         bool all = true;   // (the other layers differ in OC only)

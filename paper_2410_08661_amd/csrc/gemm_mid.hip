@@ -1,4 +1,4 @@
-// Forward of 4-bit layers for 2 to 192 rows (up to 16: long rows and small layers) and of 3-bit layers from 2 rows on: several sequences
+// Forward of 4-bit layers for 2 to 672 rows (up to 16: long rows and small layers; from 97: few tiles) and of 3-bit layers from 2 rows on: several sequences
 // decoded together, short prompts, draft tokens.  (Paper Sec. 3.2.1; the rows between the matrix-vector kernels' 16 and the sizes at which 256 x 256 tiles occupy the GPU.)
 //
 // A layer's codes are read once per panel of up to 48 rows, where passes of the 16-row kernel read them once per 16 rows
@@ -523,17 +523,30 @@ bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx) {
     return M > 1 && (L.oc % 8) == 0 && (M > 16 || L.kq >= 8);
 }
 
-// Up to 96 rows (two panels) always; up to 192 (four) where the alternative leaves most of the GPU idle: without a workspace
-// for a K split, where the GEMM's tiles would occupy at most a quarter of the CUs; with one, for layers of few channels whose
-// codes over all panels are few - the split's fixed cost (partial tiles, second launch) is then more than half of its time.
-// us, here against the GEMM with its split (and without): 4096 x 4096 at M = 97 / 128 / 192: 16.7 / 15.8 / 16.9 against 19.4 /
-// 19.7 / 23.3 (77); 5120 x 5120 at 97 / 144 / 145: 19.5 / 20.3 / 26.0 against 22.2 / 24.5 / 24.6; 1024 x 8192 at 128: 15.2
-// against 21.1; 2048 x 2048: 9.3 against 15.6; but 8192 x 2048 at 128: 16.5 against 15.9; 4096 x 11008: 39 against 28; 12288 x
-// 4096: 41 against 39 (82); 22016 x 4096: 62 against 57 (82); 13824 x 5120: 51 against 49 (100).
+// Up to 96 rows (two panels) always.  Above, by what this kernel's time goes with - tiles of 16 channels x panels for each CU - against the
+// tiled kernels', whose few tiles each walk the whole contraction and whose time hardly depends on the rows: up to 5 per CU (672 rows
+// were looked at), up to 6 for 192 rows of at most 6144 channels.  With a workspace for a K split the other side is quicker on long rows:
+// up to 5120 columns as before, up to 8192 for few channels, and small layers of up to 192 rows, where the split's fixed cost
+// (partial tiles, second launch) is more than half of its time.
+// us, here against the tiled kernels (in brackets: with the split): 2048 x 2048 at M = 240 / 480 / 640: 10.0 / 13.9 / 18.5 against 14.7 / 15.0 /
+// 15.2; 512 x 512 at 240 / 640: 4.8 / 5.7 against 10.0 / 10.1; 1024 x 8192 at 240 / 640: 17.2 / 28.8 against 40 / 41 (27 / 29); 2048 x 8192 at 336 /
+// 480: 26.3 / 37.1 against 41 / 42 (29.7 / 33.8); 4096 x 4096 at 97 / 192 / 240 / 288: 17 / 18.5 / 21.6 / 28 against 23 / 24 / 23.8 / 24 (19 / 23 /
+// 27.5 / 27.5); 5120 x 5120 at 192 / 240: 25 / 33 against 28 / 28 (26 / 30); 4096 x 11008 at 97 / 192 / 240 / 288: 34 / 38 / 49 / 62 against 62 / 61 / 61 / 61
+// (27 / 34 / 40 / 44); 5120 x 13824 at 192: 60 against 77 (44); 6144 x 6144 at 192 / 240: 32 / 41 against 36 / 36.5; but 8192 x 2048 at 97 / 192:
+// 18 / 20 against 15 / 16, 11008 x 4096: 40 / 43 against 27 / 39, 13824 x 5120: 50 / 65 against 34 / 49.
 bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws) {
-    if (M <= 96 || M > 192) return M <= 96;
-    if (!split_ws) return ceil_div(L.oc, 256) <= 64;
-    return L.oc <= 5120 && (int64_t)ceil_div(M, 48) * L.oc * L.ic <= (int64_t)3 * 5120 * 5120;
+    if (M <= 96 || M > 672) return M <= 96;
+    const int64_t panels = ceil_div(M, 48), tiles = panels * ceil_div(L.oc, 16);
+    if (!split_ws) return tiles <= 5 * 256 || (M <= 192 && L.oc <= 6144 && tiles <= 6 * 256);
+    if (L.oc > 5120) return false;
+    if (M <= 192 && panels * L.oc * L.ic <= (int64_t)3 * 5120 * 5120) return true;
+    return tiles <= 5 * 256 && (L.ic <= 5120 || (L.ic <= 8192 && L.oc <= 2048 && 2 * tiles <= 7 * 256));
+}
+
+// Layers that share their input, without a workspace: wide ones gain from the one launch where a third panel holds all rows and
+// the tiled kernels begin a second tile of 128 (two of 11008 x 4096, M = 128 / 144 / 192: 62 / 64 / 76 us against 55 / 74 / 77).
+bool fwd_mid_group_preferred(const Layer& L, int64_t M) {
+    return fwd_mid_preferred(L, M, false) || (M > 128 && M <= 144 && L.oc <= 13824);
 }
 
 // 3-bit layers with room for a copy: up to 96 rows, and while the codes over all panels are few - the copy's pass alone is 4 to 10 us

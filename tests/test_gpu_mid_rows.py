@@ -1,4 +1,4 @@
-"""The forward between the decode sizes and the large GEMM (17 to 192 rows), at the edges of its tiles: rows around the
+"""The forward between the decode sizes and the large GEMM (17 rows to a few hundred), at the edges of its tiles: rows around the
 panels of 32 and 48, channels that end inside a tile of 16 ... 64, rows of fewer groups than waves, a ragged last group,
 weak blocks of none, one and more than eight 32-column steps, a layer without quantized columns, and the group call.
 Tolerance: parity_util's bar (2e-3 in norm and per element); this kernel does not round the weights, so only the fp16 of the
@@ -209,3 +209,24 @@ def test_few_rows_group(m):
         torch.cuda.synchronize()
         for l, y in zip(layers, ys):
             assert_close(y.cpu().numpy(), qo.linear_fwd(l.w64, x), f"{l.oc} channels")
+
+
+@pytest.mark.parametrize("m", [193, 241, 433, 672])
+@pytest.mark.parametrize("oc,ic,k", [(520, 512, 8), (1032, 2056, 136), (2048, 1352, 72)])
+def test_hundreds_of_rows_of_small_layers(oc, ic, k, m):
+    """Up to 14 panels of 48 rows: the same bits with a split's workspace as without, and every row at its place."""
+    layer = HostLayer(oc, ic, k, 4, 128, seed=m)
+    w, w64 = layer.to_device(), torch.from_numpy(layer.w64).cuda()
+    xd = pad_cols(synth.make_activations(m, ic, k, seed=m))[0]
+    room = B.qeft_workspace_bytes(layer.desc, B.QEFT_OP_FWD, m)
+    back = torch.full((m + 2, oc + 8), 7.0, dtype=torch.float16, device="cuda")
+    y = back[1:m + 1, :oc]
+    B.qeft_linear_fwd(layer.desc, w, xd, y, ws=torch.empty(room, dtype=torch.uint8, device="cuda") if room else False)
+    plain = B.qeft_linear_fwd(layer.desc, w, xd, ws=False)
+    ref = xd.double() @ w64.t()
+    torch.cuda.synchronize()
+    panels = -(-m // 48)
+    if panels * -(-oc // 16) <= 5 * 256:
+        assert torch.equal(y, plain)
+    assert bool((back[0] == 7).all()) and bool((back[m + 1] == 7).all()) and bool((back[:, oc:] == 7).all())
+    assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"M={m}")
