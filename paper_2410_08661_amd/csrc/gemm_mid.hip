@@ -553,13 +553,17 @@ bool fwd_mid_group_preferred(const Layer& L, int64_t M) {
 // and the kernels behind it take as long as for a 4-bit layer.  us, through a copy against here (ten codes a word): 14848 x 4456 at
 // M = 48 / 96: 42 / 52 against 25 / 37; 5120 x 5120 at M = 40 / 96 / 192 / 240 / 333: 24 / 27 / 34 / 37 / 45 against 14 / 17 / 28 /
 // 34 / 53; 4096 x 4096 at 333 / 500: 32 / 39 against 30 / 44; 2048 x 2048 at 500 / 700 / 1000: 21 / 22 / 22 against 16 / 19 / 29; wide layers
-// sooner: 11008 x 4096 at 97: 40 against 43, 12288 x 640 at 240 / 500: 23 / 29 against 18 / 36.  Layers under 2^20 weights have the fp16
+// sooner: 12288 x 640 at 240 / 500: 23 / 29 against 18 / 36.  Layers under 2^20 weights have the fp16
 // copy alone: 512 x 512 at 48 / 1000: 17 / 21 against 5 / 7, 1000 x 1000: 49 / 53 against 6 / 12.
+// Up to 192 rows wide and long layers too: 11008 x 4096 at M = 97 / 192: 44 / 48 against 35 / 40 (dense 39 / 41 against 35 / 39), 4096 x 11008: 43 / 49
+// against 34 / 38, 8192 x 2048: 24 / 24.5 against 17 / 18, 8192 x 8192: 53 / 61 against 46 / 52 (dense 45 / 52 against 46 / 50: left), 13824 x 5120:
+// 57 / 66 against 46 / 60.
 bool fwd_mid3_preferred(const Layer& L, int64_t M, int64_t ldx) {
     if (!fwd_mid_supported(L, M, ldx)) return false;
     if (M <= 96) return true;
     const int64_t panels = ceil_div(M, 48), weights = (int64_t)L.oc * L.ic;
     if (weights < ((int64_t)1 << 20)) return panels <= 30;
+    if (M <= 192 && panels * weights <= (L.dense ? 7 : 11) * (int64_t)(5120 * 5120)) return true;
     return panels <= 15 && panels * weights <= (L.oc <= 5120 ? 5 : 1) * (int64_t)(5120 * 5120);
 }
 

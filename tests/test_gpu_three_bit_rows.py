@@ -75,3 +75,21 @@ def test_fractional_zero_points_are_rounded_once(oc, ic, k, dense):
             for size, bound in ((2 * oc * ic, TWO_ROUNDINGS), (B.qeft_workspace_bytes(h.desc, op, m), THREE_ROUNDINGS)):
                 err = _error(call(torch.empty(size, dtype=torch.uint8, device="cuda")), ref)
                 assert err <= bound, f"{what}, M={m}, workspace {size}: {err:.3e}"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dense", [False, True])
+def test_wide_layer_up_to_192_rows(dense):
+    """97 to 192 rows of a wide layer: its stored codes, so the same bits with the copy's workspace as without."""
+    k = 72
+    layer = HostLayer(8200, 11 * 128 + k, k, 3, 128, seed=5, dense=dense)   # whole groups: dense rows that end inside one go through a copy
+    w, w64 = layer.to_device(), torch.from_numpy(layer.w64).cuda()
+    for m in (97, 144, 192):
+        xd = pad_cols(synth.make_activations(m, layer.ic, k, seed=m))[0]
+        room = B.qeft_workspace_bytes(layer.desc, B.QEFT_OP_FWD, m)
+        y = B.qeft_linear_fwd(layer.desc, w, xd, ws=torch.empty(room, dtype=torch.uint8, device="cuda"))
+        plain = B.qeft_linear_fwd(layer.desc, w, xd, ws=False)
+        ref = xd.double() @ w64.t()
+        torch.cuda.synchronize()
+        assert torch.equal(y, plain), f"M={m}"
+        assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"M={m}")
