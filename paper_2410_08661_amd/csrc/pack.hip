@@ -188,8 +188,9 @@ __global__ __launch_bounds__(256) void rtn_fused_w4g128_kernel(Layer L, const __
 // derives (scale, zero-point) with the rules above, quantizes and scores the squared weight error;
 // the first candidate with the smallest error is kept (candidate 0 = plain min-max).  One group per
 // 16 lanes (a lane holds 8 consecutive columns; lanes past the group width hold zeros, which cost
-// nothing), four groups per wavefront.  The error is summed in a fixed order: a lane's 8 columns
-// left to right, one rounding each, then a tree over the 16 lanes.
+// nothing), four groups per wavefront.  The error is summed in a fixed order - a lane's 8 columns
+// left to right, one rounding each, then a balanced tree over the 16 lanes - so that the decisions
+// can be reproduced exactly elsewhere.
 //
 // The kernel is bound by vector instructions (4096 x 4096, 80 candidates: 1.3 G scores).  What keeps them few:
 //  * Scale, zero-point and reciprocal of 16 candidates are derived at once, one per lane of the group's 16, and handed
@@ -211,15 +212,15 @@ __global__ __launch_bounds__(256) void rtn_fused_w4g128_kernel(Layer L, const __
 // 4096 x 4096, 80 candidates, whole call (us): 919 with two divisions per weight and candidate and every candidate scored, 123 with the
 // bound by two columns, single candidates and the copy in a launch of its own, 115 now; 3 bits, ten codes a word 217 -> 191, dense (the
 // words in this pass too) 221 -> 176.  (Vector instructions fell by 15 %, the kernel's own time by 4: what is left runs one per 3.9 cycles.)
-// sum over the 16 lanes of a row whose neighbours (lane ^ 1) are added already, separately for even and odd lanes
+// sum over the 16 lanes of a row whose neighbours (lane ^ 1) are added already, separately for even and odd lanes.  Each step is an
+// exchange between two halves, so that both add the same two numbers and all lanes of a class end with the same bits: they decide
+// by them one by one, and a rotation by four would leave every other quad with another order (two candidates in one group's codes).
 __device__ __forceinline__ float dpp16_sum_rest(float v) {
-    auto mv = [](float x, auto ctrl) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, false));
-    };
+    auto mv = [](float x, auto ctrl) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true)); };
     v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x4E>{}));    // lane ^ 2
-    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x124>{}));   // four lanes on (rotation)
-    v = __fadd_rn(v, mv(v, std::integral_constant<int, 0x128>{}));   // eight lanes on
-    return v;
+    const int b = __builtin_bit_cast(int, v), on = __builtin_amdgcn_mov_dpp(b, 0x104, 0xf, 0x5, true);   // lane ^ 4: quads 0 and 2 read four lanes on,
+    v = __fadd_rn(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(on, b, 0x114, 0xf, 0xA, false)));   // quads 1 and 3 four lanes back
+    return __fadd_rn(v, mv(v, std::integral_constant<int, 0x128>{}));   // lane ^ 8
 }
 
 // WORDS: 4: 4-bit codes in groups of 128, 3: dense 3-bit codes in groups of 128, whose words the same lanes then store (0:
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
     auto miss = [](float x, float s, float rs, float nz, float uz) {
         return __builtin_fmaf(-__builtin_amdgcn_fmed3f(rintf(x * rs), nz, uz), s, x);
     };
-    auto xor1 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false)); };
+    auto xor1 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, true)); };
     const bool odd = (t & 1) != 0;
     // the best of the even candidates in the even lanes, of the odd ones in the odd lanes
     float best_e = __builtin_inff();

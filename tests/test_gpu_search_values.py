@@ -78,3 +78,55 @@ def test_dense_three_bit_words(oc, kq, k, n_grid, step):
     assert np.all(err <= e_all.min(axis=0) * (1 + 1e-5) + 1e-30)
     if k:
         assert np.array_equal(out.weak.cpu().numpy(), w[:, kq:])
+
+
+def _choice(w, bits, g, n_grid, step):
+    """Scale and zero-point of the candidate with the least score, the first of equals, all in fp32: a
+    lane's 8 columns left to right, square and sum in one rounding, then neighbouring lanes, pairs, quads and halves of the 16."""
+    f32 = np.float32
+    s_all, z_all, _ = qo.search_candidates(w, 0, bits, g, n_grid, step)
+    oc, ng = s_all.shape[1:]
+    v = np.zeros((oc, ng, 16, 8), dtype=f32)
+    v.reshape(oc, ng, 128)[:, :, :g] = w.astype(f32).reshape(oc, ng, g)
+    qmax = f32(2 ** bits - 1)
+    scores = []
+    for s16, z in zip(s_all, z_all):
+        s, z = s16.astype(f32)[..., None, None], z.astype(f32)[..., None, None]
+        d = v - s * np.clip(np.rint(v * (f32(1) / s)), -z, qmax - z)     # (s times a code is exact: one rounding)
+        sq = d.astype(np.float64) ** 2
+        a = sq[..., 0].astype(f32)
+        for e in range(1, 8):
+            a = (sq[..., e] + a).astype(f32)
+        while a.shape[-1] > 1:
+            a = a[..., 0::2] + a[..., 1::2]
+        scores.append(a[..., 0])
+    best = np.argmin(np.stack(scores), axis=0)[None]
+    return np.take_along_axis(s_all, best, axis=0)[0], np.take_along_axis(z_all, best, axis=0)[0]
+
+
+def _mirrored(oc, ng, g):
+    """Every value with its negative, at random places: with a small step several candidates share a scale under zero-points whose
+    errors are one another's mirror images, equal but for the order in which they are summed."""
+    r = np.random.default_rng(5)
+    h = (r.standard_normal((oc, ng, g // 2)) * 0.02).astype(np.float16)
+    return r.permuted(np.concatenate([h, -h], axis=2), axis=2).reshape(oc, ng * g)
+
+
+@pytest.mark.parametrize("kind", ["mirrored"])
+@pytest.mark.parametrize("bits,g,dense", [(4, 128, False), (3, 128, True), (3, 128, False), (4, 64, False)])
+def test_search_choice(kind, bits, g, dense):
+    """One candidate per group, the one that scores least over the whole grid, and codes, scale and zero-point all of it."""
+    oc, ng = 256, 8
+    n_grid, step = 33, 2.0 ** -12
+    w = _mirrored(oc, ng, g)
+    d = B.make_desc(oc, ng * g, 0, bits, g, B.QEFT_LAYOUT_DENSE3 if dense else B.QEFT_LAYOUT_CANONICAL)
+    out = B.Weight(d)
+    B.qeft_pack_search(d, torch.from_numpy(w).cuda(), n_grid, step, out)
+    torch.cuda.synchronize()
+    lay = qo.layout(oc, ng * g, 0, bits, g, dense=dense)
+    s, z = out.scales[:, :ng].cpu().numpy(), out.zeros[:, :ng].cpu().numpy()
+    codes = qo.codes_for_params(w, 0, bits, g, s, z)
+    packed = qo.pack_codes_dense3(codes, lay["row_stride_words"]) if dense else qo.pack_codes(codes, bits, lay["row_stride_words"])
+    assert np.array_equal(packed, out.qweight.cpu().numpy().view(np.uint32))
+    s_ref, z_ref = _choice(w, bits, g, n_grid, step)
+    assert np.array_equal(s, s_ref) and np.array_equal(z.astype(np.float32), z_ref)
