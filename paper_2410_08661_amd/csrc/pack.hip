@@ -306,9 +306,10 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
     int best_i = -1;
     for (int i0 = 0; i0 < n_grid; i0 += 16) {
         if (i0 > 0) {
-            // A candidate's codes end within s / 2 of p hi0 and p lo0 (0.52 s covers the roundings of s, z and p), so a value x beyond misses
-            // by x - p hi0 - s / 2 at least, and by more under every narrower candidate: done once that is too much for all groups
-            const float p = 1.f - (float)i0 * step, half = 0.52f * (p * (hi0 - lo0) / qmax);
+            // A candidate's codes end within s / 2 of p hi0 and p lo0, and s rounded up moves the upper end by qmax times as much: by 2^-11 of s
+            // (0.52 s covers that and the roundings of z and p), among subnormal scales by up to 2^-24.  So a value x beyond misses by
+            // x - p hi0 - half at least, and by more under every narrower candidate: done once that is too much for all groups
+            const float p = 1.f - (float)i0 * step, half = 0.52f * (p * (hi0 - lo0) / qmax) + (qmax + 1.f) * 0x1p-24f;
             auto beyond = [&](float x) {
                 const float e = fmaxf(fmaxf(x - p * hi0, p * lo0 - x) - half, 0.f);
                 return e * e;

@@ -112,13 +112,21 @@ def _mirrored(oc, ng, g):
     return r.permuted(np.concatenate([h, -h], axis=2), axis=2).reshape(oc, ng * g)
 
 
-@pytest.mark.parametrize("kind", ["mirrored"])
+def _skewed(oc, ng, g, amp):
+    """One-sided groups of a few units of the least subnormal, four alike in a row: the scales of narrow ranges are rounded by as
+    much as they are large."""
+    r = np.random.default_rng(7)
+    u = np.rint(r.exponential(amp, (oc, ng // 4, 1, g)) * np.where(r.random((oc, ng // 4, 1, g)) < 0.1, -1, 1))
+    return np.repeat((u * 2.0 ** -24).astype(np.float16), 4, axis=2).reshape(oc, ng * g)
+
+
+@pytest.mark.parametrize("kind", ["mirrored", "skewed 1.5", "skewed 4"])
 @pytest.mark.parametrize("bits,g,dense", [(4, 128, False), (3, 128, True), (3, 128, False), (4, 64, False)])
 def test_search_choice(kind, bits, g, dense):
     """One candidate per group, the one that scores least over the whole grid, and codes, scale and zero-point all of it."""
     oc, ng = 256, 8
-    n_grid, step = 33, 2.0 ** -12
-    w = _mirrored(oc, ng, g)
+    n_grid, step = (33, 2.0 ** -12) if kind == "mirrored" else (80, 0.01)
+    w = _mirrored(oc, ng, g) if kind == "mirrored" else _skewed(oc, ng, g, float(kind.split()[1]))
     d = B.make_desc(oc, ng * g, 0, bits, g, B.QEFT_LAYOUT_DENSE3 if dense else B.QEFT_LAYOUT_CANONICAL)
     out = B.Weight(d)
     B.qeft_pack_search(d, torch.from_numpy(w).cuda(), n_grid, step, out)
