@@ -315,7 +315,8 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
                 return e * e;
             };
             const float least = (beyond(lo0) + beyond(hi0)) + (beyond(lo1) + beyond(hi1));
-            if (__ballot(!(least * (1.f - 0x1p-7f) > fminf(best_e, xor1(best_e)))) == 0) break;
+            // (equal is too much as well, the earlier candidate stays: groups of zeros, the padding of a row among them)
+            if (__ballot(!(least * (1.f - 0x1p-7f) >= fminf(best_e, xor1(best_e)))) == 0) break;
         }
         const Params mine = params(i0 + t);   // candidate i0 + t
         const float s_l = mine.s, z_l = mine.z, rs_l = __fdiv_rn(1.f, s_l);
