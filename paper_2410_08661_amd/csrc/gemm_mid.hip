@@ -24,7 +24,7 @@
 // 3-bit codes are multiplied as they are stored (Codes3), fetched by the lanes that use them (us, ten codes a word): 5120 x 5120,
 // M = 2 / 16 / 40: 8.0 / 9.2 / 13.4; 15360 x 5120 (q/k/v) M = 8 / 40: 14.9 / 22.9; 27648 x 5120 (gate/up) M = 8: 25.2; 1024 x 2048, M = 8: 4.3.
 // Tried and no faster: X requests that bypass the caches (nt: 10 to 30 % slower), other orders of the groups per workgroup, 80 and 96
-// channels per workgroup (48 rows spill).
+// channels per workgroup (48 rows spill; 64 channels have 249 of 256 registers, see LEAN).
 // Tried and not kept: 64 rows per panel (registers spill, 2 to 5 times slower).
 #include <type_traits>
 
@@ -132,6 +132,9 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     constexpr int WB = mid_piece(MT, NT, F == W4);       // (at the end a partial tile),
     constexpr int PB = NT * 128;                         // and (zero-point, scale) of two groups of up to 64 channels
     static_assert(MT == 1 || XR == 4 * MT, "");
+    // the widest tile has no registers for an offset per request: taken from the first row's each time (kept, they went to scratch memory
+    // and came back behind waits for the rows just requested)
+    constexpr bool LEAN = MT * NT == 12;
     const int lane = threadIdx.x & 63;
     const int KS = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -185,9 +188,11 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
         uint32_t col[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) col[c] = (uint32_t)(2 * min(128 * g + 8 * (xc ^ (4 * c + xr)), A.kq - 8));
+        uint32_t first = xoff0;
+        if constexpr (LEAN) asm volatile("" : "+v"(first));
 #pragma unroll
         for (int u = 0; u < XR; ++u) {
-            const uint32_t off = min(xoff0 + (uint32_t)(4 * u) * xpitch, xlast) + col[u & 3];
+            const uint32_t off = min(first + (uint32_t)(4 * u) * xpitch, xlast) + col[u & 3];
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (__attribute__((address_space(3))) void*)(mine + 1024 * u), 16, (int)off, 0, 0, 0);
         }
     };
@@ -195,13 +200,16 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     // fetching its own fragment shares no bytes with its neighbours, and each of its 16 bytes is an access to the L1's tags)
     const auto wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(wbase), 0, (int)0xffffffff, 0x00020000);
     unsigned char* codes = mine + XB;
+    const uint32_t cpitch = (uint32_t)(A.stride * 4), coff0 = (uint32_t)(lane >> 3) * cpitch, clast = (uint32_t)min(oc - 1 - o0, 16 * NT) * cpitch;
     auto load_codes = [&](int p) {
         uint32_t col[2];
 #pragma unroll
         for (int c = 0; c < 2; ++c) col[c] = (uint32_t)min(128 * p + 16 * ((lane & 7) ^ (4 * c + (lane >> 4))), 4 * A.stride - 16);
+        uint32_t first = coff0;
+        if constexpr (LEAN) asm volatile("" : "+v"(first));
 #pragma unroll
         for (int u = 0; u < 2 * NT; ++u) {
-            const uint32_t off = (uint32_t)min(8 * u + (lane >> 3), oc - 1 - o0) * (uint32_t)(A.stride * 4) + col[u & 1];
+            const uint32_t off = min(first + (uint32_t)(8 * u) * cpitch, clast) + col[u & 1];
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wbuf, (__attribute__((address_space(3))) void*)(codes + 1024 * u), 16, (int)off, 0, 0, 0);
         }
     };
@@ -601,14 +609,15 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
     }
     const bool w4 = L.bits == 4;
     const int pairs = (L.ng + 1) / 2;   // (a wave's least share is two groups)
-    // (48 rows and four tiles of 4-bit codes leave LDS for seven waves, which take 16 pairs of groups in three turns: 12288 x 4096 at M = 40
-    // 20.8 us so, 19.9 in twos; longer rows stay, 8192 x 28672 at M = 96: 87 against 113)
-    if (w4 && MT == 3 && NT == 4 && KS == 8 && pairs <= 16 && tiles_at(2) * tiles_m <= 512) NT = 2, KS = 4;
     // (up to 4 rows, many tiles: the panel is little and narrow tiles start sooner; 3-bit codes, 12288 x 4096 at M = 2: 9.8 us against 11.4,
     // 15360 x 5120: 14.1 against 15.0, 27648 x 5120: 24.6 against 26.8)
     if (!w4 && M <= 4 && NT >= 3) NT = 1, KS = 4;
     const int fit = 160 * 1024 / (KS == 4 ? 2 : 1) / (mid_piece(MT, NT, w4) + NT * 128);
     KS = KS > fit ? fit : KS;
+    // (48 rows and four tiles of 4-bit codes leave LDS for seven waves, two to three on a SIMD; four, one on each, are as quick or quicker.  us, seven against four:
+    // 12288 x 4096 at M = 40 19.1 / 17.6, 4096 x 4096 at M = 97 / 192 15.7 / 15.5 and 16.5 / 15.7, 8192 x 2048 at M = 96 12.4 / 11.2, 16384 x 16384 at
+    // M = 48 61 / 58, 4096 x 11008 at M = 97 31.4 / 32.6, 8192 x 28672 at M = 96 85.5 / 85.1)
+    if (KS == 7) KS = 4;
     KS = pairs > 0 && KS > pairs ? pairs : KS;
     MidArgs A = {};
     int tiles = 0;
