@@ -576,16 +576,23 @@ bool fwd_mid3_preferred(const Layer& L, int64_t M, int64_t ldx) {
 }
 
 // 4-bit layers at 2 to 16 rows, `tiles` tiles of 16 channels in the launch: here where a row's contraction does not fit the registers of
-// one workgroup of the 16-row kernel in one pass (more than 32 groups of 128), except very wide launches, and one tile per CU of shorter
+// one workgroup of the 16-row kernel in one pass (more than 32 groups of 128), except wide launches of long rows, and one tile per CU of shorter
 // rows.  us, the 16-row kernel (M = 2: the small-M kernel) against here: 5120 x 5120 at M = 2 / 4 / 8 / 16: 9.3 / 10.3 / 10.9 / 11.5 against 7.5 /
 // 7.4 / 7.7 / 8.5; 5120 x 13824: 17.7 / 23.9 / 20.8 / 23.7 against 17.2 / 17.0 / 18.7 / 21.8; 4096 x 11008 at 4 / 8 / 16: 11.6 / 12.9 / 15.4 against
 // 10.6 / 11.6 / 13.2; 27648 x 5120 (gate/up) at 2 / 4 / 8: 22.7 / 26.6 / 28.7 against 24.6 / 25.6 / 25.4; 1024 x 8192 at 8: 9.4 against 7.3; 57344 x 8192
 // at 4 / 8 / 16: 67 / 77 / 75 against 79 / 76 / 80; at 2, 8192 x 8192: 12.0 against 12.7, 8192 x 28672: 42 against 34; 4096 x 4096 at 2 / 4 / 16: 5.6 / 6.3 / 7.0 against 5.8 / 5.9 / 6.8; but 12288 x 4096 at 8: 10.1
 // against 12.6, 22016 x 4096: 14.5 against 16.6.
+// Wide launches, 640 to 2048 tiles x 33 to 111 groups looked at (time there over time here): up to 768 tiles 1.0 to 1.5 at every M; 40 groups 0.96 to 1.2;
+// M = 3 / 4, 47 to 79 groups 0.81 to 1.07 / 0.85 to 1.02, but M = 4 at 1152 to 1536 tiles 0.97 to 1.32; 95 and 111 groups M = 4 1.0 to 1.4, M = 3 0.83 to 1.1 up to
+// 1024 tiles, 0.95 to 1.15 above, 127 groups 1.15; M = 6 to 16, 55 groups and more, 0.95 to 1.05 up to 1024 tiles, above 0.87 to 1.06 (28672 x 8192 at M = 4 / 16: 34 / 38.5 us against 39 / 42.5).
 bool fwd_mid_few_preferred(const Layer& L, int64_t M, int64_t ldx, int tiles) {
     if (L.bits != 4 || M < 2 || M > 16 || !fwd_mid_supported(L, M, ldx)) return false;
-    if (L.ng > 32) return M > 2 ? tiles <= 2048 : tiles <= 320 || (tiles <= 512 && L.ng > 128);
-    return M > 2 && tiles <= 256;
+    if (L.ng <= 32) return M > 2 && tiles <= 256;
+    if (M == 2) return tiles <= 320 || (tiles <= 512 && L.ng > 128);
+    if (tiles > 2048) return false;
+    if (M > 4) return tiles <= 1024 || L.ng <= 48;
+    if (tiles <= 768 || L.ng <= 44) return true;
+    return M == 4 ? L.ng > 90 || (tiles > 1024 && tiles <= 1536) : L.ng > (tiles > 1024 ? 90 : 120);
 }
 
 // Tiles of 16 NT channels and KS waves.  A CU holds one workgroup of eight waves or two of four (registers and LDS), and a workgroup
