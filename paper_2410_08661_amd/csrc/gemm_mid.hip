@@ -616,6 +616,14 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
     }
     const bool w4 = L.bits == 4;
     const int pairs = (L.ng + 1) / 2;   // (a wave's least share is two groups)
+    // (Few pairs leave waves without one, or LDS three waves of four: two waves instead, of which a CU holds four workgroups - three of the widest tile - and the
+    // narrowest tile with which all are resident.  us, before / in twos: 12288 x 640, four groups, at M = 48 / 96 8.4 / 7.5 and 9.6 / 8.8; 16384 x 384 at 17 8.7 / 6.5;
+    // 2 x 5504 x 2048 at 97 25.2 / 18.4, 3 x 2048 x 2048 at 192 18.5 / 15.5, 16384 x 1024 at 96 13.8 / 11.7; 32768 x 2048 at 96, not resident, 35.7 / 39.1)
+    if (w4 && pairs > 0 && (pairs <= 2 || (pairs <= 8 && MT == 3 && NT == 4 && KS == 4))) {
+        int nt = 1;
+        while (nt < 4 && tiles_at(nt) * tiles_m > 1024) ++nt;
+        if (pairs <= 2 || nt < 4 || tiles_at(4) * tiles_m <= 768) NT = nt, KS = 2;
+    }
     // (up to 4 rows, many tiles: the panel is little and narrow tiles start sooner; 3-bit codes, 12288 x 4096 at M = 2: 9.8 us against 11.4,
     // 15360 x 5120: 14.1 against 15.0, 27648 x 5120: 24.6 against 26.8)
     if (!w4 && M <= 4 && NT >= 3) NT = 1, KS = 4;

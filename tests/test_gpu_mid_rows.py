@@ -47,7 +47,9 @@ def test_mid_rows(oc, ic, k):
     (4104, 25 * 128 + 64),      # ... of 48
     (6152, 25 * 128 + 64),      # ... of 64
     (8200, 10 * 128 + 64),      # four waves: three groups each or two; tiles of 48
-    (12296, 10 * 128 + 64),     # ... of 64
+    (12296, 10 * 128 + 64),     # ... of 64; at 96 rows of 32, two waves
+    (12296, 17 * 128 + 64),     # ... of 64; at 96 rows three waves, as many as LDS holds twice
+    (16392, 5 * 128 + 64),      # ... of 64; at 96 rows two waves and tiles of 48
 ])
 def test_mid_rows_many_groups_per_wave(oc, kq):
     """What one turn of a wave's loop fetches for the next: two and three 16-row tiles, every tile width."""
