@@ -533,7 +533,7 @@ bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx) {
 
 // Up to 96 rows (two panels) always.  Above, by what this kernel's time goes with - tiles of 16 channels x panels for each CU - against the
 // tiled kernels', whose few tiles each walk the whole contraction and whose time hardly depends on the rows: up to 5 per CU (672 rows
-// were looked at), up to 6 for 192 rows of at most 6144 channels.  With a workspace for a K split the other side is quicker on long rows:
+// were looked at), for up to 192 rows up to 6 and for rows that are short for the tiled kernels' stages more.  With a workspace for a K split the other side is quicker on long rows:
 // up to 5120 columns as before, up to 8192 for few channels, and small layers of up to 192 rows, where the split's fixed cost
 // (partial tiles, second launch) is more than half of its time.
 // us, here against the tiled kernels (in brackets: with the split): 2048 x 2048 at M = 240 / 480 / 640: 10.0 / 13.9 / 18.5 against 14.7 / 15.0 /
@@ -542,10 +542,18 @@ bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx) {
 // 27.5 / 27.5); 5120 x 5120 at 192 / 240: 25 / 33 against 28 / 28 (26 / 30); 4096 x 11008 at 97 / 192 / 240 / 288: 34 / 38 / 49 / 62 against 62 / 61 / 61 / 61
 // (27 / 34 / 40 / 44); 5120 x 13824 at 192: 60 against 77 (44); 6144 x 6144 at 192 / 240: 32 / 41 against 36 / 36.5; but 8192 x 2048 at 97 / 192:
 // 18 / 20 against 15 / 16, 11008 x 4096: 40 / 43 against 27 / 39, 13824 x 5120: 50 / 65 against 34 / 49.
+// Without a workspace at M = 97 / 144 / 192: 7680 x 8192 36 / 39 / 51 against 48 / 47 / 47, 7680 x 4096 20 / 21 / 28 against 24 / 24 / 25, 7680 x 2048 13.5 / 13.7 / 17.1 against 15.1 /
+// 15.3 / 15.3; but 8192 x 8192 49 / 50 / 52 against 48 / 47 / 48.  Short rows: 12288 x 640 10.2 / 10.8 / 12.2 against 11.2 / 15.8 / 17.2, 12288 x 1536 15.7 / 16.2 / 18.1 against
+// 15.7 / 21.4 / 21.6, 8192 x 1536 13.0 / 13.3 / 14.6 against 15.6 / 15.7 / 15.7; but 12288 x 1024 12.9 / 13.0 / 14.3 against 11.0 / 14.7 / 14.7, 12288 x 2048 18.5 / 19.0 / 21.5 against
+// 15.5 / 20.7 / 21.0.
 bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws) {
     if (M <= 96 || M > 672) return M <= 96;
     const int64_t panels = ceil_div(M, 48), tiles = panels * ceil_div(L.oc, 16);
-    if (!split_ws) return tiles <= 5 * 256 || (M <= 192 && L.oc <= 6144 && tiles <= 6 * 256);
+    if (!split_ws) {
+        if (tiles <= 5 * 256 || M > 192) return tiles <= 5 * 256;
+        return (L.oc <= 6144 && tiles <= 6 * 256) || (M <= 144 && L.oc <= 7680) || (L.ng <= 5 && tiles <= 12 * 256) ||
+               (L.ng > 8 && L.ng <= 12 && L.oc <= 12288 && (M <= 144 || L.oc <= 9216 || 3 * ceil_div(L.oc, 128) > 256));   // (above 144 rows: 10240 x 1536 17.3 against 16.0, one round of 128 x 64 tiles)
+    }
     if (L.oc > 5120) return false;
     if (M <= 192 && panels * L.oc * L.ic <= (int64_t)3 * 5120 * 5120) return true;
     return tiles <= 5 * 256 && (L.ic <= 5120 || (L.ic <= 8192 && L.oc <= 2048 && 2 * tiles <= 7 * 256));

@@ -89,6 +89,27 @@ def test_workspace_never_costs_more_than_ten_percent(oc, ic, m):
         _judge(lambda: (_us(lambda: call(ws)), _us(lambda: call(False))), f"{name} {oc}x{ic} M={m} with the workspace against without")
 
 
+def _group_call(ocs, ic, m):
+    layers = [_layer(oc, ic, 128, oc + i) for i, oc in enumerate(ocs)]
+    x = torch.randn((m, ic), generator=layers[0][2], device="cuda").half()
+    ys = [torch.empty((m, oc), dtype=torch.float16, device="cuda") for oc in ocs]
+    group = B.Group([d for d, _, _ in layers], [w for _, w, _ in layers], ys)
+    return lambda: B.qeft_linear_fwd_group(None, None, x, group=group)
+
+
+def _single_call(oc, ic, m):
+    d, w, gen = _layer(oc, ic, 128, oc)
+    x = torch.randn((m, ic), generator=gen, device="cuda").half()
+    y = torch.empty((m, oc), dtype=torch.float16, device="cuda")
+    return lambda: B.qeft_linear_fwd(d, w, x, y, ws=False)
+
+
+@pytest.mark.parametrize("oc,ic,m", [(7680, 8192, 97), (7680, 8192, 128), (12288, 640, 144)])
+def test_layer_no_slower_than_its_halves_in_one_call(oc, ic, m):
+    single, halves = _single_call(oc, ic, m), _group_call((oc // 2, oc // 2), ic, m)
+    _judge(lambda: (_us(single), _us(halves)), f"forward {oc}x{ic} M={m} without workspace against a group of its halves")
+
+
 @pytest.mark.parametrize("oc,ic,k,m", [(8192, 8192, 64, 2048), (4096, 4096, 64, 1003), (11008, 4096, 8, 512), (13824, 5120, 16, 1003)])
 def test_three_bit_rows_no_slower_than_an_fp16_copy(oc, ic, k, m):
     """3-bit layers whose last group is partial: the call with its workspace against the dense product that the boundary offers
