@@ -292,12 +292,11 @@ int qeft_linear_fwd_group(int n, const qeft_desc_t* descs, const qeft_weight_t* 
     if (st != QEFT_OK) return st;
     if (M == 0) return QEFT_OK;
     hipStream_t s = (hipStream_t)stream;
-    const auto mid = [&](const Layer& L) {
-        return M > 16 && fwd_mid_supported(L, M, ldx) && (L.bits == 3 || (gemm_fwd_supported(L, M) && fwd_mid_group_preferred(L, M)));
-    };
+    const auto mid = [&](const Layer& L) { return M > 16 && fwd_mid_supported(L, M, ldx) && (L.bits == 3 || gemm_fwd_supported(L, M)); };
     if (n > 1 && mid(Ls[0])) {
         bool all = true;   // (the other layers differ in OC only)
         for (int i = 1; i < n; ++i) all = all && mid(Ls[i]);
+        all = all && (Ls[0].bits == 3 || fwd_mid_group_preferred(Ls, n, M));
         if (all) {
             __half* ys[QEFT_MAX_GROUP];
             for (int i = 0; i < n; ++i) ys[i] = (__half*)Y[i];

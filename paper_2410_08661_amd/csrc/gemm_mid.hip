@@ -559,10 +559,23 @@ bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws) {
     return tiles <= 5 * 256 && (L.ic <= 5120 || (L.ic <= 8192 && L.oc <= 2048 && 2 * tiles <= 7 * 256));
 }
 
-// Layers that share their input, without a workspace: wide ones gain from the one launch where a third panel holds all rows and
-// the tiled kernels begin a second tile of 128 (two of 11008 x 4096, M = 128 / 144 / 192: 62 / 64 / 76 us against 55 / 74 / 77).
-bool fwd_mid_group_preferred(const Layer& L, int64_t M) {
-    return fwd_mid_preferred(L, M, false) || (M > 128 && M <= 144 && L.oc <= 13824);
+// Layers that share their input, without a workspace; alone: each of them takes this kernel by itself.  Otherwise the one launch still gains where no layer is wide
+// (each alone would leave the tiled kernels few workgroups), above 144 rows on long rows and while the launch stays short, and where a third panel holds all rows
+// and the tiled kernels begin a second tile of 128.  us, one launch against the layers one by one, M = 97 / 144 / 192: 8192 + 2 x 1024 x 8192 50 / 52 / 74 against 78 / 78 / 80;
+// 2 x 8192 x 8192 76 / 78 / 99 against 96 / 94 / 96; 2 x 7168 x 7168 64 / 67 / 83.5 against 86 / 84 / 84; 2 x 8192 x 2048 26 / 24 / 34 against 32 / 32 / 33; 8192 + 1024 x 2048
+// 18 / 18 / 26 against 22 / 22 / 22; 2 x 11008 x 4096 60 / 63 / 75 against 54 / 75 / 76; 2 x 13824 x 5120 86 / 91 / - against 66 / 94 / -; 12288 + 1024 x 4096 40 / 41.5 / 51 against 37 / 47 / 47;
+// 9216 + 1024 x 4096 28 / 30 / 42 against 36 / 39 / 37.
+bool fwd_mid_group_preferred(const Layer* Ls, int n, int64_t M) {
+    bool alone = true;
+    int64_t widest = 0, sum = 0;
+    for (int i = 0; i < n; ++i) {
+        alone = alone && fwd_mid_preferred(Ls[i], M, false);
+        widest = Ls[i].oc > widest ? Ls[i].oc : widest;
+        sum += Ls[i].oc;
+    }
+    if (alone || M > 192) return alone;
+    if (M > 144) return widest <= 8192 && sum <= 14336 && Ls[0].ng > 32;
+    return widest <= (M > 128 ? 13824 : 8192) || sum <= 10240;
 }
 
 // 3-bit layers with room for a copy: up to 96 rows, and while the codes over all panels are few - the copy's pass alone is 4 to 10 us

@@ -106,7 +106,7 @@ hipError_t gemv_dot_fwd(const Layer* Ls, int n, const int* perm, const __half* X
 // ---- forward between the decode sizes and the large GEMM (gemm_mid.hip); Ls[0 .. n) share the input ----
 bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx);
 bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws);   // split_ws: the caller's workspace holds the partial tiles of the GEMM's K split
-bool fwd_mid_group_preferred(const Layer& L, int64_t M);
+bool fwd_mid_group_preferred(const Layer* Ls, int n, int64_t M);   // one launch for all of them, without a workspace
 bool fwd_mid_few_preferred(const Layer& L, int64_t M, int64_t ldx, int tiles);
 bool fwd_mid3_preferred(const Layer& L, int64_t M, int64_t ldx);     // a 3-bit layer's codes as they are, rather than a copy in the caller's workspace
 hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t ldx, __half* const* Y, const int64_t* ldy, hipStream_t s);

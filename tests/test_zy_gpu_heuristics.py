@@ -110,6 +110,13 @@ def test_layer_no_slower_than_its_halves_in_one_call(oc, ic, m):
     _judge(lambda: (_us(single), _us(halves)), f"forward {oc}x{ic} M={m} without workspace against a group of its halves")
 
 
+@pytest.mark.parametrize("ocs,ic", [((8192, 1024, 1024), 8192), ((7168, 7168), 7168)])
+def test_group_of_fewer_rows_no_slower(ocs, ic):
+    """Three panels of 48 rows hold 97 rows and 144."""
+    few, more = _group_call(ocs, ic, 97), _group_call(ocs, ic, 144)
+    _judge(lambda: (_us(few), _us(more)), f"group {ocs} x {ic} M=97 against M=144")
+
+
 @pytest.mark.parametrize("oc,ic,k,m", [(8192, 8192, 64, 2048), (4096, 4096, 64, 1003), (11008, 4096, 8, 512), (13824, 5120, 16, 1003)])
 def test_three_bit_rows_no_slower_than_an_fp16_copy(oc, ic, k, m):
     """3-bit layers whose last group is partial: the call with its workspace against the dense product that the boundary offers
