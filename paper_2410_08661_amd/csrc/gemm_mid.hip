@@ -629,6 +629,18 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
         for (int i = 0; i < n; ++i) t += ceil_div(Ls[i].oc, 16 * nt);
         return t;
     };
+    // A grid is counted in threads modulo 2^32, and a larger one ends early without an error: more rows than fit with the narrowest tiles
+    // and most waves go in several launches (3-bit layers without a workspace, results of 26 GB and more)
+    const int64_t most = 48 * (((int64_t)0xffffffff / 512 - 8) / tiles_at(1));
+    if (M > most) {
+        for (int64_t m0 = 0; m0 < M; m0 += most) {
+            __half* ys[MAX_GROUP];
+            for (int i = 0; i < n; ++i) ys[i] = Y[i] + m0 * ldy[i];
+            const hipError_t e = fwd_mid(Ls, n, X + m0 * ldx, M - m0 < most ? M - m0 : most, ldx, ys, ldy, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     int NT = 1, KS = 8;
     while (NT < 4 && tiles_at(NT) * tiles_m > 256) ++NT;
     if (tiles_at(NT) * tiles_m > 256) {

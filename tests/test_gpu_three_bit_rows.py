@@ -93,3 +93,20 @@ def test_wide_layer_up_to_192_rows(dense):
         torch.cuda.synchronize()
         assert torch.equal(y, plain), f"M={m}"
         assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"M={m}")
+
+
+def test_more_workgroups_than_one_grid_counts():
+    """Without a workspace any number of rows multiplies the stored codes: a product of rows and channels whose workgroups, counted in
+    threads, pass 2^32 (103 GB of results) is still one call."""
+    oc, ic, k, m = 51200, 7 * 128 + 8, 8, 1010000
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("needs 120 GB of device memory")
+    h = HostLayer(oc, ic, k, 3, 128, seed=11)
+    w = h.to_device()
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((m, ic), generator=gen, device="cuda", dtype=torch.float16)
+    y = torch.empty((m, oc), dtype=torch.float16, device="cuda")
+    looked = [0, 47, 48, 123456, 500000, m // 2 + 1, m - 49, m - 1]
+    y[looked] = float("nan")
+    B.qeft_linear_fwd(h.desc, w, x, y, ws=False)
+    assert_close(y[looked].cpu().numpy(), qo.linear_fwd(h.w64, x[looked].cpu().numpy()), "rows of a large batch")
