@@ -667,11 +667,12 @@ def test_backward_dx_row_split_with_workspace(oc, ic, k, m):
 
 
 @pytest.mark.parametrize("dense", [False, True])
-def test_three_bit_gemm_splits_the_copy(dense):
-    """3-bit layers at GEMM sizes: behind the fp16 copy the workspace may hold the partial tiles of a split of the copy
-    (few tiles here; forward: 18 stages of columns -> 3 splits, input gradient: 16 stages of rows -> 2 splits); with room
-    for the copy only, one workgroup per tile."""
-    oc, ic, k, m = 1024, 1024 + 128, 128, 300
+@pytest.mark.parametrize("m", [300, 760])
+def test_three_bit_gemm_splits_the_copy(m, dense):
+    """3-bit layers at GEMM sizes: behind the copy the workspace may hold the partial tiles of a split of the copy
+    (few tiles here; forward, which multiplies the stored codes at 300 rows: 18 stages of columns -> 3 splits, input gradient: 16
+    stages of rows -> 2 splits); with room for the copy only, one workgroup per tile."""
+    oc, ic, k = 1024, 1024 + 128, 128
     h = HostLayer(oc, ic, k, 3, 128, seed=5, dense=dense)
     w = h.to_device()
     copy = oc * ic * 2
@@ -695,10 +696,11 @@ def test_three_bit_gemm_splits_the_copy(dense):
 
 
 @pytest.mark.parametrize("dense", [False, True])
-@pytest.mark.parametrize("oc,ic,k,m", [(320, 1280 + 128, 128, 300), (264, 512 + 64, 64, 40)])
+@pytest.mark.parametrize("oc,ic,k,m", [(320, 1280 + 128, 128, 300), (264, 512 + 64, 64, 40), (320, 1280 + 128, 128, 1500)])
 def test_three_bit_gemm_sizes_through_the_fp16_copy(oc, ic, k, m, dense):
-    """3-bit layers at M > 16: dequantized once into the workspace, then the tensor-core kernels; the same
-    results (to the bar) without a workspace, from the general kernel."""
+    """3-bit layers of fewer than 2^20 weights at M > 16: dequantized once into the workspace, then the tensor-core kernels (input
+    gradient; forward from 1441 rows on, below that the stored codes); the same results (to the bar) without a workspace, from the
+    stored codes and the general kernel."""
     h = HostLayer(oc, ic, k, 3, 128, seed=oc + ic, dense=dense)
     w = h.to_device()
     nbytes = oc * ic * 2                                   # the copy; behind it, partial tiles when the GEMM on the copy is split
