@@ -629,8 +629,8 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
         for (int i = 0; i < n; ++i) t += ceil_div(Ls[i].oc, 16 * nt);
         return t;
     };
-    // A grid is counted in threads modulo 2^32, and a larger one ends early without an error: more rows than fit with the narrowest tiles
-    // and most waves go in several launches (3-bit layers without a workspace, results of 26 GB and more)
+    // A grid is counted in threads, in 32 bits, and a larger one runs in part only, without an error: more rows than fit with the narrowest
+    // tiles and most waves go in several launches (3-bit layers without a workspace, results of 13 GB and more)
     const int64_t most = 48 * (((int64_t)0xffffffff / 512 - 8) / tiles_at(1));
     if (M > most) {
         for (int64_t m0 = 0; m0 < M; m0 += most) {
@@ -648,14 +648,17 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
         NT = tiles_at(3) * tiles_m <= 512 ? 3 : 4;
     }
     const bool w4 = L.bits == 4;
-    const int pairs = (L.ng + 1) / 2;   // (a wave's least share is two groups)
-    // (Few pairs leave waves without one, or LDS three waves of four: two waves instead, of which a CU holds four workgroups - three of the widest tile - and the
-    // narrowest tile with which all are resident.  us, before / in twos: 12288 x 640, four groups, at M = 48 / 96 8.4 / 7.5 and 9.6 / 8.8; 16384 x 384 at 17 8.7 / 6.5;
-    // 2 x 5504 x 2048 at 97 25.2 / 18.4, 3 x 2048 x 2048 at 192 18.5 / 15.5, 16384 x 1024 at 96 13.8 / 11.7; 32768 x 2048 at 96, not resident, 35.7 / 39.1)
-    if (w4 && pairs > 0 && (pairs <= 2 || (pairs <= 8 && MT == 3 && NT == 4 && KS == 4))) {
+    const int pairs = (L.ng + 1) / 2, weak = ceil_div(L.k, 32);   // (a wave's least share is two groups, or 32 weak columns)
+    // Few pairs leave waves without one, or LDS three waves of four: two waves instead, of which a CU holds four workgroups - three of the widest tile - and the
+    // narrowest tile with which all are resident; where none is, one wave, of which 32 channels leave room for eight.  Not for launches that are resident
+    // at eight waves, nor where the weak block is most of the work and is better divided by four.  us, before / in twos: 12288 x 640, four groups, at M = 48 / 96 8.4 / 7.5 and
+    // 9.6 / 8.8; 16384 x 384 at 17 8.7 / 6.5; 2 x 5504 x 2048 at 97 25.2 / 18.4, 3 x 2048 x 2048 at 192 18.5 / 15.5, 16384 x 1024 at 96 13.8 / 11.7; 32768 x 2048 at 96, not
+    // resident, 35.7 / 39.1.  256 weak columns, in twos / fours: 8192 x 768 at 96 9.0 / 7.7, 4096 x 768 at 192 8.7 / 7.4.  Two waves / one: 28672 x 640 at 96 17.9 / 13.9.
+    if (w4 && pairs > 0 && ((pairs <= 2 && weak <= 4 && tiles_at(1) * tiles_m > 256) || (pairs <= 8 && MT == 3 && NT == 4 && KS == 4))) {
         int nt = 1;
         while (nt < 4 && tiles_at(nt) * tiles_m > 1024) ++nt;
-        if (pairs <= 2 || nt < 4 || tiles_at(4) * tiles_m <= 768) NT = nt, KS = 2;
+        if (nt < 4 || tiles_at(4) * tiles_m <= 768) NT = nt, KS = 2;
+        else if (pairs <= 2 && tiles_at(2) * tiles_m <= 2048) NT = 2, KS = 1;
     }
     // (up to 4 rows, many tiles: the panel is little and narrow tiles start sooner; 3-bit codes, 12288 x 4096 at M = 2: 9.8 us against 11.4,
     // 15360 x 5120: 14.1 against 15.0, 27648 x 5120: 24.6 against 26.8)
@@ -666,7 +669,18 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
     // 12288 x 4096 at M = 40 19.1 / 17.6, 4096 x 4096 at M = 97 / 192 15.7 / 15.5 and 16.5 / 15.7, 8192 x 2048 at M = 96 12.4 / 11.2, 16384 x 16384 at
     // M = 48 61 / 58, 4096 x 11008 at M = 97 31.4 / 32.6, 8192 x 28672 at M = 96 85.5 / 85.1)
     if (KS == 7) KS = 4;
-    KS = pairs > 0 && KS > pairs ? pairs : KS;
+    // Waves without a pair take weak columns where these are twice as many steps as pairs (eight steps beside six pairs: 3 to 7 % slower), while all workgroups
+    // stay resident (eight waves a CU, and LDS).  us, as many waves as pairs / so: 512 x 448, 256 weak
+    // columns, at M = 48 5.7 / 4.5, 8192 x 384 at 119 8.1 / 6.8; 3-bit 512 x 384, 128 of them, at 17 4.3 / 3.8; but not resident, 128 weak columns, 28672 x 384 at 96 12.9 / 16.6, 3-bit 12288 x 512 at 119 10.2 / 14.2.
+    const auto resident = [&](int waves) {
+        const int64_t per_cu = (tiles_at(NT) * tiles_m + 255) / 256;
+        return per_cu * waves <= 8 && per_cu * waves * (mid_piece(MT, NT, w4) + NT * 128) <= 160 * 1024;
+    };
+    if (pairs > 0 && KS > pairs) {
+        const int shares = weak >= 2 * pairs ? weak : pairs;
+        KS = KS < shares ? KS : shares;
+        while (KS > pairs && !resident(KS)) --KS;
+    }
     MidArgs A = {};
     int tiles = 0;
     for (int i = 0; i < MAX_GROUP; ++i) {

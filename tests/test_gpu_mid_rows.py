@@ -21,6 +21,8 @@ LAYERS = [
     (264, 1160, 0),             # nothing weak; 9 x 128 + 8 columns
     (96, 320, 320),             # nothing quantized
     (16648, 384, 64),           # more tiles than CUs; three waves of one group each
+    (520, 128 + 256, 256),      # one group: seven waves of eight have weak columns alone
+    (8200, 256 + 264, 264),     # wider tiles, four waves for one pair and nine weak steps
 ]
 
 
@@ -64,6 +66,31 @@ def test_mid_rows_many_groups_per_wave(oc, kq):
         torch.cuda.synchronize()
         assert torch.equal(y, again), f"M={m}: repeats differ"
         assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"M={m}")
+
+
+@pytest.mark.parametrize("bits,dense", [(3, False), (3, True)])
+@pytest.mark.parametrize("oc,kq,k", [(520, 128, 256), (264, 200, 264), (8200, 256, 128), (1000, 64, 96)])
+def test_few_groups_and_a_wide_weak_block_of_three_bit_layers(oc, kq, k, bits, dense):
+    layer = HostLayer(oc, kq + k, k, bits, 128, seed=oc, dense=dense)
+    w = layer.to_device()
+    for m in (2, 7, 17, 48, 97):
+        x = synth.make_activations(m, layer.ic, k, seed=m)
+        y = B.qeft_linear_fwd(layer.desc, w, pad_cols(x)[0], ws=False)
+        torch.cuda.synchronize()
+        assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), f"M={m}")
+
+
+@pytest.mark.parametrize("oc,kq,k", [(28680, 200, 128), (32768, 512, 64)])
+def test_short_rows_of_more_workgroups_than_fit_in_twos(oc, kq, k):
+    """One wave per workgroup of 32 channels."""
+    layer = HostLayer(oc, kq + k, k, 4, 128, seed=oc)
+    w, w64 = layer.to_device(), torch.from_numpy(layer.w64).cuda()
+    x = synth.make_activations(96, layer.ic, k, seed=3)
+    xd = pad_cols(x)[0]
+    y = B.qeft_linear_fwd(layer.desc, w, xd, ws=False)
+    ref = xd.double() @ w64.t()
+    torch.cuda.synchronize()
+    assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"{oc} channels")
 
 
 @pytest.mark.parametrize("m", [20, 40, 96])

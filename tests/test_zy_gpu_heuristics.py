@@ -110,6 +110,30 @@ def test_layer_no_slower_than_its_halves_in_one_call(oc, ic, m):
     _judge(lambda: (_us(single), _us(halves)), f"forward {oc}x{ic} M={m} without workspace against a group of its halves")
 
 
+@pytest.mark.parametrize("oc", [512, 4096])
+def test_short_row_no_slower_than_a_longer_one(oc):
+    """A wide weak block is divided among a workgroup's waves however few groups stand before it: with two groups no slower than with
+    six.  (Calls of 5 us: replayed from a graph.)"""
+    def replayed(ic):
+        d, w, gen = _layer(oc, ic, 256, oc + ic)
+        x = torch.randn((48, ic), generator=gen, device="cuda").half()
+        y = torch.empty((48, oc), dtype=torch.float16, device="cuda")
+        graph = torch.cuda.CUDAGraph()
+        B.qeft_linear_fwd(d, w, x, y, ws=False)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            for _ in range(50):
+                B.qeft_linear_fwd(d, w, x, y, ws=False)
+        return lambda: graph.replay(), (graph, w, x, y)
+    short, _keep = replayed(512)
+    long, _keep2 = replayed(1024)
+    for attempt in range(2):
+        t_short, t_long = _us(short, n=5) / 50, _us(long, n=5) / 50
+        if t_short <= 1.02 * t_long:
+            return
+    pytest.fail(f"forward of {oc} channels, M=48, 256 weak columns: two groups {t_short:.2f} us, six {t_long:.2f} us")
+
+
 @pytest.mark.parametrize("ocs,ic", [((8192, 1024, 1024), 8192), ((7168, 7168), 7168)])
 def test_group_of_fewer_rows_no_slower(ocs, ic):
     """Three panels of 48 rows hold 97 rows and 144."""
