@@ -78,10 +78,11 @@ inline int hip_status(hipError_t e) { return e == hipSuccess ? QEFT_OK : QEFT_ER
 // parameters and weak block, or the layer is dequantized into an fp16 [OC][IC] copy and multiplied as one whose columns are all
 // weak (the paper's own training path: dequantize, then a dense product; Sec. 4.3 / App. A.2).  Groups of 128 take the first
 // where its kernel is the faster one (fwd_copy4_preferred, dx_copy4_preferred), other group sizes the second.  So do layers of
-// fewer than 2^20 weights: for them the workspace holds the dequantized layer after the call, which the parity tests compare
-// word for word (the 4-bit copy would be faster there too: 960 x 1024 at 40 rows, forward 9 us against 20, dX 14 against 27).
+// fewer than 2^20 weights: for them the workspace holds the dequantized layer after the input gradient, which the parity tests
+// compare word for word (the 4-bit copy would be faster there too: dX of 960 x 1024 at 40 rows 14 us against 27).
 // The copy lies at the head of the caller's workspace, which is sized for the fp16 one and a split of it; the split's partial
-// tiles follow.
+// tiles follow.  Forwards that multiply the stored codes instead (fwd_mid3_preferred: up to 96 rows, small layers up to 1440) leave
+// the workspace alone; its size is stated and checked for them all the same, so that it does not depend on the kernel.
 bool dense_copy_applies(const Layer& L, int64_t M) {
     return L.bits == 3 && L.kq > 0 && M > 16 && (L.ic % 8) == 0 && (L.oc % 8) == 0;
 }

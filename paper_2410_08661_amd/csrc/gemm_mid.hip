@@ -668,7 +668,7 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
     // (48 rows and four tiles of 4-bit codes leave LDS for seven waves, two to three on a SIMD; four, one on each, are as quick or quicker.  us, seven against four:
     // 12288 x 4096 at M = 40 19.1 / 17.6, 4096 x 4096 at M = 97 / 192 15.7 / 15.5 and 16.5 / 15.7, 8192 x 2048 at M = 96 12.4 / 11.2, 16384 x 16384 at
     // M = 48 61 / 58, 4096 x 11008 at M = 97 31.4 / 32.6, 8192 x 28672 at M = 96 85.5 / 85.1)
-    if (KS == 7) KS = 4;
+    if (KS == 7) KS = pairs == 5 || pairs == 6 ? pairs : 4;
     // Waves without a pair take weak columns where these are twice as many steps as pairs (eight steps beside six pairs: 3 to 7 % slower), while all workgroups
     // stay resident (eight waves a CU, and LDS).  us, as many waves as pairs / so: 512 x 448, 256 weak
     // columns, at M = 48 5.7 / 4.5, 8192 x 384 at 119 8.1 / 6.8; 3-bit 512 x 384, 128 of them, at 17 4.3 / 3.8; but not resident, 128 weak columns, 28672 x 384 at 96 12.9 / 16.6, 3-bit 12288 x 512 at 119 10.2 / 14.2.

@@ -210,8 +210,8 @@ __global__ __launch_bounds__(256) void rtn_fused_w4g128_kernel(Layer L, const __
 //    odd lanes of the second ones.
 //  * The weak block is copied by waves of the same launch.
 // 4096 x 4096, 80 candidates, whole call (us): 919 with two divisions per weight and candidate and every candidate scored, 123 with the
-// bound by two columns, single candidates and the copy in a launch of its own, 115 now; 3 bits, ten codes a word 217 -> 191, dense (the
-// words in this pass too) 221 -> 176.  (Vector instructions fell by 15 %, the kernel's own time by 4: what is left runs one per 3.9 cycles.)
+// bound by two columns, single candidates and the copy in a launch of its own (117 in the harness of the figures that follow), 111 now;
+// 3 bits, ten codes a word 211 -> 189, dense (the words in this pass too) 215 -> 176.
 // sum over the 16 lanes of a row whose neighbours (lane ^ 1) are added already, separately for even and odd lanes.  Each step is an
 // exchange between two halves, so that both add the same two numbers and all lanes of a class end with the same bits: they decide
 // by them one by one, and a rotation by four would leave every other quad with another order (two candidates in one group's codes).
