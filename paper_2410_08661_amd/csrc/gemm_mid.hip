@@ -545,14 +545,16 @@ bool fwd_mid_supported(const Layer& L, int64_t M, int64_t ldx) {
 // Without a workspace at M = 97 / 144 / 192: 7680 x 8192 36 / 39 / 51 against 48 / 47 / 47, 7680 x 4096 20 / 21 / 28 against 24 / 24 / 25, 7680 x 2048 13.5 / 13.7 / 17.1 against 15.1 /
 // 15.3 / 15.3; but 8192 x 8192 49 / 50 / 52 against 48 / 47 / 48.  Short rows: 12288 x 640 10.2 / 10.8 / 12.2 against 11.2 / 15.8 / 17.2, 12288 x 1536 15.7 / 16.2 / 18.1 against
 // 15.7 / 21.4 / 21.6, 8192 x 1536 13.0 / 13.3 / 14.6 against 15.6 / 15.7 / 15.7; but 12288 x 1024 12.9 / 13.0 / 14.3 against 11.0 / 14.7 / 14.7, 12288 x 2048 18.5 / 19.0 / 21.5 against
-// 15.5 / 20.7 / 21.0.
+// 15.5 / 20.7 / 21.0.  Wider short rows, M = 120 / 144 / 192: 16384 x 640 - / - / 14.8 against - / - / 17.3, 14336 x 384 - / - / 11.0 against - / - / 13.3, but 20480 x 256 10.5 / 10.9 / 12.9 against 9.9 / 10.8 /
+// 11.9; nine to twelve groups where 128-row tiles begin a second: 16384 x 1408 18.1 / 18.5 / 26.2 against 16.8 / 25.4 / 23.9, 14336 x 1408 16.5 / 17.1 / 25.9 against 16.0 / 24.9 / 22.7.
 bool fwd_mid_preferred(const Layer& L, int64_t M, bool split_ws) {
     if (M <= 96 || M > 672) return M <= 96;
     const int64_t panels = ceil_div(M, 48), tiles = panels * ceil_div(L.oc, 16);
     if (!split_ws) {
         if (tiles <= 5 * 256 || M > 192) return tiles <= 5 * 256;
-        return (L.oc <= 6144 && tiles <= 6 * 256) || (M <= 144 && L.oc <= 7680) || (L.ng <= 5 && tiles <= 12 * 256) ||
-               (L.ng > 8 && L.ng <= 12 && L.oc <= 12288 && (M <= 144 || L.oc <= 9216 || 3 * ceil_div(L.oc, 128) > 256));   // (above 144 rows: 10240 x 1536 17.3 against 16.0, one round of 128 x 64 tiles)
+        return (L.oc <= 6144 && tiles <= 6 * 256) || (M <= 144 && L.oc <= 7680) || (L.ng <= 5 && L.oc <= 16384) ||
+               (L.ng > 8 && L.ng <= 12 && L.oc <= 12288 && (M <= 144 || L.oc <= 9216 || 3 * ceil_div(L.oc, 128) > 256)) ||   // (above 144 rows: 10240 x 1536 17.3 against 16.0, one round of 128 x 64 tiles)
+               (L.ng > 8 && L.ng <= 12 && L.oc <= 16384 && M > 128 && M <= 144);
     }
     if (L.oc > 5120) return false;
     if (M <= 192 && panels * L.oc * L.ic <= (int64_t)3 * 5120 * 5120) return true;

@@ -104,7 +104,7 @@ def _single_call(oc, ic, m):
     return lambda: B.qeft_linear_fwd(d, w, x, y, ws=False)
 
 
-@pytest.mark.parametrize("oc,ic,m", [(7680, 8192, 97), (7680, 8192, 128), (12288, 640, 144)])
+@pytest.mark.parametrize("oc,ic,m", [(7680, 8192, 97), (7680, 8192, 128), (12288, 640, 144), (16384, 1408, 144)])
 def test_layer_no_slower_than_its_halves_in_one_call(oc, ic, m):
     single, halves = _single_call(oc, ic, m), _group_call((oc // 2, oc // 2), ic, m)
     _judge(lambda: (_us(single), _us(halves)), f"forward {oc}x{ic} M={m} without workspace against a group of its halves")
