@@ -14,7 +14,7 @@
 // group is multiplied), chunks XOR-placed by the row on the way; the wave reads them back as fragments once, the rows into nibble
 // order, and multiplies all its channel tiles.  The codes' way through LDS is for the L1: a lane that fetches its own fragment shares no
 // line with its neighbours, and each of the 64 takes one of the L1's tag cycles, which were 70 % of the CUs' time (counters at
-// M = 40, 22016 x 4096: 34.6k of 50k cycles; matrix pipe 11k, vector issue 19k); 8 rows x 128 bytes per request are 16 cycles.  In pairs,
+// M = 40, 22016 x 4096: 34.6k of 50k cycles; matrix pipe 11k, vector issue 19k; 22.3k of 48k now); 8 rows x 128 bytes per request are 16 cycles.  In pairs,
 // because a half line fetched alone holds a whole one.  Dequantization as in the 16-row kernels, on the accumulator and without
 // rounding the weights: s (sum x (1024 + q) - (1024 + z) Sx), two FMAs per accumulator and group.  Partial tiles meet in LDS in a fixed
 // order (fp32).
