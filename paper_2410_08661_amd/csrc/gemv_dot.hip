@@ -53,6 +53,15 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
     return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, a), __builtin_bit_cast(h2, b), c, false);
 }
 
+// what a pair's code of three bits is added to, in both halves: 1024, 128, 16 for codes at bits 0, 3, 6 of a half (the exponent that gives
+// the lowest of these mantissa bits the weight 1); pairs 3 and 4 of a ten, shifted by 9, lie as 0 and 1
+__device__ __forceinline__ constexpr uint32_t base3(int p) { return p == 0 || p == 3 ? 0x64006400u : (p == 2 ? 0x4c004c00u : 0x58005800u); }
+
+// b in the lanes of m, else a (nested conditional expressions on the lane became branches in the row loop)
+__device__ __forceinline__ float pick(float a, float b, uint64_t m) {
+    return __builtin_amdgcn_inverse_ballot_w64(m) ? b : a;
+}
+
 // sum over the 64 lanes, valid in lane 63
 __device__ __forceinline__ float wave_sum_to_lane63(float t) {
     auto dpp = [](float v, auto ctrl, auto rmask) {
@@ -76,9 +85,12 @@ __device__ __forceinline__ float wave_sum_to_lane63(float t) {
 // LDS: pair-ordered activations [KS * NL][4 pieces][64 lanes] 16 B | (sum base x, sum x) float2 [KS * NL][64] |
 //      weak activations fp16 | K-split exchange float [8 waves][64]
 // W3D: three-bit codes in the dense layout (a row is one bit string, code j at bits 3 j .. 3 j + 2).  A lane's 32 columns
-// are then 96 bits = three whole words (12-byte requests, 768 bytes per range and wave), its pairs (x_2P, x_2P+1) lie at
-// bits 6 P of them - so the activations stay in column order - and both codes of a pair become 1024 + q: one 6-bit field
-// extract (pairs 5 and 10 straddle words: a funnel shift first), one multiplication by 2^13 + 1, one and-or.
+// are then 96 bits = three whole words (12-byte requests, 768 bytes per range and wave), in three tens and two left over.  The upper
+// five codes of a ten move up one bit, to the upper half of a word: pair p = (code p, code p + 5) then has its codes at bits 3 p of either
+// half.  Those of pairs 0, 1 and 2 are inside the mantissa where they lie and become 1024 + q, 128 + q and 16 + q with one and-or, pairs 3
+// and 4 follow after one shift by 9: 29 instructions beside the 16 dot products, where a field extract, a multiplication and an and-or
+// per pair took 50.  (Vector issue did not hide behind the
+// stream: 13B block 52.7 -> 48.0 us, 7B block 34.5 -> 32.3.)
 template <int NL, int DEPTH, int NKW, bool PERM, bool W3D>
 __global__ __launch_bounds__(DOT_THREADS) void gemv_w4_dot_kernel(DotLayers R, int kq, int k, int row_bytes, int gs,
                                                                    const __half* __restrict__ X, const int* __restrict__ perm, int ic,
@@ -217,7 +229,7 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w4_dot_kernel(DotLayers R, i
             if (8 * u >= kq) v = u4{0u, 0u, 0u, 0u};
             u4 p;
             if (W3D) {
-                p = v;   // column order; every code gets the base 1024, so "se" below is the whole sum
+                p = v;   // column order (a lane pairs them up when it takes them); sum x only
             } else {
                 p.x = __builtin_amdgcn_perm(v.z, v.x, 0x05040100u);   // (x0, x4)   base 1024
                 p.y = __builtin_amdgcn_perm(v.z, v.x, 0x07060302u);   // (x1, x5)   base 64
@@ -234,7 +246,7 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w4_dot_kernel(DotLayers R, i
                 // range i = u / 256, lane l = (u % 256) / 4, piece q = u % 4  ->  [i][q][l]
                 const int i = u >> 8, l = (u & 255) >> 2, q = u & 3;
                 *reinterpret_cast<u4*>(lds + 4096 * i + 1024 * q + 16 * l) = p;
-                if (q == 0) ksum[64 * i + l] = float2{1024.f * se + (W3D ? 1024.f : 64.f) * so, se + so};
+                if (q == 0) ksum[64 * i + l] = float2{1024.f * se + 64.f * so, se + so};   // (W3D: the second alone)
             }
         }
     };
@@ -273,6 +285,20 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w4_dot_kernel(DotLayers R, i
         const float2 ks2 = ksum[64 * (li0 + i) + lane];
         kbase[i] = ks2.x;
         ssum[i] = ks2.y;
+        if (W3D) {
+            uint32_t nat[16];
+#pragma unroll
+            for (int P = 0; P < 16; ++P) nat[P] = xr[i][P];
+#pragma unroll
+            for (int P = 0; P < 15; ++P) {
+                const int lo = 10 * (P / 5) + P % 5, hi = lo + 5;
+                xr[i][P] = __builtin_amdgcn_perm(nat[hi >> 1], nat[lo >> 1], ((lo & 1) ? 0x0302u : 0x0100u) | ((hi & 1) ? 0x07060000u : 0x05040000u));
+            }
+            float kb = 0.f;
+#pragma unroll
+            for (int P = 0; P < 16; ++P) kb = dot2(base3(P % 5), xr[i][P], kb);   // (pair 15: base 1024)
+            kbase[i] = kb;
+        }
     }
     float ssel[NP];   // sum x of the group this lane applies the parameters of set j to (0: none)
 #pragma unroll
@@ -299,8 +325,10 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w4_dot_kernel(DotLayers R, i
         }
     }
 
-    uint32_t m_lo = 0x000f000fu, m_hi = 0x00f000f0u, g_lo = 0x64006400u, g_hi = 0x54005400u, m3 = 0x00070007u;
-    asm volatile("" : "+v"(m_lo), "+v"(m_hi), "+v"(g_lo), "+v"(g_hi), "+v"(m3));   // in registers: (w & m) | g is then one v_and_or_b32
+    uint32_t m_lo = 0x000f000fu, m_hi = 0x00f000f0u, g_lo = 0x64006400u, g_hi = 0x54005400u;
+    asm volatile("" : "+v"(m_lo), "+v"(m_hi), "+v"(g_lo), "+v"(g_hi));   // in registers: (w & m) | g is then one v_and_or_b32
+    uint32_t m3[3] = {0x00070007u, 0x00380038u, 0x01c001c0u}, g3[3] = {base3(0), base3(1), base3(2)};   // (W3D)
+    asm volatile("" : "+v"(m3[0]), "+v"(m3[1]), "+v"(m3[2]), "+v"(g3[0]), "+v"(g3[1]), "+v"(g3[2]));
 
     float res = 0.f;   // lane j: the wave's result for its row j
     // sum x q of every group of one row's ranges, each in the four lanes of its quad
@@ -310,19 +338,17 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w4_dot_kernel(DotLayers R, i
             float a0 = 0.f, a1 = 0.f;
             if (W3D) {
                 const uint32_t w0 = wq[d][i].x, w1 = wq[d][i].y, w2 = wq[d][i].z;
+                const uint32_t t3 = w2 >> 26, tens[3] = {w0, __builtin_amdgcn_alignbit(w1, w0, 30), __builtin_amdgcn_alignbit(w2, w1, 28)};
 #pragma unroll
-                for (int P = 0; P < 16; ++P) {
-                    constexpr uint32_t spread = 0x2001u;
-                    uint32_t f;   // the pair's six bits
-                    if (P < 5) f = __builtin_amdgcn_ubfe(w0, 6 * P, 6);
-                    else if (P == 5) f = __builtin_amdgcn_alignbit(w1, w0, 30) & 63u;
-                    else if (P < 10) f = __builtin_amdgcn_ubfe(w1, 6 * P - 32, 6);
-                    else if (P == 10) f = __builtin_amdgcn_alignbit(w2, w1, 28) & 63u;
-                    else f = __builtin_amdgcn_ubfe(w2, 6 * P - 64, 6);
-                    const uint32_t pr = ((f * spread) & m3) | g_lo;
-                    if (P & 1) a1 = dot2(pr, xr[i][P], a1);
-                    else a0 = dot2(pr, xr[i][P], a0);
+                for (int t = 0; t < 3; ++t) {
+                    const uint32_t y = (tens[t] & 0xffffu) | ((tens[t] << 1) & 0xffff0000u), y9 = y >> 9;
+                    a0 = dot2((y & m3[0]) | g3[0], xr[i][5 * t + 0], a0);
+                    a1 = dot2((y & m3[1]) | g3[1], xr[i][5 * t + 1], a1);
+                    a0 = dot2((y & m3[2]) | g3[2], xr[i][5 * t + 2], a0);
+                    a1 = dot2((y9 & m3[0]) | g3[0], xr[i][5 * t + 3], a1);
+                    a0 = dot2((y9 & m3[1]) | g3[1], xr[i][5 * t + 4], a0);
                 }
+                a1 = dot2(((t3 | (t3 << 13)) & m3[0]) | g3[0], xr[i][15], a1);
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -439,15 +465,22 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w4_dot_kernel(DotLayers R, i
 // above - whole rows per wave in contiguous 1 KB requests, activations in registers - with the group structure
 // read off the layout: 1 KB = 256 words = 2560 codes = exactly 20 groups of 128, and a lane's 16 bytes = 40 codes
 // = five chunks of 8.  Inside each run of 16 lanes (640 codes = 5 groups) the boundaries 128, 256, 384, 512 fall on
-// chunk boundaries of lanes 3, 6, 9 and 12; every other lane lies in one group.  So a lane keeps five chunk sums
-// (four two-element dot products each, codes as the exact fp16 numbers 1024 + q), splits them into "its first
-// group" and "its second group" by a per-lane prefix select, and applies the two groups' scales and zero-points
-// to those two sums: s (sum x (1024 + q) - (1024 + z) sum x).  A pair of codes never straddles words (ten per
-// word): one 6-bit field extract and one multiplication by 2^13 + 1 put its codes at bits 0..2 and 16..18.
+// chunk boundaries of lanes 3, 6, 9 and 12; every other lane lies in one group.  So a lane adds up its products in column order,
+// keeps the sum as it stands behind its first group's last chunk (one select per chunk, the lanes known in advance), and applies the two
+// groups' scales and zero-points to that sum and to the rest: s ((sum x (base + q) - sum base x) - z sum x).  A pair of codes never
+// straddles words (ten per word): codes 1, 3, 5 of a word move up by 13 bits to the upper half of one copy, 7 and 9 beside 6 and 8 in another,
+// where pairs at bits 0 of a half become 1024 + q and those at bits 6 16 + q; one shift, for the pair at bits 12.  15 instructions per
+// word with the dot products; a field extract, a multiplication and an and-or per pair took 20, and the choice among five chunk sums,
+// as conditional expressions, divergent branches in
+// the row loop (vector issue is what did not hide behind the stream: 13B block 57.0 -> 48.5 us, 7B 45.6 -> 38.8, 70B 141 -> 118;
+// 5120 x 13824 13.9 -> 11.0, 8192 x 8192 12.1 -> 9.7).
 // The four parameters of a lane's two groups come with one 8-byte load per array (four consecutive groups
 // starting at an even one) and one byte permute.
-// LDS: activation chunks [NL][5][64 lanes] 16 B | chunk sums float [NL][5][64] | weak activations fp16 [128 NKW]
+// LDS: activation chunks [NLP][5][64 lanes] 16 B | chunk sums float [NLP][5][64] | weak activations fp16 [128 NKW], where NLP ranges hold
+// the units of all staging passes (a store under a condition took its load along, behind the first row's codes)
 // =============================================================================================
+constexpr int w3_units(int nl) { return (320 * nl + DOT_THREADS - 1) / DOT_THREADS; }          // staging passes: units of 8 columns per thread
+constexpr int w3_ranges(int nl) { return (w3_units(nl) * DOT_THREADS + 319) / 320; }          // ranges of LDS that hold them
 template <int NL, int DEPTH, int NKW>
 __global__ __launch_bounds__(DOT_THREADS) void gemv_w3_dot_kernel(DotLayers R, int kq, int k, int row_bytes, int gs,
                                                                    const __half* __restrict__ X, int B) {
@@ -506,9 +539,7 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w3_dot_kernel(DotLayers R, i
 
     // ---- requests: the activations this thread stages, then the first DEPTH rows ----------------------------
     // unit u = 8 columns: chunk u % 5 of lane position u / 5 (range (u / 5) / 64, lane (u / 5) % 64)
-    constexpr int XU = 4;
-    constexpr int n_units = 320 * NL;
-    static_assert(n_units <= XU * DOT_THREADS, "one staging pass");
+    constexpr int XU = w3_units(NL), NLP = w3_ranges(NL);
     u4 xv[XU];
 #pragma unroll
     for (int t = 0; t < XU; ++t) xv[t] = *reinterpret_cast<const u4*>(X + min(8 * (t * DOT_THREADS + tid), kq - 8));
@@ -517,8 +548,8 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w3_dot_kernel(DotLayers R, i
     for (int d = 0; d < DEPTH; ++d) issue(d, row_first + d);
     __builtin_amdgcn_sched_barrier(0);   // nothing below may move above the requests
 
-    float* csum = reinterpret_cast<float*>(lds + 5120 * NL);
-    unsigned char* xweak = lds + 5120 * NL + 1280 * NL;
+    float* csum = reinterpret_cast<float*>(lds + 5120 * NLP);
+    unsigned char* xweak = lds + 5120 * NLP + 1280 * NLP;
 #pragma unroll
     for (int t = 0; t < XU; ++t) {
         const int u = t * DOT_THREADS + tid;
@@ -527,23 +558,22 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w3_dot_kernel(DotLayers R, i
         const uint32_t vx = v.x, vy = v.y, vz = v.z, vw = v.w;
         const h2 a = __builtin_bit_cast(h2, vx), b = __builtin_bit_cast(h2, vy), c = __builtin_bit_cast(h2, vz), d = __builtin_bit_cast(h2, vw);
         const float su = (((float)a.x + (float)a.y) + ((float)b.x + (float)b.y)) + (((float)c.x + (float)c.y) + ((float)d.x + (float)d.y));
-        if (u < n_units) {
-            const int pos = u / 5, ch = u - 5 * pos, i = pos >> 6, l = pos & 63;
-            *reinterpret_cast<u4*>(lds + 5120 * i + 1024 * ch + 16 * l) = v;
-            csum[(5 * i + ch) * 64 + l] = su;
-        }
+        const int pos = u / 5, ch = u - 5 * pos, i = pos >> 6, l = pos & 63;
+        *reinterpret_cast<u4*>(lds + 5120 * i + 1024 * ch + 16 * l) = v;
+        csum[(5 * i + ch) * 64 + l] = su;
     }
     if (8 * tid < k) *reinterpret_cast<u4*>(xweak + 16 * tid) = xwv;
     __syncthreads();
 
     // ---- this lane's activations and group sums, for the rest of the launch ---------------------------------------
-    const int j16 = lane & 15;
-    const int bc = j16 == 3 ? 1 : (j16 == 6 ? 2 : (j16 == 9 ? 3 : (j16 == 12 ? 4 : 5)));   // chunks of the lane's first group
+    // lanes whose first group ends behind chunk 0, 1, 2, 3 (lanes 3, 6, 9, 12 of every 16) and the others, whose only group is their first
+    constexpr uint64_t ends[5] = {0x0008000800080008ull, 0x0040004000400040ull, 0x0200020002000200ull, 0x1000100010001000ull, 0xedb7edb7edb7edb7ull};
+    auto word_base = [](int r) { return r == 0 || r == 3 ? 0x64006400u : 0x4c004c00u; };   // 1024, 16 for pair r of a word
     uint32_t xr[NL][20];
-    float s_lo[NL], s_hi[NL];
+    float s_lo[NL], s_hi[NL], k_lo[NL], k_hi[NL];   // sums of x and of base x over the lane's first and second group
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-        float lo = 0.f, all = 0.f;
+        float all = 0.f, kb = 0.f, lo = 0.f, klo = 0.f;
 #pragma unroll
         for (int ch = 0; ch < 5; ++ch) {
             const u4 v = *reinterpret_cast<const u4*>(lds + 5120 * i + 1024 * ch + 16 * lane);
@@ -551,12 +581,16 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w3_dot_kernel(DotLayers R, i
             xr[i][4 * ch + 1] = v.y;
             xr[i][4 * ch + 2] = v.z;
             xr[i][4 * ch + 3] = v.w;
-            const float sc = csum[(5 * i + ch) * 64 + lane];
-            all += sc;
-            if (ch < bc) lo += sc;
+#pragma unroll
+            for (int P = 4 * ch; P < 4 * ch + 4; ++P) kb = dot2(word_base(P % 5), xr[i][P], kb);
+            all += csum[(5 * i + ch) * 64 + lane];
+            lo = pick(lo, all, ends[ch]);
+            klo = pick(klo, kb, ends[ch]);
         }
         s_lo[i] = lo;
         s_hi[i] = all - lo;
+        k_lo[i] = klo;
+        k_hi[i] = kb - klo;
     }
     uint32_t xw[NKW];
 #pragma unroll
@@ -564,28 +598,33 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w3_dot_kernel(DotLayers R, i
         const int dw = lane + 64 * t;
         xw[t] = (2 * dw < k) ? *reinterpret_cast<const uint32_t*>(xweak + 4 * dw) : 0u;
     }
-    uint32_t cmask = 0x00070007u, cmagic = 0x64006400u;
-    asm volatile("" : "+v"(cmask), "+v"(cmagic));   // in registers: (v & m) | g is then one v_and_or_b32
+    uint32_t m0 = 0x00070007u, m6 = 0x01c001c0u, g0 = 0x64006400u, g6 = 0x4c004c00u;
+    asm volatile("" : "+v"(m0), "+v"(m6), "+v"(g0), "+v"(g6));   // in registers: (v & m) | g is then one v_and_or_b32
 
     float res = 0.f;   // lane j: the wave's result for its row j
     auto compute = [&](int d, int j) {
         float y = 0.f;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            float c[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+            float a = 0.f, a_lo = 0.f;
 #pragma unroll
-            for (int P = 0; P < 20; ++P) {   // pair P: codes 2 P, 2 P + 1 of the lane's 40 = pair P % 5 of word P / 5
-                const uint32_t six = __builtin_amdgcn_ubfe(wq[d][i][P / 5], 6 * (P % 5), 6);
-                const uint32_t cp = ((six * 0x2001u) & cmask) | cmagic;
-                c[P / 4] = dot2(cp, xr[i][P], c[P / 4]);
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t w = wq[d][i][q], t = w >> 18;
+                const uint32_t ya = (w & 0xffffu) | ((w << 13) & 0xffff0000u), yb = (t << 13) | t;
+                const uint32_t cp[5] = {(ya & m0) | g0, (ya & m6) | g6, ((ya >> 6) & m6) | g6, (yb & m0) | g0, (yb & m6) | g6};
+#pragma unroll
+                for (int r = 0; r < 5; ++r) {
+                    const int P = 5 * q + r;   // codes 2 P, 2 P + 1 of the lane's 40
+                    a = dot2(cp[r], xr[i][P], a);
+                    if (P % 4 == 3) a_lo = pick(a_lo, a, ends[P / 4]);
+                }
             }
-            const float p1 = c[0], p2 = p1 + c[1], p3 = p2 + c[2], p4 = p3 + c[3], all = p4 + c[4];
-            const float a_lo = bc == 1 ? p1 : (bc == 2 ? p2 : (bc == 3 ? p3 : (bc == 4 ? p4 : all)));
-            const float a_hi = all - a_lo;
+            const float a_hi = a - a_lo;
             const h2 sp = __builtin_bit_cast(h2, __builtin_amdgcn_perm(sq[d][i].y, sq[d][i].x, selb[i]));
             const h2 zp = __builtin_bit_cast(h2, __builtin_amdgcn_perm(zq[d][i].y, zq[d][i].x, selb[i]));
-            y = fmaf((float)sp.x, fmaf(-(1024.f + (float)zp.x), s_lo[i], a_lo), y);
-            y = fmaf((float)sp.y, fmaf(-(1024.f + (float)zp.y), s_hi[i], a_hi), y);
+            y = fmaf((float)sp.x, fmaf(-(float)zp.x, s_lo[i], a_lo - k_lo[i]), y);
+            y = fmaf((float)sp.y, fmaf(-(float)zp.y, s_hi[i], a_hi - k_hi[i]), y);
+            __builtin_amdgcn_sched_barrier(0);   // (the conversions of all ranges at once would not fit the registers)
         }
 #pragma unroll
         for (int t = 0; t < NKW; ++t) y = dot2(wk[d][t], xw[t], y);
@@ -665,7 +704,7 @@ DotPlan dot_plan_w3(const Layer& L, int n_rows, bool perm) {
     const int slots = 256 * occ_wg * DOT_WAVES;
     p.B = ceil_div(n_rows, p.depth * slots);
     if (p.depth * p.B > 64) return p;
-    p.lds = (size_t)5120 * nl + 1280 * nl + 256 * nkw;
+    p.lds = (size_t)6400 * w3_ranges(nl) + 256 * nkw;
     p.ok = p.lds <= 64 * 1024;
     return p;
 }

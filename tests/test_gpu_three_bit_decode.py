@@ -38,6 +38,18 @@ def test_three_bit_rows(oc, ic, k, dense):
 
 
 @pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("kq", [2048, 2560, 2568, 5120 + 640, 7680 + 384, 4 * 2560 + 72, 12288, 15360 - 8])
+def test_three_bit_one_row_every_range_count(kq, dense):
+    """One row of 1 to 6 kilobyte requests (ten codes a word: boundaries between groups inside lanes' pieces), rows that end early in one."""
+    kq = kq // 32 * 32 if dense else kq        # (the dense kernel takes whole lane pieces)
+    layer = HostLayer(77, kq + 72, 72, 3, 128, seed=kq, dense=dense)
+    xd = pad_cols(synth.make_activations(1, layer.ic, 72, seed=kq))[0]
+    y = B.qeft_linear_fwd(layer.desc, layer.to_device(), xd, ws=False)
+    torch.cuda.synchronize()
+    assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, xd.cpu().numpy()), f"{kq} columns")
+
+
+@pytest.mark.parametrize("dense", [False, True])
 def test_three_bit_rows_many_groups_per_wave(dense):
     """Ten-code words start at every shift as a wave's groups go by; both register sets of codes; all tile widths."""
     for oc, kq in ((2056, 25 * 128 + 64), (4104, 21 * 128), (8200, 13 * 128 + 96)):
