@@ -132,9 +132,54 @@ hipError_t fwd_rows(const Layer& L, const __half* x, int64_t M, int64_t ldx, __h
     if (fwd_tile_preferred(L, M, ldx, split)) return fwd_tile(L, x, M, ldx, y, ldy, s);
     return gemm_fwd(L, x, M, ldx, y, ldy, split_ws, s);
 }
-hipError_t dx_rows(const Layer& L, const __half* dy, int64_t M, int64_t lddy, __half* dx, int64_t lddx, void* split_ws, hipStream_t s) {
-    if (dx_tile_preferred(L, M, lddy, split_ws != nullptr)) return dx_tile(L, dy, M, lddy, dx, lddx, s);
-    return gemm_dx(L, dy, M, lddy, dx, lddx, split_ws, s);
+hipError_t dx_rows(const Layer& L, const __half* dy, int64_t M, int64_t lddy, __half* dx, int64_t lddx, void* split_ws, hipStream_t s, WeakGrad* g) {
+    if (dx_tile_preferred(L, M, lddy, split_ws != nullptr)) return dx_tile(L, dy, M, lddy, dx, lddx, s, g);
+    return gemm_dx(L, dy, M, lddy, dx, lddx, split_ws, s, g);
+}
+
+// qeft_linear_bwd_dx; g: a weak gradient to take along where there is room for it, or NULL
+int linear_bwd_dx(const qeft_desc_t* desc, const qeft_weight_t* w, const void* dY, int64_t M, int64_t lddy,
+                  void* dX, int64_t lddx, void* ws, size_t ws_bytes, void* stream, WeakGrad* g) {
+    Layer L;
+    int st = make_layer(desc, w, &L);
+    if (st != QEFT_OK) return st;
+    st = check_matrix(dY, M, lddy, L.oc);
+    if (st != QEFT_OK) return st;
+    st = check_matrix(dX, M, lddx, L.ic);
+    if (st != QEFT_OK) return st;
+    if (M == 0) return QEFT_OK;
+    hipStream_t s = (hipStream_t)stream;
+    if (gemm_dx_supported(L, M)) {
+        const size_t need = ws ? gemm_dx_split_workspace(L, M) : 0;   // optional: partial tiles of a row split
+        if (need > 0) {
+            if (!aligned16(ws)) return QEFT_ERR_ALIGN;
+            if (ws_bytes < need) return QEFT_ERR_WORKSPACE;
+        }
+        return hip_status(dx_rows(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, need > 0 ? ws : nullptr, s, g));
+    }
+    if (ws && dense_copy_applies(L, M)) {
+        if (!aligned16(ws)) return QEFT_ERR_ALIGN;
+        if (ws_bytes < dense_copy_bytes(L)) return QEFT_ERR_WORKSPACE;
+        const Layer N = nibble_copy_layer(L, ws), D = dense_copy_layer(L, ws);
+        const size_t need = gemm_dx_supported(D, M) ? gemm_dx_split_workspace(D, M) : 0;
+        const bool whole = need > 0 && ws_bytes >= dense_copy_bytes(L) + need;   // what the caller gave holds a split of the fp16 copy too
+        if (nibble_copy_applies(L, M) && gemm_dx_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
+            void* split_ws = whole ? behind_nibble_copy(N, gemm_dx_split_workspace(N, M), ws, ws_bytes) : nullptr;
+            if (dx_copy4_preferred(N, D, M, lddy, split_ws != nullptr, whole)) {
+                if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
+                if (g) g->used = nibble_copy_bytes(N);
+                return hip_status(dx_rows(N, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s, g));
+            }
+        }
+        if (gemm_dx_supported(D, M)) {
+            hipError_t e = dequantize_fp16(L, (__half*)ws, s);
+            if (e != hipSuccess) return QEFT_ERR_HIP;
+            void* split_ws = whole ? (char*)ws + dense_copy_bytes(L) : nullptr;
+            if (g) g->used = dense_copy_bytes(L);
+            return hip_status(gemm_dx(D, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s, g));
+        }
+    }
+    return hip_status(bwd_dx_generic(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, s));
 }
 
 }  // namespace
@@ -321,44 +366,7 @@ int qeft_linear_fwd_group(int n, const qeft_desc_t* descs, const qeft_weight_t* 
 
 int qeft_linear_bwd_dx(const qeft_desc_t* desc, const qeft_weight_t* w, const void* dY, int64_t M, int64_t lddy,
                        void* dX, int64_t lddx, void* ws, size_t ws_bytes, void* stream) {
-    Layer L;
-    int st = make_layer(desc, w, &L);
-    if (st != QEFT_OK) return st;
-    st = check_matrix(dY, M, lddy, L.oc);
-    if (st != QEFT_OK) return st;
-    st = check_matrix(dX, M, lddx, L.ic);
-    if (st != QEFT_OK) return st;
-    if (M == 0) return QEFT_OK;
-    hipStream_t s = (hipStream_t)stream;
-    if (gemm_dx_supported(L, M)) {
-        const size_t need = ws ? gemm_dx_split_workspace(L, M) : 0;   // optional: partial tiles of a row split
-        if (need > 0) {
-            if (!aligned16(ws)) return QEFT_ERR_ALIGN;
-            if (ws_bytes < need) return QEFT_ERR_WORKSPACE;
-        }
-        return hip_status(dx_rows(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, need > 0 ? ws : nullptr, s));
-    }
-    if (ws && dense_copy_applies(L, M)) {
-        if (!aligned16(ws)) return QEFT_ERR_ALIGN;
-        if (ws_bytes < dense_copy_bytes(L)) return QEFT_ERR_WORKSPACE;
-        const Layer N = nibble_copy_layer(L, ws), D = dense_copy_layer(L, ws);
-        const size_t need = gemm_dx_supported(D, M) ? gemm_dx_split_workspace(D, M) : 0;
-        const bool whole = need > 0 && ws_bytes >= dense_copy_bytes(L) + need;   // what the caller gave holds a split of the fp16 copy too
-        if (nibble_copy_applies(L, M) && gemm_dx_supported(N, M) && nibble_copy_bytes(N) <= ws_bytes) {
-            void* split_ws = whole ? behind_nibble_copy(N, gemm_dx_split_workspace(N, M), ws, ws_bytes) : nullptr;
-            if (dx_copy4_preferred(N, D, M, lddy, split_ws != nullptr, whole)) {
-                if (expand3(L, (uint32_t*)ws, N.words, N.stride, s) != hipSuccess) return QEFT_ERR_HIP;
-                return hip_status(dx_rows(N, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s));
-            }
-        }
-        if (gemm_dx_supported(D, M)) {
-            hipError_t e = dequantize_fp16(L, (__half*)ws, s);
-            if (e != hipSuccess) return QEFT_ERR_HIP;
-            void* split_ws = whole ? (char*)ws + dense_copy_bytes(L) : nullptr;
-            return hip_status(gemm_dx(D, (const __half*)dY, M, lddy, (__half*)dX, lddx, split_ws, s));
-        }
-    }
-    return hip_status(bwd_dx_generic(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, s));
+    return linear_bwd_dx(desc, w, dY, M, lddy, dX, lddx, ws, ws_bytes, stream, nullptr);
 }
 
 int qeft_linear_fwd_irregular(const qeft_desc_t* desc, const qeft_weight_t* w, const int32_t* perm, const void* X,
@@ -516,11 +524,11 @@ int qeft_linear_bwd(const qeft_desc_t* desc, const qeft_weight_t* w, const void*
     size_t need_dx = gemm_dx_supported(L, M) ? gemm_dx_split_workspace(L, M) : 0;
     if (dense_copy_applies(L, M)) need_dx = dense_copy_bytes(L);
     const bool split = need_dx > 0 && ws && aligned16(ws) && ws_bytes >= need_dx;
-    if (!split && gemm_dx_dw_supported(L, M) && !dx_tile_preferred(L, M, lddy, false))   // (few tiles: the small-tile kernel, then the weak gradient)
-        return hip_status(gemm_dx_dw(L, (const __half*)dY, M, lddy, (__half*)dX, lddx, (const __half*)Xw, ldxw, dW,
-                                     out_dtype == QEFT_DTYPE_F32, accumulate != 0, ws, (hipStream_t)stream));
-    st = qeft_linear_bwd_dx(desc, w, dY, M, lddy, dX, lddx, split ? ws : nullptr, split ? ws_bytes : 0, stream);
-    if (st != QEFT_OK) return st;
+    // (the weak gradient goes along in a launch of dX that has room for it: beside the sum of a split's partial tiles, behind the tiles)
+    WeakGrad g = {L.oc, L.k, (const __half*)Xw, ldxw, dW, out_dtype == QEFT_DTYPE_F32, accumulate != 0, (unsigned char*)ws, ws_bytes, 0, false};
+    if (!ws || !aligned16(ws)) g.ws = nullptr, g.ws_bytes = 0;
+    st = linear_bwd_dx(desc, w, dY, M, lddy, dX, lddx, split ? ws : nullptr, split ? ws_bytes : 0, stream, &g);
+    if (st != QEFT_OK || g.done) return st;
     return qeft_weak_grad(desc, dY, M, lddy, Xw, ldxw, dW, out_dtype, accumulate, ws, ws_bytes, stream);
 }
 

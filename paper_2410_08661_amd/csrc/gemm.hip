@@ -27,6 +27,7 @@
 #include <utility>
 
 #include "gemm_common.h"
+#include "weak_strip.h"
 
 namespace qeft {
 namespace {
@@ -1170,203 +1171,6 @@ __global__ __launch_bounds__(256) void gemm_dx_rega_kernel(Layer L, const __half
     dx_rega_body<ONCE>(lds, L, dY, M, lddy, dX, lddx, tiles_ic, splits, rps, tail_first, part);
 }
 
-// ======================================================================================= weak gradient
-// A[i = c][k = m] = Xw[m][c], B[j = oc][k = m] = dY[m][oc]: both operands are read transposed.
-// The tokens are split over `splits` workgroups per strip of output channels; each writes an fp32 partial
-// [OC][k] slab, summed in slab order by a second kernel (no atomics: deterministic).
-// The kernel is sized for what bounds it - reading dY once from
-// HBM: a workgroup owns 64 output channels x up to 128 weak columns over a range of tokens, so the
-// MFMA tiles hold no padding and a dY row contributes 128 contiguous bytes.  Both operands have
-// the contraction index (the token) as their row index; instead of transposing 8 x 8 blocks in
-// registers, the tiles go to LDS as they are ([token][column], rows padded by 64 bytes) and the
-// fragments are read with the transposing LDS load of gfx950 (ds_read_b64_tr_b16: the 16 lanes
-// of a group each name 4 consecutive halfs; output lane l receives element l % 4 of source
-// lanes l / 4, l / 4 + 4, l / 4 + 8, l / 4 + 12).  With source lane s pointing at row k0 + s / 4,
-// columns c0 + 4 (s % 4) .., a group receives columns c0 .. c0 + 15 of rows k0 .. k0 + 3 - four
-// consecutive contraction steps for 16 MFMA rows; two such loads make one fragment.
-// Wave w multiplies weak columns 32 w .. 32 w + 31 against the 64 channels.  With one split
-// the result goes straight to dW, otherwise into fp32 slabs as above.
-constexpr int WG_OC = 64;                             // output channels per workgroup
-// Row pitches: a transposing fragment read takes, per half wave, 4 rows x 64 bytes (two 16-lane groups side by
-// side), so consecutive rows must sit 16 (or 48) banks apart: 256 + 64 and 128 + 64 bytes.  (With + 32 bytes a
-// third of the LDS cycles of this kernel were bank conflicts.)
-constexpr int WG_A_PITCH = 128 * 2 + 64;              // bytes per token row of the Xw tile
-constexpr int WG_B_PITCH = WG_OC * 2 + 64;            // ... of the dY tile
-constexpr int WG_A_BYTES = BK * WG_A_PITCH, WG_B_BYTES = BK * WG_B_PITCH;
-constexpr int WG_LDS = 2 * (WG_A_BYTES + WG_B_BYTES); // A0 A1 B0 B1
-
-// A weak block wider than 128 columns is taken in halves of 128 (workgroup index = ((strip, half), split)): the two halves
-// of a strip read the same dY rows and sit next to each other in the grid.
-// (bid: the workgroup's index among the strip workgroups; lds: its dynamic shared memory, WG_LDS bytes)
-__device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid, int oc_total, int k_total, const __half* __restrict__ dY, int M,
-                                                     int64_t lddy, const __half* __restrict__ Xw, int64_t ldxw,
-                                                     float* __restrict__ part, int splits, int chunk, void* dW,
-                                                     int out_f32, int accumulate) {
-    typedef short s4 __attribute__((ext_vector_type(4)));
-    typedef short s8 __attribute__((ext_vector_type(8)));
-    using lds_s4 = __attribute__((address_space(3))) s4;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int halves = (k_total + 127) >> 7;
-    const int split = bid % splits, rest = bid / splits;
-    const int kh = rest % halves, t_oc = rest / halves;
-    const int k = min(128, k_total - 128 * kh);   // this workgroup's weak columns: 128 kh .. 128 kh + k - 1
-    Xw += 128 * kh;
-    const int oc0 = t_oc * WG_OC;
-    const int mb = split * chunk, me = min(mb + chunk, M);
-    const int nst = (me - mb + BK - 1) / BK;
-    const int fr = lane & 31, fk = lane >> 5;
-
-    // producers: 16-byte chunks, copied as they are.  Xw tile: 64 tokens x 16 chunks, four per
-    // thread (token ar + 16 u, chunk ac); dY tile: 64 tokens x 8 chunks, two per thread (token
-    // br + 32 u, chunk bc).  Chunks past k or past the last channel read column 0 and are zeroed.
-    const int ar = tid >> 4, ac = tid & 15, br = tid >> 3, bc = tid & 7;
-    const bool a_ok = 8 * ac < k, b_ok = oc0 + 8 * bc < oc_total;
-    const u4 zero4 = u4{0u, 0u, 0u, 0u};
-    // Addresses: a scalar base per stage plus a per-thread byte offset computed once (this kernel is bound by
-    // its single wave's instruction stream, and per-load address arithmetic was a third of it).  A stage whose
-    // 64 tokens would pass the end of the matrices is fetched 64 tokens back from the end instead (M >= 64) and
-    // put() keeps only the rows that belong to it; stages past the range re-read the last one and store zeros.
-    using gptr = const __attribute__((address_space(1))) char*;
-    using g_u4 = const __attribute__((address_space(1))) u4;
-    uint32_t aoff[4], boff[2];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) aoff[u] = (uint32_t)(((int64_t)(ar + 16 * u) * ldxw + (a_ok ? 8 * ac : 0)) * 2);
-#pragma unroll
-    for (int u = 0; u < 2; ++u) boff[u] = (uint32_t)(((int64_t)(br + 32 * u) * lddy + (b_ok ? oc0 + 8 * bc : 0)) * 2);
-    const bool cols_full = __builtin_amdgcn_readfirstlane((int)(k >= 8 * 16 && oc0 + WG_OC <= oc_total)) != 0;   // no thread's chunk is zeroed
-    auto first_token = [&](int st) { return min(mb + BK * min(st, nst - 1), M - BK); };   // of the 64 tokens fetched for stage st
-    // three stages of fetches in flight per thread (registers), a fourth in LDS being multiplied
-    u4 va[3][4], vb[3][2];
-    auto fetch = [&](auto set_c, int st) {
-        constexpr int SET = decltype(set_c)::value;
-        const int t0 = first_token(st);
-        const char* ab = reinterpret_cast<const char*>(Xw) + (int64_t)t0 * ldxw * 2;
-        const char* bb = reinterpret_cast<const char*>(dY) + (int64_t)t0 * lddy * 2;
-        asm volatile("" : "+s"(ab), "+s"(bb));
-#pragma unroll
-        for (int u = 0; u < 4; ++u) va[SET][u] = *reinterpret_cast<g_u4*>((gptr)ab + aoff[u]);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) vb[SET][u] = *reinterpret_cast<g_u4*>((gptr)bb + boff[u]);
-    };
-    auto put = [&](auto set_c, int st, int buf) {   // stage st, held by register set SET, into LDS buffer buf
-        constexpr int SET = decltype(set_c)::value;
-        const int m0 = mb + BK * st, t0 = first_token(st);
-        unsigned char* sA = lds + buf * WG_A_BYTES;
-        unsigned char* sB = lds + 2 * WG_A_BYTES + buf * WG_B_BYTES;
-        if (cols_full && st < nst && m0 + BK <= me) {   // a whole stage, whole columns (wave-uniform): the registers as they are
-#pragma unroll
-            for (int u = 0; u < 4; ++u) *reinterpret_cast<u4*>(sA + (ar + 16 * u) * WG_A_PITCH + 16 * ac) = va[SET][u];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) *reinterpret_cast<u4*>(sB + (br + 32 * u) * WG_B_PITCH + 16 * bc) = vb[SET][u];
-        } else if (st >= nst) {   // past the range: a tile of zeros
-#pragma unroll
-            for (int u = 0; u < 4; ++u) *reinterpret_cast<u4*>(sA + (ar + 16 * u) * WG_A_PITCH + 16 * ac) = zero4;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) *reinterpret_cast<u4*>(sB + (br + 32 * u) * WG_B_PITCH + 16 * bc) = zero4;
-        } else {
-            // fetched row r holds token t0 + r; it belongs to the stage when that lies in [m0, me), and its tile row
-            // is token - m0.  shift = m0 - t0 > 0 only for the last stage of the matrices: fetched rows [shift, 64)
-            // fill tile rows [0, 64 - shift), the rest of the tile is zero.
-            const int shift = m0 - t0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int r = ar + 16 * u, tok = t0 + r;
-                if (r >= shift) *reinterpret_cast<u4*>(sA + (r - shift) * WG_A_PITCH + 16 * ac) = (a_ok && tok < me) ? va[SET][u] : zero4;
-                if (r >= BK - shift) *reinterpret_cast<u4*>(sA + r * WG_A_PITCH + 16 * ac) = zero4;
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int r = br + 32 * u, tok = t0 + r;
-                if (r >= shift) *reinterpret_cast<u4*>(sB + (r - shift) * WG_B_PITCH + 16 * bc) = (b_ok && tok < me) ? vb[SET][u] : zero4;
-                if (r >= BK - shift) *reinterpret_cast<u4*>(sB + r * WG_B_PITCH + 16 * bc) = zero4;
-            }
-        }
-    };
-
-    f16v acc[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-
-    // fragment addressing: lane = 16 g + s; rows (tokens) 8 (g / 2) + s / 4 (+ 4 for the second
-    // load, + 16 per k-block), columns 16 (g % 2) + 4 (s % 4) of the wave's 32
-    const int g = lane >> 4, s = lane & 15;
-    const int frow = 8 * (g >> 1) + (s >> 2), fcol = 16 * (g & 1) + 4 * (s & 3);
-    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)lds;
-    const uint32_t fa = lds0 + frow * WG_A_PITCH + 2 * (32 * wave + fcol);
-    const uint32_t fb = lds0 + 2 * WG_A_BYTES + frow * WG_B_PITCH + 2 * fcol;
-    auto frag = [&](uint32_t addr, int pitch) {   // 8 contraction steps: rows +0..3 and +4..7
-        const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(size_t)(addr));
-        const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(size_t)(addr + 4 * pitch));
-        return __builtin_bit_cast(h8, s8{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w});
-    };
-
-    // stage st (already in LDS buffer st & 1, fetched through register set SET): refill the set
-    // with stage st + 3, multiply, move stage st + 1 from the next set into the other buffer
-    auto stage = [&](auto set_c, int st) {
-        constexpr int SET = decltype(set_c)::value;
-        const int cur = st & 1;
-        fetch(set_c, st + 3);
-        __builtin_amdgcn_sched_barrier(0);   // issue the fetches first: they are what the stage waits for
-        const uint32_t a0 = fa + cur * WG_A_BYTES, b0 = fb + cur * WG_B_BYTES;
-        // fragments are read one k-block ahead of the MFMAs that use them (one wave per SIMD: nothing else hides the LDS latency)
-        h8 a[2], bl[2], bh[2];
-        auto frags = [&](int ks) {
-            a[ks & 1] = frag(a0 + 16 * ks * WG_A_PITCH, WG_A_PITCH);
-            bl[ks & 1] = frag(b0 + 16 * ks * WG_B_PITCH, WG_B_PITCH);
-            bh[ks & 1] = frag(b0 + 16 * ks * WG_B_PITCH + 64, WG_B_PITCH);
-        };
-        frags(0);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ks < 3) frags(ks + 1);
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks & 1], bl[ks & 1], acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks & 1], bh[ks & 1], acc[1], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        put(std::integral_constant<int, (SET + 1) % 3>{}, st + 1, cur ^ 1);
-        __syncthreads();
-    };
-    fetch(std::integral_constant<int, 0>{}, 0);
-    fetch(std::integral_constant<int, 1>{}, 1);
-    fetch(std::integral_constant<int, 2>{}, 2);
-    put(std::integral_constant<int, 0>{}, 0, 0);
-    __syncthreads();
-    // always three stages per turn, with no branch between them (the compiler's wait counting then
-    // lets two stages of fetches stay in flight); stages past the range multiply zeros
-    for (int st = 0; st < nst; st += 3) {
-        stage(std::integral_constant<int, 0>{}, st);
-        stage(std::integral_constant<int, 1>{}, st + 1);
-        stage(std::integral_constant<int, 2>{}, st + 2);
-    }
-    if (32 * wave >= k) return;   // this wave's weak columns do not exist
-    // lane (fr, fk) holds, for channel oc0 + 32 t + fr, weak columns 32 wave + 8 g + 4 fk .. + 3
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int j = oc0 + 32 * t + fr;
-        if (j >= oc_total) continue;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int i = 32 * wave + 8 * q + 4 * fk;
-            if (i >= k) continue;
-            f4 r = f4{acc[t][4 * q + 0], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
-            const size_t at = (size_t)j * k_total + 128 * kh + i;
-            if (splits > 1) {
-                *reinterpret_cast<f4*>(part + (size_t)split * oc_total * k_total + at) = r;
-            } else if (out_f32) {
-                f4* o = reinterpret_cast<f4*>((float*)dW + at);
-                *o = accumulate ? *o + r : r;
-            } else {
-                __half* o = (__half*)dW + at;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = __float2half_rn(accumulate ? __half2float(o[e]) + r[e] : r[e]);
-            }
-        }
-    }
-}
-
 __global__ __launch_bounds__(256) void weak_grad_strip_kernel(int oc_total, int k_total, const __half* __restrict__ dY, int M,
                                                               int64_t lddy, const __half* __restrict__ Xw, int64_t ldxw,
                                                               float* __restrict__ part, int splits, int chunk, void* dW,
@@ -1379,16 +1183,15 @@ __global__ __launch_bounds__(256) void weak_grad_strip_kernel(int oc_total, int 
 // tiles of gemm_dx_rega_kernel (no split), the rest the strips of weak_grad_strip_kernel.  Both read dY; the
 // strips are dispatched as compute units fall free, i.e. into the partly empty last round of tiles (688 tiles on
 // 256 units leave 80 of them idle for a third of the launch), where they cost nothing.
+template <bool ONCE>
 __global__ __launch_bounds__(256) void gemm_dx_dw_kernel(Layer L, const __half* __restrict__ dY, int M, int64_t lddy,
-                                                         __half* __restrict__ dX, int64_t lddx, int tiles_ic, int n_dx,
-                                                         const __half* __restrict__ Xw, int64_t ldxw, float* __restrict__ part,
-                                                         int splits, int chunk, void* dW, int out_f32, int accumulate) {
+                                                         __half* __restrict__ dX, int64_t lddx, int tiles_ic, int n_dx, Strips S) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     if ((int)blockIdx.x >= n_dx) {
-        weak_grad_strip_body(lds, (int)blockIdx.x - n_dx, L.oc, L.k, dY, M, lddy, Xw, ldxw, part, splits, chunk, dW, out_f32, accumulate);
+        weak_grad_strip(lds, (int)blockIdx.x - n_dx, S);
         return;
     }
-    dx_rega_body<false>(lds, L, dY, M, lddy, dX, lddx, tiles_ic, 1, 0, 0, nullptr);
+    dx_rega_body<ONCE>(lds, L, dY, M, lddy, dX, lddx, tiles_ic, 1, 0, 0, nullptr);
 }
 
 __global__ __launch_bounds__(256) void weak_grad_reduce_kernel(const float* __restrict__ part, int splits, int64_t n,
@@ -1429,9 +1232,9 @@ namespace {
 // Sum of the partial tiles of the split tiles: workgroup (tail index, r) adds the `splits` slots of rows 8 r .. 8 r + 7
 // of one tile, 8 outputs (16 bytes) per thread, fp32 sum in split order, one rounding.  n: columns of the output
 // (tiles_n tiles of them); pm: rows of a panel (a slot has room for 256).
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const __half* __restrict__ part, int splits, int tiles_all, int tiles_n,
-                                                            int tail_first, int M, int pm, int n, __half* __restrict__ Y, int64_t ldy) {
-    const int tt = blockIdx.x >> 5, part32 = blockIdx.x & 31;
+__device__ __forceinline__ void splitk_reduce_body(int bid, const __half* __restrict__ part, int splits, int tiles_all, int tiles_n,
+                                                   int tail_first, int M, int pm, int n, __half* __restrict__ Y, int64_t ldy) {
+    const int tt = bid >> 5, part32 = bid & 31;
     const int tile = split_tail_tile(tiles_all, tail_first, tt);
     if (tile < 0) return;
     int t_n, t_m;
@@ -1446,6 +1249,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const __half* __rest
         float acc[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+#pragma unroll 4
         for (int p = 0; p < splits; ++p) {
             const u4 v = ld16(p0 + (size_t)p * (BT * BT) + row * BT + 8 * c);
             const h8 h = __builtin_bit_cast(h8, v);
@@ -1464,6 +1268,21 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const __half* __rest
                 if (col + e < n) y[e] = __float2half_rn(acc[e]);
         }
     }
+}
+
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const __half* __restrict__ part, int splits, int tiles_all, int tiles_n,
+                                                            int tail_first, int M, int pm, int n, __half* __restrict__ Y, int64_t ldy) {
+    splitk_reduce_body((int)blockIdx.x, part, splits, tiles_all, tiles_n, tail_first, M, pm, n, Y, ldy);
+}
+// The same behind an input gradient that was split, with the strips of the weak gradient ahead of it in the grid: either alone is short and
+// leaves most of the GPU waiting for it.  One launch instead of two, the whole backward, us: 4096 x 4096 at M = 200 / 512 / 777 34 / 42.5 / 56 ->
+// 29 / 37 / 51; 11008 x 4096 at 512 / 2048 72 / 206 -> 66 / 200; 3-bit 5120 x 5120 at 1000 91 -> 85.  65 KB of LDS for every workgroup leaves a CU two at
+// a time; with its partial tiles four requests at a time the sum takes no longer for it.
+__global__ __launch_bounds__(256) void splitk_reduce_dw_kernel(const __half* __restrict__ part, int splits, int tiles_all, int tiles_n,
+                                                               int tail_first, int M, int n, __half* __restrict__ dX, int64_t lddx, Strips S) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    if ((int)blockIdx.x < S.n) weak_grad_strip(lds, (int)blockIdx.x, S);
+    else splitk_reduce_body((int)blockIdx.x - S.n, part, splits, tiles_all, tiles_n, tail_first, M, BT, n, dX, lddx);
 }
 
 // Which tiles to split and how, for a launch of `tiles` tiles whose contraction has `chunks` units of 8 stages.
@@ -1586,7 +1405,11 @@ GemmSplit gemm_dx_split(const Layer& L, int64_t M) {
     return GemmSplit{p.splits, 8 * p.chunks_per_split, ceil_div(L.ic, BT) * ceil_div(M, BT), p.tail_first > 0};
 }
 
-hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s) {
+// (defined below: tiles and strips in one launch)
+static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, const Strips& S, hipStream_t s);
+static bool gemm_dx_dw_preferred(const Layer& L, const Strips& S);
+
+hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s, WeakGrad* g) {
     const int tiles_m = ceil_div(M, BT), tiles_ic = ceil_div(L.ic, BT);
     hipError_t e;
     if (L.oc % BK == 0 && L.kq % 128 == 0 && L.k % 8 == 0) {
@@ -1603,9 +1426,26 @@ hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __
             __half* part = (__half*)ws;
             kern<<<split_grid(tiles, p.tail_first, p.splits), 256, DX_LDS, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, p.splits,
                                                                                               p.chunks_per_split * 8 * BK, p.tail_first, part);
-            splitk_reduce_kernel<<<32 * split_tail_tiles(tiles, p.tail_first), 256, 0, s>>>(part, p.splits, tiles, tiles_ic, p.tail_first, (int)M,
-                                                                                           BT, L.ic, dX, lddx);
+            const int n_sum = 32 * split_tail_tiles(tiles, p.tail_first);
+            const Strips S = make_strips(g, dY, M, lddy, g ? (size_t)((unsigned char*)ws - g->ws) + split_workspace(tiles, p) : 0);
+            if (S.n > 0) {
+                static bool dw_attr = false;
+                if (!dw_attr) {
+                    e = hipFuncSetAttribute((const void*)splitk_reduce_dw_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WG_LDS);
+                    if (e != hipSuccess) return e;
+                    dw_attr = true;
+                }
+                splitk_reduce_dw_kernel<<<S.n + n_sum, 256, WG_LDS, s>>>(part, p.splits, tiles, tiles_ic, p.tail_first, (int)M, L.ic, dX, lddx, S);
+                e = hipGetLastError();
+                return e == hipSuccess ? finish_strips(g, S, s) : e;
+            }
+            splitk_reduce_kernel<<<n_sum, 256, 0, s>>>(part, p.splits, tiles, tiles_ic, p.tail_first, (int)M, BT, L.ic, dX, lddx);
             return hipGetLastError();
+        }
+        const Strips S = make_strips(g, dY, M, lddy, g ? g->used : 0);
+        if (S.n > 0 && gemm_dx_dw_preferred(L, S)) {
+            e = gemm_dx_dw(L, dY, M, lddy, dX, lddx, S, s);
+            return e == hipSuccess ? finish_strips(g, S, s) : e;
         }
         kern<<<xcd_grid(tiles), 256, DX_LDS, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, 1, 0, 0, nullptr);
     } else {
@@ -1620,43 +1460,6 @@ hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __
 bool weak_grad_mfma_supported(int oc, int k, int64_t M) {
     return M >= 64 && k >= 8 && k <= BT && (k % 8) == 0 && (oc % 8) == 0;
 }
-
-namespace {
-// The most ways the tokens are split for the strip kernel: about one workgroup per CU, every split a whole number of
-// stages.  The workspace is sized for it.
-int weak_grad_strip_most(int oc, int k, int64_t M) {
-    const int tiles = ceil_div(oc, WG_OC) * ceil_div(k, 128);
-    const int stages = ceil_div(M, BK);
-    int want = ceil_div(256, tiles);
-    if (want > stages) want = stages;
-    if (want < 1) want = 1;
-    return ceil_div(M, ceil_div(stages, want) * BK);
-}
-// The split taken: a stage of 64 tokens costs a workgroup about 0.62 us where the strip's 128 weak columns all exist, 1.06 where
-// some do not; workgroups past one per CU count in full there, by 0.3 here (a stage that waits leaves room for another's); a
-// split costs the second launch and its partial slab's way through memory (2 us once, 0.65 us per MB
-// and, in narrower blocks, 0.13 us each).  Measured, as many splits as
-// above against the rule's, us: 4096 channels, k = 128, M = 200 / 512 / 1003: 12.3 / 12.4 / 14.1 against 7.6 / 9.0 / 13.1 (one, one,
-// two; four at M = 4096 either way); 11008 channels, M = 512 / 2048: 19.0 / 26.0 against 9.5 / 22.6 (one; two at M = 3000);
-// 1024 channels, k = 128, M = 2048: 14.5 against 12.2 (four of eight).  Narrower blocks, one split against two: 13824 channels,
-// k = 64, M = 200 / 777 / 1500 / 3000: 9.0 / 17.8 / 27.4 / 49.8 against 13.5 / 19.2 / 23.1 / 36.3.
-void weak_grad_strip_split(int oc, int k, int64_t M, int& splits, int& chunk) {
-    const int tiles = ceil_div(oc, WG_OC) * ceil_div(k, 128);
-    const int stages = ceil_div(M, BK), most = weak_grad_strip_most(oc, k, M);
-    const bool full = k % 128 == 0;
-    const double slab_mb = (double)oc * k * 4e-6, stage_us = full ? 0.62 : 1.06;
-    double best = 1e30;
-    for (int s = 1; s <= most; ++s) {
-        const double w = (double)tiles * s / 256.0;
-        const double t = (w <= 1 ? 1 : (full ? w : 0.7 + 0.3 * w)) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + ((full ? 0.0 : 0.13) + 0.65 * slab_mb) * s : 0.0);
-        if (t < best) {
-            best = t;
-            chunk = ceil_div(stages, s) * BK;
-        }
-    }
-    splits = ceil_div(M, chunk);
-}
-}  // namespace
 
 size_t weak_grad_mfma_workspace(int oc, int k, int64_t M) {
     const int splits = weak_grad_strip_most(oc, k, M);
@@ -1676,12 +1479,15 @@ hipError_t weak_grad_mfma(int oc, int k, const __half* dY, int64_t M, int64_t ld
     }
     weak_grad_strip_kernel<<<ceil_div(oc, WG_OC) * ceil_div(k, 128) * splits, 256, WG_LDS, s>>>(oc, k, dY, (int)M, lddy, Xw, ldxw, (float*)ws, splits,
                                                                                           chunk, dW, out_f32, accumulate);
-    if (splits > 1) weak_grad_reduce_kernel<<<ceil_div(n, 256), 256, 0, s>>>((const float*)ws, splits, n, dW, out_f32, accumulate);
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess && splits > 1 ? weak_grad_reduce((const float*)ws, splits, n, dW, out_f32, accumulate, s) : e;
+}
+hipError_t weak_grad_reduce(const float* part, int splits, int64_t n, void* dW, int out_f32, int accumulate, hipStream_t s) {
+    weak_grad_reduce_kernel<<<ceil_div(n, 256), 256, 0, s>>>(part, splits, n, dW, out_f32, accumulate);
     return hipGetLastError();
 }
 
-// dX and dW_weak of one layer in one launch (see gemm_dx_dw_kernel); false when the shapes do not fit both
-// register kernels (the caller then makes the two calls one after the other).
+// dX and dW_weak of one layer in one launch (see gemm_dx_dw_kernel), for layers the register kernel takes.
 // Taken when the weak block is one strip wide (k <= 128).  The strips follow the tiles in the grid, so they start on
 // whichever compute units finish their last tile first: in the idle part of a partly empty last round, or, when the
 // tiles fill their rounds, in the few microseconds by which the tiles' ends differ.  Inside the combined launch a strip
@@ -1691,28 +1497,19 @@ hipError_t weak_grad_mfma(int oc, int k, const __half* dY, int64_t M, int64_t ld
 // 4096 x 4096 (256 tiles) 165 -> 163, 4096 x 11008 (688 tiles) 363 -> 350, 5120 x 5120 281 -> 262, 13824 x 5120
 // 699 -> 670; with a 256-wide weak block (two half strips per strip of channels) 8192 x 8192 at M = 2048 257 -> 252
 // but 28672 x 8192 862 -> 877.
-bool gemm_dx_dw_supported(const Layer& L, int64_t M) {
-    return gemm_dx_supported(L, M) && L.oc % BK == 0 && L.kq % 128 == 0 && L.k % 8 == 0 && L.k > 0 && L.k <= 128 &&
-           weak_grad_mfma_supported(L.oc, L.k, M);
-}
+static bool gemm_dx_dw_preferred(const Layer& L, const Strips& S) { return L.k > 0 && S.k <= 128; }
 
-hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, const __half* Xw,
-                      int64_t ldxw, void* dW, int out_f32, int accumulate, void* ws, hipStream_t s) {
+static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, const Strips& S, hipStream_t s) {
     const int tiles = ceil_div(L.ic, BT) * ceil_div(M, BT), n_dx = xcd_grid(tiles);
-    int splits, chunk;
-    const int64_t n = (int64_t)L.oc * L.k;
-    weak_grad_strip_split(L.oc, L.k, M, splits, chunk);
-    static bool attr = false;
+    static bool attr[2] = {};
     constexpr int LDS_BYTES = DX_LDS > WG_LDS ? DX_LDS : WG_LDS;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void*)gemm_dx_dw_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+    const auto kern = L.once ? gemm_dx_dw_kernel<true> : gemm_dx_dw_kernel<false>;
+    if (!attr[L.once]) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
-        attr = true;
+        attr[L.once] = true;
     }
-    const int n_dw = ceil_div(L.oc, WG_OC) * ceil_div(L.k, 128) * splits;
-    gemm_dx_dw_kernel<<<n_dx + n_dw, 256, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, ceil_div(L.ic, BT), n_dx, Xw, ldxw, (float*)ws, splits,
-                                                         chunk, dW, out_f32, accumulate);
-    if (splits > 1) weak_grad_reduce_kernel<<<ceil_div(n, 256), 256, 0, s>>>((const float*)ws, splits, n, dW, out_f32, accumulate);
+    kern<<<n_dx + S.n, 256, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, ceil_div(L.ic, BT), n_dx, S);
     return hipGetLastError();
 }
 

@@ -25,6 +25,7 @@
 
 #include "gemm_common.h"
 #include "qeft_internal.h"
+#include "weak_strip.h"
 
 namespace qeft {
 using namespace gemm;
@@ -407,10 +408,17 @@ __global__ __launch_bounds__(128 * KW, MINW) void fwd_tile_kernel(Layer L, const
 // vectors.  A tile is either quantized or weak, whatever Kq (the GEMM of gemm.hip
 // puts a partial group and weak columns into one tile and then takes its LDS-staged form); weak ones read fp16 with the 16-bit form.
 // RAGGED: OC is no multiple of 64.
+// D: strips of the weak gradient behind the tiles (the one-call backward), on CUs that have no tile or are done with theirs.  The whole backward, two
+// launches -> one, us: 1024 x 8192 at M = 128 17 -> 12; 2048 x 3000 with 16 weak columns at 128 / 1000 23 / 37 -> 17 / 32; 5120 x 5120 with 64 at 333 / 777
+// 49 / 104 -> 41 / 94.
 template <int J, int KW, int MINW, bool ONCE, bool RAGGED>
 __global__ __launch_bounds__(128 * KW, MINW) void dx_tile_kernel(Layer L, const __half* __restrict__ dY, int M, int64_t lddy,
-                                                                __half* __restrict__ dX, int64_t lddx, int tiles_n, int tiles_m) {
+                                                                __half* __restrict__ dX, int64_t lddx, int tiles_n, int tiles_m, Strips D) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    if ((int)blockIdx.x >= (int)gridDim.x - D.n) {   // behind the tiles: a strip of the weak gradient, by four waves
+        if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < 4) weak_grad_strip(lds, (int)blockIdx.x - ((int)gridDim.x - D.n), D);
+        return;
+    }
     constexpr int DX = 2;
     using Rows = RowTile<J, DX>;
     constexpr int NX = Rows::NX, XT = Rows::XT, S = 2 * J;
@@ -706,19 +714,21 @@ hipError_t launch_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, _
 }
 
 template <int J, int KW, int MINW, bool ONCE, bool RAGGED>
-hipError_t launch_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s) {
+hipError_t launch_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s, WeakGrad* g) {
     static bool attr = false;
     constexpr int XT = 32 * J * 128, QL = KW * (2 * XT + 2 * 4096 + 2 * (ONCE ? 384 : 256)), WL = KW * 2 * (XT / 2 + 32 * 272);
     constexpr int A = QL > WL ? QL : WL, LDS_BYTES = A > finish_lds<J, KW>() ? A : finish_lds<J, KW>();
-    static_assert(LDS_BYTES <= 160 * 1024, "");
+    static_assert(LDS_BYTES <= 160 * 1024 && LDS_BYTES >= WG_LDS, "");
     if (!attr) {
         hipError_t e = hipFuncSetAttribute((const void*)dx_tile_kernel<J, KW, MINW, ONCE, RAGGED>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
         attr = true;
     }
     const int tn = dx_tiles(L), tm = ceil_div(M, 32 * J);
-    dx_tile_kernel<J, KW, MINW, ONCE, RAGGED><<<xcd_grid(tn * tm), 128 * KW, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, tn, tm);
-    return hipGetLastError();
+    const Strips D = make_strips(g, dY, M, lddy, g ? g->used : 0);
+    dx_tile_kernel<J, KW, MINW, ONCE, RAGGED><<<xcd_grid(tn * tm) + D.n, 128 * KW, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, tn, tm, D);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? finish_strips(g, D, s) : e;
 }
 
 }  // namespace
@@ -824,12 +834,12 @@ hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __h
     if (L.once) return two ? launch_fwd<2, 2, 2, true>(L, X, M, ldx, Y, ldy, s) : launch_fwd<4, 2, 1, true>(L, X, M, ldx, Y, ldy, s);
     return two ? launch_fwd<2, 2, 2, false>(L, X, M, ldx, Y, ldy, s) : launch_fwd<4, 2, 1, false>(L, X, M, ldx, Y, ldy, s);
 }
-hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s) {
-    using Launch = hipError_t (*)(const Layer&, const __half*, int64_t, int64_t, __half*, int64_t, hipStream_t);
+hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s, WeakGrad* g) {
+    using Launch = hipError_t (*)(const Layer&, const __half*, int64_t, int64_t, __half*, int64_t, hipStream_t, WeakGrad*);
 #define QEFT_DX(O, R) {launch_dx<2, 4, 2, O, R>, launch_dx<4, 2, 1, O, R>}
     static const Launch table[2][2][2] = {{QEFT_DX(false, false), QEFT_DX(false, true)}, {QEFT_DX(true, false), QEFT_DX(true, true)}};
 #undef QEFT_DX
-    return table[L.once ? 1 : 0][L.oc % 64 != 0 ? 1 : 0][est_dx(L, M).j == 2 ? 0 : 1](L, dY, M, lddy, dX, lddx, s);
+    return table[L.once ? 1 : 0][L.oc % 64 != 0 ? 1 : 0][est_dx(L, M).j == 2 ? 0 : 1](L, dY, M, lddy, dX, lddx, s, g);
 }
 
 }  // namespace qeft

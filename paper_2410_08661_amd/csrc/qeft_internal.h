@@ -111,6 +111,19 @@ bool fwd_mid_few_preferred(const Layer& L, int64_t M, int64_t ldx, int tiles);
 bool fwd_mid3_preferred(const Layer& L, int64_t M, int64_t ldx);     // a 3-bit layer's codes as they are, rather than a copy in the caller's workspace
 hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t ldx, __half* const* Y, const int64_t* ldy, hipStream_t s);
 
+// A weak-block gradient to take along with an input gradient, where the kernels chosen for that have room for it beside their own work (done is
+// set then).  ws: the caller's workspace, its first `used` bytes taken.
+struct WeakGrad {
+    int oc, k;
+    const __half* Xw;
+    int64_t ldxw;
+    void* dW;
+    int out_f32, accumulate;
+    unsigned char* ws;
+    size_t ws_bytes, used;
+    bool done;
+};
+
 // ---- forward and input gradient in tiles of 128 channels x 64 / 128 rows (gemm_tile.hip) for layers the GEMMs below support.
 // split_ws: the caller's workspace holds the partial tiles of the GEMM's split ----
 bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws);
@@ -120,7 +133,7 @@ bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws);
 bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx, bool split_n, bool split_d);
 bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy, bool split_n, bool split_d);
 hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s);
-hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s);
+hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s, WeakGrad* g = nullptr);
 
 // ---- prefill / fine-tune path: MFMA GEMMs (gemm.hip) ---------------------------------------
 bool gemm_fwd_supported(const Layer& L, int64_t M);
@@ -136,16 +149,14 @@ struct GemmSplit {
 GemmSplit gemm_fwd_split(const Layer& L, int64_t M);
 GemmSplit gemm_dx_split(const Layer& L, int64_t M);
 bool gemm_dx_supported(const Layer& L, int64_t M);
-hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s);
+hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s, WeakGrad* g = nullptr);
 size_t gemm_dx_split_workspace(const Layer& L, int64_t M);
 bool weak_grad_mfma_supported(int oc, int k, int64_t M);
 size_t weak_grad_mfma_workspace(int oc, int k, int64_t M);
 hipError_t weak_grad_mfma(int oc, int k, const __half* dY, int64_t M, int64_t lddy, const __half* Xw, int64_t ldxw,
                           void* dW, int out_f32, int accumulate, void* ws, hipStream_t s);
 
-// input gradient and weak-block gradient of one layer in one launch (ws: the weak gradient's workspace)
-bool gemm_dx_dw_supported(const Layer& L, int64_t M);
-hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, const __half* Xw,
-                      int64_t ldxw, void* dW, int out_f32, int accumulate, void* ws, hipStream_t s);
+// dW = the sum of the strips' partial slabs, in their order
+hipError_t weak_grad_reduce(const float* part, int splits, int64_t n, void* dW, int out_f32, int accumulate, hipStream_t s);
 
 }  // namespace qeft

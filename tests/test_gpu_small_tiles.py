@@ -108,3 +108,29 @@ def test_fractional_zero_points():
     torch.cuda.synchronize()
     assert_close(y.cpu().numpy(), qo.linear_fwd(layer.w64, x), "forward")
     assert_close(dx.cpu().numpy(), qo.linear_bwd_dx(layer.w64, dy), "input gradient")
+
+
+@pytest.mark.parametrize("oc,ic,k,bits", [(264, 1160, 72, 4), (4104, 712, 8, 4), (2048, 2048 + 128, 128, 4), (1024, 8192, 256, 4), (1024, 1152, 128, 3), (2560, 2048, 64, 3)])
+@pytest.mark.parametrize("m", [64, 130, 520, 1000])
+def test_backward_takes_the_weak_gradient_along(m, oc, ic, k, bits):
+    """The weak gradient's strips behind the tiles of dX, or beside the sum of a split's partial tiles, with and without slabs of their own and
+    room for them: bit for bit the two calls, nothing written past the workspace.  (The calls' own values are checked elsewhere.)"""
+    layer = HostLayer(oc, ic, k, bits, 128, seed=oc + m)
+    w, d = layer.to_device(), layer.desc
+    dy, x = (pad_cols(a)[0] for a in (synth.make_grad_output(m, oc, m), synth.make_activations(m, ic, k, m)))
+    xw = x[:, ic - k:].contiguous()
+    sizes = [B.qeft_workspace_bytes(d, op, m) for op in (B.QEFT_OP_WEAK_GRAD, B.QEFT_OP_BWD, B.QEFT_OP_BWD_DX)]
+    for n in sorted({sizes[0], sizes[1], sizes[1] + sizes[0] + 16}):
+        if bits == 3 and n < sizes[2]:
+            continue                               # (the general kernel)
+        ws = torch.full((n + 64,), 171, dtype=torch.uint8, device="cuda")
+        want_dx = B.qeft_linear_bwd_dx(d, w, dy, ws=torch.empty(sizes[2], dtype=torch.uint8, device="cuda") if n >= sizes[2] > 0 else False)
+        for accumulate in (False, True):
+            want = torch.full((oc, k), 0.5, dtype=torch.float32, device="cuda")
+            got = want.clone()
+            B.qeft_weak_grad(d, dy, xw, want, accumulate=accumulate)
+            dx, _ = B.qeft_linear_bwd(d, w, dy, xw, dW=got, accumulate=accumulate, ws=ws[:n])
+            torch.cuda.synchronize()
+            assert torch.equal(got, want), f"dW, {n} bytes"
+            assert torch.equal(dx, want_dx), f"dX, {n} bytes"
+            assert bool((ws[n:] == 171).all())
