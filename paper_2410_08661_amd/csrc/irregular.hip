@@ -14,7 +14,7 @@ namespace qeft {
 namespace {
 
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-typedef int i4 __attribute__((ext_vector_type(4)));
+typedef int i2 __attribute__((ext_vector_type(2)));
 
 // A workgroup takes whole rows, one after the other: the row is copied into LDS with 16-byte
 // loads, then every thread assembles 8 stored columns from 2-byte LDS reads through the table
@@ -72,92 +72,91 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(const unsigned short*
     }
 }
 
-// Rows of up to 8 K channels: the same, with this thread's table entries held in registers for all rows of
-// the workgroup (NC chunks of 8 columns per thread), two row buffers so that one barrier per row suffices,
-// and the next row's 16-byte loads in flight while the current one is assembled.
-template <int NC>
-__global__ __launch_bounds__(256) void gather_rows_reg_kernel(const unsigned short* __restrict__ X, int M, int64_t ldx,
-                                                              const int* __restrict__ perm, int ic, int chunks,
-                                                              unsigned short* __restrict__ Xs, int64_t lds_, int rows_per_wg) {
-    extern __shared__ __attribute__((aligned(16))) unsigned short rowbuf[];   // [2][8 * chunks]
-    const int pitch = 8 * chunks;
-    int p[NC][8];
+// Rows of up to 8 K channels (a multiple of 8): the same, with this thread's table entries held in registers for all rows of the
+// workgroup, two row buffers so that one barrier per row suffices, and the next row's loads in flight while the current one is
+// assembled.  A thread owns pairs of neighbouring stored columns, 256 pairs apart: neighbouring lanes then meet neighbouring banks where the
+// table ascends (eight columns per thread had eight lanes on one), and the table comes as 8-byte loads beside the first row's.
+// Bound by latency at a few hundred rows - table and row, LDS, stores - hence a row or two per workgroup there.
+// us, eight columns per thread and up to eight rows per workgroup -> now: gather / scatter of 777 x 4096 6.8 / 6.7 -> 4.4 / 4.3, 1024 x 8192 12.0 / 16.8 ->
+// 6.8 / 9.6, 4096 x 4096 15.3 / 18.1 -> 10.9 / 15.0 (67 MB: 6.1 / 4.5 TB/s), 4096 x 8192 28.7 / 31.7 -> 21.6 / 22.6; 100 x 5120 5.6 / 6.0 -> 4.3 / 3.2.
+// ND: pairs per thread; NC: 16-byte chunks of a row per thread.
+template <int ND>
+__device__ __forceinline__ void load_table(const int* __restrict__ perm, int ic, uint32_t (&p)[ND]) {   // two byte offsets within a row (ic <= 8192)
 #pragma unroll
-    for (int i = 0; i < NC; ++i) {
-        const int c = threadIdx.x + 256 * i;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int j = 8 * c + e;
-            p[i][e] = j < ic ? min(max(perm[j], 0), ic - 1) : -1;
-        }
+    for (int i = 0; i < ND; ++i) {
+        const i2 v = *reinterpret_cast<const i2*>(perm + min(2 * ((int)threadIdx.x + 256 * i), ic - 2));
+        p[i] = (uint32_t)(2 * min(max(v.x, 0), ic - 1)) | ((uint32_t)(2 * min(max(v.y, 0), ic - 1)) << 16);
     }
+}
+
+template <int ND>
+__global__ __launch_bounds__(256) void gather_rows_reg_kernel(const unsigned short* __restrict__ X, int M, int64_t ldx,
+                                                              const int* __restrict__ perm, int ic,
+                                                              unsigned short* __restrict__ Xs, int64_t lds_, int rows_per_wg) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char rowbytes[];   // [2][2 ic]
+    constexpr int NC = (ND + 3) / 4;
+    const int chunks = ic >> 3, pairs = ic >> 1;
     const int m0 = blockIdx.x * rows_per_wg, m1 = min(m0 + rows_per_wg, M);
     u4 nxt[NC];
-    auto fetch = [&](int m) {   // chunk indices are clamped, not tested: the loads stay straight-line (ldx >= 8 * chunks)
+    auto fetch = [&](int m) {   // chunk indices are clamped, not tested: the loads stay straight-line
         const unsigned short* row = X + (size_t)m * ldx;
 #pragma unroll
         for (int i = 0; i < NC; ++i) nxt[i] = *reinterpret_cast<const u4*>(row + 8 * min((int)threadIdx.x + 256 * i, chunks - 1));
     };
-    if (m0 < m1) fetch(m0);
+    fetch(m0);
+    uint32_t p[ND];
+    load_table(perm, ic, p);
     for (int m = m0; m < m1; ++m) {
-        unsigned short* buf = rowbuf + ((m - m0) & 1) * pitch;
+        unsigned char* buf = rowbytes + ((m - m0) & 1) * 2 * ic;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
             const int c = threadIdx.x + 256 * i;
-            if (c < chunks) *reinterpret_cast<u4*>(buf + 8 * c) = nxt[i];
+            if (c < chunks) *reinterpret_cast<u4*>(buf + 16 * c) = nxt[i];
         }
         fetch(min(m + 1, m1 - 1));
         __syncthreads();
+        uint32_t* out = reinterpret_cast<uint32_t*>(Xs + (size_t)m * lds_);
 #pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            const int c = threadIdx.x + 256 * i;
-            if (c < chunks) {
-                uint32_t v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = p[i][e] >= 0 ? buf[p[i][e]] : 0u;
-                *reinterpret_cast<u4*>(Xs + (size_t)m * lds_ + 8 * c) = u4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
-            }
+        for (int i = 0; i < ND; ++i) {
+            const int d = threadIdx.x + 256 * i;
+            const uint32_t lo = *reinterpret_cast<const unsigned short*>(buf + (p[i] & 0xffffu)), hi = *reinterpret_cast<const unsigned short*>(buf + (p[i] >> 16));
+            if (d < pairs) out[d] = lo | (hi << 16);
         }
         // the buffer written two rows later is this one: every thread passes the next row's barrier first
     }
 }
 
-template <int NC>
+template <int ND>
 __global__ __launch_bounds__(256) void scatter_rows_reg_kernel(const unsigned short* __restrict__ Ds, int M, int64_t ldd,
-                                                               const int* __restrict__ perm, int ic, int chunks,
+                                                               const int* __restrict__ perm, int ic,
                                                                unsigned short* __restrict__ dX, int64_t lddx, int rows_per_wg) {
-    extern __shared__ __attribute__((aligned(16))) unsigned short rowbuf[];   // [2][8 * chunks]
-    const int pitch = 8 * chunks, full = ic >> 3;
-    int p[NC][8];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-        const int c = threadIdx.x + 256 * i;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int j = 8 * c + e;
-            p[i][e] = j < ic ? min(max(perm[j], 0), ic - 1) : -1;
-        }
-    }
+    extern __shared__ __attribute__((aligned(16))) unsigned char rowbytes[];   // [2][2 ic]
+    const int chunks = ic >> 3, pairs = ic >> 1;
     const int m0 = blockIdx.x * rows_per_wg, m1 = min(m0 + rows_per_wg, M);
-    u4 nxt[NC];
+    uint32_t nxt[ND];
     auto fetch = [&](int m) {
-        const unsigned short* row = Ds + (size_t)m * ldd;
+        const uint32_t* row = reinterpret_cast<const uint32_t*>(Ds + (size_t)m * ldd);
 #pragma unroll
-        for (int i = 0; i < NC; ++i) nxt[i] = *reinterpret_cast<const u4*>(row + 8 * min((int)threadIdx.x + 256 * i, chunks - 1));
+        for (int i = 0; i < ND; ++i) nxt[i] = row[min((int)threadIdx.x + 256 * i, pairs - 1)];
     };
-    if (m0 < m1) fetch(m0);
+    fetch(m0);
+    uint32_t p[ND];
+    load_table(perm, ic, p);
     for (int m = m0; m < m1; ++m) {
-        unsigned short* buf = rowbuf + ((m - m0) & 1) * pitch;
+        unsigned char* buf = rowbytes + ((m - m0) & 1) * 2 * ic;
         unsigned short* row = dX + (size_t)m * lddx;
 #pragma unroll
-        for (int i = 0; i < NC; ++i)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (p[i][e] >= 0) buf[p[i][e]] = (unsigned short)(nxt[i][e >> 1] >> (16 * (e & 1)));
+        for (int i = 0; i < ND; ++i) {   // (pairs past the row's last repeat it)
+            *reinterpret_cast<unsigned short*>(buf + (p[i] & 0xffffu)) = (unsigned short)nxt[i];
+            *reinterpret_cast<unsigned short*>(buf + (p[i] >> 16)) = (unsigned short)(nxt[i] >> 16);
+        }
         fetch(min(m + 1, m1 - 1));
         __syncthreads();
-        for (int c = threadIdx.x; c < full; c += 256) *reinterpret_cast<u4*>(row + 8 * c) = *reinterpret_cast<const u4*>(buf + 8 * c);
-        for (int j = 8 * full + threadIdx.x; j < ic; j += 256) row[j] = buf[j];
+#pragma unroll
+        for (int i = 0; i < (ND + 3) / 4; ++i) {
+            const int c = threadIdx.x + 256 * i;
+            if (c < chunks) *reinterpret_cast<u4*>(row + 8 * c) = *reinterpret_cast<const u4*>(buf + 16 * c);
+        }
     }
 }
 
@@ -198,6 +197,8 @@ __global__ __launch_bounds__(256) void scatter_cols_kernel(const unsigned short*
     }
 }
 
+inline int reg_rows_per_wg(int64_t M) { return M >= 4096 ? 4 : (M >= 1024 ? 2 : 1); }
+
 // rows per workgroup: enough workgroups for every CU a few times over, whole rows each
 inline int rows_per_wg(int64_t M) { return M >= 4096 ? 4 : (M >= 1024 ? 2 : 1); }
 
@@ -208,11 +209,10 @@ size_t irregular_workspace(int ic, int64_t M) { return (size_t)M * (size_t)((ic 
 hipError_t gather_cols(const __half* X, int64_t M, int64_t ldx, const int* perm, int ic, __half* Xs, int64_t ldo, hipStream_t s) {
     const int chunks = (ic + 7) / 8;   // ldo >= 8 * chunks, a multiple of 8
     const int row_bytes = chunks * 16;
-    if (chunks <= 1024 && (ic & 7) == 0 && (ldx & 7) == 0 && ((uintptr_t)X & 15) == 0) {   // whole 16-byte chunks only: no read past a row's IC elements
-        const int rw = M >= 2048 ? 8 : (M >= 512 ? 4 : 1);   // table entries are fetched once per workgroup: several rows each
-        const int nc = ceil_div(chunks, 256);
-        auto kern = nc <= 1 ? gather_rows_reg_kernel<1> : (nc <= 2 ? gather_rows_reg_kernel<2> : gather_rows_reg_kernel<4>);
-        kern<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)X, (int)M, ldx, perm, ic, chunks, (unsigned short*)Xs, ldo, rw);
+    if (chunks <= 1024 && (ic & 7) == 0 && (ldx & 7) == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)perm & 7) == 0) {   // whole 16-byte chunks only: no read past a row's IC elements
+        const int rw = reg_rows_per_wg(M);
+        auto kern = ic <= 1024 ? gather_rows_reg_kernel<2> : (ic <= 2048 ? gather_rows_reg_kernel<4> : (ic <= 4096 ? gather_rows_reg_kernel<8> : gather_rows_reg_kernel<16>));
+        kern<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)X, (int)M, ldx, perm, ic, (unsigned short*)Xs, ldo, rw);
         return hipGetLastError();
     }
     if (row_bytes <= ROW_LDS_MAX && (ldx & 7) == 0 && ((uintptr_t)X & 15) == 0) {
@@ -230,12 +230,10 @@ hipError_t gather_cols(const __half* X, int64_t M, int64_t ldx, const int* perm,
 hipError_t scatter_cols(const __half* Ds, int64_t M, const int* perm, int ic, __half* dX, int64_t lddx, hipStream_t s) {
     const int chunks = (ic + 7) / 8;
     const int row_bytes = chunks * 16;
-    if (chunks <= 1024 && (lddx & 7) == 0 && ((uintptr_t)dX & 15) == 0) {
-        const int rw = M >= 2048 ? 8 : (M >= 512 ? 4 : 1);
-        const int nc = ceil_div(chunks, 256);
-        auto kern = nc <= 1 ? scatter_rows_reg_kernel<1> : (nc <= 2 ? scatter_rows_reg_kernel<2> : scatter_rows_reg_kernel<4>);
-        kern<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)Ds, (int)M, (int64_t)chunks * 8, perm, ic, chunks,
-                                                        (unsigned short*)dX, lddx, rw);
+    if (chunks <= 1024 && (ic & 7) == 0 && (lddx & 7) == 0 && ((uintptr_t)dX & 15) == 0 && ((uintptr_t)perm & 7) == 0) {
+        const int rw = reg_rows_per_wg(M);
+        auto kern = ic <= 1024 ? scatter_rows_reg_kernel<2> : (ic <= 2048 ? scatter_rows_reg_kernel<4> : (ic <= 4096 ? scatter_rows_reg_kernel<8> : scatter_rows_reg_kernel<16>));
+        kern<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)Ds, (int)M, (int64_t)chunks * 8, perm, ic, (unsigned short*)dX, lddx, rw);
         return hipGetLastError();
     }
     if (row_bytes <= ROW_LDS_MAX && (lddx & 7) == 0 && ((uintptr_t)dX & 15) == 0) {
