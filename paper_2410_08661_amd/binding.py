@@ -1,9 +1,11 @@
-"""ctypes binding of libqeft.so: the same entry points as include/qeft.h.
+"""Binding of libqeft.so: the same entry points as include/qeft.h.
 
 Argument marshalling only.  `raw` exposes the C functions as they are (integers for
 pointers), the functions below take torch tensors and pass `data_ptr()` and the current
 HIP stream.  PyTorch is used for device memory and streams, nothing else; there is no
-fallback path: if the library is missing the import fails.
+fallback path: if the library is missing the import fails.  The calls of training and decode loops
+go through `_marshal` (csrc/marshal.cpp), which does the same natively for exact tensors on
+the current GPU and returns None for anything else: ctypes then.
 """
 from __future__ import annotations
 
@@ -21,6 +23,7 @@ QEFT_ERR_WORKSPACE, QEFT_ERR_UNSUPPORTED, QEFT_ERR_HIP = -5, -6, -7
 QEFT_OP_FWD, QEFT_OP_BWD_DX, QEFT_OP_WEAK_GRAD, QEFT_OP_FWD_IRREGULAR, QEFT_OP_BWD_DX_IRREGULAR, QEFT_OP_BWD = 0, 1, 2, 3, 4, 5
 QEFT_DTYPE_F16, QEFT_DTYPE_F32 = 0, 1
 QEFT_LAYOUT_CANONICAL, QEFT_LAYOUT_DENSE3 = 0, 1
+_DTYPES = {torch.float16: QEFT_DTYPE_F16, torch.float32: QEFT_DTYPE_F32}
 
 
 class qeft_desc_t(C.Structure):
@@ -143,6 +146,20 @@ class Weight:
         return lay.qweight_bytes + lay.scales_bytes + lay.zeros_bytes + lay.weak_bytes
 
 
+def _load_marshal():
+    try:
+        from . import _marshal as m
+    except ImportError as e:
+        raise ImportError(f"{os.path.join(_HERE, '_marshal.so')} is not built or does not load: run `python -m paper_2410_08661_amd.build`") from e
+    m.init(tuple(C.cast(getattr(raw, n), C.c_void_p).value for n in (
+        "qeft_linear_fwd", "qeft_linear_fwd_group", "qeft_linear_bwd_dx", "qeft_linear_bwd", "qeft_linear_fwd_irregular",
+        "qeft_linear_bwd_dx_irregular", "qeft_weak_grad")), qeft_desc_t, Weight)
+    return m
+
+
+_native = _load_marshal()
+
+
 def qeft_pack(desc: qeft_desc_t, W: torch.Tensor, out: Weight | None = None) -> Weight:
     out = out or Weight(desc, W.device)
     ws = out.c_struct()
@@ -199,17 +216,19 @@ def _workspace(desc, op, M, device):
 def qeft_linear_fwd(desc, w: Weight, X: torch.Tensor, Y: torch.Tensor | None = None, ws=None) -> torch.Tensor:
     """ws: a uint8 device tensor of qeft_workspace_bytes(desc, QEFT_OP_FWD, M) bytes; None allocates one when the
     operation can use it (3-bit layers at M > 16), False passes none (the library then runs its general kernel)."""
-    M = X.shape[0]
     if Y is None:
-        Y = _empty_rows(M, desc.out_features, torch.float16, X.device)
+        Y = _empty_rows(X.shape[0], desc.out_features, torch.float16, X.device)
     if ws is None:
-        ws, _ = _workspace(desc, QEFT_OP_FWD, M, X.device)
+        ws, _ = _workspace(desc, QEFT_OP_FWD, X.shape[0], X.device)
     elif ws is False:
         ws = None
-    wst = w.c_struct()
-    _check(raw.qeft_linear_fwd(C.byref(desc), C.byref(wst), _ptr(X), M, X.stride(0) if M else desc.in_features,
-                               _ptr(Y), Y.stride(0) if M else desc.out_features, _ptr(ws),
-                               ws.numel() if ws is not None else 0, _stream()), "qeft_linear_fwd")
+    st = _native.linear_fwd(desc, w, X, Y, ws)
+    if st is None:
+        M, wst = X.shape[0], w.c_struct()
+        st = raw.qeft_linear_fwd(C.byref(desc), C.byref(wst), _ptr(X), M, X.stride(0) if M else desc.in_features,
+                                 _ptr(Y), Y.stride(0) if M else desc.out_features, _ptr(ws),
+                                 ws.numel() if ws is not None else 0, _stream())
+    _check(st, "qeft_linear_fwd")
     return Y
 
 
@@ -231,61 +250,68 @@ class Group:
 
 def qeft_linear_fwd_group(descs, ws, X: torch.Tensor, Ys=None, group: Group | None = None):
     """Forward of several layers that share the input X; returns the list of outputs."""
-    M = X.shape[0]
     if group is None:
         if Ys is None:
-            Ys = [_empty_rows(M, d.out_features, torch.float16, X.device) for d in descs]
+            Ys = [_empty_rows(X.shape[0], d.out_features, torch.float16, X.device) for d in descs]
         group = Group(descs, ws, Ys)
-    _check(raw.qeft_linear_fwd_group(group.n, group.descs, group.wst, _ptr(X), M,
-                                     X.stride(0) if M else group.descs[0].in_features, group.ys, group.ldy, _stream()),
-           "qeft_linear_fwd_group")
+    st = _native.linear_fwd_group(group.n, group.descs, group.wst, X, group.ys, group.ldy)
+    if st is None:
+        M = X.shape[0]
+        st = raw.qeft_linear_fwd_group(group.n, group.descs, group.wst, _ptr(X), M,
+                                       X.stride(0) if M else group.descs[0].in_features, group.ys, group.ldy, _stream())
+    _check(st, "qeft_linear_fwd_group")
     return group.Ys
 
 
 def qeft_linear_bwd_dx(desc, w: Weight, dY: torch.Tensor, dX: torch.Tensor | None = None, ws=None) -> torch.Tensor:
-    M = dY.shape[0]
     if dX is None:
-        dX = _empty_rows(M, desc.in_features, torch.float16, dY.device)
+        dX = _empty_rows(dY.shape[0], desc.in_features, torch.float16, dY.device)
     if ws is None:
-        ws, _ = _workspace(desc, QEFT_OP_BWD_DX, M, dY.device)
+        ws, _ = _workspace(desc, QEFT_OP_BWD_DX, dY.shape[0], dY.device)
     elif ws is False:
         ws = None
-    wst = w.c_struct()
-    _check(raw.qeft_linear_bwd_dx(C.byref(desc), C.byref(wst), _ptr(dY), M, dY.stride(0) if M else desc.out_features,
-                                  _ptr(dX), dX.stride(0) if M else desc.in_features, _ptr(ws),
-                                  ws.numel() if ws is not None else 0, _stream()), "qeft_linear_bwd_dx")
+    st = _native.linear_bwd_dx(desc, w, dY, dX, ws)
+    if st is None:
+        M, wst = dY.shape[0], w.c_struct()
+        st = raw.qeft_linear_bwd_dx(C.byref(desc), C.byref(wst), _ptr(dY), M, dY.stride(0) if M else desc.out_features,
+                                    _ptr(dX), dX.stride(0) if M else desc.in_features, _ptr(ws),
+                                    ws.numel() if ws is not None else 0, _stream())
+    _check(st, "qeft_linear_bwd_dx")
     return dX
 
 
 def qeft_linear_fwd_irregular(desc, w: Weight, perm: torch.Tensor, X: torch.Tensor, Y: torch.Tensor | None = None,
                               ws=None) -> torch.Tensor:
     """Forward of a layer whose weak columns stay at arbitrary channels; perm int32 [IC] on the device."""
-    M = X.shape[0]
     if Y is None:
-        Y = _empty_rows(M, desc.out_features, torch.float16, X.device)
+        Y = _empty_rows(X.shape[0], desc.out_features, torch.float16, X.device)
     if ws is None:
-        ws, _ = _workspace(desc, QEFT_OP_FWD_IRREGULAR, M, X.device)
-    wst = w.c_struct()
-    _check(raw.qeft_linear_fwd_irregular(C.byref(desc), C.byref(wst), _ptr(perm), _ptr(X), M,
-                                         X.stride(0) if M else desc.in_features, _ptr(Y),
-                                         Y.stride(0) if M else desc.out_features, _ptr(ws),
-                                         ws.numel() if ws is not None else 0, _stream()), "qeft_linear_fwd_irregular")
+        ws, _ = _workspace(desc, QEFT_OP_FWD_IRREGULAR, X.shape[0], X.device)
+    st = _native.linear_fwd_irregular(desc, w, perm, X, Y, ws)
+    if st is None:
+        M, wst = X.shape[0], w.c_struct()
+        st = raw.qeft_linear_fwd_irregular(C.byref(desc), C.byref(wst), _ptr(perm), _ptr(X), M,
+                                           X.stride(0) if M else desc.in_features, _ptr(Y),
+                                           Y.stride(0) if M else desc.out_features, _ptr(ws),
+                                           ws.numel() if ws is not None else 0, _stream())
+    _check(st, "qeft_linear_fwd_irregular")
     return Y
 
 
 def qeft_linear_bwd_dx_irregular(desc, w: Weight, perm: torch.Tensor, dY: torch.Tensor, dX: torch.Tensor | None = None,
                                  ws=None) -> torch.Tensor:
-    M = dY.shape[0]
     if dX is None:
-        dX = _empty_rows(M, desc.in_features, torch.float16, dY.device)
+        dX = _empty_rows(dY.shape[0], desc.in_features, torch.float16, dY.device)
     if ws is None:
-        ws, _ = _workspace(desc, QEFT_OP_BWD_DX_IRREGULAR, M, dY.device)
-    wst = w.c_struct()
-    _check(raw.qeft_linear_bwd_dx_irregular(C.byref(desc), C.byref(wst), _ptr(perm), _ptr(dY), M,
-                                            dY.stride(0) if M else desc.out_features, _ptr(dX),
-                                            dX.stride(0) if M else desc.in_features, _ptr(ws),
-                                            ws.numel() if ws is not None else 0, _stream()),
-           "qeft_linear_bwd_dx_irregular")
+        ws, _ = _workspace(desc, QEFT_OP_BWD_DX_IRREGULAR, dY.shape[0], dY.device)
+    st = _native.linear_bwd_dx_irregular(desc, w, perm, dY, dX, ws)
+    if st is None:
+        M, wst = dY.shape[0], w.c_struct()
+        st = raw.qeft_linear_bwd_dx_irregular(C.byref(desc), C.byref(wst), _ptr(perm), _ptr(dY), M,
+                                              dY.stride(0) if M else desc.out_features, _ptr(dX),
+                                              dX.stride(0) if M else desc.in_features, _ptr(ws),
+                                              ws.numel() if ws is not None else 0, _stream())
+    _check(st, "qeft_linear_bwd_dx_irregular")
     return dX
 
 
@@ -331,15 +357,19 @@ def qeft_merge_weak(tuned: torch.Tensor, base: torch.Tensor, target: torch.Tenso
 
 def qeft_weak_grad(desc, dY: torch.Tensor, Xw: torch.Tensor, dW: torch.Tensor | None = None, accumulate=False,
                    out_dtype=torch.float32, ws=None) -> torch.Tensor:
-    M = dY.shape[0]
     if dW is None:
         dW = torch.zeros((desc.out_features, desc.n_weak), dtype=out_dtype, device=dY.device)
-    code = {torch.float16: QEFT_DTYPE_F16, torch.float32: QEFT_DTYPE_F32}[dW.dtype]
+    code = _DTYPES[dW.dtype]
     if ws is None:
-        ws, _ = _workspace(desc, QEFT_OP_WEAK_GRAD, M, dY.device)
-    _check(raw.qeft_weak_grad(C.byref(desc), _ptr(dY), M, dY.stride(0) if M else desc.out_features, _ptr(Xw),
-                              Xw.stride(0) if M else max(desc.n_weak, 8), _ptr(dW), code, int(bool(accumulate)),
-                              _ptr(ws), ws.numel() if ws is not None else 0, _stream()), "qeft_weak_grad")
+        ws, _ = _workspace(desc, QEFT_OP_WEAK_GRAD, dY.shape[0], dY.device)
+    accumulate = int(bool(accumulate))
+    st = _native.weak_grad(desc, dY, Xw, dW, code, accumulate, ws)
+    if st is None:
+        M = dY.shape[0]
+        st = raw.qeft_weak_grad(C.byref(desc), _ptr(dY), M, dY.stride(0) if M else desc.out_features, _ptr(Xw),
+                                Xw.stride(0) if M else max(desc.n_weak, 8), _ptr(dW), code, accumulate,
+                                _ptr(ws), ws.numel() if ws is not None else 0, _stream())
+    _check(st, "qeft_weak_grad")
     return dW
 
 
@@ -347,7 +377,7 @@ def qeft_weak_grad_noalloc(desc, dY: torch.Tensor, Xw: torch.Tensor, dW: torch.T
     """qeft_weak_grad without a workspace argument: the library's own per-GPU scratch array takes the partial sums.
     dW must be given (this call allocates nothing, here or in the library)."""
     M = dY.shape[0]
-    code = {torch.float16: QEFT_DTYPE_F16, torch.float32: QEFT_DTYPE_F32}[dW.dtype]
+    code = _DTYPES[dW.dtype]
     _check(raw.qeft_weak_grad_noalloc(C.byref(desc), _ptr(dY), M, dY.stride(0) if M else desc.out_features, _ptr(Xw),
                                       Xw.stride(0) if M else max(desc.n_weak, 8), _ptr(dW), code, int(bool(accumulate)),
                                       _stream()), "qeft_weak_grad_noalloc")
@@ -358,18 +388,20 @@ def qeft_linear_bwd(desc, w: Weight, dY: torch.Tensor, Xw: torch.Tensor, dX: tor
                     dW: torch.Tensor | None = None, accumulate=False, out_dtype=torch.float32, ws=None):
     """dX and dW_weak of one layer in one call; returns (dX, dW).  ws: None allocates the weak gradient's workspace;
     a tensor of qeft_workspace_bytes(desc, QEFT_OP_BWD, M) bytes also lets dX split its rows where that pays."""
-    M = dY.shape[0]
     if dX is None:
-        dX = _empty_rows(M, desc.in_features, torch.float16, dY.device)
+        dX = _empty_rows(dY.shape[0], desc.in_features, torch.float16, dY.device)
     if dW is None:
         dW = torch.zeros((desc.out_features, desc.n_weak), dtype=out_dtype, device=dY.device)
-    code = {torch.float16: QEFT_DTYPE_F16, torch.float32: QEFT_DTYPE_F32}[dW.dtype]
+    code = _DTYPES[dW.dtype]
     if ws is None:
-        ws, _ = _workspace(desc, QEFT_OP_WEAK_GRAD, M, dY.device)
-    wst = w.c_struct()
-    _check(raw.qeft_linear_bwd(C.byref(desc), C.byref(wst), _ptr(dY), M, dY.stride(0) if M else desc.out_features, _ptr(dX),
-                               dX.stride(0) if M else desc.in_features, _ptr(Xw), Xw.stride(0) if M else max(desc.n_weak, 8),
-                               _ptr(dW), code, int(bool(accumulate)), _ptr(ws), ws.numel() if ws is not None else 0, _stream()),
-           "qeft_linear_bwd")
+        ws, _ = _workspace(desc, QEFT_OP_WEAK_GRAD, dY.shape[0], dY.device)
+    accumulate = int(bool(accumulate))
+    st = _native.linear_bwd(desc, w, dY, dX, Xw, dW, code, accumulate, ws)
+    if st is None:
+        M, wst = dY.shape[0], w.c_struct()
+        st = raw.qeft_linear_bwd(C.byref(desc), C.byref(wst), _ptr(dY), M, dY.stride(0) if M else desc.out_features, _ptr(dX),
+                                 dX.stride(0) if M else desc.in_features, _ptr(Xw), Xw.stride(0) if M else max(desc.n_weak, 8),
+                                 _ptr(dW), code, accumulate, _ptr(ws), ws.numel() if ws is not None else 0, _stream())
+    _check(st, "qeft_linear_bwd")
     return dX, dW
 

@@ -1,4 +1,4 @@
-"""Builds libqeft.so for gfx950 with hipcc (cross-compiles without a GPU).
+"""Builds libqeft.so for gfx950 with hipcc (cross-compiles without a GPU), and the host-side module between torch tensors and its calls.
 
     python -m paper_2410_08661_amd.build
 """
@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -14,6 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libqeft.so")
+MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
 
 SOURCES = ["api.hip", "generic.hip", "pack.hip", "irregular.hip", "reorder.hip", "gemv.hip", "gemv_dot.hip", "gemm.hip", "gemm_mid.hip", "gemm_tile.hip", "noalloc.hip"]
 
@@ -44,10 +46,25 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC))) if os.path.isabs(HIPCC) else "/opt/rocm"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(t, "include"), "-I", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-I", os.path.join(rocm, "include"), "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH,
+           "-L", os.path.join(t, "lib"), "-ltorch_python", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"marshal.cpp failed:\n{r.stdout}\n{r.stderr}")
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        host = ex.submit(_build_marshal)
         objs = list(ex.map(_compile, SOURCES))
+        host.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
