@@ -49,7 +49,10 @@ template <int N>
 __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14)); }
 __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-// 8 consecutive activations to the order in which the codes of a word come out of the conversion: (0,4)(1,5)(2,6)(3,7)
+// The pairs of codes of a word lie four apart, (0,4)(1,5)(2,6)(3,7), where each takes a shift and a mask (7 instructions per word).  Either the
+// activations are brought into that order - 4 instructions per 8 of a row -, or the codes into theirs, two instructions more per word: a byte of
+// the word beside the same byte of the word moved down by a code.
+__device__ __forceinline__ uint32_t neighbours(uint32_t w, uint32_t w4, int p) { return __builtin_amdgcn_perm(w4, w, 0x0c040c00u + 0x00010001u * (uint32_t)p); }
 __device__ __forceinline__ u4 permute_x(u4 v) {
     u4 r;
     r.x = __builtin_amdgcn_perm(v.z, v.x, 0x05040100u);
@@ -64,11 +67,12 @@ enum Fmt { W4 = 0, W3_DENSE = 1, W3_TEN = 2 };
 
 // Three-bit codes.  A lane's 32 columns of a group are 96 consecutive bits of a dense row: three words.  Ten codes to a word
 // (W3_TEN): columns 32 c .. + 31 start at code p = 32 c % 10 of word 32 c / 10, and p <= 8, so they lie in four words whose 30-bit
-// payloads are first joined to the same three (nine instructions, the shift 3 p the lane's own).  Each ten of the 32 codes then become
-// five pairs (i, i + 5): the upper five move up one bit, to the upper half, and every pair is a shift and a mask away; codes 30 and 31
-// are a pair of their own.  38 instructions per 32 codes where a field extract and a multiplication per pair took 50.
+// payloads are first joined to the same three (nine instructions, the shift 3 p the lane's own).  Pairs are neighbours, as the activations lie:
+// in each ten of the 32 codes the odd ones move up by 13 bits to the upper half, and every pair is a shift and a mask away; codes 30 and
+// 31 are a pair of their own.  (Pairs of codes five apart take two instructions less per 32 codes, but 15 for every 16 rows to bring the
+// activations into their order.)
 struct Codes3 {
-    uint32_t y[3], r;
+    uint32_t ya[3], yb[3], r;
     template <Fmt F>
     __device__ __forceinline__ void take(u4 w, uint32_t shift) {
         uint32_t a = w.x, b = w.y, c = w.z;
@@ -78,28 +82,20 @@ struct Codes3 {
             b = __builtin_amdgcn_alignbit(c2, c1, shift);
             c = __builtin_amdgcn_alignbit(c3, c2, shift);
         }
-        const uint32_t t1 = __builtin_amdgcn_alignbit(b, a, 30), t2 = __builtin_amdgcn_alignbit(c, b, 28), t3 = c >> 26;
-        y[0] = (a & 0xffffu) | ((a << 1) & 0xffff0000u);
-        y[1] = (t1 & 0xffffu) | ((t1 << 1) & 0xffff0000u);
-        y[2] = (t2 & 0xffffu) | ((t2 << 1) & 0xffff0000u);
+        const uint32_t t[3] = {a, __builtin_amdgcn_alignbit(b, a, 30), __builtin_amdgcn_alignbit(c, b, 28)}, t3 = c >> 26;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            ya[i] = (t[i] & 0xffffu) | ((t[i] << 13) & 0xffff0000u);   // codes 0 .. 5 of the ten
+            yb[i] = (t[i] >> 18) | ((t[i] >> 18) << 13);               // 6 .. 9
+        }
         r = t3 | (t3 << 13);
     }
-    __device__ __forceinline__ uint32_t bits(int P) const { return P == 15 ? r : (y[P / 5 < 3 ? P / 5 : 0] >> (3 * (P % 5))); }   // pair P at bits 0 .. 2 of each half
-};
-
-// 32 consecutive activations in the order of those pairs
-__device__ __forceinline__ void pair_x3(u4 (&v)[4]) {
-    uint32_t o[16];
-#pragma unroll
-    for (int P = 0; P < 15; ++P) {
-        const int lo = 10 * (P / 5) + P % 5, hi = lo + 5;
-        const uint32_t a = v[lo >> 3][(lo >> 1) & 3], b = v[hi >> 3][(hi >> 1) & 3];
-        o[P] = __builtin_amdgcn_perm(b, a, ((lo & 1) ? 0x0302u : 0x0100u) | ((hi & 1) ? 0x07060000u : 0x05040000u));
+    // codes 2 P and 2 P + 1 at bits 0 .. 2 of each half
+    __device__ __forceinline__ uint32_t bits(int P) const {
+        const int i = P / 5 < 3 ? P / 5 : 0, q = P % 5;
+        return P == 15 ? r : (q < 3 ? ya[i] >> (6 * q) : yb[i] >> (6 * (q - 3)));
     }
-    o[15] = v[3][3];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = u4{o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]};
-}
+};
 
 // bytes of LDS of a wave, without the parameters
 constexpr int mid_piece(int MT, int NT, bool codes) {
@@ -135,6 +131,7 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
     // the widest tile has no registers for an offset per request: taken from the first row's each time (kept, they went to scratch memory
     // and came back behind waits for the rows just requested)
     constexpr bool LEAN = MT * NT == 12;
+    constexpr bool AS_THEY_LIE = F != W4 || 2 * MT > NT;   // the activations stay in column order
     const int lane = threadIdx.x & 63;
     const int KS = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -328,13 +325,11 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
                     for (int a = 0; a < MT; ++a) xa[a][q] = live ? xa[a][q] : u4{0u, 0u, 0u, 0u};
                 }
             }
+            if constexpr (!AS_THEY_LIE) {
 #pragma unroll
-            for (int a = 0; a < MT; ++a) {
-                if constexpr (F != W4) pair_x3(xa[a]);
-                else {
+                for (int a = 0; a < MT; ++a)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) xa[a][q] = permute_x(xa[a][q]);
-                }
             }
             f4 sx[MT];
 #pragma unroll
@@ -353,10 +348,10 @@ __global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
                 if constexpr (F != W4) c3.take<F>(w, wshift);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const uint32_t wi = w[q];
+                    const uint32_t wi = w[q], w4 = wi >> 4;
                     u4 c;
 #pragma unroll
-                    for (int p = 0; p < 4; ++p) c[p] = ((F == W4 ? wi >> (4 * p) : c3.bits(4 * q + p)) & mask) | magic;
+                    for (int p = 0; p < 4; ++p) c[p] = ((F != W4 ? c3.bits(4 * q + p) : (AS_THEY_LIE ? neighbours(wi, w4, p) : wi >> (4 * p))) & mask) | magic;
 #pragma unroll
                     for (int a = 0; a < MT; ++a) tmp[a] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(xa[a][q]), as_h8(c), tmp[a], 0, 0, 0);
                 }
