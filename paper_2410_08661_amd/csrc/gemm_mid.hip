@@ -121,8 +121,9 @@ struct MidArgs {
 // One workgroup: 16 NT channels x 16 MT rows of Y over the whole contraction, which its KS waves divide; the partial tiles
 // meet in LDS at the end (fp32, fixed order).
 // XR: requests of activations per group, 4 rows each (MT = 1: as many as there are rows; else all of the tile's).
+constexpr int mid_waves(int MT, int NT) { return MT == 1 && NT == 1 ? 12 : 8; }   // the most waves of a workgroup
 template <int MT, int NT, Fmt F, int XR>
-__global__ __launch_bounds__(512) void fwd_mid_kernel(MidArgs A) {
+__global__ __launch_bounds__(64 * mid_waves(MT, NT)) void fwd_mid_kernel(MidArgs A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int XB = MT * 4096;                        // a wave's piece of LDS: a group of activations, (4-bit) the codes of two groups,
     constexpr int WB = mid_piece(MT, NT, F == W4);       // (at the end a partial tile),
@@ -628,7 +629,7 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
     };
     // A grid is counted in threads, in 32 bits, and a larger one runs in part only, without an error: more rows than fit with the narrowest
     // tiles and most waves go in several launches (3-bit layers without a workspace, results of 13 GB and more)
-    const int64_t most = 48 * (((int64_t)0xffffffff / 512 - 8) / tiles_at(1));
+    const int64_t most = 48 * (((int64_t)0xffffffff / 768 - 8) / tiles_at(1));
     if (M > most) {
         for (int64_t m0 = 0; m0 < M; m0 += most) {
             __half* ys[MAX_GROUP];
@@ -644,6 +645,10 @@ hipError_t fwd_mid(const Layer* Ls, int n, const __half* X, int64_t M, int64_t l
         KS = 4;
         NT = tiles_at(3) * tiles_m <= 512 ? 3 : 4;
     }
+    // (up to 8 rows, one narrow tile per CU and many groups: a third wave on each SIMD.  us, the 7B block in 4 / 3 bits, the down projection with eight waves / twelve: M = 2 41.6 /
+    // 41.1 and 44.4 / 44.1, M = 8 43.7 / 42.9 and 46.8 / 46.5; 3000 x 12000 at 8 8.1 / 7.8; from 16 rows on no better: M = 16 48.6 / 48.7, 2048 x 16384 in 3 bits at 30
+    // 16.4 / 17.4; sixteen waves no better than twelve, 4096 x 4096 at 8 6.6 / 6.7)
+    if (NT == 1 && KS == 8 && M <= 8 && L.ng >= 64) KS = 12;
     const bool w4 = L.bits == 4;
     const int pairs = (L.ng + 1) / 2, weak = ceil_div(L.k, 32);   // (a wave's least share is two groups, or 32 weak columns)
     // Few pairs leave waves without one, or LDS three waves of four: two waves instead, of which a CU holds four workgroups - three of the widest tile - and the

@@ -259,3 +259,17 @@ def test_hundreds_of_rows_of_small_layers(oc, ic, k, m):
         assert torch.equal(y, plain)
     assert bool((back[0] == 7).all()) and bool((back[m + 1] == 7).all()) and bool((back[:, oc:] == 7).all())
     assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"M={m}")
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("oc,kq,k", [(72, 64 * 128, 8), (4096, 75 * 128 + 72, 72), (264, 64 * 128 - 8, 0)])
+def test_few_rows_of_many_groups(oc, kq, k, bits):
+    """Twelve waves, of which the last have a pair of groups less, one group of a pair or none in the last turn."""
+    layer = HostLayer(oc, kq + k, k, bits, 128, seed=oc)
+    w, w64 = layer.to_device(), torch.from_numpy(layer.w64).cuda()
+    for m in (2, 4, 5, 8, 9):
+        xd = pad_cols(synth.make_activations(m, layer.ic, k, seed=m))[0]
+        y = B.qeft_linear_fwd(layer.desc, w, xd, ws=False)
+        ref = xd.double() @ w64.t()
+        torch.cuda.synchronize()
+        assert_close(y.cpu().numpy(), ref.cpu().numpy(), f"{oc} channels, M={m}")
