@@ -17,7 +17,7 @@ BUILD_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libqeft.so")
 MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
 
-SOURCES = ["api.hip", "generic.hip", "pack.hip", "irregular.hip", "reorder.hip", "gemv.hip", "gemv_dot.hip", "gemm.hip", "gemm_mid.hip", "gemm_tile.hip", "noalloc.hip"]
+SOURCES = ["api.hip", "generic.hip", "pack.hip", "irregular.hip", "reorder.hip", "gemv.hip", "gemv_dot.hip", "gemm.hip", "gemm_mid.hip", "gemm_tile.hip", "dx_panel.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -133,6 +133,7 @@ hipError_t fwd_rows(const Layer& L, const __half* x, int64_t M, int64_t ldx, __h
     return gemm_fwd(L, x, M, ldx, y, ldy, split_ws, s);
 }
 hipError_t dx_rows(const Layer& L, const __half* dy, int64_t M, int64_t lddy, __half* dx, int64_t lddx, void* split_ws, hipStream_t s, WeakGrad* g) {
+    if (dx_panel_preferred(L, M, lddy, split_ws != nullptr)) return dx_panel(L, dy, M, lddy, dx, lddx, s, g);
     if (dx_tile_preferred(L, M, lddy, split_ws != nullptr)) return dx_tile(L, dy, M, lddy, dx, lddx, s, g);
     return gemm_dx(L, dy, M, lddy, dx, lddx, split_ws, s, g);
 }

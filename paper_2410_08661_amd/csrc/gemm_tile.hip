@@ -798,6 +798,18 @@ bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
     return est_dx(L, M).t < 0.95 * est_gemm(L.ic, M, ceil_div(L.oc, 64), 1.3) * (L.kq % 128 == 0 && L.oc % 64 == 0 ? 1.0 : 3.3);
 }
 
+// The panel kernel for few rows, where its estimate is 10 % ahead of what would run otherwise (32-bit offsets as above).  Callers that give the room for
+// a split of more than 256 rows keep the split's arithmetic (2048 x 1152 at 512 rows: 21 us, 12 by panels).
+bool dx_panel_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
+    if (L.ng <= 0 || M <= 16 || lddy > (QEFT_MAX_DIM >> 1)) return false;
+    const GemmSplit p = split_ws ? gemm_dx_split(L, M) : GemmSplit{1, 0, 0, false};
+    if (p.splits > 1 && M > 256) return false;
+    double other = est_dx(L, M).t;
+    if (!dx_tile_preferred(L, M, lddy, split_ws))
+        other = p.splits > 1 && !p.tail ? est_split(p, 12, 1.5) : est_gemm(L.ic, M, ceil_div(L.oc, 64), 1.3) * (L.kq % 128 == 0 && L.oc % 64 == 0 ? 1.0 : 3.3);
+    return dx_panel_estimate(L, M) < 0.9 * other;
+}
+
 // A 3-bit layer whose quantized columns are not whole stages (forward: 64 columns) or whole groups (input gradient): its 4-bit copy
 // N has the kernels above but not the register GEMM, which its fp16 copy D always has, with a split where there is room.  Either
 // way's time is the kernel's estimate and the copy's pass (and, for D, four times the weights to read), fitted to both ways of 190
@@ -818,7 +830,7 @@ bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx,
     return est_fwd(N, M).t + 0.2 * n + 3.5 < 0.94 * t16;
 }
 bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy, bool split_n, bool split_d) {
-    if (N.kq % 128 == 0 && N.oc % 64 == 0) return true;
+    if ((N.kq % 128 == 0 && N.oc % 64 == 0) || dx_panel_preferred(N, M, lddy, split_n)) return true;
     if (!dx_tile_preferred(N, M, lddy, split_n)) return false;
     const GemmSplit p = split_d ? gemm_dx_split(D, M) : GemmSplit{1, 0, 0, false};
     const double rounds = (int64_t)dx_tiles(N) * ceil_div(M, 64) > 512 ? 1.25 : 1.0, n = (double)N.oc * N.ic / (1 << 20);   // (a third round of tiles is underestimated)
