@@ -1,5 +1,5 @@
 // Input gradient of 4-bit layers (and 4-bit copies of 3-bit ones) for few rows: fine-tuning steps of some ten to some hundred tokens
-// (paper Sec. 3.3).  Tiles of 32 or 64 channels x 32 or 64 rows, so that a layer's few thousand channels occupy the CUs without a workspace: tiles of 128
+// (paper Sec. 3.3).  Tiles of 32 or 64 channels x 32, 64 or 128 rows, so that a layer's few thousand channels occupy the CUs without a workspace: tiles of 128
 // channels leave 33 workgroups for 64 rows of a 4096-wide layer, and a split of 256 x 256 tiles multiplies three quarters of padding and sums
 // partial tiles in a second launch.
 //
@@ -15,6 +15,9 @@
 // Measured, input and weak gradient in one call, small tiles or split -> here, us: 4096 x 4096 at M = 64 / 128 / 192 26 / 27 / 28.5 -> 14 / 16.5 / 18;
 // 4096 x 11008 at 64 30 -> 23; 5120 x 5120 with 64 weak columns at 64 / 128 35.5 -> 19 / 22.5; 2048 x 3000 with 16 at 64 /
 // 192 17 -> 8.5 / 10.5; 13824 x 5120 with 16 at 64 to 192 88 -> 60; 3-bit 5120 x 5120 at 64 36 -> 29; 8192 x 1024 at 64 25 -> 16; 520 x 1160 at 128 11 -> 5.5.
+// 64 x 128 tiles, with the forward before it: 4096 x 4096 at 300 / 384 / 512 54.8 / 57.8 / 63 -> 47.3 / 50.5 / 60.6; 5120 x 5120 with 64 at 256 62.6 -> 58;
+// 13824 x 5120 with 16 at 256 132 -> 124.  There products, conversions and LDS take about a microsecond each of a stage's three; conversions spread between the
+// products by scheduling groups gave nothing more.
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -42,7 +45,7 @@ __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70 | 
 __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 constexpr int DXP_PAR = 384;                                       // - zero * scale or zero, scale of 64 rows
-constexpr int dxp_piece(int NI, int J) { return J * 4096 + NI * 4096 + DXP_PAR; }   // a wave's LDS: dY, codes (NI KB) or weak block (4 NI KB), parameters; its partial tile
+constexpr int dxp_piece(int NI, int J) { return J * 4096 + NI * 1024 + DXP_PAR; }   // a wave's LDS: dY, codes, parameters of a stage; 32 channels of its partial tile
 
 // Tiles of 32 NI channels (of one group: 128 is a multiple of them) x 32 J rows.
 template <int NI, int J, bool ONCE>
@@ -60,31 +63,13 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
     if (v >= tiles_n * tiles_m) return;
     const int t_n = v / tiles_m, t_m = v - t_n * tiles_m;   // neighbours on an XCD share their codes
     constexpr int C = 32 * NI;
-    static_assert(NI * J * 4096 <= dxp_piece(NI, J), "");
-    const int nq = (L.kq + C - 1) / C, nst = (L.oc + 63) >> 6;
+    const int nq = (L.kq + C - 1) / C;
     const bool weak = t_n >= nq;
     const int c0 = weak ? L.kq + C * (t_n - nq) : C * t_n, m0 = t_m * 32 * J;
     unsigned char* mine = lds + (size_t)wave * dxp_piece(NI, J);
-    unsigned char* wl = mine + J * 4096;
-    const uint32_t at_y = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)mine;
-    const uint32_t at_w = at_y + J * 4096, at_p = at_w + NI * 4096;
-
-    // 64 weight rows of stage st: from 64 st on, the last 64 where OC is no multiple of 64 (what is shared with the stage before counts as zeros)
-    auto first_row = [&](int st) { return min(64 * st, L.oc - 64); };
+    const uint32_t at = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)mine;
     const auto ybuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(dY + (size_t)m0 * lddy), 0, (int)0xffffffff, 0x00020000);
     const uint32_t ypitch = (uint32_t)lddy * 2u, ylast = (uint32_t)min(M - 1 - m0, 32 * J) * ypitch;
-    const uint32_t ycol = 16u * (uint32_t)((lane & 7) ^ (lane >> 3));   // slot lane % 8 of row 8 u + lane / 8 holds chunk slot ^ row % 8
-    auto load_y = [&](int r0) {
-#pragma unroll
-        for (int u = 0; u < 4 * J; ++u)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ybuf, (__attribute__((address_space(3))) void*)(mine + 1024 * u), 16,
-                                                     (int)(min((uint32_t)(8 * u + (lane >> 3)) * ypitch, ylast) + ycol), 2 * r0, 0, 0);
-    };
-    h8 b[4][J];
-    auto read_y = [&](int ks, int chunk) {
-#pragma unroll
-        for (int j = 0; j < J; ++j) b[ks][j] = *reinterpret_cast<const lds_h8*>((size_t)(at_y + (uint32_t)((32 * j + fr) * 128 + ((chunk ^ (fr & 7)) << 4))));
-    };
     const h8 zero8 = __builtin_bit_cast(h8, u4{0u, 0u, 0u, 0u});
 
     f16v acc[NI][J];
@@ -96,6 +81,23 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
     if (!weak) {
+        // 64 weight rows of stage st: from 64 st on, the last 64 where OC is no multiple of 64 (what is shared with the stage before counts as zeros)
+        auto first_row = [&](int st) { return min(64 * st, L.oc - 64); };
+        const int nst = (L.oc + 63) >> 6;
+        unsigned char* wl = mine + J * 4096;
+        const uint32_t at_w = at + J * 4096, at_p = at_w + NI * 1024;
+        const uint32_t ycol = 16u * (uint32_t)((lane & 7) ^ (lane >> 3));   // slot lane % 8 of row 8 u + lane / 8 holds chunk slot ^ row % 8
+        auto load_y = [&](int r0) {
+#pragma unroll
+            for (int u = 0; u < 4 * J; ++u)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ybuf, (__attribute__((address_space(3))) void*)(mine + 1024 * u), 16,
+                                                         (int)(min((uint32_t)(8 * u + (lane >> 3)) * ypitch, ylast) + ycol), 2 * r0, 0, 0);
+        };
+        h8 b[4][J];
+        auto read_y = [&](int ks, int chunk) {
+#pragma unroll
+            for (int j = 0; j < J; ++j) b[ks][j] = *reinterpret_cast<const lds_h8*>((size_t)(at + (uint32_t)((32 * j + fr) * 128 + ((chunk ^ (fr & 7)) << 4))));
+        };
         const size_t wpitch = (size_t)L.stride * 4, ppitch = (size_t)L.gs * 2;
         const unsigned char* wt = reinterpret_cast<const unsigned char*>(L.qweight) + c0 / 2;
         const unsigned char* st_ = reinterpret_cast<const unsigned char*>(L.scales + c0 / 128) + (size_t)lane * ppitch;
@@ -134,66 +136,83 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
                     raw[i][p] = __builtin_amdgcn_ds_read_tr4_b64_v2i32((lds_v2i*)(size_t)(at_w + (uint32_t)((32 * p + 16 * fk + (lane & 15)) * (16 * NI) + 16 * i + 8 * ((lane >> 4) & 1))));
             u4 sc[4], zp[4];
             f4 nz[4][2];
+            constexpr int PH = J == 4 ? 2 : 1;   // (128 rows: fragments of two k-blocks at a time, or registers go to scratch memory)
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int chunk = 4 * (ks >> 1) + 2 * fk + (ks & 1);
-                sc[ks] = *reinterpret_cast<const lds_u4*>((size_t)(at_p + 256u + 16u * chunk));
-                if constexpr (ONCE) {
+            for (int ph = 0; ph < PH; ++ph) {
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) nz[ks][h] = *reinterpret_cast<const lds_f4*>((size_t)(at_p + 32u * chunk + 16u * h));
-                } else
-                    zp[ks] = *reinterpret_cast<const lds_u4*>((size_t)(at_p + 16u * chunk));
-                read_y(ks, chunk);
-            }
-            wave_lds_fence();
-            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): all is in registers before its place is filled again
-            __builtin_amdgcn_sched_barrier(0);
-            issue(st + KS);
-            __builtin_amdgcn_sched_barrier(0);
-            if (64 * st + 64 > L.oc) {
+                for (int ks = 4 * ph / PH; ks < 4 * (ph + 1) / PH; ++ks) {
+                    const int chunk = 4 * (ks >> 1) + 2 * fk + (ks & 1);
+                    sc[ks] = *reinterpret_cast<const lds_u4*>((size_t)(at_p + 256u + 16u * chunk));
+                    if constexpr (ONCE) {
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const bool live = first_row(st) + 8 * (4 * (ks >> 1) + 2 * fk + (ks & 1)) >= 64 * st;
-#pragma unroll
-                    for (int j = 0; j < J; ++j) b[ks][j] = live ? b[ks][j] : zero8;
+                        for (int h = 0; h < 2; ++h) nz[ks][h] = *reinterpret_cast<const lds_f4*>((size_t)(at_p + 32u * chunk + 16u * h));
+                    } else
+                        zp[ks] = *reinterpret_cast<const lds_u4*>((size_t)(at_p + 16u * chunk));
+                    read_y(ks, chunk);
                 }
-            }
+                __builtin_amdgcn_sched_barrier(0);
+                if (ph == PH - 1) {
+                    wave_lds_fence();
+                    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): all is in registers before its place is filled again
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue(st + KS);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (64 * st + 64 > L.oc) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
+                    for (int ks = 4 * ph / PH; ks < 4 * (ph + 1) / PH; ++ks) {
+                        const bool live = first_row(st) + 8 * (4 * (ks >> 1) + 2 * fk + (ks & 1)) >= 64 * st;
 #pragma unroll
-                for (int i = 0; i < NI; ++i) {
-                    const uint32_t w = (uint32_t)raw[i][ks >> 1][ks & 1], w4 = w >> 4;
-                    const h2 k1024 = h2{(_Float16)1024.f, (_Float16)1024.f};
-                    u4 a;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) {   // rows 2 p and 2 p + 1: a byte of the word beside the same byte moved down by a code
-                        const h2 q = bits_h2((__builtin_amdgcn_perm(w4, w, 0x0c040c00u + 0x00010001u * (uint32_t)p) & mask) | magic) - k1024;
-                        const h2 s = bits_h2(sc[ks][p]);
-                        if constexpr (ONCE) {
-                            const _Float16 lo = dequant_once_first(q.x, s.x, nz[ks][p >> 1][2 * (p & 1)]);
-                            a[p] = h2_bits(h2{lo, dequant_once(q.y, s.y, nz[ks][p >> 1][2 * (p & 1) + 1])});
-                        } else
-                            a[p] = h2_bits((q - bits_h2(zp[ks][p])) * s);
+                        for (int j = 0; j < J; ++j) b[ks][j] = live ? b[ks][j] : zero8;
                     }
-#pragma unroll
-                    for (int j = 0; j < J; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), b[ks][j], acc[i][j], 0, 0, 0);
                 }
+#pragma unroll
+                for (int ks = 4 * ph / PH; ks < 4 * (ph + 1) / PH; ++ks)
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) {
+                        const uint32_t w = (uint32_t)raw[i][ks >> 1][ks & 1], w4 = w >> 4;
+                        const h2 k1024 = h2{(_Float16)1024.f, (_Float16)1024.f};
+                        u4 a;
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) {   // rows 2 p and 2 p + 1: a byte of the word beside the same byte moved down by a code
+                            const h2 q = bits_h2((__builtin_amdgcn_perm(w4, w, 0x0c040c00u + 0x00010001u * (uint32_t)p) & mask) | magic) - k1024;
+                            const h2 s = bits_h2(sc[ks][p]);
+                            if constexpr (ONCE) {
+                                const _Float16 lo = dequant_once_first(q.x, s.x, nz[ks][p >> 1][2 * (p & 1)]);
+                                a[p] = h2_bits(h2{lo, dequant_once(q.y, s.y, nz[ks][p >> 1][2 * (p & 1) + 1])});
+                            } else
+                                a[p] = h2_bits((q - bits_h2(zp[ks][p])) * s);
+                        }
+#pragma unroll
+                        for (int j = 0; j < J; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), b[ks][j], acc[i][j], 0, 0, 0);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     } else {
         const size_t kpitch = (size_t)L.k * 2;
+        // stages of 32 weight rows
         constexpr int CH = 4 * NI, WP = 64 * NI;   // chunks and bytes of a row of the tile's weak columns
+        static_assert(J * 2048 + 32 * WP <= dxp_piece(NI, J), "");
+        auto first_row = [&](int st) { return min(32 * st, L.oc - 32); };
+        const int nst = (L.oc + 31) >> 5;
+        unsigned char* wl = mine + J * 2048;
         const uint32_t wcol = 2u * (uint32_t)min(c0 - L.kq + 8 * (lane % CH), L.k - 8);
+        const uint32_t ycol = 16u * (uint32_t)((lane & 3) ^ ((lane >> 3) & 3));   // slot lane % 4 of row 16 u + lane / 4 holds chunk slot ^ row / 2 % 4
         auto issue = [&](int st) {
             const int r0 = first_row(min(st, nst - 1));
             const auto wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(L.weak + (size_t)r0 * L.k), 0, (int)0xffffffff, 0x00020000);
 #pragma unroll
-            for (int u = 0; u < CH; ++u)
+            for (int u = 0; u < 2 * NI; ++u)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(wbuf, (__attribute__((address_space(3))) void*)(wl + 1024 * u), 16,
                                                          (int)((uint32_t)((64 * u + lane) / CH) * (uint32_t)kpitch + wcol), 0, 0, 0);
-            load_y(r0);
+#pragma unroll
+            for (int u = 0; u < 2 * J; ++u)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ybuf, (__attribute__((address_space(3))) void*)(mine + 1024 * u), 16,
+                                                         (int)(min((uint32_t)(16 * u + (lane >> 2)) * ypitch, ylast) + ycol), 2 * r0, 0, 0);
         };
         const int g = lane >> 4, s = lane & 15;
-        const uint32_t fa = at_w + (uint32_t)((8 * (g >> 1) + (s >> 2)) * WP + 2 * (16 * (g & 1) + 4 * (s & 3)));
+        const uint32_t fa = at + J * 2048 + (uint32_t)((8 * (g >> 1) + (s >> 2)) * WP + 2 * (16 * (g & 1) + 4 * (s & 3)));
         issue(wave);
 #pragma clang loop unroll(disable)
         for (int st = wave; st < nst; st += KS) {
@@ -201,26 +220,27 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
             wait_vm<0>();
             __builtin_amdgcn_sched_barrier(0);
             wave_lds_fence();
-            h8 a[4][NI];
+            h8 a[2][NI], b[2][J];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {   // rows 16 ks + 8 fk .. + 7: chunk 2 ks + fk
+            for (int ks = 0; ks < 2; ++ks) {   // rows 16 ks + 8 fk .. + 7: chunk 2 ks + fk
 #pragma unroll
                 for (int i = 0; i < NI; ++i) {
                     const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(size_t)(fa + (uint32_t)(16 * WP * ks + 64 * i)));
                     const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(size_t)(fa + (uint32_t)(16 * WP * ks + 64 * i + 4 * WP)));
                     a[ks][i] = __builtin_bit_cast(h8, s8{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w});
                 }
-                read_y(ks, 2 * ks + fk);
+#pragma unroll
+                for (int j = 0; j < J; ++j) b[ks][j] = *reinterpret_cast<const lds_h8*>((size_t)(at + (uint32_t)((32 * j + fr) * 64 + (((2 * ks + fk) ^ ((fr >> 1) & 3)) << 4))));
             }
             wave_lds_fence();
             __builtin_amdgcn_s_waitcnt(0xC07F);
             __builtin_amdgcn_sched_barrier(0);
             issue(st + KS);
             __builtin_amdgcn_sched_barrier(0);
-            if (64 * st + 64 > L.oc) {   // both operands: nothing counted already may meet the zeros of the other
+            if (32 * st + 32 > L.oc) {   // both operands: nothing counted already may meet the zeros of the other
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const bool live = first_row(st) + 8 * (2 * ks + fk) >= 64 * st;
+                for (int ks = 0; ks < 2; ++ks) {
+                    const bool live = first_row(st) + 8 * (2 * ks + fk) >= 32 * st;
 #pragma unroll
                     for (int i = 0; i < NI; ++i) a[ks][i] = live ? a[ks][i] : zero8;
 #pragma unroll
@@ -228,7 +248,7 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
                 }
             }
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
+            for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
                 for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -236,29 +256,29 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
         }
     }
 
-    // the waves' partial tiles meet in LDS (each in its wave's piece); wave w sums quarters w, w + KS, ...: quarter 4 (J i + j) + g of lane (fr, fk) is
-    // channels 32 i + 8 g + 4 fk .. + 3 of row 32 j + fr
+    // the waves' partial tiles meet in LDS (each in its wave's piece), 32 channels at a time; wave w sums quarters w, w + KS, ...: quarter 4 j + g of
+    // lane (fr, fk) is channels 8 g + 4 fk .. + 3 of row 32 j + fr
     wait_vm<0>();   // (requests of a stage past the wave's last)
-    __syncthreads();
+    const int limit = weak ? L.ic : L.kq;
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+    for (int i = 0; i < NI; ++i) {
+        __syncthreads();
 #pragma unroll
         for (int j = 0; j < J; ++j)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<f4*>(mine + ((4 * (J * i + j) + g) << 10) + 16 * lane) =
-                    f4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-    __syncthreads();
-    const int limit = weak ? L.ic : L.kq;
-    for (int q = wave; q < 4 * NI * J; q += KS) {
-        f4 y = *reinterpret_cast<const f4*>(lds + (q << 10) + 16 * lane);
-        for (int w = 1; w < KS; ++w) {
-            const f4 p = *reinterpret_cast<const f4*>(lds + (size_t)w * dxp_piece(NI, J) + (q << 10) + 16 * lane);
+                *reinterpret_cast<f4*>(mine + ((4 * j + g) << 10) + 16 * lane) = f4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+        __syncthreads();
+        for (int q = wave; q < 4 * J; q += KS) {
+            f4 y = *reinterpret_cast<const f4*>(lds + (q << 10) + 16 * lane);
+            for (int w = 1; w < KS; ++w) {
+                const f4 p = *reinterpret_cast<const f4*>(lds + (size_t)w * dxp_piece(NI, J) + (q << 10) + 16 * lane);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] += p[e];
+                for (int e = 0; e < 4; ++e) y[e] += p[e];
+            }
+            const int m = m0 + 32 * (q >> 2) + fr, c = c0 + 32 * i + 8 * (q & 3) + 4 * fk;
+            if (m < M && c < limit) *reinterpret_cast<u2*>(dX + (size_t)m * lddx + c) = u2{pack2(y[0], y[1]), pack2(y[2], y[3])};
         }
-        const int t = q >> 2, m = m0 + 32 * (t % J) + fr, c = c0 + 32 * (t / J) + 8 * (q & 3) + 4 * fk;
-        if (m < M && c < limit) *reinterpret_cast<u2*>(dX + (size_t)m * lddx + c) = u2{pack2(y[0], y[1]), pack2(y[2], y[3])};
     }
 }
 
@@ -288,16 +308,16 @@ hipError_t launch(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __h
 namespace {
 struct Pick {
     double us;
-    int tile;   // 0: 32 channels x 32 rows, 1: 32 x 64, 2: 64 x 64
+    int tile;   // 0: 32 channels x 32 rows, 1: 32 x 64, 2: 64 x 64, 3: 64 x 128
 };
 Pick pick(const Layer& L, int64_t M) {
     const double n = ceil_div(ceil_div(L.oc, 64), 8), wide = L.ic / 1024.0;
     const int apart = 4 * L.stride % 4096;
     const bool few = 4 * L.stride > 2048 && (apart < 192 || apart > 4096 - 192);
-    const double c0[3] = {0.4, 0.75, 1.2}, c1[3] = {0.7, 0.6, 0.55}, c2[3] = {0.05, 0.06, 0.065};
+    const double c0[4] = {0.4, 0.75, 1.2, 2.1}, c1[4] = {0.7, 0.6, 0.55, 0.7}, c2[4] = {0.05, 0.06, 0.065, 0.065};
     Pick best = {1e30, 0};
-    for (int t = 0; t < 3; ++t) {
-        const int64_t wgs = (int64_t)dxp_tiles(L, t == 2 ? 64 : 32) * ceil_div(M, t == 0 ? 32 : 64);
+    for (int t = 0; t < 4; ++t) {
+        const int64_t wgs = (int64_t)dxp_tiles(L, t >= 2 ? 64 : 32) * ceil_div(M, t == 0 ? 32 : (t == 3 ? 128 : 64));
         const double us = (few ? 8.5 : 3.5) + (few ? 1.1 : 1.0) * n * (c0[t] + c1[t] * (double)wgs / 256 + c2[t] * wide);
         if (wgs <= 256 && us < best.us) best = {us, t};
     }
@@ -307,7 +327,7 @@ Pick pick(const Layer& L, int64_t M) {
 double dx_panel_estimate(const Layer& L, int64_t M) { return pick(L, M).us; }
 hipError_t dx_panel(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s, WeakGrad* g) {
     using Launch = hipError_t (*)(const Layer&, const __half*, int64_t, int64_t, __half*, int64_t, hipStream_t, WeakGrad*);
-    static const Launch table[3][2] = {{launch<1, 1, false>, launch<1, 1, true>}, {launch<1, 2, false>, launch<1, 2, true>}, {launch<2, 2, false>, launch<2, 2, true>}};
+    static const Launch table[4][2] = {{launch<1, 1, false>, launch<1, 1, true>}, {launch<1, 2, false>, launch<1, 2, true>}, {launch<2, 2, false>, launch<2, 2, true>}, {launch<2, 4, false>, launch<2, 4, true>}};
     return table[pick(L, M).tile][L.once ? 1 : 0](L, dY, M, lddy, dX, lddx, s, g);
 }
 

@@ -1,4 +1,4 @@
-"""Input gradient in tiles of 32 or 64 channels x 32 or 64 rows, at their edges: channels and rows that end inside a tile, a partial last group,
+"""Input gradient in tiles of 32 or 64 channels x 32 to 128 rows, at their edges: channels and rows that end inside a tile, a partial last group,
 stages the waves do not divide evenly, a last stage that begins at OC - 64, weak blocks narrower than a tile, of several, or none, 3-bit layers
 through their 4-bit copy (one rounding).  Tolerance: parity_util's bar (weights rounded to fp16 once, 2^-11 relative each, over at least 64
 terms; fp16 results)."""
@@ -13,14 +13,14 @@ pytestmark = pytest.mark.gpu
 
 # (oc, ic, k, bits)
 LAYERS = [(64, 72, 0, 4), (72, 264, 8, 4), (520, 1160, 8, 4), (1032, 2000, 264, 4), (4096, 328, 200, 4), (584, 4104, 72, 4), (4104, 1024, 128, 4), (1096, 2048, 64, 3),
-          (2048, 1152, 128, 3)]
+          (2048, 1152, 128, 3), (264, 7880, 200, 4), (320, 7808, 128, 3)]
 
 
 @pytest.mark.parametrize("oc,ic,k,bits", LAYERS)
 def test_panel_input_gradient(oc, ic, k, bits):
     layer = HostLayer(oc, ic, k, bits, 128, seed=oc + ic)
     w, w64 = layer.to_device(), torch.from_numpy(layer.w64).cuda()
-    for m in (17, 32, 33, 64, 65, 127, 200):
+    for m in (17, 32, 33, 64, 65, 127, 200, 255, 500):
         dy = pad_cols(synth.make_grad_output(m, oc, m))[0]
         back = torch.full((m + 2, ic + 8), 7.0, dtype=torch.float16, device="cuda")
         dx = back[1:m + 1, :ic]
