@@ -209,9 +209,12 @@ __global__ __launch_bounds__(256) void rtn_fused_w4g128_kernel(Layer L, const __
 //  * Candidates are scored in twos, whose sums over the 16 lanes share their moves; even lanes keep the best of the first ones,
 //    odd lanes of the second ones.
 //  * The weak block is copied by waves of the same launch.
+//  * Where a quotient itself is needed its divisor is short, and three instructions give the bits of a division's ten (short_div); the
+//    row and chunk of a wave are scalar; the row broadcasts start from nothing that has to be cleared; a candidate past the grid's end scores as no number.
 // 4096 x 4096, 80 candidates, whole call (us): 919 with two divisions per weight and candidate and every candidate scored, 123 with the
-// bound by two columns, single candidates and the copy in a launch of its own (117 in the harness of the figures that follow), 111 now;
-// 3 bits, ten codes a word 211 -> 189, dense (the words in this pass too) 215 -> 176.
+// bound by two columns, single candidates and the copy in a launch of its own (117 in the harness of the figures that follow), 110 with general
+// divisions, 91 now; 3 bits, ten codes a word 211 -> 188 -> 165, dense (the words in this pass too) 215 -> 174 -> 147.
+// Of a pair's hundred vector instructions eighty are the five per value and candidate; a packed or 16-bit form would not give the same sums.
 // sum over the 16 lanes of a row whose neighbours (lane ^ 1) are added already, separately for even and odd lanes.  Each step is an
 // exchange between two halves, so that both add the same two numbers and all lanes of a class end with the same bits: they decide
 // by them one by one, and a rotation by four would leave every other quad with another order (two candidates in one group's codes).
@@ -223,6 +226,16 @@ __device__ __forceinline__ float dpp16_sum_rest(float v) {
     return __fadd_rn(v, mv(v, std::integral_constant<int, 0x128>{}));   // lane ^ 8
 }
 
+// Reciprocal and quotient rounded correctly, where the divisor b is a normal number of at most 11 bits (Newton's step, and Markstein's correction of
+// a quotient by its remainder; a general division takes about ten instructions).  1 / b: the instruction's error of 1 ulp leaves 2^-46 after the step, and no 1 / b
+// of such a b lies within 2^-36 of half way between two floats.  a / b: a * rb errs by 1.5 ulp at most, so the remainder is exact, and the
+// corrected quotient is off by 2^-23 ulp before its rounding, a / b never within 2^-12 ulp of half way.  No infinities.
+__device__ __forceinline__ float short_rcp(float b) {
+    const float r = __builtin_amdgcn_rcpf(b);
+    return __builtin_fmaf(__builtin_fmaf(-b, r, 1.f), r, r);
+}
+__device__ __forceinline__ float short_div(float a, float b, float rb, float q) { return __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q); }   // q = a * rb
+
 // WORDS: 4: 4-bit codes in groups of 128, 3: dense 3-bit codes in groups of 128, whose words the same lanes then store (0:
 // rtn_words_kernel does).
 template <int WORDS>
@@ -232,7 +245,7 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
                                                             int copy_waves, int n_grid, float step) {
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-    const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6) - copy_waves;
+    const int64_t wv = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - copy_waves;
     const int lane = threadIdx.x & 63;
     if (wv < 0) {   // the launch's first waves copy the weak block, 8 columns per lane (a launch of its own took 5 us)
         const int64_t idx = 64 * (wv + copy_waves) + lane;
@@ -262,7 +275,7 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
     }
     auto two_least = [](float& a, float& b) {   // of the 16 lanes of a row, in every lane
         auto merge = [&](auto ctrl) {
-            auto mv = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, false)); };
+            auto mv = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true)); };
             const float c = mv(a), d = mv(b);
             b = fminf(fmaxf(a, c), fminf(b, d));
             a = fminf(a, c);
@@ -276,21 +289,23 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
     hi0 = -hi0, hi1 = -hi1;
     two_least(hi0, hi1);
     hi0 = -hi0, hi1 = -hi1;
-    const float qmax = (float)((1 << L.bits) - 1);
-    // scale and zero-point of candidate i of this lane's group
+    const float qmax = (float)((1 << L.bits) - 1), rqmax = short_rcp(qmax);
+    // scale, its reciprocal and zero-point of candidate i of this lane's group
     struct Params {
-        float s, z;
+        float s, rs, z;
     };
     auto params = [&](int i) {
         const float p = __fsub_rn(1.f, __fmul_rn((float)i, step));
         const float lo = __fmul_rn(p, lo0), hi = __fmul_rn(p, hi0);
-        const float s32 = __fdiv_rn(__fsub_rn(hi, lo), qmax);
-        Params r{1.f, 0.f};
+        const float range = __fsub_rn(hi, lo), s32 = short_div(range, qmax, rqmax, range * rqmax);
+        Params r{1.f, 1.f, 0.f};
         if (s32 != 0.f) {
             __half s16 = __float2half_rn(s32);
             if (__half2float(s16) == 0.f) s16 = __ushort_as_half((unsigned short)1);
             r.s = __half2float(s16);
-            r.z = rintf(__fdiv_rn(__fsub_rn(0.f, lo), r.s));
+            r.rs = short_rcp(r.s);
+            const float below = __fsub_rn(0.f, lo);
+            r.z = rintf(short_div(below, r.s, r.rs, below * r.rs));
             r.z = fminf(fmaxf(r.z, 0.f), qmax);
         }
         return r;
@@ -304,37 +319,43 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
     // the best of the even candidates in the even lanes, of the odd ones in the odd lanes
     float best_e = __builtin_inff();
     int best_i = -1;
+    // the better of the neighbours' two classes: scores are no less than 0, and as whole numbers need no instruction to quiet a NaN
+    auto least_of_both = [&]() {
+        const uint32_t mine = __builtin_bit_cast(uint32_t, best_e), its = __builtin_bit_cast(uint32_t, xor1(best_e));
+        return __builtin_bit_cast(float, mine < its ? mine : its);
+    };
+    float to_beat = best_e;
     for (int i0 = 0; i0 < n_grid; i0 += 16) {
         if (i0 > 0) {
             // A candidate's codes end within s / 2 of p hi0 and p lo0, and s rounded up moves the upper end by qmax times as much: by 2^-11 of s
             // (0.52 s covers that and the roundings of z and p), among subnormal scales by up to 2^-24.  So a value x beyond misses by
             // x - p hi0 - half at least, and by more under every narrower candidate: done once that is too much for all groups
-            const float p = 1.f - (float)i0 * step, half = 0.52f * (p * (hi0 - lo0) / qmax) + (qmax + 1.f) * 0x1p-24f;
+            const float p = 1.f - (float)i0 * step, half = 0.52f * (p * (hi0 - lo0) * rqmax) + (qmax + 1.f) * 0x1p-24f;
             auto beyond = [&](float x) {
                 const float e = fmaxf(fmaxf(x - p * hi0, p * lo0 - x) - half, 0.f);
                 return e * e;
             };
             const float least = (beyond(lo0) + beyond(hi0)) + (beyond(lo1) + beyond(hi1));
             // (equal is too much as well, the earlier candidate stays: groups of zeros, the padding of a row among them)
-            if (__ballot(!(least * (1.f - 0x1p-7f) >= fminf(best_e, xor1(best_e)))) == 0) break;
+            if (__ballot(!(least * (1.f - 0x1p-7f) >= to_beat)) == 0) break;
         }
         const Params mine = params(i0 + t);   // candidate i0 + t
-        const float s_l = mine.s, z_l = mine.z, rs_l = __fdiv_rn(1.f, s_l);
+        // (past the grid's end: no number, whose score is never the better one)
+        const float s_l = i0 + t < n_grid ? mine.s : __builtin_nanf(""), z_l = mine.z, rs_l = mine.rs;
         auto missed = [&](float x) {
             const float e = miss(x, s_l, rs_l, -z_l, qmax - z_l);
             return e * e;
         };
-        const float bound_l = i0 + t < n_grid ? ((missed(lo0) + missed(hi0)) + (missed(lo1) + missed(hi1))) * (1.f - 0x1p-10f) : __builtin_inff();
+        const float bound_l = ((missed(lo0) + missed(hi0)) + (missed(lo1) + missed(hi1))) * (1.f - 0x1p-10f);
         auto pair = [&](auto j_c) {
             constexpr int J = decltype(j_c)::value;
             // any of the four groups' candidates J, J + 1 that could still win
-            const float best = fminf(best_e, xor1(best_e));
-            if ((__ballot(bound_l < best) & (0x0003000300030003ull << J)) == 0) return;
+            if ((__ballot(bound_l < to_beat) & (0x0003000300030003ull << J)) == 0) return;
             float acc[2];
             auto score = [&](auto k_c) {
                 constexpr int K = decltype(k_c)::value;
                 auto from = [](float x) {   // lane J + K of the row of 16
-                    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + J + K, 0xf, 0xf, false));
+                    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150 + J + K, 0xf, 0xf, false));
                 };
                 const float s = from(s_l), rs = from(rs_l), z = from(z_l), uz = qmax - z;
                 float a = 0.f;
@@ -349,9 +370,10 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
             score(std::integral_constant<int, 1>{});
             // both sums over the 16 lanes at once: the first ends in the even lanes, the second in the odd ones
             const float err = dpp16_sum_rest(__fadd_rn(odd ? acc[1] : acc[0], xor1(odd ? acc[0] : acc[1])));
-            const bool better = err < best_e && i0 + J + (t & 1) < n_grid;
+            const bool better = err < best_e;
             best_e = better ? err : best_e;
             best_i = better ? i0 + J + (t & 1) : best_i;
+            to_beat = least_of_both();
         };
         pair(std::integral_constant<int, 0>{});
         pair(std::integral_constant<int, 2>{});
@@ -367,7 +389,7 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
     const int other_i = __builtin_amdgcn_update_dpp(0, best_i, 0xB1, 0xf, 0xf, false);
     if (other_e < best_e || (other_e == best_e && (uint32_t)other_i < (uint32_t)best_i)) best_i = other_i;
     Params best = params(best_i);
-    if (best_i < 0) best = Params{1.f, 0.f};
+    if (best_i < 0) best = Params{1.f, 1.f, 0.f};
     if (t == 0) {
         const bool real = grp < L.ng;
         scales[(size_t)o * L.gs + grp] = __float2half_rn(real ? best.s : 0.f);
@@ -377,8 +399,10 @@ __global__ __launch_bounds__(256) void search_params_kernel(Layer L, const __hal
         uint32_t out = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float q = __fadd_rn(rintf(__fdiv_rn(v[e], best.s)), best.z);
-            out |= (uint32_t)fminf(fmaxf(q, 0.f), qmax) << (WORDS * e);
+            // (beyond 1024 of scale an infinity may be, and any code clamps: the correction leads from there past it)
+            const float q0 = __builtin_amdgcn_fmed3f(v[e] * best.rs, -1024.f, 1024.f);
+            const float q = __fadd_rn(rintf(short_div(v[e], best.s, best.rs, q0)), best.z);
+            out |= (uint32_t)__builtin_amdgcn_fmed3f(q, 0.f, qmax) << (WORDS * e);   // (no number: 0)
         }
         if (!live) out = 0u;
         if constexpr (WORDS == 4) {

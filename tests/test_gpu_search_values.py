@@ -138,3 +138,24 @@ def test_search_choice(kind, bits, g, dense):
     assert np.array_equal(packed, out.qweight.cpu().numpy().view(np.uint32))
     s_ref, z_ref = _choice(w, bits, g, n_grid, step)
     assert np.array_equal(s, s_ref) and np.array_equal(z.astype(np.float32), z_ref)
+
+
+@pytest.mark.parametrize("bits,dense", [(4, False), (3, True)])
+def test_divisions_by_short_numbers(bits, dense):
+    """Scales, zero-points and codes come from quotients by numbers of 11 bits, corrected by their remainder instead of divided: the same
+    bits as the division rules give over the whole range of scales (single candidate), and infinities end at the outermost codes."""
+    r = np.random.default_rng(5)
+    oc, ic = 64, 1024
+    w = (r.standard_normal((oc, ic)) * 2.0 ** r.integers(-24, 14, (oc, 1))).clip(-65504, 65504).astype(np.float16)
+    w[::3] = (r.integers(-15, 16, (len(w[::3]), ic)) * 2.0 ** r.integers(-24, 10, (len(w[::3]), 1))).astype(np.float16)
+    w[5, 40], w[6, 50], w[7, 60] = np.inf, -np.inf, np.nan
+    d = B.make_desc(oc, ic, 0, bits, 128, B.QEFT_LAYOUT_DENSE3 if dense else B.QEFT_LAYOUT_CANONICAL)
+    out, ref = B.qeft_pack_search(d, pad_cols(w)[1][:, :ic], 1, 0.5), B.qeft_pack(d, pad_cols(w)[1][:, :ic])
+    torch.cuda.synchronize()
+    whole = [i for i in range(oc) if i not in (5, 6, 7)]
+    assert torch.equal(out.scales[whole], ref.scales[whole]) and torch.equal(out.zeros[whole], ref.zeros[whole])
+    assert torch.equal(out.qweight[whole], ref.qweight[whole])
+    # a group with a value that is no finite number has scale 1 and zero-point 0
+    assert bool((out.scales[5:8, 0] == 1).all()) and bool((out.zeros[5:8, 0] == 0).all())
+    codes = B.qeft_unpack(d, out)[0].cpu()
+    assert [int(codes[5, 40]), int(codes[6, 50]), int(codes[7, 60])] == [2 ** bits - 1, 0, 0]
