@@ -1171,12 +1171,13 @@ __global__ __launch_bounds__(256) void gemm_dx_rega_kernel(Layer L, const __half
     dx_rega_body<ONCE>(lds, L, dY, M, lddy, dX, lddx, tiles_ic, splits, rps, tail_first, part);
 }
 
+template <int KW>
 __global__ __launch_bounds__(256) void weak_grad_strip_kernel(int oc_total, int k_total, const __half* __restrict__ dY, int M,
                                                               int64_t lddy, const __half* __restrict__ Xw, int64_t ldxw,
                                                               float* __restrict__ part, int splits, int chunk, void* dW,
                                                               int out_f32, int accumulate) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-    weak_grad_strip_body(lds, (int)blockIdx.x, oc_total, k_total, dY, M, lddy, Xw, ldxw, part, splits, chunk, dW, out_f32, accumulate);
+    weak_grad_strip_body<KW>(lds, (int)blockIdx.x, oc_total, k_total, dY, M, lddy, Xw, ldxw, part, splits, chunk, dW, out_f32, accumulate);
 }
 
 // The input gradient and the weak block's gradient of one layer in ONE launch: the first n_dx workgroups are the
@@ -1276,7 +1277,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const __half* __rest
 }
 // The same behind an input gradient that was split, with the strips of the weak gradient ahead of it in the grid: either alone is short and
 // leaves most of the GPU waiting for it.  One launch instead of two, the whole backward, us: 4096 x 4096 at M = 200 / 512 / 777 34 / 42.5 / 56 ->
-// 29 / 37 / 51; 11008 x 4096 at 512 / 2048 72 / 206 -> 66 / 200; 3-bit 5120 x 5120 at 1000 91 -> 85.  65 KB of LDS for every workgroup leaves a CU two at
+// 29 / 37 / 51; 11008 x 4096 at 512 / 2048 72 / 206 -> 66 / 200; 3-bit 5120 x 5120 at 1000 91 -> 85.  65 KB of LDS for every workgroup (49 in pieces of 64 weak columns) leaves a CU two or three at
 // a time; with its partial tiles four requests at a time the sum takes no longer for it.
 __global__ __launch_bounds__(256) void splitk_reduce_dw_kernel(const __half* __restrict__ part, int splits, int tiles_all, int tiles_n,
                                                                int tail_first, int M, int n, __half* __restrict__ dX, int64_t lddx, Strips S) {
@@ -1435,7 +1436,7 @@ hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __
                     if (e != hipSuccess) return e;
                     dw_attr = true;
                 }
-                splitk_reduce_dw_kernel<<<S.n + n_sum, 256, WG_LDS, s>>>(part, p.splits, tiles, tiles_ic, p.tail_first, (int)M, L.ic, dX, lddx, S);
+                splitk_reduce_dw_kernel<<<S.n + n_sum, 256, wg_lds(S.kw), s>>>(part, p.splits, tiles, tiles_ic, p.tail_first, (int)M, L.ic, dX, lddx, S);
                 e = hipGetLastError();
                 return e == hipSuccess ? finish_strips(g, S, s) : e;
             }
@@ -1468,19 +1469,17 @@ size_t weak_grad_mfma_workspace(int oc, int k, int64_t M) {
 
 hipError_t weak_grad_mfma(int oc, int k, const __half* dY, int64_t M, int64_t lddy, const __half* Xw, int64_t ldxw,
                           void* dW, int out_f32, int accumulate, void* ws, hipStream_t s) {
-    int splits, chunk;
-    const int64_t n = (int64_t)oc * k;
-    weak_grad_strip_split(oc, k, M, splits, chunk);
-    static bool strip_attr = false;
-    if (!strip_attr) {
-        hipError_t e = hipFuncSetAttribute((const void*)weak_grad_strip_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WG_LDS);
+    const StripPlan p = weak_grad_strip_split(oc, k, M);
+    const auto kern = p.kw == 128 ? weak_grad_strip_kernel<128> : weak_grad_strip_kernel<64>;
+    static bool strip_attr[2] = {};
+    if (!strip_attr[p.kw == 128]) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, wg_lds(p.kw));
         if (e != hipSuccess) return e;
-        strip_attr = true;
+        strip_attr[p.kw == 128] = true;
     }
-    weak_grad_strip_kernel<<<ceil_div(oc, WG_OC) * ceil_div(k, 128) * splits, 256, WG_LDS, s>>>(oc, k, dY, (int)M, lddy, Xw, ldxw, (float*)ws, splits,
-                                                                                          chunk, dW, out_f32, accumulate);
+    kern<<<p.workgroups(oc, k), 256, wg_lds(p.kw), s>>>(oc, k, dY, (int)M, lddy, Xw, ldxw, (float*)ws, p.splits, p.chunk, dW, out_f32, accumulate);
     hipError_t e = hipGetLastError();
-    return e == hipSuccess && splits > 1 ? weak_grad_reduce((const float*)ws, splits, n, dW, out_f32, accumulate, s) : e;
+    return e == hipSuccess && p.splits > 1 ? weak_grad_reduce((const float*)ws, p.splits, (int64_t)oc * k, dW, out_f32, accumulate, s) : e;
 }
 hipError_t weak_grad_reduce(const float* part, int splits, int64_t n, void* dW, int out_f32, int accumulate, hipStream_t s) {
     weak_grad_reduce_kernel<<<ceil_div(n, 256), 256, 0, s>>>(part, splits, n, dW, out_f32, accumulate);

@@ -13,7 +13,7 @@ namespace gemm {
 // The tokens are split over `splits` workgroups per strip of output channels; each writes an fp32 partial
 // [OC][k] slab, summed in slab order by a second kernel (no atomics: deterministic).
 // The kernel is sized for what bounds it - reading dY once from
-// HBM: a workgroup owns 64 output channels x up to 128 weak columns over a range of tokens, so the
+// HBM: a workgroup owns 64 output channels x up to 128 or 64 weak columns over a range of tokens, so the
 // MFMA tiles hold no padding and a dY row contributes 128 contiguous bytes.  Both operands have
 // the contraction index (the token) as their row index; instead of transposing 8 x 8 blocks in
 // registers, the tiles go to LDS as they are ([token][column], rows padded by 64 bytes) and the
@@ -22,20 +22,21 @@ namespace gemm {
 // lanes l / 4, l / 4 + 4, l / 4 + 8, l / 4 + 12).  With source lane s pointing at row k0 + s / 4,
 // columns c0 + 4 (s % 4) .., a group receives columns c0 .. c0 + 15 of rows k0 .. k0 + 3 - four
 // consecutive contraction steps for 16 MFMA rows; two such loads make one fragment.
-// Wave w multiplies weak columns 32 w .. 32 w + 31 against the 64 channels.  With one split
+// Wave w multiplies weak columns 32 w .. 32 w + 31 against the 64 channels; in pieces of 64 columns 32 (w % 2) .. against 32 channels.  With one split
 // the result goes straight to dW, otherwise into fp32 slabs as above.
 constexpr int WG_OC = 64;                             // output channels per workgroup
 // Row pitches: a transposing fragment read takes, per half wave, 4 rows x 64 bytes (two 16-lane groups side by
 // side), so consecutive rows must sit 16 (or 48) banks apart: 256 + 64 and 128 + 64 bytes.  (With + 32 bytes a
 // third of the LDS cycles of this kernel were bank conflicts.)
-constexpr int WG_A_PITCH = 128 * 2 + 64;              // bytes per token row of the Xw tile
+constexpr int wg_a_pitch(int kw) { return kw * 2 + 64; }   // bytes per token row of the Xw tile
 constexpr int WG_B_PITCH = WG_OC * 2 + 64;            // ... of the dY tile
-constexpr int WG_A_BYTES = BK * WG_A_PITCH, WG_B_BYTES = BK * WG_B_PITCH;
-constexpr int WG_LDS = 2 * (WG_A_BYTES + WG_B_BYTES); // A0 A1 B0 B1
+constexpr int wg_lds(int kw) { return 2 * BK * (wg_a_pitch(kw) + WG_B_PITCH); }   // A0 A1 B0 B1
+constexpr int WG_LDS = wg_lds(128);
 
-// A weak block wider than 128 columns is taken in halves of 128 (workgroup index = ((strip, half), split)): the two halves
+// A weak block wider than KW = 128 or 64 columns is taken in pieces of KW (workgroup index = ((strip, piece), split)): the pieces
 // of a strip read the same dY rows and sit next to each other in the grid.
-// (bid: the workgroup's index among the strip workgroups; lds: its dynamic shared memory, WG_LDS bytes)
+// (bid: the workgroup's index among the strip workgroups; lds: its dynamic shared memory, wg_lds(KW) bytes)
+template <int KW>
 __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid, int oc_total, int k_total, const __half* __restrict__ dY, int M,
                                                      int64_t lddy, const __half* __restrict__ Xw, int64_t ldxw,
                                                      float* __restrict__ part, int splits, int chunk, void* dW,
@@ -45,20 +46,23 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
     using lds_s4 = __attribute__((address_space(3))) s4;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int halves = (k_total + 127) >> 7;
+    constexpr int WG_A_PITCH = wg_a_pitch(KW), WG_A_BYTES = BK * WG_A_PITCH, WG_B_BYTES = BK * WG_B_PITCH;
+    constexpr int CH = KW / 8, AU = CH / 4, AR = 256 / CH;   // Xw: chunks of a token, requests of a thread, tokens apart
+    constexpr int T = KW / 64;                               // 32 x 32 tiles of a wave: all of the strip's channels, or half
+    const int halves = (k_total + KW - 1) / KW;
     const int split = bid % splits, rest = bid / splits;
     const int kh = rest % halves, t_oc = rest / halves;
-    const int k = min(128, k_total - 128 * kh);   // this workgroup's weak columns: 128 kh .. 128 kh + k - 1
-    Xw += 128 * kh;
+    const int k = min(KW, k_total - KW * kh);   // this workgroup's weak columns: KW kh .. KW kh + k - 1
+    Xw += KW * kh;
     const int oc0 = t_oc * WG_OC;
     const int mb = split * chunk, me = min(mb + chunk, M);
     const int nst = (me - mb + BK - 1) / BK;
     const int fr = lane & 31, fk = lane >> 5;
 
-    // producers: 16-byte chunks, copied as they are.  Xw tile: 64 tokens x 16 chunks, four per
-    // thread (token ar + 16 u, chunk ac); dY tile: 64 tokens x 8 chunks, two per thread (token
+    // producers: 16-byte chunks, copied as they are.  Xw tile: 64 tokens x CH chunks, AU per
+    // thread (token ar + AR u, chunk ac); dY tile: 64 tokens x 8 chunks, two per thread (token
     // br + 32 u, chunk bc).  Chunks past k or past the last channel read column 0 and are zeroed.
-    const int ar = tid >> 4, ac = tid & 15, br = tid >> 3, bc = tid & 7;
+    const int ar = tid / CH, ac = tid % CH, br = tid >> 3, bc = tid & 7;
     const bool a_ok = 8 * ac < k, b_ok = oc0 + 8 * bc < oc_total;
     const u4 zero4 = u4{0u, 0u, 0u, 0u};
     // Addresses: a scalar base per stage plus a per-thread byte offset computed once (this kernel is bound by
@@ -67,15 +71,15 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
     // put() keeps only the rows that belong to it; stages past the range re-read the last one and store zeros.
     using gptr = const __attribute__((address_space(1))) char*;
     using g_u4 = const __attribute__((address_space(1))) u4;
-    uint32_t aoff[4], boff[2];
+    uint32_t aoff[AU], boff[2];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) aoff[u] = (uint32_t)(((int64_t)(ar + 16 * u) * ldxw + (a_ok ? 8 * ac : 0)) * 2);
+    for (int u = 0; u < AU; ++u) aoff[u] = (uint32_t)(((int64_t)(ar + AR * u) * ldxw + (a_ok ? 8 * ac : 0)) * 2);
 #pragma unroll
     for (int u = 0; u < 2; ++u) boff[u] = (uint32_t)(((int64_t)(br + 32 * u) * lddy + (b_ok ? oc0 + 8 * bc : 0)) * 2);
-    const bool cols_full = __builtin_amdgcn_readfirstlane((int)(k >= 8 * 16 && oc0 + WG_OC <= oc_total)) != 0;   // no thread's chunk is zeroed
+    const bool cols_full = __builtin_amdgcn_readfirstlane((int)(k >= KW && oc0 + WG_OC <= oc_total)) != 0;   // no thread's chunk is zeroed
     auto first_token = [&](int st) { return min(mb + BK * min(st, nst - 1), M - BK); };   // of the 64 tokens fetched for stage st
     // three stages of fetches in flight per thread (registers), a fourth in LDS being multiplied
-    u4 va[3][4], vb[3][2];
+    u4 va[3][AU], vb[3][2];
     auto fetch = [&](auto set_c, int st) {
         constexpr int SET = decltype(set_c)::value;
         const int t0 = first_token(st);
@@ -83,7 +87,7 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
         const char* bb = reinterpret_cast<const char*>(dY) + (int64_t)t0 * lddy * 2;
         asm volatile("" : "+s"(ab), "+s"(bb));
 #pragma unroll
-        for (int u = 0; u < 4; ++u) va[SET][u] = *reinterpret_cast<g_u4*>((gptr)ab + aoff[u]);
+        for (int u = 0; u < AU; ++u) va[SET][u] = *reinterpret_cast<g_u4*>((gptr)ab + aoff[u]);
 #pragma unroll
         for (int u = 0; u < 2; ++u) vb[SET][u] = *reinterpret_cast<g_u4*>((gptr)bb + boff[u]);
     };
@@ -94,12 +98,12 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
         unsigned char* sB = lds + 2 * WG_A_BYTES + buf * WG_B_BYTES;
         if (cols_full && st < nst && m0 + BK <= me) {   // a whole stage, whole columns (wave-uniform): the registers as they are
 #pragma unroll
-            for (int u = 0; u < 4; ++u) *reinterpret_cast<u4*>(sA + (ar + 16 * u) * WG_A_PITCH + 16 * ac) = va[SET][u];
+            for (int u = 0; u < AU; ++u) *reinterpret_cast<u4*>(sA + (ar + AR * u) * WG_A_PITCH + 16 * ac) = va[SET][u];
 #pragma unroll
             for (int u = 0; u < 2; ++u) *reinterpret_cast<u4*>(sB + (br + 32 * u) * WG_B_PITCH + 16 * bc) = vb[SET][u];
         } else if (st >= nst) {   // past the range: a tile of zeros
 #pragma unroll
-            for (int u = 0; u < 4; ++u) *reinterpret_cast<u4*>(sA + (ar + 16 * u) * WG_A_PITCH + 16 * ac) = zero4;
+            for (int u = 0; u < AU; ++u) *reinterpret_cast<u4*>(sA + (ar + AR * u) * WG_A_PITCH + 16 * ac) = zero4;
 #pragma unroll
             for (int u = 0; u < 2; ++u) *reinterpret_cast<u4*>(sB + (br + 32 * u) * WG_B_PITCH + 16 * bc) = zero4;
         } else {
@@ -108,8 +112,8 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
             // fill tile rows [0, 64 - shift), the rest of the tile is zero.
             const int shift = m0 - t0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int r = ar + 16 * u, tok = t0 + r;
+            for (int u = 0; u < AU; ++u) {
+                const int r = ar + AR * u, tok = t0 + r;
                 if (r >= shift) *reinterpret_cast<u4*>(sA + (r - shift) * WG_A_PITCH + 16 * ac) = (a_ok && tok < me) ? va[SET][u] : zero4;
                 if (r >= BK - shift) *reinterpret_cast<u4*>(sA + r * WG_A_PITCH + 16 * ac) = zero4;
             }
@@ -122,19 +126,20 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
         }
     };
 
-    f16v acc[2];
+    f16v acc[T];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
 
     // fragment addressing: lane = 16 g + s; rows (tokens) 8 (g / 2) + s / 4 (+ 4 for the second
     // load, + 16 per k-block), columns 16 (g % 2) + 4 (s % 4) of the wave's 32
     const int g = lane >> 4, s = lane & 15;
+    const int wa = T == 2 ? wave : wave & 1, wb = T == 2 ? 0 : wave >> 1;   // the wave's weak columns 32 wa .., channels 32 wb ..
     const int frow = 8 * (g >> 1) + (s >> 2), fcol = 16 * (g & 1) + 4 * (s & 3);
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)lds;
-    const uint32_t fa = lds0 + frow * WG_A_PITCH + 2 * (32 * wave + fcol);
-    const uint32_t fb = lds0 + 2 * WG_A_BYTES + frow * WG_B_PITCH + 2 * fcol;
+    const uint32_t fa = lds0 + frow * WG_A_PITCH + 2 * (32 * wa + fcol);
+    const uint32_t fb = lds0 + 2 * WG_A_BYTES + frow * WG_B_PITCH + 2 * (32 * wb + fcol);
     auto frag = [&](uint32_t addr, int pitch) {   // 8 contraction steps: rows +0..3 and +4..7
         const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(size_t)(addr));
         const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(size_t)(addr + 4 * pitch));
@@ -150,18 +155,18 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
         __builtin_amdgcn_sched_barrier(0);   // issue the fetches first: they are what the stage waits for
         const uint32_t a0 = fa + cur * WG_A_BYTES, b0 = fb + cur * WG_B_BYTES;
         // fragments are read one k-block ahead of the MFMAs that use them (one wave per SIMD: nothing else hides the LDS latency)
-        h8 a[2], bl[2], bh[2];
+        h8 a[2], b[T][2];
         auto frags = [&](int ks) {
             a[ks & 1] = frag(a0 + 16 * ks * WG_A_PITCH, WG_A_PITCH);
-            bl[ks & 1] = frag(b0 + 16 * ks * WG_B_PITCH, WG_B_PITCH);
-            bh[ks & 1] = frag(b0 + 16 * ks * WG_B_PITCH + 64, WG_B_PITCH);
+#pragma unroll
+            for (int t = 0; t < T; ++t) b[t][ks & 1] = frag(b0 + 16 * ks * WG_B_PITCH + 64 * t, WG_B_PITCH);
         };
         frags(0);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             if (ks < 3) frags(ks + 1);
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks & 1], bl[ks & 1], acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks & 1], bh[ks & 1], acc[1], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks & 1], b[t][ks & 1], acc[t], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
         put(std::integral_constant<int, (SET + 1) % 3>{}, st + 1, cur ^ 1);
@@ -179,18 +184,18 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
         stage(std::integral_constant<int, 1>{}, st + 1);
         stage(std::integral_constant<int, 2>{}, st + 2);
     }
-    if (32 * wave >= k) return;   // this wave's weak columns do not exist
-    // lane (fr, fk) holds, for channel oc0 + 32 t + fr, weak columns 32 wave + 8 g + 4 fk .. + 3
+    if (32 * wa >= k) return;   // this wave's weak columns do not exist
+    // lane (fr, fk) holds, for channel oc0 + 32 (wb + t) + fr, weak columns 32 wa + 8 g + 4 fk .. + 3
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int j = oc0 + 32 * t + fr;
+    for (int t = 0; t < T; ++t) {
+        const int j = oc0 + 32 * (wb + t) + fr;
         if (j >= oc_total) continue;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int i = 32 * wave + 8 * q + 4 * fk;
+            const int i = 32 * wa + 8 * q + 4 * fk;
             if (i >= k) continue;
             f4 r = f4{acc[t][4 * q + 0], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
-            const size_t at = (size_t)j * k_total + 128 * kh + i;
+            const size_t at = (size_t)j * k_total + KW * kh + i;
             if (splits > 1) {
                 *reinterpret_cast<f4*>(part + (size_t)split * oc_total * k_total + at) = r;
             } else if (out_f32) {
@@ -211,12 +216,13 @@ struct Strips {
     int64_t lddy, ldxw;
     const __half *dY, *Xw;
     float* part;
-    int splits, chunk;
+    int splits, chunk, kw;
     void* dW;
     int out_f32, accumulate;
 };
 __device__ __forceinline__ void weak_grad_strip(unsigned char* lds, int bid, const Strips& S) {
-    weak_grad_strip_body(lds, bid, S.oc, S.k, S.dY, S.M, S.lddy, S.Xw, S.ldxw, S.part, S.splits, S.chunk, S.dW, S.out_f32, S.accumulate);
+    if (S.kw == 128) weak_grad_strip_body<128>(lds, bid, S.oc, S.k, S.dY, S.M, S.lddy, S.Xw, S.ldxw, S.part, S.splits, S.chunk, S.dW, S.out_f32, S.accumulate);
+    else weak_grad_strip_body<64>(lds, bid, S.oc, S.k, S.dY, S.M, S.lddy, S.Xw, S.ldxw, S.part, S.splits, S.chunk, S.dW, S.out_f32, S.accumulate);
 }
 
 // The most ways the tokens are split for the strip kernel: about one workgroup per CU, every split a whole number of
@@ -229,29 +235,44 @@ inline int weak_grad_strip_most(int oc, int k, int64_t M) {
     if (want < 1) want = 1;
     return ceil_div(M, ceil_div(stages, want) * BK);
 }
-// The split taken: a stage of 64 tokens costs a workgroup about 0.62 us where the strip's 128 weak columns all exist, 1.06 where
-// some do not; workgroups past one per CU count in full there, by 0.3 here (a stage that waits leaves room for another's); a
+// The split and the pieces taken: a stage of 64 tokens costs a workgroup about 0.62 us where the piece's 128 weak columns all exist, 1.06 where
+// some do not, 0.42 and 0.7 in pieces of 64 (half the multiplications, two thirds of the loads and LDS accesses, in a stream that nothing else hides);
+// workgroups past one per CU count in full there, by 0.3 where columns are missing (a stage that waits leaves room for another's); a
 // split costs the second launch and its partial slab's way through memory (2 us once, 0.65 us per MB
-// and, in narrower blocks, 0.13 us each).  Measured, as many splits as
-// above against the rule's, us: 4096 channels, k = 128, M = 200 / 512 / 1003: 12.3 / 12.4 / 14.1 against 7.6 / 9.0 / 13.1 (one, one,
-// two; four at M = 4096 either way); 11008 channels, M = 512 / 2048: 19.0 / 26.0 against 9.5 / 22.6 (one; two at M = 3000);
-// 1024 channels, k = 128, M = 2048: 14.5 against 12.2 (four of eight).  Narrower blocks, one split against two: 13824 channels,
-// k = 64, M = 200 / 777 / 1500 / 3000: 9.0 / 17.8 / 27.4 / 49.8 against 13.5 / 19.2 / 23.1 / 36.3.
-inline void weak_grad_strip_split(int oc, int k, int64_t M, int& splits, int& chunk) {
-    const int tiles = ceil_div(oc, WG_OC) * ceil_div(k, 128);
+// and, where columns are missing, 0.13 us each).  Pieces of 64 read dY once for each: in whole blocks of 128 only where all have a CU
+// of their own (8192 channels, k = 256, M = 512 / 4096: 10.9 / 50.5 us against 10.0 / 40.2 by 128), and unsplit: behind tiles that fill the GPU twice as many
+// workgroups cost more than their shorter time saves (1024 x 8192 at 2000, forward and backward: 90.9 us against 88.9).  Measured, pieces of 128 -> this rule, us:
+// 4096 channels, k = 128, M = 200 / 512 / 777 / 1000: 7.5 / 8.8 / 12.3 / 12.9 -> 5.9 / 6.9 / 9.4 / 10.8; 5120 channels at
+// 1000 / 2000 14.0 / 19.3 -> 10.8 / 17.0; 13824 channels, k = 64, M = 200 / 777 / 1500 / 3000: 8.8 / 18.0 / 23.4 / 36.9 -> 6.0 / 9.7 /
+// 13.6 / 22.7; 4096 channels, k = 16, M = 777 / 2000 11.0 / 14.2 -> 9.0 / 11.3.  As many splits as above against the rule's, pieces of 128: 11008 channels,
+// M = 512 / 2048: 19.0 / 26.0 against 9.5 / 22.6 (one; two at M = 3000).
+struct StripPlan {
+    int splits, chunk, kw;
+    int workgroups(int oc, int k) const { return ceil_div(oc, WG_OC) * ceil_div(k, kw) * splits; }
+};
+inline StripPlan weak_grad_strip_split(int oc, int k, int64_t M) {
     const int stages = ceil_div(M, BK), most = weak_grad_strip_most(oc, k, M);
-    const bool full = k % 128 == 0;
-    const double slab_mb = (double)oc * k * 4e-6, stage_us = full ? 0.62 : 1.06;
+    const double slab_mb = (double)oc * k * 4e-6;
     double best = 1e30;
-    for (int s = 1; s <= most; ++s) {
-        const double w = (double)tiles * s / 256.0;
-        const double t = (w <= 1 ? 1 : (full ? w : 0.7 + 0.3 * w)) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + ((full ? 0.0 : 0.13) + 0.65 * slab_mb) * s : 0.0);
-        if (t < best) {
-            best = t;
-            chunk = ceil_div(stages, s) * BK;
+    StripPlan p = {1, stages * BK, 128};
+    for (int kw = 64; kw <= 128; kw += 64) {
+        const int tiles = ceil_div(oc, WG_OC) * ceil_div(k, kw);
+        const bool full = k % kw == 0;
+        if (kw == 128 && k <= 64) break;
+        const double stage_us = kw == 128 ? (full ? 0.62 : 1.06) : (full ? 0.42 : 0.7);
+        for (int s = 1; s <= most; ++s) {
+            const double w = (double)tiles * s / 256.0;
+            if (kw == 64 && k % 128 == 0 && (w > 1 || s > 1)) break;
+            const double t = (w <= 1 ? 1 : (full && kw == 128 ? w : 0.7 + 0.3 * w)) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + ((full ? 0.0 : 0.13) + 0.65 * slab_mb) * s : 0.0);
+            if (t < best) {
+                best = t;
+                p.chunk = ceil_div(stages, s) * BK;
+                p.kw = kw;
+            }
         }
     }
-    splits = ceil_div(M, chunk);
+    p.splits = ceil_div(M, p.chunk);
+    return p;
 }
 
 // The strips of g for a launch of an input gradient, cut as they would be alone (same bits): S.n = 0 where there are none to take or the
@@ -259,13 +280,16 @@ inline void weak_grad_strip_split(int oc, int k, int64_t M, int& splits, int& ch
 inline Strips make_strips(const WeakGrad* g, const __half* dY, int64_t M, int64_t lddy, size_t used) {
     Strips S = {};
     if (!g || !weak_grad_mfma_supported(g->oc, g->k, M)) return S;
-    weak_grad_strip_split(g->oc, g->k, M, S.splits, S.chunk);
+    const StripPlan p = weak_grad_strip_split(g->oc, g->k, M);
+    S.splits = p.splits;
+    S.chunk = p.chunk;
+    S.kw = p.kw;
     if (S.splits > 1) {
         const size_t need = (size_t)S.splits * g->oc * g->k * sizeof(float);
         if (!g->ws || g->ws_bytes < need || ((g->ws_bytes - need) & ~(size_t)15) < used) return S;
         S.part = reinterpret_cast<float*>(g->ws + ((g->ws_bytes - need) & ~(size_t)15));
     }
-    S.n = ceil_div(g->oc, WG_OC) * ceil_div(g->k, 128) * S.splits;
+    S.n = p.workgroups(g->oc, g->k);
     S.oc = g->oc;
     S.k = g->k;
     S.M = (int)M;
