@@ -734,8 +734,12 @@ __global__ __launch_bounds__(256) void gemm_dx_kernel(Layer L, const __half* __r
 // Everything else is the forward kernel's pipeline: 4 waves of 128 x 128, 16 slots of four MFMAs
 // per stage, quantized fragments converted three slots ahead, dY staged through LDS unchanged,
 // one barrier per stage after slot 11.  A tile is 256 channels = two halves, each quantized or
-// weak (Kq is a multiple of 128 here); the two waves that own a half follow its kind.
-// Requires OC % 64 == 0, Kq % 128 == 0 and k % 8 == 0.
+// weak; the two waves that own a half follow its kind.  Where Kq is no multiple of 128 the last quantized half ends early - its
+// words past the row's are clamped, its channels past Kq not stored - and the weak halves begin behind it: the tiles cover
+// dx_columns(L) columns, the weak channels moved up by as many as are missing there.  (That share of a half is multiplied for nothing; a half of both kinds
+// would give its two waves different code.  Forward and backward,
+// us, small tiles -> here: 8192 x 8192 with 64 weak columns at M = 1500 540 -> 387; 5120 x 5120 with 64 at 2048 271 -> 228; 4096 x 11008 with 16 at 777 235 -> 187.)
+// Requires dx_in_registers(L).
 constexpr int DX_LINE = 144;                      // 64 rows x 2 bytes + 16: consecutive lines 4 banks apart
 constexpr int DX_HALF = 128 * DX_LINE;            // lines of one half (a quantized half uses the first 32)
 constexpr int DX_LINES = 2 * DX_HALF;
@@ -765,6 +769,7 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
     using g_u4 = const __attribute__((address_space(1))) u4;
     using g_u16 = const __attribute__((address_space(1))) unsigned short;
     constexpr bool ANYQ = H0 == 0 || H1 == 0;
+    const int w0 = (L.kq + 127) & ~127;   // the column at which the weak halves begin
     constexpr int NW = 2 * (H0 + H1);   // weak items per thread: (row pair, 8 channels) blocks
     const int fr = lane & 31, fk = lane >> 5;
     auto sbase = [](const char* p) {
@@ -800,7 +805,7 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
 #pragma unroll
     for (int n = 0; n < NW; ++n) {
         const int half = (H0 == 1) ? n / 2 : 1;
-        const int kc = ic0 + 128 * half - L.kq + 8 * (xc + 8 * (n & 1));
+        const int kc = ic0 + 128 * half - w0 + 8 * (xc + 8 * (n & 1));
         woff[n] = ((uint32_t)(2 * rp) * (uint32_t)L.k + (uint32_t)max(min(kc, L.k - 8), 0)) * 2u;
     }
 
@@ -1118,7 +1123,7 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
             QEFT_STEPS64(step)
         };
         run_stages(stage);
-        store_f16_lds<false, 8>(acc, lds + wave * TILE_BYTES, dX, lddx, icw, L.ic, m0, M, lane);
+        store_f16_lds<false, 8>(acc, lds + wave * TILE_BYTES, dX, lddx, icw - (w0 - L.kq), L.ic, m0, M, lane);
     };
 #undef QEFT_STEPS64
 #undef QEFT_STEPS8
@@ -1156,7 +1161,7 @@ __device__ __forceinline__ void dx_rega_body(unsigned char* lds, Layer L, const 
         dX = part + (size_t)slot * (BT * BT) - ((size_t)m0 * BT + ic0);
         lddx = BT;
     }
-    // a half is weak when it starts at or past Kq (Kq % 128 == 0); without a weak block the surplus
+    // a half is weak when it starts at or past Kq; without a weak block the surplus
     // half of the last tile runs as a quantized one on clamped addresses and stores nothing
     const bool w0 = L.k > 0 && ic0 >= L.kq, w1 = L.k > 0 && ic0 + 128 >= L.kq;
     if (w0) dx_tile<1, 1, ONCE>(L, dY, M, lddy, dX, lddx, ic0, m0, lds);
@@ -1393,7 +1398,7 @@ bool gemm_dx_supported(const Layer& L, int64_t M) {
 
 // Row split of the input gradient, as for the forward: units of 8 stages (512 rows).
 static SplitPlan gemm_dx_plan(const Layer& L, int64_t M) {
-    if (!(L.oc % BK == 0 && L.kq % 128 == 0 && L.k % 8 == 0)) return SplitPlan();
+    if (!dx_in_registers(L) || L.kq % 128 != 0) return SplitPlan();   // (a slot has no room for the weak channels' other place)
     return plan_split(ceil_div(L.ic, BT) * ceil_div(M, BT), L.oc / BK);
 }
 
@@ -1411,9 +1416,10 @@ static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_
 static bool gemm_dx_dw_preferred(const Layer& L, const Strips& S);
 
 hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s, WeakGrad* g) {
-    const int tiles_m = ceil_div(M, BT), tiles_ic = ceil_div(L.ic, BT);
+    const bool in_registers = dx_in_registers(L);
+    const int tiles_m = ceil_div(M, BT), tiles_ic = ceil_div(in_registers ? dx_columns(L) : L.ic, BT);
     hipError_t e;
-    if (L.oc % BK == 0 && L.kq % 128 == 0 && L.k % 8 == 0) {
+    if (in_registers) {
         static bool attr[2] = {};
         const auto kern = L.once ? gemm_dx_rega_kernel<true> : gemm_dx_rega_kernel<false>;
         if (!attr[L.once]) {
@@ -1499,7 +1505,7 @@ hipError_t weak_grad_reduce(const float* part, int splits, int64_t n, void* dW, 
 static bool gemm_dx_dw_preferred(const Layer& L, const Strips& S) { return L.k > 0 && S.k <= 128; }
 
 static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, const Strips& S, hipStream_t s) {
-    const int tiles = ceil_div(L.ic, BT) * ceil_div(M, BT), n_dx = xcd_grid(tiles);
+    const int tiles_ic = ceil_div(dx_columns(L), BT), n_dx = xcd_grid(tiles_ic * ceil_div(M, BT));
     static bool attr[2] = {};
     constexpr int LDS_BYTES = DX_LDS > WG_LDS ? DX_LDS : WG_LDS;
     const auto kern = L.once ? gemm_dx_dw_kernel<true> : gemm_dx_dw_kernel<false>;
@@ -1508,7 +1514,7 @@ static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_
         if (e != hipSuccess) return e;
         attr[L.once] = true;
     }
-    kern<<<n_dx + S.n, 256, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, ceil_div(L.ic, BT), n_dx, S);
+    kern<<<n_dx + S.n, 256, LDS_BYTES, s>>>(L, dY, (int)M, lddy, dX, lddx, tiles_ic, n_dx, S);
     return hipGetLastError();
 }
 

@@ -764,6 +764,12 @@ double est_gemm(int channels, int64_t M, int stages, double per_stage) {
 }
 // the tiled GEMM with every tile split: a share's stages, the partial tiles' traffic (us per slot), the second launch
 double est_split(const GemmSplit& p, double fixed, double per_stage) { return fixed + p.stages * per_stage + 0.035 * p.tiles * p.splits; }
+// the unsplit input gradient
+double est_gemm_dx(const Layer& L, int64_t M) {
+    const int stages = ceil_div(L.oc, 64);
+    if (!dx_in_registers(L)) return 3.3 * est_gemm(L.ic, M, stages, 1.3);
+    return est_gemm(dx_columns(L), M, stages, L.kq % 128 == 0 ? 1.3 : 1.4);
+}
 }  // namespace
 
 // (32-bit offsets from a panel's first row: 128 rows of up to 2^23 elements.)  The estimate has to be 5 % ahead.  Measured
@@ -785,8 +791,9 @@ bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws) {
 // 4096 x 11008 at 320 (0.88) 57.6 against 59.5, 5120 x 5120 at 333 (0.91) 40.0 against 42.2, 4096 x 4096 at 333 / 512 (0.99) 33.0 / 35.7
 // against 34.1 / 35.8.  The short launches would gain 1 to 2 us (2048 x 1152 at 333 / 512 rows, 0.78: 20.3 / 21.1 against 19.0 / 18.9) and
 // keep the split's arithmetic, which callers that give the room for it rely on (the one-call backward's test there).  A partial last
-// group leaves the GEMM its LDS-staged form, at 3.3 to 4.5 times the time (4096 x 4096 with 8 weak columns, M = 227: 310 us; 4096 x
-// 11008, M = 1938: 641 us), and so does an OC that is no multiple of 64 (us, that form against this kernel: 4104 x 4096 at M = 64 / 777 /
+// group costs the register GEMM part of a half and its split; estimated at 1.4 us a stage it is taken where it is ahead (forward and backward, us,
+// it against this kernel: 4096 x 4096 with 64 weak columns at 777 / 1500 / 2048 121 / 146 / 169 against 91 / 150 / 212, 13824 x 5120 with 64 at 777 / 1500
+// 361 / 486 against 339 / 510).  An OC that is no multiple of 64 leaves the GEMM its LDS-staged form, at 3.3 to 4.5 times the time (us, that form against this kernel: 4104 x 4096 at M = 64 / 777 /
 // 2048: 292 / 292 / 292 against 35 / 60 / 111; 7184 x 5712 at 64 / 512 / 2048: 572 / 569 / 559 against 53 / 93 / 260).
 bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
     if (L.ng <= 0 || M <= 16 || lddy > (QEFT_MAX_DIM >> 1)) return false;
@@ -795,7 +802,7 @@ bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
         const double split = est_split(p, 12, 1.5);
         return !p.tail && est_dx(L, M).t < (split < 28 ? 0.75 : 0.85) * split;
     }
-    return est_dx(L, M).t < 0.95 * est_gemm(L.ic, M, ceil_div(L.oc, 64), 1.3) * (L.kq % 128 == 0 && L.oc % 64 == 0 ? 1.0 : 3.3);
+    return est_dx(L, M).t < 0.95 * est_gemm_dx(L, M);
 }
 
 // The panel kernel for few rows, where its estimate is 10 % ahead of what would run otherwise (32-bit offsets as above).  Of more than 256 rows, splits
@@ -807,7 +814,7 @@ bool dx_panel_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) 
     if (p.splits > 1 && M > 256 && (p.tail || p.stages > 8 || est_split(p, 12, 1.5) < 28)) return false;
     double other = est_dx(L, M).t;
     if (!dx_tile_preferred(L, M, lddy, split_ws))
-        other = p.splits > 1 && !p.tail ? est_split(p, 12, 1.5) : est_gemm(L.ic, M, ceil_div(L.oc, 64), 1.3) * (L.kq % 128 == 0 && L.oc % 64 == 0 ? 1.0 : 3.3);
+        other = p.splits > 1 && !p.tail ? est_split(p, 12, 1.5) : est_gemm_dx(L, M);
     return dx_panel_estimate(L, M) < 0.9 * other;
 }
 
@@ -832,14 +839,15 @@ bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx,
 }
 bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy, bool split_n, bool split_d) {
     if ((N.kq % 128 == 0 && N.oc % 64 == 0) || dx_panel_preferred(N, M, lddy, split_n)) return true;
-    if (!dx_tile_preferred(N, M, lddy, split_n)) return false;
+    const bool tiles = dx_tile_preferred(N, M, lddy, split_n);
+    if (!tiles && !dx_in_registers(N)) return false;
     const GemmSplit p = split_d ? gemm_dx_split(D, M) : GemmSplit{1, 0, 0, false};
     const double rounds = (int64_t)dx_tiles(N) * ceil_div(M, 64) > 512 ? 1.25 : 1.0, n = (double)N.oc * N.ic / (1 << 20);   // (a third round of tiles is underestimated)
     // (rows that are not whole stages leave the fp16 copy the LDS-staged form; us, 4-bit copy against it: 4104 x 4096 with 64 weak columns,
     // M = 64 / 777 / 2048: 41 / 67 / 174 against 160 / 166 / 168; 4456 x 14848 at 64 / 184 / 777: 51 / 75 / 229 against 206 / 208 / 218)
     double gemm = D.oc % 64 == 0 ? est_gemm(D.ic, M, D.oc / 64, 1.3) : est_gemm(D.ic, M, ceil_div(D.oc, 64), 2.0);
     if (p.splits > 1) gemm = p.tail ? gemm - D.oc / 64 * 1.3 + p.stages * 1.5 + 12 : est_split(p, 12, 1.5);   // (tail: the last round's tiles only)
-    return rounds * est_dx(N, M).t + 0.28 * n + 1.5 < 0.9 * (1.05 * gemm + 0.85 * n);
+    return (tiles ? rounds * est_dx(N, M).t : est_gemm_dx(N, M)) + 0.28 * n + 1.5 < 0.9 * (1.05 * gemm + 0.85 * n);
 }
 
 hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, hipStream_t s) {

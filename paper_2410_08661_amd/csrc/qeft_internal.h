@@ -154,6 +154,9 @@ struct GemmSplit {
 GemmSplit gemm_fwd_split(const Layer& L, int64_t M);
 GemmSplit gemm_dx_split(const Layer& L, int64_t M);
 bool gemm_dx_supported(const Layer& L, int64_t M);
+// The input gradient's GEMM with weights in registers: whole stages of 64 rows, blocks of 8 weak channels; its tiles cover dx_columns columns.
+inline bool dx_in_registers(const Layer& L) { return L.oc % 64 == 0 && L.k % 8 == 0 && (L.kq % 128 == 0 || (L.kq >= 128 && L.kq % 8 == 0)); }
+inline int dx_columns(const Layer& L) { return L.k > 0 ? (L.kq + 127) / 128 * 128 + L.k : L.ic; }
 hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s, WeakGrad* g = nullptr);
 size_t gemm_dx_split_workspace(const Layer& L, int64_t M);
 bool weak_grad_mfma_supported(int oc, int k, int64_t M);
