@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     const int nq = weak_split ? 0 : (is_split ? min(sps, L.kq / BK - s_first) : L.kq / BK);
     // weak stages: whole 64-column stages take the direct path below (A fragments straight from the fp16
     // block), a ragged block the LDS-staged stages at the end
-    const int nwf = weak_split ? min(sps, L.k / BK - s_first) : ((L.k % BK == 0 && last_split) ? L.k / BK : 0);
+    const int nwf = weak_split ? min(sps, L.k / BK - s_first) : ((L.kq % BK == 0 && L.k % BK == 0 && last_split) ? L.k / BK : 0);
     const int ns = nq + nwf;
     if (is_split) {
         // the epilogue addresses Y[m][oc] with absolute indices: point it at the slot's (m0, oc0)
@@ -333,18 +333,41 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    // weak block operands: chunk u of this thread is tile row xr + 32 u, 16-byte column xc of the stage
-    // (branch-free fetches: columns past k read the row's last 8 and are zeroed when stored)
-    const int nw = (nwf || !last_split) ? 0 : (L.k + BK - 1) / BK;
+    // the columns behind the whole stages, as fp16 through LDS: the weak block where it is ragged, and ahead of it the rest of the quantized
+    // columns where those are (n_rest, whole words).  Chunk u of this thread is tile row xr + 32 u, 16-byte column xc of the stage
+    // (columns past the end read the row's last 8 and are zeroed when stored).  Such a stage costs about three of the others, once; before, these layers had
+    // the small tiles at any size: 4096 x 11008 with 16 weak columns at 4096 rows 396 -> 304 us, 8192 x 8192 at 1500 225 -> 189, 13824 x 5120 at 777 141 -> 114
+    const int c_tail = L.kq / BK * BK, n_rest = L.kq - c_tail, n_tail = L.ic - c_tail;
+    const int nw = (nwf || !last_split) ? 0 : (n_tail + BK - 1) / BK;
     const u4 zero4 = u4{0u, 0u, 0u, 0u};
     u4 wa[8], wb[J];
     auto load_weak = [&](int w) {
-        const int col = min(BK * w + 8 * xc, L.k - 8);
+        const int col = min(BK * w + 8 * xc, n_tail - 8);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int r = xr + 32 * u;
-            wa[u] = ld16(L.weak + (size_t)min(oc0 + r, L.oc - 1) * L.k + col);
-            if (u < J) wb[u < J ? u : 0] = ld16(X + (size_t)min(m0 + r, M - 1) * ldx + L.kq + col);
+        for (int u = 0; u < J; ++u) wb[u] = ld16(X + (size_t)min(m0 + xr + 32 * u, M - 1) * ldx + c_tail + col);
+        if (col < n_rest) {
+            uint32_t word[8];
+            _Float16 sc[8], zp[8];
+            const _Float16 *ps = reinterpret_cast<const _Float16*>(L.scales) + (c_tail >> 7), *pz = reinterpret_cast<const _Float16*>(L.zeros) + (c_tail >> 7);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const size_t row = (size_t)min(oc0 + xr + 32 * u, L.oc - 1);
+                word[u] = L.qweight[row * L.stride + ((c_tail + col) >> 3)];
+                sc[u] = ps[row * L.gs];
+                zp[u] = pz[row * L.gs];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float nz = ONCE ? neg_zs(zp[u], sc[u]) : 0.f;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    const h2 q = h2{(_Float16)(float)((word[u] >> (8 * p)) & 15u), (_Float16)(float)((word[u] >> (8 * p + 4)) & 15u)};
+                    wa[u][p] = h2_bits(ONCE ? h2{dequant_once(q.x, sc[u], nz), dequant_once(q.y, sc[u], nz)} : (q - h2{zp[u], zp[u]}) * h2{sc[u], sc[u]});
+                }
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) wa[u] = ld16(L.weak + (size_t)min(oc0 + xr + 32 * u, L.oc - 1) * L.k + (col - n_rest));
         }
     };
 
@@ -599,7 +622,7 @@ __global__ __launch_bounds__(256) void gemm_fwd_rega_kernel(Layer L, const __hal
     auto store_weak = [&](int w, int q) {   // chunks 2 q, 2 q + 1 of this thread, of stage w
         unsigned char* sB = lds + (w & 1) * TILE_BYTES;
         unsigned char* sA = lds + (2 + (w & 1)) * TILE_BYTES;
-        const bool ok = BK * w + 8 * xc < L.k;
+        const bool ok = BK * w + 8 * xc < n_tail;
 #pragma unroll
         for (int u = 2 * q; u < 2 * q + 2; ++u) {
             *reinterpret_cast<u4*>(sA + tile_off(xr + 32 * u, xc)) = ok ? wa[u] : zero4;
@@ -1353,7 +1376,7 @@ GemmSplit gemm_fwd_split(const Layer& L, int64_t M) {
 hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, void* ws, hipStream_t s) {
     const int tiles_oc = ceil_div(L.oc, BT), tiles_m = ceil_div(M, BT);
     hipError_t e;
-    if (L.kq % BK == 0 && (L.kq > 0 || (L.k > 0 && L.k % BK == 0))) {   // whole stages: weights straight into MFMA operand registers
+    if (fwd_in_registers(L)) {   // weights straight into MFMA operand registers
         // as many panels as of 256 rows, each of the fewest rows: the tiles, the splits and the workspace stay what they are,
         // and a tile multiplies less padding (us, panels of 256 rows before -> now: 13824 x 5120 with its split, M = 300 / 333 /
         // 400 / 1300: 74 / 75 / 77 / 204 -> 58 / 65 / 72 / 185; 4096 x 11008, M = 777: 96 -> 89; multiples of 256 unchanged)

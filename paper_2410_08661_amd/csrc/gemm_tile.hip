@@ -762,6 +762,13 @@ double est_gemm(int channels, int64_t M, int stages, double per_stage) {
     const int64_t tiles = (int64_t)ceil_div(channels, 256) * ceil_div(M, 256);
     return (double)((tiles + 255) / 256) * stages * per_stage + 8;
 }
+// the unsplit forward; a last stage of quantized columns that ends early is converted ahead of its products, and so are the weak columns behind it
+double est_gemm_fwd(const Layer& L, int64_t M) {
+    const int whole = ceil_div(L.kq, 64) + ceil_div(L.k, 64);
+    if (L.kq % 64 == 0) return est_gemm(L.oc, M, whole, 1.15 * panel(M));
+    if (!fwd_in_registers(L)) return 2.4 * est_gemm(L.oc, M, whole, 1.15);
+    return est_gemm(L.oc, M, L.kq / 64 + 3 * ceil_div(L.ic - L.kq / 64 * 64, 64), 1.3 * panel(M));
+}
 // the tiled GEMM with every tile split: a share's stages, the partial tiles' traffic (us per slot), the second launch
 double est_split(const GemmSplit& p, double fixed, double per_stage) { return fixed + p.stages * per_stage + 0.035 * p.tiles * p.splits; }
 // the unsplit input gradient
@@ -776,14 +783,14 @@ double est_gemm_dx(const Layer& L, int64_t M) {
 // with a split workspace, GEMM against this kernel: forward 4096 x 4096, M = 333: 32 us against 26, M = 512: 34 against 29,
 // 5120 x 5120, M = 333: 38 against 33, 6144 x 6144, M = 320: 48 against 44; M = 777 on 4096 x 4096: 43 against 40 (GEMM
 // kept: too close), 4096 x 11008, M = 333: 56 against 62; input gradient 2560 x 7168, M = 320: 36 against 32.
-// Rows whose quantized part is not whole stages have only the LDS-staged GEMM as the alternative, at 2.4 times the time
-// (4096 x 4096 with 8 weak columns, M = 227: 193 us against 26).
+// Rows whose quantized part is not whole stages are the register GEMM's too, without a split and with a last stage at three times the others' time (with 8 or 16
+// weak columns, it against this kernel: 4096 x 4096 at 1500 / 2048 / 4096 86 / 91 / 119 us against 71 / 82 / 161, 5120 x 5120 at 1500 / 2048 106 / 107 against 95 / 139, 11008 x
+// 4096 at 333 / 777 68 / 80 against 62 / 105).  Rows of less than a stage leave the LDS-staged GEMM, at 2.4 times the time.
 bool fwd_tile_preferred(const Layer& L, int64_t M, int64_t ldx, bool split_ws) {
     if (L.ng <= 0 || M <= 16 || ldx > (QEFT_MAX_DIM >> 1)) return false;
     const GemmSplit p = split_ws ? gemm_fwd_split(L, M) : GemmSplit{1, 0, 0, false};
     if (p.splits > 1) return !p.tail && est_fwd(L, M).t < 0.95 * est_split(p, 11, 1.45 * panel(M));
-    const double g = est_gemm(L.oc, M, ceil_div(L.kq, 64) + ceil_div(L.k, 64), 1.15 * (L.kq % 64 == 0 ? panel(M) : 1.0)) * (L.kq % 64 == 0 ? 1.0 : 2.4);
-    return est_fwd(L, M).t < 0.95 * g;
+    return est_fwd(L, M).t < 0.95 * est_gemm_fwd(L, M);
 }
 // The input gradient.  Against the split the estimate has to be 15 % ahead (its weak tiles run longer than
 // estimated), 25 % where the split takes less than 28 us.  Measured, split GEMM against this kernel: 2560 x 7168 at M = 256 / 320 /
@@ -828,14 +835,15 @@ bool dx_panel_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) 
 // 5120 x 13824 with 72 at M = 803: 256 against 189.
 bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx, bool split_n, bool split_d) {
     if (N.kq % 64 == 0 || (fwd_mid_supported(N, M, ldx) && fwd_mid_preferred(N, M, split_n))) return true;
-    if (!fwd_tile_preferred(N, M, ldx, split_n)) return false;
+    const bool tiles = fwd_tile_preferred(N, M, ldx, split_n);
+    if (!tiles && !fwd_in_registers(N)) return false;
     const GemmSplit p = split_d ? gemm_fwd_split(D, M) : GemmSplit{1, 0, 0, false};
     const double n = (double)N.oc * N.ic / (1 << 20);
     double t16;
     if (D.ic % 64 != 0) t16 = 1.1 * est_gemm(D.oc, M, ceil_div(D.ic, 64), 1.15 * 2.4) + 1.2 * n;
     else if (p.splits > 1 && !p.tail) t16 = 8 + 1.31 * p.stages + 0.09 * p.tiles * p.splits + n;
     else t16 = est_gemm(D.oc, M, D.ic / 64, 1.45 * panel(M)) + 2 + 1.1 * n - (p.tail ? 1.45 * (D.ic / 64 * panel(M) - p.stages) - 10 : 0);
-    return est_fwd(N, M).t + 0.2 * n + 3.5 < 0.94 * t16;
+    return (tiles ? est_fwd(N, M).t : est_gemm_fwd(N, M)) + 0.2 * n + 3.5 < 0.94 * t16;
 }
 bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy, bool split_n, bool split_d) {
     if ((N.kq % 128 == 0 && N.oc % 64 == 0) || dx_panel_preferred(N, M, lddy, split_n)) return true;

@@ -142,6 +142,8 @@ hipError_t dx_panel(const Layer& L, const __half* dY, int64_t M, int64_t lddy, _
 
 // ---- prefill / fine-tune path: MFMA GEMMs (gemm.hip) ---------------------------------------
 bool gemm_fwd_supported(const Layer& L, int64_t M);
+// The forward's GEMM with weights in registers: at least a stage of quantized columns (what is left of them, whole words, goes with the weak block), or whole stages of fp16 ones.
+inline bool fwd_in_registers(const Layer& L) { return L.kq >= 64 ? L.kq % 8 == 0 : (L.kq == 0 && L.k > 0 && L.k % 64 == 0); }
 // ws: optional device workspace of gemm_fwd_split_workspace() bytes (16-byte aligned); with it, launches of few tiles, or with a
 // sparsely filled last round of tiles, split K (for dX: the weight rows) of those tiles
 hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, void* ws, hipStream_t s);
