@@ -1376,7 +1376,7 @@ GemmSplit gemm_fwd_split(const Layer& L, int64_t M) {
 hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, void* ws, hipStream_t s) {
     const int tiles_oc = ceil_div(L.oc, BT), tiles_m = ceil_div(M, BT);
     hipError_t e;
-    if (fwd_in_registers(L)) {   // weights straight into MFMA operand registers
+    if (fwd_in_registers(L) && (L.kq % BK == 0 || ldx <= (QEFT_MAX_DIM >> 1))) {   // weights straight into MFMA operand registers (32-bit offsets within a panel)
         // as many panels as of 256 rows, each of the fewest rows: the tiles, the splits and the workspace stay what they are,
         // and a tile multiplies less padding (us, panels of 256 rows before -> now: 13824 x 5120 with its split, M = 300 / 333 /
         // 400 / 1300: 74 / 75 / 77 / 204 -> 58 / 65 / 72 / 185; 4096 x 11008, M = 777: 96 -> 89; multiples of 256 unchanged)
@@ -1439,7 +1439,7 @@ static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_
 static bool gemm_dx_dw_preferred(const Layer& L, const Strips& S);
 
 hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s, WeakGrad* g) {
-    const bool in_registers = dx_in_registers(L);
+    const bool in_registers = dx_in_registers(L) && (L.kq % 128 == 0 || lddy <= (QEFT_MAX_DIM >> 1));   // (32-bit offsets within a panel)
     const int tiles_m = ceil_div(M, BT), tiles_ic = ceil_div(in_registers ? dx_columns(L) : L.ic, BT);
     hipError_t e;
     if (in_registers) {
