@@ -792,7 +792,6 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
     using g_u4 = const __attribute__((address_space(1))) u4;
     using g_u16 = const __attribute__((address_space(1))) unsigned short;
     constexpr bool ANYQ = H0 == 0 || H1 == 0;
-    const int w0 = (L.kq + 127) & ~127;   // the column at which the weak halves begin
     constexpr int NW = 2 * (H0 + H1);   // weak items per thread: (row pair, 8 channels) blocks
     const int fr = lane & 31, fk = lane >> 5;
     auto sbase = [](const char* p) {
@@ -828,7 +827,7 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
 #pragma unroll
     for (int n = 0; n < NW; ++n) {
         const int half = (H0 == 1) ? n / 2 : 1;
-        const int kc = ic0 + 128 * half - w0 + 8 * (xc + 8 * (n & 1));
+        const int kc = ic0 + 128 * half - ((L.kq + 127) & ~127) + 8 * (xc + 8 * (n & 1));   // (the weak halves begin at a multiple of 128)
         woff[n] = ((uint32_t)(2 * rp) * (uint32_t)L.k + (uint32_t)max(min(kc, L.k - 8), 0)) * 2u;
     }
 
@@ -1146,7 +1145,7 @@ __device__ __forceinline__ void dx_tile(const Layer& L, const __half* __restrict
             QEFT_STEPS64(step)
         };
         run_stages(stage);
-        store_f16_lds<false, 8>(acc, lds + wave * TILE_BYTES, dX, lddx, icw - (w0 - L.kq), L.ic, m0, M, lane);
+        store_f16_lds<false, 8>(acc, lds + wave * TILE_BYTES, dX, lddx, icw - (-L.kq & 127), L.ic, m0, M, lane);
     };
 #undef QEFT_STEPS64
 #undef QEFT_STEPS8
