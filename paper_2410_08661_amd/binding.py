@@ -5,12 +5,13 @@ pointers), the functions below take torch tensors and pass `data_ptr()` and the 
 HIP stream.  PyTorch is used for device memory and streams, nothing else; there is no
 fallback path: if the library is missing the import fails.  The calls of training and decode loops
 go through `_marshal` (csrc/marshal.cpp), which does the same natively for exact tensors on
-the current GPU and returns None for anything else: ctypes then.
+the current GPU and returns None for anything else: ctypes then, as everywhere where `_marshal.so` is missing.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import types
 
 import torch  # imported first on purpose: the library must bind to the HIP runtime torch loaded
 
@@ -146,14 +147,16 @@ class Weight:
         return lay.qweight_bytes + lay.scales_bytes + lay.zeros_bytes + lay.weak_bytes
 
 
+_MARSHALLED = ("qeft_linear_fwd", "qeft_linear_fwd_group", "qeft_linear_bwd_dx", "qeft_linear_bwd", "qeft_linear_fwd_irregular",
+               "qeft_linear_bwd_dx_irregular", "qeft_weak_grad")
+
+
 def _load_marshal():
     try:
         from . import _marshal as m
-    except ImportError as e:
-        raise ImportError(f"{os.path.join(_HERE, '_marshal.so')} is not built or does not load: run `python -m paper_2410_08661_amd.build`") from e
-    m.init(tuple(C.cast(getattr(raw, n), C.c_void_p).value for n in (
-        "qeft_linear_fwd", "qeft_linear_fwd_group", "qeft_linear_bwd_dx", "qeft_linear_bwd", "qeft_linear_fwd_irregular",
-        "qeft_linear_bwd_dx_irregular", "qeft_weak_grad")), qeft_desc_t, Weight)
+    except ImportError:   # not built, or not for this torch: every call is ctypes'
+        return types.SimpleNamespace(**{n.removeprefix("qeft_"): lambda *args: None for n in _MARSHALLED})
+    m.init(tuple(C.cast(getattr(raw, n), C.c_void_p).value for n in _MARSHALLED), qeft_desc_t, Weight)
     return m
 
 

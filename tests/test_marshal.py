@@ -1,8 +1,12 @@
 """The native way from tensors to the C functions: what it takes, what it leaves to ctypes, and that both give the same."""
+import subprocess
+import sys
+
 import pytest
 import torch
 
 from paper_2410_08661_amd import binding as B
+from paper_2410_08661_amd import build
 
 
 class Sub(torch.Tensor):
@@ -73,3 +77,22 @@ def test_native_calls_report_errors_and_keep_to_the_current_stream():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, want)
+
+
+def test_the_binding_does_without_the_module():
+    code = ("import sys; sys.modules['paper_2410_08661_amd._marshal'] = None\n"
+            "from paper_2410_08661_amd import binding as B\n"
+            "d = B.make_desc(64, 256, 8, 4, 128)\n"
+            "for n in ('linear_fwd', 'linear_fwd_group', 'linear_bwd_dx', 'linear_bwd', 'linear_fwd_irregular', 'linear_bwd_dx_irregular', 'weak_grad'):\n"
+            "    assert getattr(B._native, n)(d, None, None) is None\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=build.ROOT)
+    assert r.returncode == 0, r.stderr
+
+
+def test_a_build_without_a_host_compiler(monkeypatch, tmp_path, capsys):
+    old = tmp_path / "_marshal.so"
+    old.write_bytes(b"of another torch")
+    monkeypatch.setattr(build, "MARSHAL_PATH", str(old))
+    monkeypatch.setenv("PATH", str(tmp_path))
+    assert build._build_marshal() is False and not old.exists()
+    assert "ctypes" in capsys.readouterr().err
