@@ -1375,7 +1375,7 @@ GemmSplit gemm_fwd_split(const Layer& L, int64_t M) {
 hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, void* ws, hipStream_t s) {
     const int tiles_oc = ceil_div(L.oc, BT), tiles_m = ceil_div(M, BT);
     hipError_t e;
-    if (fwd_in_registers(L) && (L.kq % BK == 0 || ldx <= (QEFT_MAX_DIM >> 1))) {   // weights straight into MFMA operand registers (32-bit offsets within a panel)
+    if (fwd_in_registers(L, M, ldx)) {   // weights straight into MFMA operand registers
         // as many panels as of 256 rows, each of the fewest rows: the tiles, the splits and the workspace stay what they are,
         // and a tile multiplies less padding (us, panels of 256 rows before -> now: 13824 x 5120 with its split, M = 300 / 333 /
         // 400 / 1300: 74 / 75 / 77 / 204 -> 58 / 65 / 72 / 185; 4096 x 11008, M = 777: 96 -> 89; multiples of 256 unchanged)
@@ -1438,7 +1438,7 @@ static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_
 static bool gemm_dx_dw_preferred(const Layer& L, const Strips& S);
 
 hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s, WeakGrad* g) {
-    const bool in_registers = dx_in_registers(L) && (L.kq % 128 == 0 || lddy <= (QEFT_MAX_DIM >> 1));   // (32-bit offsets within a panel)
+    const bool in_registers = dx_in_registers(L, M, lddy);
     const int tiles_m = ceil_div(M, BT), tiles_ic = ceil_div(in_registers ? dx_columns(L) : L.ic, BT);
     hipError_t e;
     if (in_registers) {
@@ -1497,6 +1497,7 @@ size_t weak_grad_mfma_workspace(int oc, int k, int64_t M) {
 
 hipError_t weak_grad_mfma(int oc, int k, const __half* dY, int64_t M, int64_t lddy, const __half* Xw, int64_t ldxw,
                           void* dW, int out_f32, int accumulate, void* ws, hipStream_t s) {
+    if (!strip_offsets_fit(lddy) || !strip_offsets_fit(ldxw)) return weak_grad_generic(oc, k, dY, M, lddy, Xw, ldxw, dW, out_f32, accumulate, s);
     const StripPlan p = weak_grad_strip_split(oc, k, M);
     const auto kern = p.kw == 128 ? weak_grad_strip_kernel<128> : weak_grad_strip_kernel<64>;
     static bool strip_attr[2] = {};

@@ -834,9 +834,10 @@ bool dx_panel_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) 
 // 109 / 434 against 91 / 99 / 119 / 277; forward of 13824 x 5120 with 16 at M = 210 / 571 / 1066: 64 / 150 / 234 against 116 / 180 / 243, of
 // 5120 x 13824 with 72 at M = 803: 256 against 189.
 bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx, bool split_n, bool split_d) {
-    if (N.kq % 64 == 0 || (fwd_mid_supported(N, M, ldx) && fwd_mid_preferred(N, M, split_n))) return true;
+    const bool in_registers = fwd_in_registers(N, M, ldx);
+    if ((N.kq % 64 == 0 && in_registers) || (fwd_mid_supported(N, M, ldx) && fwd_mid_preferred(N, M, split_n))) return true;
     const bool tiles = fwd_tile_preferred(N, M, ldx, split_n);
-    if (!tiles && (!fwd_in_registers(N) || ldx > (QEFT_MAX_DIM >> 1))) return false;
+    if (!tiles && !in_registers) return false;
     const GemmSplit p = split_d ? gemm_fwd_split(D, M) : GemmSplit{1, 0, 0, false};
     const double n = (double)N.oc * N.ic / (1 << 20);
     double t16;
@@ -846,9 +847,10 @@ bool fwd_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t ldx,
     return (tiles ? est_fwd(N, M).t : est_gemm_fwd(N, M)) + 0.2 * n + 3.5 < 0.94 * t16;
 }
 bool dx_copy4_preferred(const Layer& N, const Layer& D, int64_t M, int64_t lddy, bool split_n, bool split_d) {
-    if ((N.kq % 128 == 0 && N.oc % 64 == 0) || dx_panel_preferred(N, M, lddy, split_n)) return true;
+    const bool in_registers = dx_in_registers(N, M, lddy);
+    if ((N.kq % 128 == 0 && in_registers) || dx_panel_preferred(N, M, lddy, split_n)) return true;
     const bool tiles = dx_tile_preferred(N, M, lddy, split_n);
-    if (!tiles && (!dx_in_registers(N) || lddy > (QEFT_MAX_DIM >> 1))) return false;
+    if (!tiles && !in_registers) return false;
     const GemmSplit p = split_d ? gemm_dx_split(D, M) : GemmSplit{1, 0, 0, false};
     const double rounds = (int64_t)dx_tiles(N) * ceil_div(M, 64) > 512 ? 1.25 : 1.0, n = (double)N.oc * N.ic / (1 << 20);   // (a third round of tiles is underestimated)
     // (rows that are not whole stages leave the fp16 copy the LDS-staged form; us, 4-bit copy against it: 4104 x 4096 with 64 weak columns,

@@ -142,8 +142,12 @@ hipError_t dx_panel(const Layer& L, const __half* dY, int64_t M, int64_t lddy, _
 
 // ---- prefill / fine-tune path: MFMA GEMMs (gemm.hip) ---------------------------------------
 bool gemm_fwd_supported(const Layer& L, int64_t M);
+// The register kernels address a panel's rows (256 at most) by 32-bit byte offsets from its first.  What they do not reach - a pitch of more than 8.4
+// million elements under 256 rows - is the LDS-staged kernels', whose row addresses are of 64 bits.
+inline bool panel_offsets_fit(int64_t rows, int64_t ld) { return ld <= (int64_t)1 << 32 && ((rows < 256 ? rows : 256) - 1) * 2 * ld + 128 <= (int64_t)1 << 32; }
 // The forward's GEMM with weights in registers: at least a stage of quantized columns (what is left of them, whole words, goes with the weak block), or whole stages of fp16 ones.
 inline bool fwd_in_registers(const Layer& L) { return L.kq >= 64 ? L.kq % 8 == 0 : (L.kq == 0 && L.k > 0 && L.k % 64 == 0); }
+inline bool fwd_in_registers(const Layer& L, int64_t M, int64_t ldx) { return fwd_in_registers(L) && panel_offsets_fit(M, ldx) && panel_offsets_fit(L.oc, L.k); }
 // ws: optional device workspace of gemm_fwd_split_workspace() bytes (16-byte aligned); with it, launches of few tiles, or with a
 // sparsely filled last round of tiles, split K (for dX: the weight rows) of those tiles
 hipError_t gemm_fwd(const Layer& L, const __half* X, int64_t M, int64_t ldx, __half* Y, int64_t ldy, void* ws, hipStream_t s);
@@ -158,6 +162,7 @@ GemmSplit gemm_dx_split(const Layer& L, int64_t M);
 bool gemm_dx_supported(const Layer& L, int64_t M);
 // The input gradient's GEMM with weights in registers: whole stages of 64 rows, blocks of 8 weak channels; its tiles cover dx_columns columns.
 inline bool dx_in_registers(const Layer& L) { return L.oc % 64 == 0 && L.k % 8 == 0 && (L.kq % 128 == 0 || (L.kq >= 128 && L.kq % 8 == 0)); }
+inline bool dx_in_registers(const Layer& L, int64_t M, int64_t lddy) { return dx_in_registers(L) && panel_offsets_fit(M, lddy); }
 inline int dx_columns(const Layer& L) { return L.k > 0 ? (L.kq + 127) / 128 * 128 + L.k : L.ic; }
 hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s, WeakGrad* g = nullptr);
 size_t gemm_dx_split_workspace(const Layer& L, int64_t M);

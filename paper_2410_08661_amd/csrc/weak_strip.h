@@ -210,6 +210,9 @@ __device__ __forceinline__ void weak_grad_strip_body(unsigned char* lds, int bid
     }
 }
 
+// A stage's 64 tokens are addressed by 32-bit byte offsets from its first: pitches of up to 2^25 elements, past them the general kernel.
+inline bool strip_offsets_fit(int64_t ld) { return ld <= 2 * (int64_t)QEFT_MAX_DIM; }
+
 // The strips as a launch carries them; n workgroups (0: none).
 struct Strips {
     int n, oc, k, M;
@@ -279,7 +282,7 @@ inline StripPlan weak_grad_strip_split(int oc, int k, int64_t M) {
 // workspace has no room for their slabs behind what the input gradient uses of it.
 inline Strips make_strips(const WeakGrad* g, const __half* dY, int64_t M, int64_t lddy, size_t used) {
     Strips S = {};
-    if (!g || !weak_grad_mfma_supported(g->oc, g->k, M)) return S;
+    if (!g || !weak_grad_mfma_supported(g->oc, g->k, M) || !strip_offsets_fit(lddy) || !strip_offsets_fit(g->ldxw)) return S;
     const StripPlan p = weak_grad_strip_split(g->oc, g->k, M);
     S.splits = p.splits;
     S.chunk = p.chunk;
