@@ -81,7 +81,8 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
     if (!weak) {
-        // 64 weight rows of stage st: from 64 st on, the last 64 where OC is no multiple of 64 (what is shared with the stage before counts as zeros)
+        // 64 weight rows of stage st: from 64 st on, the last 64 where OC is no multiple of 64 (what is shared with the stage before counts as zeros,
+        // in both operands: an infinite weight counted already may not meet the zeros of dY)
         auto first_row = [&](int st) { return min(64 * st, L.oc - 64); };
         const int nst = (L.oc + 63) >> 6;
         unsigned char* wl = mine + J * 4096;
@@ -162,6 +163,13 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
 #pragma unroll
                     for (int ks = 4 * ph / PH; ks < 4 * (ph + 1) / PH; ++ks) {
                         const bool live = first_row(st) + 8 * (4 * (ks >> 1) + 2 * fk + (ks & 1)) >= 64 * st;
+                        const u4 zero4 = u4{0u, 0u, 0u, 0u};
+                        sc[ks] = live ? sc[ks] : zero4;   // (s = 0 and z = 0: a weight of zero whatever its code)
+                        if constexpr (ONCE) {
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) nz[ks][h] = live ? nz[ks][h] : f4{0.f, 0.f, 0.f, 0.f};
+                        } else
+                            zp[ks] = live ? zp[ks] : zero4;
 #pragma unroll
                         for (int j = 0; j < J; ++j) b[ks][j] = live ? b[ks][j] : zero8;
                     }

@@ -2,9 +2,11 @@
 stages the waves do not divide evenly, a last stage that begins at OC - 64, weak blocks narrower than a tile, of several, or none, 3-bit layers
 through their 4-bit copy (one rounding).  Tolerance: parity_util's bar (weights rounded to fp16 once, 2^-11 relative each, over at least 64
 terms; fp16 results)."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import qeft_oracle as qo
 from paper_2410_08661_amd import binding as B
 from paper_2410_08661_amd import synth
 from parity_util import HostLayer, assert_close, pad_cols
@@ -33,3 +35,27 @@ def test_panel_input_gradient(oc, ic, k, bits):
         assert torch.equal(first, dx), f"M={m}: repeats differ"
         assert bool((back[0] == 7).all()) and bool((back[m + 1] == 7).all()) and bool((back[:, ic:] == 7).all()), f"M={m}: wrote outside"
         assert_close(dx.cpu().numpy(), ref.cpu().numpy(), f"M={m}")
+
+
+@pytest.mark.parametrize("oc,ic,k,bits,row", [(72, 264, 8, 4, 20), (520, 1160, 8, 4, 460), (1096, 2048, 64, 3, 1040), (1032, 2000, 264, 4, 1000)])
+def test_infinite_weights_in_rows_of_two_stages(oc, ic, k, bits, row):
+    """A row that the last stage shares with the one before: its weights past fp16's range are infinities in one group and one weak column, and stay that
+    (fetched again beside rows of zeros they would make no number of them)."""
+    layer = HostLayer(oc, ic, k, bits, 128, seed=oc)
+    assert oc % 64 and oc // 64 * 64 > row >= oc - 64
+    layer.codes[row, :128], layer.zeros[row, 0], layer.scales[row, 0] = 7, 1, 3e4
+    layer.qweight = qo.pack_codes(layer.codes, bits, layer.lay["row_stride_words"])
+    layer.weak[row, 3] = float("-inf")
+    w = layer.to_device()
+    for m in (17, 33, 64, 128):
+        dy = synth.make_grad_output(m, oc, m)
+        dy[:, row] += 0.25                          # (no zero among them)
+        d = pad_cols(dy)[0]
+        dx = B.qeft_linear_bwd_dx(layer.desc, w, d, ws=None if bits == 3 else False)
+        torch.cuda.synchronize()
+        got = dx.cpu().numpy()
+        ends = np.r_[0:128, layer.kq + 3]
+        want = np.where(np.sign(dy[:, row, None].astype(np.float64)) * np.where(ends < 128, 1.0, -1.0) > 0, np.inf, -np.inf)
+        assert np.array_equal(got[:, ends], want), f"M={m}"
+        rest = np.setdiff1d(np.arange(ic), ends)
+        assert_close(got[:, rest], dy.astype(np.float64) @ layer.w64[:, rest], f"M={m}")
