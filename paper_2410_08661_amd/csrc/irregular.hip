@@ -72,24 +72,34 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(const unsigned short*
     }
 }
 
-// Rows of up to 8 K channels (a multiple of 8): the same, with this thread's table entries held in registers for all rows of the
+// Rows of up to 8 K channels (gathered ones a multiple of 8): the same, with this thread's table entries held in registers for all rows of the
 // workgroup, two row buffers so that one barrier per row suffices, and the next row's loads in flight while the current one is
 // assembled.  A thread owns pairs of neighbouring stored columns, 256 pairs apart: neighbouring lanes then meet neighbouring banks where the
 // table ascends (eight columns per thread had eight lanes on one), and the table comes as 8-byte loads beside the first row's.
 // Bound by latency at a few hundred rows - table and row, LDS, stores - hence a row or two per workgroup there.
 // us, eight columns per thread and up to eight rows per workgroup -> now: gather / scatter of 777 x 4096 6.8 / 6.7 -> 4.4 / 4.3, 1024 x 8192 12.0 / 16.8 ->
 // 6.8 / 9.6, 4096 x 4096 15.3 / 18.1 -> 10.9 / 15.0 (67 MB: 6.1 / 4.5 TB/s), 4096 x 8192 28.7 / 31.7 -> 21.6 / 22.6; 100 x 5120 5.6 / 6.0 -> 4.3 / 3.2.
-// ND: pairs per thread; NC: 16-byte chunks of a row per thread.
-template <int ND>
+// ND: pairs per thread; NC: 16-byte chunks of a row per thread.  TWOS: the table lies on 8 bytes, in whole pairs; else its entries come one by one, and a last
+// one without a neighbour is beside a place of its own behind the row.
+template <int ND, bool TWOS>
 __device__ __forceinline__ void load_table(const int* __restrict__ perm, int ic, uint32_t (&p)[ND]) {   // two byte offsets within a row (ic <= 8192)
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
-        const i2 v = *reinterpret_cast<const i2*>(perm + min(2 * ((int)threadIdx.x + 256 * i), ic - 2));
-        p[i] = (uint32_t)(2 * min(max(v.x, 0), ic - 1)) | ((uint32_t)(2 * min(max(v.y, 0), ic - 1)) << 16);
+        int x, y;
+        if constexpr (TWOS) {
+            const i2 v = *reinterpret_cast<const i2*>(perm + min(2 * ((int)threadIdx.x + 256 * i), ic - 2));
+            x = min(max(v.x, 0), ic - 1);
+            y = min(max(v.y, 0), ic - 1);
+        } else {
+            const int j = 2 * min((int)threadIdx.x + 256 * i, (ic - 1) >> 1);
+            x = min(max(perm[j], 0), ic - 1);
+            y = j + 1 < ic ? min(max(perm[min(j + 1, ic - 1)], 0), ic - 1) : ic;
+        }
+        p[i] = (uint32_t)(2 * x) | ((uint32_t)(2 * y) << 16);
     }
 }
 
-template <int ND>
+template <int ND, bool TWOS>
 __global__ __launch_bounds__(256) void gather_rows_reg_kernel(const unsigned short* __restrict__ X, int M, int64_t ldx,
                                                               const int* __restrict__ perm, int ic,
                                                               unsigned short* __restrict__ Xs, int64_t lds_, int rows_per_wg) {
@@ -105,7 +115,7 @@ __global__ __launch_bounds__(256) void gather_rows_reg_kernel(const unsigned sho
     };
     fetch(m0);
     uint32_t p[ND];
-    load_table(perm, ic, p);
+    load_table<ND, TWOS>(perm, ic, p);
     for (int m = m0; m < m1; ++m) {
         unsigned char* buf = rowbytes + ((m - m0) & 1) * 2 * ic;
 #pragma unroll
@@ -126,12 +136,12 @@ __global__ __launch_bounds__(256) void gather_rows_reg_kernel(const unsigned sho
     }
 }
 
-template <int ND>
+template <int ND, bool TWOS>
 __global__ __launch_bounds__(256) void scatter_rows_reg_kernel(const unsigned short* __restrict__ Ds, int M, int64_t ldd,
                                                                const int* __restrict__ perm, int ic,
                                                                unsigned short* __restrict__ dX, int64_t lddx, int rows_per_wg) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char rowbytes[];   // [2][2 ic]
-    const int chunks = ic >> 3, pairs = ic >> 1;
+    extern __shared__ __attribute__((aligned(16))) unsigned char rowbytes[];   // [2][16 chunks]
+    const int whole = ic >> 3, chunks = (ic + 7) >> 3, pairs = (ic + 1) >> 1;   // (TWOS: IC a multiple of 8)
     const int m0 = blockIdx.x * rows_per_wg, m1 = min(m0 + rows_per_wg, M);
     uint32_t nxt[ND];
     auto fetch = [&](int m) {
@@ -141,9 +151,9 @@ __global__ __launch_bounds__(256) void scatter_rows_reg_kernel(const unsigned sh
     };
     fetch(m0);
     uint32_t p[ND];
-    load_table(perm, ic, p);
+    load_table<ND, TWOS>(perm, ic, p);
     for (int m = m0; m < m1; ++m) {
-        unsigned char* buf = rowbytes + ((m - m0) & 1) * 2 * ic;
+        unsigned char* buf = rowbytes + ((m - m0) & 1) * 16 * chunks;
         unsigned short* row = dX + (size_t)m * lddx;
 #pragma unroll
         for (int i = 0; i < ND; ++i) {   // (pairs past the row's last repeat it)
@@ -155,7 +165,11 @@ __global__ __launch_bounds__(256) void scatter_rows_reg_kernel(const unsigned sh
 #pragma unroll
         for (int i = 0; i < (ND + 3) / 4; ++i) {
             const int c = threadIdx.x + 256 * i;
-            if (c < chunks) *reinterpret_cast<u4*>(row + 8 * c) = *reinterpret_cast<const u4*>(buf + 16 * c);
+            if (c < whole) *reinterpret_cast<u4*>(row + 8 * c) = *reinterpret_cast<const u4*>(buf + 16 * c);
+        }
+        if constexpr (!TWOS) {
+            const int c = 8 * whole + threadIdx.x;
+            if (c < ic) row[c] = *reinterpret_cast<const unsigned short*>(buf + 2 * c);
         }
     }
 }
@@ -197,6 +211,8 @@ __global__ __launch_bounds__(256) void scatter_cols_kernel(const unsigned short*
     }
 }
 
+inline int pairs_size(int ic) { return ic <= 1024 ? 0 : (ic <= 2048 ? 1 : (ic <= 4096 ? 2 : 3)); }   // 2, 4, 8 or 16 pairs per thread
+
 inline int reg_rows_per_wg(int64_t M) { return M >= 4096 ? 4 : (M >= 1024 ? 2 : 1); }
 
 // rows per workgroup: enough workgroups for every CU a few times over, whole rows each
@@ -209,10 +225,12 @@ size_t irregular_workspace(int ic, int64_t M) { return (size_t)M * (size_t)((ic 
 hipError_t gather_cols(const __half* X, int64_t M, int64_t ldx, const int* perm, int ic, __half* Xs, int64_t ldo, hipStream_t s) {
     const int chunks = (ic + 7) / 8;   // ldo >= 8 * chunks, a multiple of 8
     const int row_bytes = chunks * 16;
-    if (chunks <= 1024 && (ic & 7) == 0 && (ldx & 7) == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)perm & 7) == 0) {   // whole 16-byte chunks only: no read past a row's IC elements
+    if (chunks <= 1024 && (ic & 7) == 0 && (ldx & 7) == 0 && ((uintptr_t)X & 15) == 0) {   // whole 16-byte chunks only: no read past a row's IC elements
+        using Kern = void (*)(const unsigned short*, int, int64_t, const int*, int, unsigned short*, int64_t, int);
+        static const Kern table[2][4] = {{gather_rows_reg_kernel<2, false>, gather_rows_reg_kernel<4, false>, gather_rows_reg_kernel<8, false>, gather_rows_reg_kernel<16, false>},
+                                         {gather_rows_reg_kernel<2, true>, gather_rows_reg_kernel<4, true>, gather_rows_reg_kernel<8, true>, gather_rows_reg_kernel<16, true>}};
         const int rw = reg_rows_per_wg(M);
-        auto kern = ic <= 1024 ? gather_rows_reg_kernel<2> : (ic <= 2048 ? gather_rows_reg_kernel<4> : (ic <= 4096 ? gather_rows_reg_kernel<8> : gather_rows_reg_kernel<16>));
-        kern<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)X, (int)M, ldx, perm, ic, (unsigned short*)Xs, ldo, rw);
+        table[((uintptr_t)perm & 7) == 0][pairs_size(ic)]<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)X, (int)M, ldx, perm, ic, (unsigned short*)Xs, ldo, rw);
         return hipGetLastError();
     }
     if (row_bytes <= ROW_LDS_MAX && (ldx & 7) == 0 && ((uintptr_t)X & 15) == 0) {
@@ -230,10 +248,13 @@ hipError_t gather_cols(const __half* X, int64_t M, int64_t ldx, const int* perm,
 hipError_t scatter_cols(const __half* Ds, int64_t M, const int* perm, int ic, __half* dX, int64_t lddx, hipStream_t s) {
     const int chunks = (ic + 7) / 8;
     const int row_bytes = chunks * 16;
-    if (chunks <= 1024 && (ic & 7) == 0 && (lddx & 7) == 0 && ((uintptr_t)dX & 15) == 0 && ((uintptr_t)perm & 7) == 0) {
+    if (chunks <= 1024 && (lddx & 7) == 0 && ((uintptr_t)dX & 15) == 0) {
+        using Kern = void (*)(const unsigned short*, int, int64_t, const int*, int, unsigned short*, int64_t, int);
+        static const Kern table[2][4] = {{scatter_rows_reg_kernel<2, false>, scatter_rows_reg_kernel<4, false>, scatter_rows_reg_kernel<8, false>, scatter_rows_reg_kernel<16, false>},
+                                         {scatter_rows_reg_kernel<2, true>, scatter_rows_reg_kernel<4, true>, scatter_rows_reg_kernel<8, true>, scatter_rows_reg_kernel<16, true>}};
         const int rw = reg_rows_per_wg(M);
-        auto kern = ic <= 1024 ? scatter_rows_reg_kernel<2> : (ic <= 2048 ? scatter_rows_reg_kernel<4> : (ic <= 4096 ? scatter_rows_reg_kernel<8> : scatter_rows_reg_kernel<16>));
-        kern<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)Ds, (int)M, (int64_t)chunks * 8, perm, ic, (unsigned short*)dX, lddx, rw);
+        table[(ic & 7) == 0 && ((uintptr_t)perm & 7) == 0][pairs_size(ic)]<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)Ds, (int)M, (int64_t)chunks * 8, perm, ic,
+                                                                                                                      (unsigned short*)dX, lddx, rw);
         return hipGetLastError();
     }
     if (row_bytes <= ROW_LDS_MAX && (lddx & 7) == 0 && ((uintptr_t)dX & 15) == 0) {

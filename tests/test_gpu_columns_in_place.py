@@ -22,7 +22,18 @@ def test_gathered_columns(ic):
         assert torch.equal(B.qeft_reorder(a, perm, 1), a[:, perm.long()]), f"{m} rows"
 
 
-@pytest.mark.parametrize("ic", [w for w in WIDTHS if w >= 128] + [2049])
+@pytest.mark.parametrize("ic", [w for w in WIDTHS if w <= 8192])
+def test_gathered_columns_by_a_table_on_four_bytes(ic):
+    perm = torch.zeros(ic + 1, dtype=torch.int32, device="cuda")[1:]
+    perm.copy_(_table(ic, ic))
+    assert perm.data_ptr() % 8 == 4
+    for m in (1, 1025, 4099):
+        back = torch.randn((m + 2, ic + 8), device="cuda").half()
+        a = back[1:m + 1, :ic]
+        assert torch.equal(B.qeft_reorder(a, perm, 1), a[:, perm.long()]), f"{m} rows"
+
+
+@pytest.mark.parametrize("ic", [w for w in WIDTHS if w >= 128] + [129, 1023, 1026, 2047, 2049, 4092, 4097, 8190, 8191, 8193])
 def test_scattered_columns(ic):
     oc, k = 64, 8
     d = B.make_desc(oc, ic, k, 4, 128)
