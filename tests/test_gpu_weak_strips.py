@@ -1,5 +1,5 @@
 """Weak block's gradient in pieces of 64 and of 128 columns: pieces that end early, channels and tokens that end inside a strip and a stage,
-more than one split.  Tolerance per element: fp32 sums of M products that are exact in fp32, (M + 2) 2^-24 of the sum of their magnitudes."""
+more than one split, more pieces than CUs.  Tolerance per element: fp32 sums of M products that are exact in fp32, (M + 2) 2^-24 of the sum of their magnitudes."""
 import pytest
 import torch
 
@@ -10,7 +10,7 @@ from parity_util import pad_cols
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("oc,k", [(72, 8), (136, 64), (1000, 72), (264, 128), (520, 192), (64, 256), (4104, 40), (8256, 128)])
+@pytest.mark.parametrize("oc,k", [(72, 8), (136, 64), (1000, 72), (264, 128), (520, 192), (64, 256), (4104, 40), (8256, 128), (16456, 72), (16448, 96), (26176, 72), (9032, 136)])
 def test_weak_gradient_in_pieces(oc, k):
     d = B.make_desc(oc, k + 128, k, 4, 128)
     for m in (64, 65, 127, 128, 191, 449, 1000):
