@@ -812,14 +812,15 @@ bool dx_tile_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
     return est_dx(L, M).t < 0.95 * est_gemm_dx(L, M);
 }
 
-// The panel kernel for few rows, where its estimate is 10 % ahead of what would run otherwise (32-bit offsets as above).  Of more than 256 rows, splits
+// The panel kernel for few rows, where its estimate is 10 % ahead of what would run otherwise (32-bit offsets as above; the small tiles of up to 512 weight rows are
+// estimated 1.6 us too long: 488 x 5064 at M = 277 9.1 us there against 10.3).  Of more than 256 rows, splits
 // of longer parts than one chunk of 8 stages are as fast (5120 x 5120 with 64 weak columns at 384, forward before it: 72.8 us against 75.7; 4096 x 4096
 // at 384, single chunks: 57.8 and 50.5), and short ones keep their arithmetic, as above (2048 x 1152 at 512 rows: 21 us, 12 by panels).
 bool dx_panel_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) {
     if (L.ng <= 0 || M <= 16 || lddy > (QEFT_MAX_DIM >> 1)) return false;
     const GemmSplit p = split_ws ? gemm_dx_split(L, M) : GemmSplit{1, 0, 0, false};
     if (p.splits > 1 && M > 256 && (p.tail || p.stages > 8 || est_split(p, 12, 1.5) < 28)) return false;
-    double other = est_dx(L, M).t;
+    double other = est_dx(L, M).t - (L.oc <= 512 ? 1.6 : 0.0);
     if (!dx_tile_preferred(L, M, lddy, split_ws))
         other = p.splits > 1 && !p.tail ? est_split(p, 12, 1.5) : est_gemm_dx(L, M);
     return dx_panel_estimate(L, M) < 0.9 * other;
