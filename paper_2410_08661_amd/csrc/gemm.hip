@@ -1435,7 +1435,7 @@ GemmSplit gemm_dx_split(const Layer& L, int64_t M) {
 
 // (defined below: tiles and strips in one launch)
 static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, const Strips& S, hipStream_t s);
-static bool gemm_dx_dw_preferred(const Layer& L, const Strips& S);
+static bool gemm_dx_dw_preferred(const Strips& S);
 
 hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, void* ws, hipStream_t s, WeakGrad* g) {
     const bool in_registers = dx_in_registers(L, M, lddy);
@@ -1472,7 +1472,7 @@ hipError_t gemm_dx(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __
             return hipGetLastError();
         }
         const Strips S = make_strips(g, dY, M, lddy, g ? g->used : 0);
-        if (S.n > 0 && gemm_dx_dw_preferred(L, S)) {
+        if (S.n > 0 && gemm_dx_dw_preferred(S)) {
             e = gemm_dx_dw(L, dY, M, lddy, dX, lddx, S, s);
             return e == hipSuccess ? finish_strips(g, S, s) : e;
         }
@@ -1516,16 +1516,16 @@ hipError_t weak_grad_reduce(const float* part, int splits, int64_t n, void* dW, 
 }
 
 // dX and dW_weak of one layer in one launch (see gemm_dx_dw_kernel), for layers the register kernel takes.
-// Taken when the weak block is one strip wide (k <= 128).  The strips follow the tiles in the grid, so they start on
+// Taken for weak blocks of up to 128 columns (one piece of 128, or two of 64).  The strips follow the tiles in the grid, so they start on
 // whichever compute units finish their last tile first: in the idle part of a partly empty last round, or, when the
 // tiles fill their rounds, in the few microseconds by which the tiles' ends differ.  Inside the combined launch a strip
 // workgroup has a compute unit to itself (the launch reserves the tile kernel's LDS and registers for every workgroup;
 // on its own the strip kernel runs two per unit), so a weak gradient that is heavy next to that idle time loses more
 // than it gains.  Measured at M = 4096, the two calls against the one: 11008 x 4096 (256 tiles) 388 -> 382 us,
 // 4096 x 4096 (256 tiles) 165 -> 163, 4096 x 11008 (688 tiles) 363 -> 350, 5120 x 5120 281 -> 262, 13824 x 5120
-// 699 -> 670; with a 256-wide weak block (two half strips per strip of channels) 8192 x 8192 at M = 2048 257 -> 252
+// 699 -> 670; with a 256-wide weak block (two pieces of 128 per strip of channels) 8192 x 8192 at M = 2048 257 -> 252
 // but 28672 x 8192 862 -> 877.
-static bool gemm_dx_dw_preferred(const Layer& L, const Strips& S) { return L.k > 0 && S.k <= 128; }
+static bool gemm_dx_dw_preferred(const Strips& S) { return S.k <= 128; }
 
 static hipError_t gemm_dx_dw(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, const Strips& S, hipStream_t s) {
     const int tiles_ic = ceil_div(dx_columns(L), BT), n_dx = xcd_grid(tiles_ic * ceil_div(M, BT));

@@ -246,7 +246,7 @@ __global__ __launch_bounds__(DOT_THREADS) void gemv_w4_dot_kernel(DotLayers R, i
                 // range i = u / 256, lane l = (u % 256) / 4, piece q = u % 4  ->  [i][q][l]
                 const int i = u >> 8, l = (u & 255) >> 2, q = u & 3;
                 *reinterpret_cast<u4*>(lds + 4096 * i + 1024 * q + 16 * l) = p;
-                if (q == 0) ksum[64 * i + l] = float2{1024.f * se + 64.f * so, se + so};   // (W3D: the second alone)
+                if (q == 0) ksum[64 * i + l] = float2{W3D ? 0.f : 1024.f * se + 64.f * so, se + so};   // (W3D: the second alone, the first at its lane)
             }
         }
     };

@@ -213,8 +213,6 @@ __global__ __launch_bounds__(256) void scatter_cols_kernel(const unsigned short*
 
 inline int pairs_size(int ic) { return ic <= 1024 ? 0 : (ic <= 2048 ? 1 : (ic <= 4096 ? 2 : 3)); }   // 2, 4, 8 or 16 pairs per thread
 
-inline int reg_rows_per_wg(int64_t M) { return M >= 4096 ? 4 : (M >= 1024 ? 2 : 1); }
-
 // rows per workgroup: enough workgroups for every CU a few times over, whole rows each
 inline int rows_per_wg(int64_t M) { return M >= 4096 ? 4 : (M >= 1024 ? 2 : 1); }
 
@@ -229,7 +227,7 @@ hipError_t gather_cols(const __half* X, int64_t M, int64_t ldx, const int* perm,
         using Kern = void (*)(const unsigned short*, int, int64_t, const int*, int, unsigned short*, int64_t, int);
         static const Kern table[2][4] = {{gather_rows_reg_kernel<2, false>, gather_rows_reg_kernel<4, false>, gather_rows_reg_kernel<8, false>, gather_rows_reg_kernel<16, false>},
                                          {gather_rows_reg_kernel<2, true>, gather_rows_reg_kernel<4, true>, gather_rows_reg_kernel<8, true>, gather_rows_reg_kernel<16, true>}};
-        const int rw = reg_rows_per_wg(M);
+        const int rw = rows_per_wg(M);
         table[((uintptr_t)perm & 7) == 0][pairs_size(ic)]<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)X, (int)M, ldx, perm, ic, (unsigned short*)Xs, ldo, rw);
         return hipGetLastError();
     }
@@ -252,7 +250,7 @@ hipError_t scatter_cols(const __half* Ds, int64_t M, const int* perm, int ic, __
         using Kern = void (*)(const unsigned short*, int, int64_t, const int*, int, unsigned short*, int64_t, int);
         static const Kern table[2][4] = {{scatter_rows_reg_kernel<2, false>, scatter_rows_reg_kernel<4, false>, scatter_rows_reg_kernel<8, false>, scatter_rows_reg_kernel<16, false>},
                                          {scatter_rows_reg_kernel<2, true>, scatter_rows_reg_kernel<4, true>, scatter_rows_reg_kernel<8, true>, scatter_rows_reg_kernel<16, true>}};
-        const int rw = reg_rows_per_wg(M);
+        const int rw = rows_per_wg(M);
         table[(ic & 7) == 0 && ((uintptr_t)perm & 7) == 0][pairs_size(ic)]<<<ceil_div(M, rw), 256, 2 * row_bytes, s>>>((const unsigned short*)Ds, (int)M, (int64_t)chunks * 8, perm, ic,
                                                                                                                       (unsigned short*)dX, lddx, rw);
         return hipGetLastError();
