@@ -124,6 +124,7 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
             wait_vm<0>();
             __builtin_amdgcn_sched_barrier(0);
             asm volatile("" : "+v"(sv), "+v"(zv));   // (used behind the wait)
+            if (first_row(st) + lane < 64 * st) sv = zv = 0u;   // (a weight of zero, whatever its code)
             if constexpr (ONCE) *reinterpret_cast<lds_f32*>((size_t)(at_p + 4u * lane)) = neg_zs(bits_h2(zv).x, bits_h2(sv).x);
             else *reinterpret_cast<lds_u16*>((size_t)(at_p + 2u * lane)) = (uint16_t)zv;
             *reinterpret_cast<lds_u16*>((size_t)(at_p + 256u + 2u * lane)) = (uint16_t)sv;
@@ -163,13 +164,6 @@ __global__ __launch_bounds__(512) void dx_panel_kernel(Layer L, const __half* __
 #pragma unroll
                     for (int ks = 4 * ph / PH; ks < 4 * (ph + 1) / PH; ++ks) {
                         const bool live = first_row(st) + 8 * (4 * (ks >> 1) + 2 * fk + (ks & 1)) >= 64 * st;
-                        const u4 zero4 = u4{0u, 0u, 0u, 0u};
-                        sc[ks] = live ? sc[ks] : zero4;   // (s = 0 and z = 0: a weight of zero whatever its code)
-                        if constexpr (ONCE) {
-#pragma unroll
-                            for (int h = 0; h < 2; ++h) nz[ks][h] = live ? nz[ks][h] : f4{0.f, 0.f, 0.f, 0.f};
-                        } else
-                            zp[ks] = live ? zp[ks] : zero4;
 #pragma unroll
                         for (int j = 0; j < J; ++j) b[ks][j] = live ? b[ks][j] : zero8;
                     }
