@@ -170,7 +170,8 @@ int qeft_unpack(const qeft_desc_t* desc, const qeft_weight_t* w, uint8_t* codes,
  * and without it (ws NULL) the forward multiplies the stored codes and the input gradient takes the slow general kernel; a workspace that is too small is
  * QEFT_ERR_WORKSPACE.  The copy is rewritten by every call (the weak block may have changed).
  * QEFT_OP_BWD (qeft_linear_bwd): the larger of QEFT_OP_WEAK_GRAD's amount, which that call requires, and
- * QEFT_OP_BWD_DX's, which it uses when given (the two steps use the workspace one after the other). */
+ * QEFT_OP_BWD_DX's, which it uses when given.  (The sum of the two, QEFT_OP_BWD_DX's rounded up to 16, also holds
+ * the partial sums of both steps at once, see there.) */
 size_t qeft_workspace_bytes(const qeft_desc_t* desc, int op, int64_t M);
 
 /* Forward of the fused layer (Sec. 3.2.1): Y = X[:, :Kq] . dq(Q)^T + X[:, Kq:] . weak^T in
@@ -196,7 +197,8 @@ int qeft_linear_fwd_group(int n, const qeft_desc_t* descs, const qeft_weight_t* 
 
 /* Input gradient through the full mixed weight (Sec. 3.3): dX = dY . W, i.e.
  * dX[:, :Kq] = dY . dq(Q) and dX[:, Kq:] = dY . weak (the weak block's current values).
- * dY fp16 [M][lddy] (lddy >= OC), dX fp16 [M][lddx] (lddx >= IC). */
+ * dY fp16 [M][lddy] (lddy >= OC), dX fp16 [M][lddx] (lddx >= IC).  Up to some hundred rows, and where the large tiles would
+ * leave the GPU idle, smaller tiles run instead, which do not touch a workspace that is given for the split. */
 int qeft_linear_bwd_dx(const qeft_desc_t* desc, const qeft_weight_t* w, const void* dY, int64_t M,
                        int64_t lddy, void* dX, int64_t lddx, void* ws, size_t ws_bytes, void* stream);
 
@@ -269,17 +271,17 @@ int qeft_weak_grad(const qeft_desc_t* desc, const void* dY, int64_t M, int64_t l
 /* The backward pass of one layer in one call (Sec. 3.3, Eq. 5): dX = dY . W through the full mixed weight and
  * dW (+)= dY^T . Xw for the weak block, arguments as in qeft_linear_bwd_dx and qeft_weak_grad.  The same kernels
  * run as in those two calls, and the results equal theirs bit for bit; what the call chooses is how they go out:
- *   - with room in ws for what qeft_linear_bwd_dx can use (qeft_workspace_bytes(desc, QEFT_OP_BWD, M), the larger
- *     of the two steps' amounts: the partial tiles of a row split of dX where that split applies, the copy of
- *     a 3-bit layer - without which its dX takes the slow general kernel): dX with that workspace, then the weak
- *     gradient, as qeft_linear_bwd_dx with its workspace followed by qeft_weak_grad (the workspace serves one after
- *     the other);
- *   - else, where both steps take the large tensor-core tiles and the weak block is at most 128 wide: ONE launch - the
- *     weak gradient's workgroups follow the dX tiles in the grid and are dispatched as compute units fall free, so
- *     they run in what the last round of tiles leaves idle (dX of 4096 x 11008 at M = 4096: 688 tiles on 256 units;
- *     350 us against 363 us for the two calls); results as qeft_linear_bwd_dx without workspace followed by
- *     qeft_weak_grad;
- *   - else the two calls one after the other, dX without workspace.
+ *   - dX goes as qeft_linear_bwd_dx with this workspace where ws has room for what that can use (its amount is QEFT_OP_BWD_DX's: the
+ *     partial tiles of a row split where that split applies, the copy of a 3-bit layer - without which its dX takes the slow
+ *     general kernel), else as qeft_linear_bwd_dx without one.  What dX uses lies at the head of ws;
+ *   - the weak gradient's workgroups join a launch of dX where the kernel taken has room for them, and are dispatched as compute
+ *     units fall free: behind the tiles of the kernels for few rows and for few tiles, behind the large tiles if the weak block is at
+ *     most 128 wide (dX of 4096 x 11008 at M = 4096: 688 tiles on 256 units, 350 us against 363 us for the two calls), and
+ *     beside the sum of a split's partial tiles.  If their tokens are split, their partial sums lie at the end of ws, in the last
+ *     QEFT_OP_WEAK_GRAD bytes at most;
+ *   - where they cannot join - the general kernels, M < 64, the two steps' partial sums not both in ws - the weak gradient goes as
+ *     qeft_weak_grad after dX, and the workspace serves one after the other.  QEFT_OP_BWD bytes may be too few for both at once (a
+ *     split of dX with split tokens); the sum of the two amounts never is.
  * ws / ws_bytes: at least qeft_workspace_bytes(desc, QEFT_OP_WEAK_GRAD, M) bytes, 16-byte aligned, required as for
  * qeft_weak_grad (QEFT_ERR_WORKSPACE before anything is launched); more than that is optional.
  * n_weak == 0: only dX is computed, without workspace (Xw, dW, ws may be NULL). */
