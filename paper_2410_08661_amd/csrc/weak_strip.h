@@ -241,8 +241,9 @@ inline int weak_grad_strip_most(int oc, int k, int64_t M) {
 // The split and the pieces taken: a stage of 64 tokens costs a workgroup about 0.62 us where the piece's 128 weak columns all exist, 1.06 where
 // some do not, 0.42 and 0.7 in pieces of 64 (half the multiplications, two thirds of the loads and LDS accesses, in a stream that nothing else hides);
 // workgroups past one per CU count in full there, by 0.3 where columns are missing (a stage that waits leaves room for another's).  Twice as many pieces
-// read dY twice as often: they count in full where strips begin between cache lines (OC no multiple of 64), by 0.6 past two per CU elsewhere (by 0.3 too, us against pieces
-// of 128: 27160 / 12216 channels, k = 96 / 72, M = 1441 / 1990 51.7 / 37.1 against 33.8 / 29.5; 13824, k = 224, 4096: 100 against 78.6; but 14336, k = 96, 1331 20.8 against 24.4).
+// read dY twice as often: they count in full where strips begin between cache lines (OC no multiple of 64), by 0.6 elsewhere where unsplit ones are more than two per CU (by 0.3 too, us against pieces
+// of 128: 27160 / 12216 channels, k = 96 / 72, M = 1441 / 1990 51.7 / 37.1 against 33.8 / 29.5; 13824, k = 224, 4096: 100 against 78.6; but 14336, k = 96, 1331 20.8 against 24.4, 11008, k = 72, 2183
+// in two splits 26.7 against 28.7).
 // Three pieces in place of two gain at any number of them (26200, k = 136, 77: 12.3 against 15.6).  A
 // split costs the second launch and its partial slab's way through memory (2 us once, 0.65 us per MB
 // and, where columns are missing, 0.13 us each).  Pieces of 64 read dY once for each: in whole blocks of 128 only where all have a CU
@@ -269,7 +270,7 @@ inline StripPlan weak_grad_strip_split(int oc, int k, int64_t M) {
         for (int s = 1; s <= most; ++s) {
             const double w = (double)tiles * s / 256.0;
             if (kw == 64 && k % 128 == 0 && (w > 1 || s > 1)) break;
-            const double t = (w <= 1 ? 1 : ((full && kw == 128) || (twice && oc % WG_OC != 0) ? w : (twice && w > 2 ? 0.1 + 0.6 * w : 0.7 + 0.3 * w))) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + ((full ? 0.0 : 0.13) + 0.65 * slab_mb) * s : 0.0);
+            const double t = (w <= 1 ? 1 : ((full && kw == 128) || (twice && oc % WG_OC != 0) ? w : (twice && tiles > 2 * 256 ? 0.1 + 0.6 * w : 0.7 + 0.3 * w))) * stage_us * ceil_div(stages, s) + (s > 1 ? 2.0 + ((full ? 0.0 : 0.13) + 0.65 * slab_mb) * s : 0.0);
             if (t < best) {
                 best = t;
                 p.chunk = ceil_div(stages, s) * BK;
