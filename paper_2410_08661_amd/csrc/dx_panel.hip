@@ -307,12 +307,13 @@ hipError_t launch(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __h
 // Estimated time (us) of the best tile for a call, all of whose workgroups have a CU of their own (more than that and a few of them take a second
 // turn: none then).  n: stages of a wave; fitted to the shapes above at 17 to 512 rows, within 15 %.  No less than a stage takes however few tiles share the
 // caches, and than many rows bring with them (tall narrow layers and thousands of rows, over 1000 layers looked at, were estimated at half of their time: us, here against
-// what ran otherwise, 24064 x 576 with 64 weak columns at M = 57 51 / 38, 26880 x 384 with 128 at 224 62 / 48, 6960 x 896 at 1182 51 / 38, 10752 x 360 with 72 at 4087 104 / 81).
+// the small tiles, 6960 x 896 at M = 1182 51 / 38, 10752 x 360 with 72 weak columns at 4087 104 / 81) - except against a split (split), whose partial tiles are rounded to fp16:
+// it is the quicker one for some of these layers (24064 x 576 with 64 at 57: 51 / 38), and the tile of a call stays the one that leaves most CUs to the weak gradient's strips.
 // Rows of codes about a multiple of 4 KB apart put a
 // request's 64 lines on few channels of the L2 (8192 x 8192 with 256 weak columns at M = 64 / 128, forward before it: 40.5 / 42.5 us here, 37.5 / 40 by a split).
 namespace {
 struct Pick {
-    double us;
+    double us, least;
     int tile;   // 0: 32 channels x 32 rows, 1: 32 x 64, 2: 64 x 64, 3: 64 x 128
 };
 Pick pick(const Layer& L, int64_t M) {
@@ -320,19 +321,20 @@ Pick pick(const Layer& L, int64_t M) {
     const int apart = 4 * L.stride % 4096;
     const bool few = 4 * L.stride > 2048 && (apart < 192 || apart > 4096 - 192);
     const double c0[4] = {0.4, 0.75, 1.2, 2.1}, c1[4] = {0.7, 0.6, 0.55, 0.7}, c2[4] = {0.05, 0.06, 0.065, 0.065};
-    const double fixed[4] = {3.0, 3.0, 4.0, 5.3}, stage[4] = {0.9, 1.28, 1.43, 2.17};
-    Pick best = {1e30, 0};
+    const double fixed[4] = {3.0, 3.0, 4.0, 5.3}, stage[4] = {0.9, 1.28, 1.43, 2.17}, rows = 0.6e-6 * (double)M * (L.oc + L.ic);
+    Pick best = {1e30, 1e30, 0};
     for (int t = 0; t < 4; ++t) {
         const int64_t wgs = (int64_t)dxp_tiles(L, t >= 2 ? 64 : 32) * ceil_div(M, t == 0 ? 32 : (t == 3 ? 128 : 64));
         const double us = (few ? 8.5 : 3.5) + (few ? 1.1 : 1.0) * n * (c0[t] + c1[t] * (double)wgs / 256 + c2[t] * wide);
-        if (wgs <= 256 && us < best.us) best = {us, t};
+        if (wgs <= 256 && us < best.us) best = {us, fixed[t] + n * stage[t] + rows, t};
     }
-    const double least = fixed[best.tile] + n * stage[best.tile] + 0.6e-6 * (double)M * (L.oc + L.ic);
-    if (best.us < least) best.us = least;   // (the tile stays: one of fewer workgroups leaves CUs to the weak gradient's)
     return best;
 }
 }  // namespace
-double dx_panel_estimate(const Layer& L, int64_t M) { return pick(L, M).us; }
+double dx_panel_estimate(const Layer& L, int64_t M, bool split) {
+    const Pick p = pick(L, M);
+    return split || p.us > p.least ? p.us : p.least;
+}
 hipError_t dx_panel(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s, WeakGrad* g) {
     using Launch = hipError_t (*)(const Layer&, const __half*, int64_t, int64_t, __half*, int64_t, hipStream_t, WeakGrad*);
     static const Launch table[4][2] = {{launch<1, 1, false>, launch<1, 1, true>}, {launch<1, 2, false>, launch<1, 2, true>}, {launch<2, 2, false>, launch<2, 2, true>}, {launch<2, 4, false>, launch<2, 4, true>}};

@@ -820,10 +820,9 @@ bool dx_panel_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws) 
     if (L.ng <= 0 || M <= 16 || lddy > (QEFT_MAX_DIM >> 1)) return false;
     const GemmSplit p = split_ws ? gemm_dx_split(L, M) : GemmSplit{1, 0, 0, false};
     if (p.splits > 1 && M > 256 && (p.tail || p.stages > 8 || est_split(p, 12, 1.5) < 28)) return false;
-    double other = est_dx(L, M).t - (L.oc <= 512 ? 1.6 : 0.0);
-    if (!dx_tile_preferred(L, M, lddy, split_ws))
-        other = p.splits > 1 && !p.tail ? est_split(p, 12, 1.5) : est_gemm_dx(L, M);
-    return dx_panel_estimate(L, M) < 0.9 * other;
+    const bool tiles = dx_tile_preferred(L, M, lddy, split_ws), split = !tiles && p.splits > 1 && !p.tail;
+    const double other = tiles ? est_dx(L, M).t - (L.oc <= 512 ? 1.6 : 0.0) : (split ? est_split(p, 12, 1.5) : est_gemm_dx(L, M));
+    return dx_panel_estimate(L, M, split) < 0.9 * other;
 }
 
 // A 3-bit layer whose quantized columns are not whole stages (forward: 64 columns) or whole groups (input gradient): its 4-bit copy

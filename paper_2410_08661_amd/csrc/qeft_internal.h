@@ -136,7 +136,7 @@ hipError_t fwd_tile(const Layer& L, const __half* X, int64_t M, int64_t ldx, __h
 hipError_t dx_tile(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s, WeakGrad* g = nullptr);
 
 // ---- input gradient of few rows in tiles of 32 or 64 channels x 32 to 128 rows (dx_panel.hip), for layers the GEMMs below support ----
-double dx_panel_estimate(const Layer& L, int64_t M);   // us; more than any call takes where the tiles do not all find a CU
+double dx_panel_estimate(const Layer& L, int64_t M, bool split);   // us, beside a split's or another; more than any call takes where the tiles do not all find a CU
 bool dx_panel_preferred(const Layer& L, int64_t M, int64_t lddy, bool split_ws);
 hipError_t dx_panel(const Layer& L, const __half* dY, int64_t M, int64_t lddy, __half* dX, int64_t lddx, hipStream_t s, WeakGrad* g = nullptr);
 
